@@ -5,20 +5,27 @@
 // projection.)
 //
 // One workgroup (4 waves, 2 x 2) owns 256 tokens x 256 output features (two
-// heads); a wave owns 128 tokens x one head as 4 x 4 accumulators of
-// v_mfma_f32_32x32x16_bf16 with the features on the accumulator rows.  A lane
-// then holds, for one token, features 8j + 4(l/32) + {0..3} of every 32-block:
+// heads); a wave owns 128 tokens x one head as 8 x 8 accumulators of
+// v_mfma_f32_16x16x32_bf16 with the features on the accumulator rows.  A lane
+// then holds, for one token, features 4(l/16) + {0..3} of every 16-block:
 // both members (i, i + 64) of a rotary pair sit in the same lane and register
 // index, and four consecutive features make one 8-byte piece of the output row.
+//
+// Why 16 x 16 x 32 and not 32 x 32 x 16 (same rate on paper, same operand bytes from LDS):
+// the launch is held by the power limit, and the smaller tile moves half the accumulator
+// bytes per product through the register file.  In registers alone, on Gaussian
+// activations x N(0, 0.02^2) weights, 256 CUs sustain 2044 TFLOP/s with it against 1757
+// (2444 / 2422 on zeros, where nothing is limited).  Measured on this kernel, 8192^3:
+// 1358 -> 1467 TFLOP/s; 6656 rows x 28672 outputs x 4096: 1293 -> 1386.
 //
 // The contraction runs in steps of 32 through a 5-stage LDS ring filled by
 // direct global->LDS loads (16 bytes per lane; the gather is free, every lane
 // carries its own row pointer).  A row of a stage is 64 bytes; the 16-byte
 // chunk c of row r is stored at position c ^ ((r >> 2) & 3), which makes both
 // the 1 KB-contiguous fill and the ds_read_b128 of the MFMA operands
-// conflict-free.  One barrier per stage, placed between the two 16-wide
-// contraction sub-steps so that the operands of the next stage are already in
-// flight while the second sub-step's MFMAs run.
+// conflict-free.  One barrier per stage, placed between the two halves of the
+// token blocks so that the operands of the next stage are already in flight
+// while the second half's MFMAs run.
 //
 // Tiles are numbered so that each XCD (workgroup id mod 8) works through its own
 // contiguous run of tiles, 8 token tiles deep, and its L2 sees few distinct
@@ -59,6 +66,14 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
         : "s"(lds_base), "v"(gptr)
         : "memory", "m0");
 }
+// c += a . b on a 16 x 16 tile, 32 of the contraction.  Written out so that the accumulator
+// stays where it is: left to itself the register allocator rotates the 64 accumulators of a
+// wave through copies (584 of them per two steps) once they are four registers each.  The
+// compiler does not see the result's latency: acc_settle() before the first reader.
+__device__ __forceinline__ void mfma_16x16x32(f32x4& c, bf16x8 a, bf16x8 b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 template <int N>
 __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -75,7 +90,7 @@ __device__ __forceinline__ float silu_f32(float a) {
 // what a tile is and which part of it a lane owns (filled by the kernels, read by the
 // epilogue)
 struct TileCtx {
-    int lane, wave, hh, l32, wt, wf;
+    int lane, wave, g4, l16, wt, wf;
     int split, ft, mat, feat0, row0, heads_out;
     bf16_t* out;
 };
@@ -84,9 +99,9 @@ struct TileCtx {
 // 16 B per lane; or store the fp32 partial tile of a split contraction.  Called after the
 // main loop, when nothing is still writing the LDS stages.
 template <int MODE, bool EXTRA>
-__device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x16 (&acc)[4][4],
+__device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[8][8],
                                               const TileCtx& c, unsigned char* smem) {
-    const int lane = c.lane, wave = c.wave, hh = c.hh, l32 = c.l32, wt = c.wt, wf = c.wf;
+    const int lane = c.lane, wave = c.wave, g4 = c.g4, l16 = c.l16, wt = c.wt, wf = c.wf;
     const int split = c.split, ft = c.ft, mat = c.mat, feat0 = c.feat0, row0 = c.row0;
     const int heads_out = c.heads_out;
     bf16_t* out = c.out;
@@ -102,16 +117,12 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x16 (&acc)
         for (int tb = 0; tb < 4; ++tb) {
             const int rbase = row0 + wt * 128 + tb * 32;
             if (rbase >= p.m) break;   // wave-uniform
-            unsigned char* erow = epf + l32 * kEpiStrideF32;
 #pragma unroll
-            for (int fb = 0; fb < 4; ++fb)
+            for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 v;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc[fb][tb][4 * j + e];
-                    *reinterpret_cast<f32x4*>(erow + (fb * 32 + 8 * j + 4 * hh) * 4) = v;
-                }
+                for (int mt = 0; mt < 8; ++mt)
+                    *reinterpret_cast<f32x4*>(epf + (nt * 16 + l16) * kEpiStrideF32 +
+                                              (mt * 16 + 4 * g4) * 4) = acc[mt][tb * 2 + nt];
 #pragma unroll
             for (int it = 0; it < 16; ++it) {
                 const int idx = it * 64 + lane;
@@ -132,18 +143,15 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x16 (&acc)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
-            for (int tbl = 0; tbl < 2; ++tbl) {
-                const int tb = half * 2 + tbl;
-                unsigned char* erow = epi + (tbl * 32 + l32) * kEpiStride;
+            for (int nt = 0; nt < 4; ++nt) {
+                unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
-                for (int fb = 0; fb < 4; ++fb)
+                for (int mt = 0; mt < 8; ++mt) {
+                    bf16x4 v;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        bf16x4 v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)acc[fb][tb][4 * j + e];
-                        *reinterpret_cast<bf16x4*>(erow + (fb * 32 + 8 * j + 4 * hh) * 2) = v;
-                    }
+                    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)acc[mt][half * 4 + nt][e];
+                    *reinterpret_cast<bf16x4*>(erow + (mt * 16 + 4 * g4) * 2) = v;
+                }
             }
 #pragma unroll
             for (int it = 0; it < 16; ++it) {
@@ -165,27 +173,25 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x16 (&acc)
         return;
     }
     if (MODE == kProjGated) {
-        // the wave's 128 tokens x 64 outputs: gate in blocks 0, 1 and up in blocks 2, 3
+        // the wave's 128 tokens x 64 outputs: gate in feature blocks 0..3 and up in 4..7
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
-            for (int tbl = 0; tbl < 2; ++tbl) {
-                const int tb = half * 2 + tbl;
-                unsigned char* erow = epi + (tbl * 32 + l32) * kEpiStride;
+            for (int nt = 0; nt < 4; ++nt) {
+                const int tt = half * 4 + nt;
+                unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
-                for (int fbp = 0; fbp < 2; ++fbp)
+                for (int mt = 0; mt < 4; ++mt) {
+                    bf16x4 v;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        bf16x4 v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float a = (float)(bf16_t)acc[fbp][tb][4 * j + e];
-                            const float b = (float)(bf16_t)acc[fbp + 2][tb][4 * j + e];
-                            const float s = (float)(bf16_t)silu_f32(a);
-                            v[e] = (bf16_t)(s * b);
-                        }
-                        *reinterpret_cast<bf16x4*>(erow + (fbp * 32 + 8 * j + 4 * hh) * 2) = v;
+                    for (int e = 0; e < 4; ++e) {
+                        const float a = (float)(bf16_t)acc[mt][tt][e];
+                        const float b = (float)(bf16_t)acc[mt + 4][tt][e];
+                        const float s = (float)(bf16_t)silu_f32(a);
+                        v[e] = (bf16_t)(s * b);
                     }
+                    *reinterpret_cast<bf16x4*>(erow + (mt * 16 + 4 * g4) * 2) = v;
+                }
             }
 #pragma unroll
             for (int it = 0; it < 8; ++it) {
@@ -208,76 +214,74 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x16 (&acc)
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int tbl = 0; tbl < 2; ++tbl) {
-            const int tb = half * 2 + tbl;
-            const int row = min(row0 + wt * 128 + tb * 32 + l32, p.m - 1);
+        for (int nt = 0; nt < 4; ++nt) {
+            const int tt = half * 4 + nt;
+            const int row = min(row0 + wt * 128 + tt * 16 + l16, p.m - 1);
             const float4* cs = reinterpret_cast<const float4*>(p.cs + (int64_t)row * (D / 2));
-            unsigned char* erow = epi + (tbl * 32 + l32) * kEpiStride;
+            unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
             float rnorm = 1.f;
             if (EXTRA) {
                 if (bias) {
 #pragma unroll
-                    for (int fb = 0; fb < 4; ++fb)
+                    for (int mt = 0; mt < 8; ++mt) {
+                        const bf16x4 bv =
+                            *reinterpret_cast<const bf16x4*>(bias + mt * 16 + 4 * g4);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const bf16x4 bv =
-                                *reinterpret_cast<const bf16x4*>(bias + fb * 32 + 8 * j + 4 * hh);
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[fb][tb][4 * j + e] += (float)bv[e];
-                        }
+                        for (int e = 0; e < 4; ++e) acc[mt][tt][e] += (float)bv[e];
+                    }
                 }
                 if (gain) {
-                    // the lane holds 64 of the token's 128 features, lane ^ 32 the other 64
+                    // the lane holds 32 of the token's 128 features, lanes ^ 16, ^ 32 and
+                    // ^ 48 the others
                     float ss = 0.f;
 #pragma unroll
-                    for (int fb = 0; fb < 4; ++fb)
+                    for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) ss += acc[fb][tb][r] * acc[fb][tb][r];
+                        for (int e = 0; e < 4; ++e) ss += acc[mt][tt][e] * acc[mt][tt][e];
+                    ss += __shfl_xor(ss, 16);
                     ss += __shfl_xor(ss, 32);
                     rnorm = 1.0f / sqrtf(ss * (1.0f / D) + p.norm_eps);
                 }
             }
 #pragma unroll
-            for (int fbp = 0; fbp < 2; ++fbp)
+            for (int mt = 0; mt < 4; ++mt) {
+                const int i0 = mt * 16 + 4 * g4;   // pair index of element 0
+                float a[4], b[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i0 = fbp * 32 + 8 * j + 4 * hh;   // pair index of element 0
-                    float a[4], b[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        a[e] = acc[fbp][tb][4 * j + e];
-                        b[e] = acc[fbp + 2][tb][4 * j + e];
-                    }
-                    if (EXTRA && gain) {
-                        const bf16x4 ga = *reinterpret_cast<const bf16x4*>(gain + i0);
-                        const bf16x4 gb = *reinterpret_cast<const bf16x4*>(gain + i0 + D / 2);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            a[e] = a[e] * rnorm * (float)ga[e];
-                            b[e] = b[e] * rnorm * (float)gb[e];
-                        }
-                    }
-                    if (rotate) {
-                        const float4 t0 = cs[i0 / 2], t1 = cs[i0 / 2 + 1];
-                        const float c[4] = {t0.x, t0.z, t1.x, t1.z};
-                        const float s[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float ra = a[e] * c[e] - b[e] * s[e];
-                            const float rb = b[e] * c[e] + a[e] * s[e];
-                            a[e] = ra;
-                            b[e] = rb;
-                        }
-                    }
-                    bf16x4 va, vb;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        va[e] = (bf16_t)a[e];
-                        vb[e] = (bf16_t)b[e];
-                    }
-                    *reinterpret_cast<bf16x4*>(erow + i0 * 2) = va;
-                    *reinterpret_cast<bf16x4*>(erow + (i0 + D / 2) * 2) = vb;
+                for (int e = 0; e < 4; ++e) {
+                    a[e] = acc[mt][tt][e];
+                    b[e] = acc[mt + 4][tt][e];
                 }
+                if (EXTRA && gain) {
+                    const bf16x4 ga = *reinterpret_cast<const bf16x4*>(gain + i0);
+                    const bf16x4 gb = *reinterpret_cast<const bf16x4*>(gain + i0 + D / 2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        a[e] = a[e] * rnorm * (float)ga[e];
+                        b[e] = b[e] * rnorm * (float)gb[e];
+                    }
+                }
+                if (rotate) {
+                    const float4 t0 = cs[i0 / 2], t1 = cs[i0 / 2 + 1];
+                    const float c[4] = {t0.x, t0.z, t1.x, t1.z};
+                    const float s[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float ra = a[e] * c[e] - b[e] * s[e];
+                        const float rb = b[e] * c[e] + a[e] * s[e];
+                        a[e] = ra;
+                        b[e] = rb;
+                    }
+                }
+                bf16x4 va, vb;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    va[e] = (bf16_t)a[e];
+                    vb[e] = (bf16_t)b[e];
+                }
+                *reinterpret_cast<bf16x4*>(erow + i0 * 2) = va;
+                *reinterpret_cast<bf16x4*>(erow + (i0 + D / 2) * 2) = vb;
+            }
         }
         // the wave's own 64 tokens x 256 B, now 16 B per lane and 256 B per row
 #pragma unroll
@@ -302,7 +306,7 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
     const int wt = wave >> 1, wf = wave & 1;
 
     // ---- which tile --------------------------------------------------------------
@@ -370,48 +374,46 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
     };
 
     // ---- read side -----------------------------------------------------------------
-    // operand of row r, sub-step ks: chunk ks*2 + hh at position chunk ^ ((r >> 2) & 3)
-    int off_x[2], off_w[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        const int pos = (ks * 2 + hh) ^ ((l32 >> 2) & 3);
-        off_x[ks] = (wt * 128 + l32) * kRowBytes + pos * 16;
-        off_w[ks] = kOperandBytes + (wf * 128 + l32) * kRowBytes + pos * 16;
-    }
-    bf16x8 fx[2][4], fw[2][4];
-    auto load_frags = [&](int stage, int ks, int slot) {
-        const unsigned char* sb = smem + stage * kStageBytes;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            fw[slot][b] = *reinterpret_cast<const bf16x8*>(sb + off_w[ks] + b * 32 * kRowBytes);
-            fx[slot][b] = *reinterpret_cast<const bf16x8*>(sb + off_x[ks] + b * 32 * kRowBytes);
-        }
+    // operand of row r (16 rows per MFMA block, contraction chunk g4 of the stage's four):
+    // position g4 ^ ((r >> 2) & 3)
+    const int pos = g4 ^ ((l16 >> 2) & 3);
+    const int off_x = (wt * 128 + l16) * kRowBytes + pos * 16;
+    const int off_w = kOperandBytes + (wf * 128 + l16) * kRowBytes + pos * 16;
+    bf16x8 fw[8], fx[2][4];   // [feature block], [half of the token blocks][token block]
+    auto ld_w = [&](int stage, int mt) {
+        return *reinterpret_cast<const bf16x8*>(smem + stage * kStageBytes + off_w +
+                                                mt * 16 * kRowBytes);
+    };
+    auto ld_x = [&](int stage, int nt) {
+        return *reinterpret_cast<const bf16x8*>(smem + stage * kStageBytes + off_x +
+                                                nt * 16 * kRowBytes);
     };
 
-    f32x16 acc[4][4];   // [feature block][token block]
+    f32x4 acc[8][8];   // [feature block][token block]
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
+    for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
+        for (int nt = 0; nt < 8; ++nt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[fb][tb][r] = 0.f;
-    // 16 MFMAs of one contraction sub-step.  One fill instruction goes out after every
-    // fourth MFMA (half a stage per sub-step), so the memory pipeline sees a steady
-    // trickle instead of a burst that stalls the wave; the operands of the next
-    // sub-step (stage lstage, sub-step lks) are read from LDS in the same rhythm,
-    // two per four MFMAs, into the other register slot
-    auto mfma16 = [&](int slot, int fill_stage, int j0, int adv, int lstage, int lks) {
-        const unsigned char* sb = smem + lstage * kStageBytes;
+            for (int r = 0; r < 4; ++r) acc[mt][nt][r] = 0.f;
+    // Half a stage: 32 MFMAs on token blocks 4 half .. + 4, one fill instruction after every
+    // eighth (half a stage's fills per half, so the memory pipeline sees a steady trickle
+    // instead of a burst that stalls the wave).  The operands of the next half are read from
+    // LDS in the same rhythm: token blocks 4..7 of this stage, or token blocks 0..3 of stage
+    // lstage and its feature blocks, each right after its last use.
+    auto mfma32 = [&](int half, int fill_stage, int j0, int adv, int lstage) {
 #pragma unroll
-        for (int fb = 0; fb < 4; ++fb) {
-            fw[slot ^ 1][fb] = *reinterpret_cast<const bf16x8*>(sb + off_w[lks] + fb * 32 * kRowBytes);
-            fx[slot ^ 1][fb] = *reinterpret_cast<const bf16x8*>(sb + off_x[lks] + fb * 32 * kRowBytes);
+        for (int n = 0; n < 4; ++n) {
+            fx[half ^ 1][n] = ld_x(lstage, half == 0 ? 4 + n : n);
 #pragma unroll
-            for (int tb = 0; tb < 4; ++tb)
-                acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[slot][fb], fx[slot][tb],
-                                                                      acc[fb][tb], 0, 0, 0);
+            for (int mt = 2 * n; mt < 2 * n + 2; ++mt) {
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    mfma_16x16x32(acc[mt][4 * half + nt], fw[mt], fx[half][nt]);
+                if (half == 1) fw[mt] = ld_w(lstage, mt);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            issue_one(fill_stage, j0 + (fb >> 1), fb & 1, adv);
+            issue_one(fill_stage, j0 + (n >> 1), n & 1, adv);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -431,23 +433,27 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
     }
     wait_vm<8 * (NS - 3) + 4>();  // stage 0 of this wave has landed
     __syncthreads();              // ... and everyone's
-    load_frags(0, 0, 0);
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt) fw[mt] = ld_w(0, mt);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) fx[0][nt] = ld_x(0, nt);
     int st_cur = 0;               // t mod NS
     for (int t = 0; t < n_k; ++t) {
         const int st_next = st_cur + 1 == NS ? 0 : st_cur + 1;
         const int st_fill = st_cur == 0 ? NS - 1 : st_cur - 1;          // (t + NS - 1) mod NS
         const int st_fill_b = st_fill == 0 ? NS - 1 : st_fill - 1;      // (t + NS - 2) mod NS
-        mfma16(0, st_fill_b, 2, t + NS - 1 < n_k ? BK : 0, st_cur, 1);
+        mfma32(0, st_fill_b, 2, t + NS - 1 < n_k ? BK : 0, st_cur);
         wait_vm<8 * (NS - 3)>();  // stage t+1 has landed; the younger ones stay in flight
         __syncthreads();          // ... for everyone; and everyone is done with stage t-1
-        mfma16(1, st_fill, 0, t + NS < n_k ? BK : 0, st_next, 0);
+        mfma32(1, st_fill, 0, t + NS < n_k ? BK : 0, st_next);
         st_cur = st_next;
     }
     wait_vm<0>();                 // the ring's trailing fills must not land in the staging
+    acc_settle();
 
     // ---- epilogue -----------------------------------------------------------------------
     TileCtx ctx;
-    ctx.lane = lane; ctx.wave = wave; ctx.hh = hh; ctx.l32 = l32; ctx.wt = wt; ctx.wf = wf;
+    ctx.lane = lane; ctx.wave = wave; ctx.g4 = g4; ctx.l16 = l16; ctx.wt = wt; ctx.wf = wf;
     ctx.split = split; ctx.ft = ft; ctx.mat = mat; ctx.feat0 = feat0; ctx.row0 = row0;
     ctx.heads_out = heads_out; ctx.out = out;
     tile_epilogue<MODE, EXTRA>(p, acc, ctx, smem);
@@ -467,8 +473,8 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
 // r .. r + 15, one logical chunk) must differ in (r & 1, position) - with c ^ (r & 7) rows r
 // and r + 8 met in one bank group and every read took two passes (SQ_LDS_BANK_CONFLICT).
 //
-// A step is 64 MFMAs per wave in four quarters; quarter q multiplies the wave's four
-// feature blocks by its token block q for all four 16-wide sub-steps.  The feature
+// A step is 128 MFMAs per wave in four quarters; quarter q multiplies the wave's eight
+// feature blocks by its token blocks 2 q, 2 q + 1 for both 32-wide sub-steps.  The feature
 // operands of a whole step live in registers (loaded during the second half of the
 // previous step), so the W units of step T are free again when T begins and are refilled
 // with step T + 2 during its first two quarters; X_q is free after quarter q - 1 and is
@@ -485,7 +491,7 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
     const int wt = wave >> 1, wf = wave & 1;
 
     // ---- which tile (as above) ---------------------------------------------------------
@@ -553,29 +559,30 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     };
 
     // ---- read side: byte offsets of the lane's operand pieces --------------------------
-    // feature block fb: base_w + fb * 4096; token quarter q: base_x + q * 8192
-    uint32_t base_w[2][4], base_x[2][4];
+    // sub-step ks (32 of the contraction: chunks 4 ks + g4); feature block mt (16 rows):
+    // base_w + mt * 2048; token block nt of quarter q: base_x + q * 8192 + nt * 2048
+    uint32_t base_w[2][2], base_x[2][2];
 #pragma unroll
     for (int par = 0; par < 2; ++par)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const uint32_t swz = (uint32_t)(((2 * ks + hh) ^ ((l32 >> 1) & 7)) * 16);
-            base_w[par][ks] = par * 8 * kUnitBytes + 2 * wf * kUnitBytes + l32 * 128 + swz;
-            base_x[par][ks] = par * 8 * kUnitBytes + 4 * kUnitBytes + (wt * 32 + l32) * 128 + swz;
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint32_t swz = (uint32_t)(((4 * ks + g4) ^ (l16 >> 1)) * 16);
+            base_w[par][ks] = par * 8 * kUnitBytes + 2 * wf * kUnitBytes + l16 * 128 + swz;
+            base_x[par][ks] = par * 8 * kUnitBytes + 4 * kUnitBytes + (wt * 32 + l16) * 128 + swz;
         }
     auto ld = [&](uint32_t off) { return *reinterpret_cast<const bf16x8*>(smem + off); };
 
-    bf16x8 fw01[2][4][2];   // [step parity][feature block][sub-step 0, 1]
-    bf16x8 fw23[4][2];      // [feature block][sub-step 2, 3]
-    bf16x8 fx[2][4];        // [quarter parity][sub-step]
+    bf16x8 fw0[2][8];   // [step parity][feature block], sub-step 0
+    bf16x8 fw1[8];      // [feature block], sub-step 1
+    bf16x8 fx[2][2][2]; // [quarter parity][sub-step][token block]
 
-    f32x16 acc[4][4];   // [feature block][token block]
+    f32x4 acc[8][8];   // [feature block][token block]
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
+    for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
+        for (int nt = 0; nt < 8; ++nt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[fb][tb][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[mt][nt][r] = 0.f;
 
     // ---- prologue: steps 0 and 1 requested; operands of step 0, quarter 0 loaded --------
 #pragma unroll
@@ -593,34 +600,33 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     wait_vm<22>();     // W0..W3 and X0 of step 0 (the first ten of 32 instructions) landed
     __syncthreads();
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb) {
-        fw01[0][fb][0] = ld(base_w[0][0] + fb * 4096);
-        fw01[0][fb][1] = ld(base_w[0][1] + fb * 4096);
-        fw23[fb][0] = ld(base_w[0][2] + fb * 4096);
-        fw23[fb][1] = ld(base_w[0][3] + fb * 4096);
+    for (int mt = 0; mt < 8; ++mt) {
+        fw0[0][mt] = ld(base_w[0][0] + mt * 2048);
+        fw1[mt] = ld(base_w[0][1] + mt * 2048);
     }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fx[0][ks] = ld(base_x[0][ks]);
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) fx[0][ks][nt] = ld(base_x[0][ks] + nt * 2048);
     __syncthreads();   // everybody holds step 0's feature operands: its W units may be refilled
 
-    // One quarter: 16 MFMAs in four groups (sub-step outer, feature block inner) on token
-    // block Q with the token operands fx[Q & 1]; one fill instruction after every group.
+    // One quarter: 32 MFMAs in four groups (sub-step outer, token block inner, eight feature
+    // blocks each) on token blocks 2 Q, 2 Q + 1; one fill instruction after every group.
     // The LDS reads of the quarter (token operands of the next quarter; in quarter 2 the
-    // sub-step 0, 1 feature operands of the next step into the other register set; in
-    // quarter 3 the sub-step 2, 3 ones, each right after its last use - which is why
-    // quarter 3 runs sub-steps 2, 3 first) all go out in the first three groups, so that
-    // they have returned when the barrier that ends the quarter waits for them.
-    // PAR = parity of the step.
+    // sub-step 0 feature operands of the next step into the other register set; in quarter 3
+    // the sub-step 1 ones, each right after its last use - which is why quarter 3 runs
+    // sub-step 1 first) all go out in the first three groups, so that they have returned when
+    // the barrier that ends the quarter waits for them.  PAR = parity of the step.
 #define PKV_QUARTER(PAR, Q, ADV)                                                          \
     {                                                                                     \
         _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_) {                                \
-            const int ks = (Q) == 3 ? (g_ + 2) & 3 : g_;                                  \
-            _Pragma("unroll") for (int fb = 0; fb < 4; ++fb) {                            \
-                const bf16x8 a_ = ks < 2 ? fw01[PAR][fb][ks] : fw23[fb][ks - 2];          \
-                acc[fb][Q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, fx[(Q) & 1][ks], \
-                                                                     acc[fb][Q], 0, 0, 0); \
-                if ((Q) == 3 && ks >= 2)   /* last use: take step T + 1's operand */      \
-                    fw23[fb][ks - 2] = ld(base_w[(PAR) ^ 1][ks] + fb * 4096);             \
+            const int ks = (Q) == 3 ? 1 - (g_ >> 1) : g_ >> 1;                            \
+            const int nt = g_ & 1;                                                        \
+            _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                            \
+                const bf16x8 a_ = ks == 0 ? fw0[PAR][mt] : fw1[mt];                       \
+                mfma_16x16x32(acc[mt][2 * (Q) + nt], a_, fx[(Q) & 1][ks][nt]);            \
+                if ((Q) == 3 && g_ == 1)   /* last use: take step T + 1's operand */      \
+                    fw1[mt] = ld(base_w[(PAR) ^ 1][1] + mt * 2048);                       \
             }                                                                             \
             __builtin_amdgcn_sched_barrier(0);                                            \
             /* fill: quarters 0, 1 -> feature units 2 Q, 2 Q + 1; 2, 3 -> token units */  \
@@ -629,16 +635,17 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
             /* token operands of the next quarter: 2, 1, 1, 0 per group */                \
             _Pragma("unroll") for (int n_ = 0; n_ < 4; ++n_) {                            \
                 if ((n_ < 2 ? 0 : n_ - 1) != g_) continue;                                \
-                if ((Q) < 3) fx[((Q) + 1) & 1][n_] = ld(base_x[PAR][n_] + ((Q) + 1) * 8192); \
-                else fx[0][n_] = ld(base_x[(PAR) ^ 1][n_]);                               \
+                const int k2 = n_ >> 1, t2 = n_ & 1;                                      \
+                if ((Q) < 3)                                                              \
+                    fx[((Q) + 1) & 1][k2][t2] =                                           \
+                        ld(base_x[PAR][k2] + ((Q) + 1) * 8192 + t2 * 2048);               \
+                else fx[0][k2][t2] = ld(base_x[(PAR) ^ 1][k2] + t2 * 2048);               \
             }                                                                             \
-            /* quarter 2: feature operands of sub-steps 0, 1 of the next step: blocks     \
-               0 | 1, 2 | 3 | - per group */                                              \
+            /* quarter 2: sub-step 0 feature operands of the next step: 2, 4, 2, 0 */     \
             if ((Q) == 2) {                                                               \
-                _Pragma("unroll") for (int fb = 0; fb < 4; ++fb) {                        \
-                    if ((fb == 0 ? 0 : fb == 3 ? 2 : 1) != g_) continue;                  \
-                    fw01[(PAR) ^ 1][fb][0] = ld(base_w[(PAR) ^ 1][0] + fb * 4096);        \
-                    fw01[(PAR) ^ 1][fb][1] = ld(base_w[(PAR) ^ 1][1] + fb * 4096);        \
+                _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                        \
+                    if ((mt < 2 ? 0 : mt < 6 ? 1 : 2) != g_) continue;                    \
+                    fw0[(PAR) ^ 1][mt] = ld(base_w[(PAR) ^ 1][0] + mt * 2048);            \
                 }                                                                         \
             }                                                                             \
             __builtin_amdgcn_sched_barrier(0);                                            \
@@ -661,9 +668,10 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 #undef PKV_STEP
 #undef PKV_QUARTER
     wait_vm<0>();                 // the ring's trailing fills must not land in the staging
+    acc_settle();
 
     TileCtx ctx;
-    ctx.lane = lane; ctx.wave = wave; ctx.hh = hh; ctx.l32 = l32; ctx.wt = wt; ctx.wf = wf;
+    ctx.lane = lane; ctx.wave = wave; ctx.g4 = g4; ctx.l16 = l16; ctx.wt = wt; ctx.wf = wf;
     ctx.split = split; ctx.ft = ft; ctx.mat = mat; ctx.feat0 = feat0; ctx.row0 = row0;
     ctx.heads_out = heads_out; ctx.out = out;
     tile_epilogue<MODE, EXTRA>(p, acc, ctx, smem);
