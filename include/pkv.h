@@ -25,7 +25,7 @@
  *   pkv_workspace_bytes(), 256-byte aligned, and may be reused between calls
  *   on the same stream.  Calls that can be in flight at the same time
  *   (different streams) need workspaces of their own: the kernels keep
- *   partial results, flags and work counters there.
+ *   partial results and work counters there.
  * Layout: token-major, contiguous.  Keys/values [tokens, n_kv_heads,
  *   head_dim]; queries/outputs [rows, n_q_heads, head_dim]; hidden states
  *   [tokens, hidden]; weights [out_features, hidden] (row-major, so both
@@ -59,15 +59,14 @@
  *   head_dim * (n_keys rounded up to 64) * 2 < 2^32 and rows * n_q_heads
  *   (query tokens * n_q_heads) < 2^31; beyond that they return
  *   PKV_ERR_UNSUPPORTED.
- * Environment: three variables change HOW pkv_sparse_row_attn (bf16, head_dim
+ * Environment: two variables change HOW pkv_sparse_row_attn (bf16, head_dim
  *   128) works, never what it computes; they exist for measurements and
- *   tests.  PKV_ATTN_WAVES=4 (read once per process): workgroups of four
- *   waves instead of eight.  PKV_ATTN_VT=1 / 0 (read at every call): always
- *   / never make a transposed copy of the value cache in the workspace
- *   before the main kernel (unset: decided by problem size).
- *   PKV_ATTN_RANGES=n (read once): process the keys of every row tile in n
- *   ranges (unset: decided by problem size).  Workspace sizes do not depend
- *   on the first two; set the third before asking for sizes.
+ *   tests.  PKV_ATTN_VT=1 / 0 (read at every call): always / never make a
+ *   transposed copy of the value cache in the workspace before the main
+ *   kernel (unset: decided by problem size).  PKV_ATTN_RANGES=n (read once):
+ *   process the keys of every row tile in n ranges (unset: decided by problem
+ *   size).  Workspace sizes do not depend on the first; set the second before
+ *   asking for sizes.
  */
 #ifndef PKV_H
 #define PKV_H

@@ -479,7 +479,7 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
 // previous step), so the W units of step T are free again when T begins and are refilled
 // with step T + 2 during its first two quarters; X_q is free after quarter q - 1 and is
 // refilled in quarters 2 and 3.  One barrier per quarter, two fill instructions per wave
-// and unit, one fill instruction every four MFMAs, as in the kernel above.
+// and unit, one fill instruction every eight MFMAs, as in the kernel above.
 // Needs an even number (>= 2) of steps per split.
 constexpr int kUnitBytes = 64 * 128;
 constexpr int kSlabLdsBytes = 16 * kUnitBytes;

@@ -154,18 +154,11 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
 
     // work item: kv head (fastest, so that a head stays on one XCD when
     // hkv == 8), key split, row tile (heaviest tiles first)
-    // normally one work item per workgroup; the repair pass (p.flags set) is launched
-    // with a small grid whose workgroups walk over all items and skip the unmarked ones;
-    // the count of marked tiles sits behind the flags, and is zero almost always
-    if (p.flags && p.flags[p.n_tiles * p.hkv] == 0) return;
-    for (int wg0 = blockIdx.x; wg0 < p.n_tiles * p.n_splits * p.hkv; wg0 += gridDim.x) {
-    int wg = wg0;
+    int wg = blockIdx.x;
     const int g = wg % p.hkv;
     wg /= p.hkv;
     const int split = wg % p.n_splits;
     const int tile = p.n_tiles - 1 - wg / p.n_splits;
-    // repair pass: only the tiles that the pipelined kernel marked
-    if (p.flags && p.flags[tile * p.hkv + g] == 0) continue;
 
     // ---- my two columns ----------------------------------------------------
     int limit[2], row[2], head[2];
@@ -216,9 +209,6 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
 
     float m_run[2] = {-INFINITY, -INFINITY};
     float l_run[2] = {0.f, 0.f};
-    // state at the context boundary (p.ctx_keys, a multiple of the key tile), for the
-    // log-sum-exp over the context keys alone; NaN marks "boundary not reached"
-    float m_ctx[2] = {0.f, 0.f}, l_ctx[2] = {-1.f, -1.f};
     f32x16 o_acc[DB][2];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -240,17 +230,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
             stage_k[i] = *reinterpret_cast<const uint4*>(
                 p.k + ((int64_t)kk * p.hkv + g) * D + dch * 8);
             if (kPV) {
-                if (p.v) {
-                    // no V^T copy was made (the pipelined kernel read the cache as it is):
-                    // the same piece of the value row, transposed on its way into LDS.  Rows
-                    // past the cache repeat its last row; their probabilities are zero.
-                    stage_v[i] = *reinterpret_cast<const uint4*>(
-                        p.v + ((int64_t)kk * p.hkv + g) * D + dch * 8);
-                } else {
-                    const int d = c / (kBN / 8), kch = c % (kBN / 8);
-                    stage_v[i] = *reinterpret_cast<const uint4*>(
-                        p.vt + ((int64_t)g * D + d) * p.n_pad + t0 + kch * 8);
-                }
+                const int d = c / (kBN / 8), kch = c % (kBN / 8);
+                stage_v[i] = *reinterpret_cast<const uint4*>(
+                    p.vt + ((int64_t)g * D + d) * p.n_pad + t0 + kch * 8);
             }
         }
     };
@@ -262,16 +244,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
             *reinterpret_cast<uint4*>(k_lds + buf * L::kElems + key * L::kStride + dch * 8) =
                 stage_k[i];
             if (kPV) {
-                if (p.v) {
-                    const bf16x8 e = __builtin_bit_cast(bf16x8, stage_v[i]);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        v_lds[buf * L::vElems + (dch * 8 + j) * L::vStride + key] = e[j];
-                } else {
-                    const int d = c / (kBN / 8), kch = c % (kBN / 8);
-                    *reinterpret_cast<uint4*>(v_lds + buf * L::vElems + d * L::vStride + kch * 8) =
-                        stage_v[i];
-                }
+                const int d = c / (kBN / 8), kch = c % (kBN / 8);
+                *reinterpret_cast<uint4*>(v_lds + buf * L::vElems + d * L::vStride + kch * 8) =
+                    stage_v[i];
             }
         }
     };
@@ -374,13 +349,6 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
                 }
         }
 
-        if (p.lse_ctx && t0 + kBN == p.ctx_keys) {
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                m_ctx[cb] = m_run[cb];
-                l_ctx[cb] = l_run[cb];
-            }
-        }
         if (it + 1 < n_iter) store_tile(buf ^ 1);
         __syncthreads();
     }
@@ -413,12 +381,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_mfma_kernel(AttnParams p) {
             }
             if (p.lse && hh == 0)
                 p.lse[colg] = m_run[cb] * p.scale + logf(l_run[cb]);
-            if (p.lse_ctx && hh == 0)   // tiles that end below the boundary: all they saw
-                p.lse_ctx[colg] = l_ctx[cb] < 0.f ? m_run[cb] * p.scale + logf(l_run[cb])
-                                                  : m_ctx[cb] * p.scale + logf(l_ctx[cb]);
         }
-    }
-    __syncthreads();   // LDS and s_red are reused by the next work item
     }
 }
 
@@ -462,17 +425,15 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(
     const bf16_t* __restrict__ v, bf16_t* __restrict__ vt, int n_keys, int n_pad,
     int hkv, int d, int* zero, int n_zero) {
     __shared__ bf16_t tile[64][64 + 2];
-    // this pre-pass also clears what the attention kernel expects at zero: the count of
-    // tiles marked for the repair pass, the work-queue counters and, when the keys are
-    // split, the marks themselves
+    // this pre-pass also clears the work-queue counters of the attention kernel
     if (zero && blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
     transpose_v_tile(v, vt, n_keys, n_pad, hkv, d, blockIdx.x, blockIdx.y, tile);
 }
 
-// What the pipelined kernel expects at zero when no V^T pre-pass runs before it.
-__global__ __launch_bounds__(256) void attn_clear_kernel(int* zero, int n_zero) {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n_zero; i += gridDim.x * 256) zero[i] = 0;
+// The work-queue counters of the pipelined kernel when no V^T pre-pass runs before it.
+__global__ __launch_bounds__(64) void attn_clear_kernel(int* zero, int n_zero) {
+    for (int i = threadIdx.x; i < n_zero; i += 64) zero[i] = 0;
 }
 
 bool mfma_attn_supported(const pkv_layer_cfg& cfg) {
@@ -483,20 +444,15 @@ bool mfma_attn_supported(const pkv_layer_cfg& cfg) {
 
 int64_t pad64(int64_t n) { return (n + 63) & ~(int64_t)63; }
 
-// workspace: V^T [hkv, D, n_pad] (rounded up to 256 bytes), then one int per
-// (row tile, kv head) for the repair pass, the count of marked tiles, and one work-queue
-// counter per kv head
+// workspace: V^T [hkv, D, n_pad] (rounded up to 256 bytes), then one work-queue counter per
+// kv head
 size_t attn_vt_bytes(const pkv_layer_cfg& cfg, int64_t n_keys) {
     const size_t b = (size_t)cfg.n_kv_heads * cfg.head_dim * pad64(n_keys) * sizeof(bf16_t);
     return (b + 255) & ~(size_t)255;
 }
-size_t attn_flag_bytes(const pkv_layer_cfg& cfg, int64_t m) {
-    const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
-    // + marked count + one work-queue counter per kv head
-    const size_t b = ((size_t)ceil_div(m, bm) * cfg.n_kv_heads + 1 + cfg.n_kv_heads) * sizeof(int);
-    return (b + 255) & ~(size_t)255;
+size_t attn_queue_bytes(const pkv_layer_cfg& cfg) {
+    return ((size_t)cfg.n_kv_heads * sizeof(int) + 255) & ~(size_t)255;
 }
-// partial results that a small kernel merges.
 constexpr int kMaxCtxRanges = 32;   // ranges per tile when a boundary is forced
 
 // ctx_keys > 0: a range boundary must sit exactly at ctx_keys (a multiple of 64), because
@@ -637,6 +593,12 @@ bool attn_plan_splits_at(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, in
     return false;
 }
 
+// a launch whose jobs all run at once, one per CU, needs no work queue
+bool attn_one_job_per_cu(const pkv_layer_cfg& cfg, int64_t m, int n_splits) {
+    const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
+    return ceil_div(m, bm) * cfg.n_kv_heads * n_splits <= attn_cu_count();
+}
+
 size_t attn_partial_bytes(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m,
                           int64_t ctx_keys = 0) {
     int n_splits, split_len;
@@ -652,7 +614,7 @@ size_t attn_partial_bytes(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m,
 
 template <int D, bool kPV>
 pkv_status launch_attn_mfma(const AttnParams& p, hipStream_t st) {
-    static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent  // per process; the attribute is per function
+    static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     auto kern = attn_mfma_kernel<D, kPV>;
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -661,8 +623,7 @@ pkv_status launch_attn_mfma(const AttnParams& p, hipStream_t st) {
             return PKV_ERR_LAUNCH;
         configured.store(true, std::memory_order_release);
     }
-    int64_t grid = (int64_t)p.n_tiles * p.n_splits * p.hkv;
-    if (p.flags && grid > 256) grid = 256;   // repair pass: one resident workgroup per CU
+    const int64_t grid = (int64_t)p.n_tiles * p.n_splits * p.hkv;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kAttnThreads), AttnLds<D>::bytes,
                        st, p);
     return launch_status();
@@ -673,7 +634,7 @@ pkv_status launch_attn_mfma(const AttnParams& p, hipStream_t st) {
 size_t sparse_row_attn_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m,
                                 int64_t ctx_keys) {
     if (!mfma_attn_supported(cfg)) return 0;
-    return attn_vt_bytes(cfg, n_keys) + attn_flag_bytes(cfg, m) +
+    return attn_vt_bytes(cfg, n_keys) + attn_queue_bytes(cfg) +
            attn_partial_bytes(cfg, n_keys, m, ctx_keys);
 }
 
@@ -726,26 +687,23 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
     if (mfma_attn_supported(cfg)) {
         const int n_pad = (int)pad64(n_keys);
         bf16_t* vt = (bf16_t*)ws;
-        int* const ints = reinterpret_cast<int*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys));
-        const int n_flags =
-            (int)ceil_div(m, 256 / (cfg.n_q_heads / cfg.n_kv_heads)) * cfg.n_kv_heads;
         int n_splits = 1, split_len = n_pad;
         if (lse_ctx_out)
             attn_plan_splits_at(cfg, n_keys, m, ctx_keys, &n_splits, &split_len);
         else
             attn_plan_splits(cfg, n_keys, m, &n_splits, &split_len);
-        // cleared by the pre-pass: marked count + queue counters, and the marks when split
-        int* zero = d == 128 ? (n_splits > 1 ? ints : ints + n_flags) : nullptr;
-        const int n_zero = (n_splits > 1 ? n_flags : 0) + 1 + cfg.n_kv_heads;
-        // The eight-wave pipelined kernel can transpose the values on their way out of LDS
-        // instead of reading a V^T copy made here.  Its loop then issues half as many bytes per
-        // LDS instruction and needs ~2 % more clocks (about 1 % more time at the clock the part
-        // grants: 131k keys x 26470 rows 21.6 -> 21.8 ms); the copy costs its bytes at ~5.5 TB/s
-        // plus a launch, and doing without it costs one small launch (a fill kernel for the
-        // counters that the pre-pass otherwise clears).  The copy is skipped when that is the
-        // cheaper side, which it is for everything but the largest launches (measured, copy ->
-        // no copy: 128 rows over 32k keys 106 -> 85 us, 1766 rows 487 -> 470 us, 6681 rows
-        // 1496 -> 1486 us, 13235 rows 2785 -> 2784 us).
+        // the work-queue counters, which a launch with no more jobs than CUs does without
+        int* queue = nullptr;
+        if (d == 128 && !attn_one_job_per_cu(cfg, m, n_splits))
+            queue = reinterpret_cast<int*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys));
+        // The pipelined kernel can transpose the values on their way out of LDS instead of
+        // reading a V^T copy made here.  Its loop then issues half as many bytes per LDS
+        // instruction and needs ~2 % more clocks (about 1 % more time at the clock the part
+        // grants: 131k keys x 26470 rows 21.6 -> 21.8 ms); the copy costs its bytes at
+        // ~5.5 TB/s plus a launch.  The copy is skipped when that is the cheaper side, which it
+        // is for everything but the largest launches (measured, copy -> no copy: 128 rows over
+        // 32k keys 106 -> 85 us, 1766 rows 487 -> 470 us, 6681 rows 1496 -> 1486 us, 13235
+        // rows 2785 -> 2784 us).
         bool nat_v = false;
         if (d == 128) {
             const int src = attn_dma128_v_source();
@@ -754,19 +712,21 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                 const double copy_us = 3.0 + (double)n_pad * cfg.n_kv_heads * d * 4.0 / 5.5e6;
                 const double main_us = 1.68 * (double)ceil_div(m, bm) * cfg.n_kv_heads *
                                        (double)(n_pad / 64) * (m > 768 ? 0.5 : 1.0) / 256.0;
-                nat_v = copy_us - 4.0 > 0.012 * main_us;
+                nat_v = copy_us - (queue ? 4.0 : 0.0) > 0.012 * main_us;
             } else {
                 nat_v = src == 0;
             }
         }
-        if (nat_v)
-            hipLaunchKernelGGL(attn_clear_kernel, dim3((unsigned)std::min(64, (n_zero + 255) / 256)),
-                               dim3(256), 0, st, zero, n_zero);
-        else
+        if (nat_v) {
+            if (queue)
+                hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue,
+                                   cfg.n_kv_heads);
+        } else {
             hipLaunchKernelGGL(transpose_v_kernel,
                                dim3((unsigned)(n_pad / 64), (unsigned)(cfg.n_kv_heads * d / 64)),
                                dim3(256), 0, st, (const bf16_t*)v_cache, vt, (int)n_keys, n_pad,
-                               cfg.n_kv_heads, d, zero, n_zero);
+                               cfg.n_kv_heads, d, queue, cfg.n_kv_heads);
+        }
         if (launch_status() != PKV_OK) return PKV_ERR_LAUNCH;
         AttnParams p = {};
         p.q = (const bf16_t*)q;
@@ -790,23 +750,17 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         p.scale = scale;
         p.scale_log2 = scale * 1.4426950408889634f;
         if (d != 128) return launch_attn_mfma<64, true>(p, st);
-        // pipelined kernel with a fixed softmax reference per column, then the exact
-        // kernel on the tiles it marked (normally none: those workgroups exit at once)
-        p.flags = ints;
-        p.queue = p.flags + p.n_tiles * p.hkv + 1;
+        p.queue = queue;
         p.dma_splits = n_splits;
         p.dma_split_len = split_len;
         p.lse_ctx = lse_ctx_out;
         p.ctx_keys = (int)ctx_keys;
         if (n_splits > 1) {
             p.part_o = reinterpret_cast<float*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys) +
-                                                attn_flag_bytes(cfg, m));
+                                                attn_queue_bytes(cfg));
             p.part_lse = p.part_o + (size_t)n_splits * m * cfg.n_q_heads * d;
         }
-        const pkv_status rc = launch_attn_dma128(p, st);
-        if (rc != PKV_OK) return rc;
-        // (p.v set: the exact kernel, too, reads the cache as it is for the tiles it redoes)
-        return launch_attn_mfma<128, true>(p, st);
+        return launch_attn_dma128(p, st);
     }
     const int block = d <= 64 ? 64 : (d <= 128 ? 128 : 256);
     const dim3 grid((unsigned)m, (unsigned)cfg.n_q_heads);

@@ -2,18 +2,23 @@
 // (Paper: Sec. 4.3 Stage II - complete recomputation, but only for the selected
 // tokens; Sec. 5.3 - this attention over the long cache dominates the cost.)
 //
-// Same tile, same LDS layout, same arithmetic as attn_dma128_kernel
-// (sparse_row_attn_dma.hip):
+// A workgroup owns 256 (row, head) columns of one kv head, 32 per wave, and everything is
+// computed transposed,
 //     S^T = K Q^T,   O^T += V^T P^T     (v_mfma_f32_32x32x16_bf16)
-// with a fixed softmax reference per column and marked tiles redone by the exact
-// kernel.  What differs is who does the work.  There a workgroup is 4 waves of 64
-// columns, one wave per SIMD, and the softmax arithmetic of a wave can only hide
-// under its own MFMAs: the counters show the matrix pipe busy 63 % of the time, the
-// rest is VALU work and waits of the one instruction stream.  Here a workgroup is 8
-// waves of 32 columns, two waves per SIMD (~250 registers each): while one wave
-// issues softmax arithmetic or waits for LDS, the other wave's MFMAs run.  The price
-// is LDS traffic - every wave reads the whole K and V^T tile for half the MFMAs, 1 KB
-// per MFMA instead of 512 B - which the 64-bank LDS of this part carries.
+// so that the probabilities go from the S^T accumulators straight into the second MFMA.
+// K and value tiles of 64 keys reach LDS by direct global->LDS loads, four stages deep; the
+// LDS tiles are unpadded, a 16-byte-chunk XOR swizzle (applied on the global address side of
+// the load) keeps the MFMA operand reads conflict free.  (The loads are inline asm because the
+// compiler would otherwise make every LDS read wait for all outstanding global->LDS loads.)
+// Two waves per SIMD (~250 registers each): while one wave issues softmax arithmetic or waits
+// for LDS, the other wave's MFMAs run.
+//
+// The softmax reference of a column is the maximum of its first 32 keys, fixed: no maximum, no
+// rescaling and no branch in the hot loop.  A job whose sums then leave the safe range is done
+// again on the spot with the true maxima of its columns (found by one more pass over its keys).
+// Until this was part of the kernel, marked tiles went to a second kernel, launched behind every
+// call: 5 us per call, and with the counters and marks it needed cleared beforehand 10 us of
+// the calls with no more jobs than CUs (637 rows over 4k keys 90 -> 84 us, 512 over 512 32 -> 27).
 //
 // A wave's sub-step (32 keys) is 16 MFMAs in a three-deep software pipeline:
 //     S^T(u+2) from K operands loaded one sub-step earlier,
@@ -93,11 +98,16 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
 
     // Work distribution: one workgroup per CU claims (kv head, row tile[, key range]) jobs,
     // heaviest first, from one counter per kv head; it prefers its home head (whose K/V its
-    // XCD's L2 holds) unless another head is kStealLag or more jobs behind.
+    // XCD's L2 holds) unless another head is kStealLag or more jobs behind.  A launch with no
+    // more jobs than CUs has no counters (p.queue null): every workgroup is one job.
     const int home = blockIdx.x % p.hkv;
     const int jobs_per_head = p.n_tiles * p.dma_splits;
+    bool first = true;
   for (;;) {
-    if (tid == 0) {
+    if (p.queue == nullptr) {
+        if (tid == 0) s_job = first ? home * jobs_per_head + blockIdx.x / p.hkv : -1;
+        first = false;
+    } else if (tid == 0) {
         int job = -1;
         // at most hkv failed claims: each one finds a head exhausted for good
         for (int attempt = 0; attempt <= p.hkv && job < 0; ++attempt) {
@@ -154,10 +164,7 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     for (int w = 0; w < NW; ++w) tile_max = max(tile_max, s_red[w]);
     const int key_end = min(tile_max + 1, n_keys_job);
     const int n_iter = __builtin_amdgcn_readfirstlane((key_end + kBN - 1) / kBN);
-    if (n_iter <= 0) {        // block-uniform: no valid row, or no row reaches this range
-        if (tid == 0 && p.dma_splits == 1) p.flags[tile * p.hkv + g] = 0;
-        continue;
-    }
+    if (n_iter <= 0) continue;   // block-uniform: no valid row, or no row reaches this range
     // sub-steps [0, u_unm) lie entirely at or below every limit of this wave; a wave without
     // a valid column has nothing to mask
     const int u_unm = __builtin_amdgcn_readfirstlane(lmin == 0x7fffffff ? 0x3fffffff
@@ -178,12 +185,8 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
         }
     }
 
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = -INFINITY, l_run;
     f32x16 o_acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
 
     // ---- global -> LDS ------------------------------------------------------------------------
     // K stage: key row r at byte r*256, 16-byte chunk c at c ^ (r & 15).  V^T stage: row d at
@@ -294,11 +297,11 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     f32x16 s_a, s_b;          // S^T of even / odd sub-steps
     bf16x8 pb_a[2], pb_b[2];  // P^T of even / odd sub-steps: [16-key half]
     bf16x8 ka[KC], va[2][DB];
-    float rs = 0.f;           // this lane's sum of the probabilities being produced
+    float rs;                 // this lane's sum of the probabilities being produced
     float msc;                // reference maximum times c2 (0 while it is -inf)
     constexpr float kGrow = 1.0e24f;   // ~2^80
-    float rs_max = 0.f;
-    float e_half = 0.f;
+    float rs_max;
+    float e_half;
     float x_next;
 
 #define W8_LOAD_KA(ST, H)                                                                \
@@ -397,6 +400,18 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
         __syncthreads();                                                                 \
     }
 
+    // Two attempts at most.  The first takes the maximum of a column's first 32 keys as its
+    // softmax reference; where probabilities leave the safe range because later scores lie far
+    // above it, the workgroup finds the true maxima of its columns and goes over its keys once
+    // more with those (cold: one 64-key tile at a time).
+    bool exact = false;
+    float l_tot;
+    for (;;) {
+        l_run = rs = rs_max = e_half = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
     // ---- prologue -------------------------------------------------------------------------
     W8_DMA_K(0)
     W8_DMA_V(0)
@@ -424,7 +439,7 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     }
     W8_LOAD_KA(1, 0)            // operands of S^T(2)
     // the reference of the column: the maximum of its first 32 keys, fixed from here on
-    {
+    if (!exact) {
         float mx = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -432,8 +447,8 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
             if (key <= limit) mx = fmaxf(mx, s_a[r]);
         }
         m_run = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        msc = (m_run == -INFINITY ? 0.f : m_run) * c2;
     }
+    msc = (m_run == -INFINITY ? 0.f : m_run) * c2;
     // P(0) in full
     W8_SM_PREP(s_a, 0, 0, true)
 #pragma unroll
@@ -465,6 +480,42 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     // accumulators are read
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
+    l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    {
+        const bool bad = !(rs_max < kGrow) || !(l_tot < 3.0e38f);
+        const int wave_bad = __any(bad) ? 1 : 0;   // over all lanes, before the branch
+        __syncthreads();                       // s_red held the tile limits so far
+        if (lane == 0) s_red[wave] = wave_bad;
+        __syncthreads();
+        int marked = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) marked |= s_red[w];
+        if (exact || !marked) break;           // block-uniform
+        exact = true;
+        float mx = -INFINITY;
+        for (int t = 0; t < n_iter; ++t) {
+            __syncthreads();      // nobody reads the stage that is about to be filled
+            W8_DMA_K(t)
+            wait_vm<0>();
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                W8_LOAD_KA(t & 3, h)
+                f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc) s = mfma32(ka[kc], qreg[kc], s);
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (t * kBN + h * 32 + 16 * (r / 8) + 8 * hh + (r % 8) <= limit)
+                        mx = fmaxf(mx, s[r]);
+            }
+        }
+        m_run = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        __syncthreads();
+    }
+    }   // second attempt
+
 #undef W8_DMA_K
 #undef W8_DMA_V
 #undef W8_DMA_PREP
@@ -479,27 +530,6 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
 #undef W8_TILE
 
     // ---- epilogue ------------------------------------------------------------------------------
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    {
-        const bool bad = !(rs_max < kGrow) || !(l_tot < 3.0e38f);
-        const int wave_bad = __any(bad) ? 1 : 0;   // over all lanes, before the branch
-        __syncthreads();                       // s_red held the tile limits so far
-        if (lane == 0) s_red[wave] = wave_bad;
-        __syncthreads();
-        if (tid == 0) {
-            int marked = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) marked |= s_red[w];
-            int* const flag = &p.flags[tile * p.hkv + g];
-            int* const count = &p.flags[p.n_tiles * p.hkv];   // behind the flags
-            if (p.dma_splits == 1) {
-                *flag = marked;
-                if (marked) atomicAdd(count, 1);
-            } else if (marked && atomicOr(flag, 1) == 0) {   // flags were cleared beforehand
-                atomicAdd(count, 1);
-            }
-        }
-    }
     if (valid) {
         const float inv = 1.f / l_tot;
         // A row whose keys all lie in the first range has its whole result in that range's
