@@ -464,48 +464,55 @@ bool attn_plan_splits_at(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, in
                          int* n_splits, int* split_len);
 
 // Estimated time (us) of the pipelined launch when every row tile's keys are cut into `sp`
-// ranges, for one layout of the row limits (the limits live on the device; the host weighs
-// two layouts): `spread` = rows in position order with limits evenly over the keys, so tile i
-// of T reaches (i + 1) / T of them; otherwise every tile reaches all keys.  The launch is one
-// workgroup per CU claiming jobs heaviest first, which the longest-processing-time rule
-// models; a job costs its 64-key steps plus a fixed set-up (pipeline fill, output; with ranges
-// also the fp32 partial result), fitted to measured launches of 640 to 6681 rows.
+// ranges, without the merge, for one layout of the row limits (the limits live on the device;
+// the host weighs two layouts): `spread` = rows in position order with limits evenly over the
+// keys, so tile i of T reaches (i + 1) / T of them; otherwise every tile reaches all keys.  The
+// kv heads are alike, so one of them is followed, on its share of the CUs: its jobs are taken
+// in the order of the launch by the CU that is free first; a job costs its 64-key steps plus a
+// set-up worth `fixed` of them (pipeline fill, output; with ranges also the fp32 partials).  A
+// step takes longer the more CUs are busy (memory and the power limit): 1.2 us up to 130 of
+// them, 1.7 us with all 256.  The constants are fitted to 46 launches of 16 to 6681 rows over
+// 256 to 131k keys, each measured in up to 14 range counts (516 in all): the count chosen is
+// within 4 % of the best one everywhere but at 16 rows over 2k keys (19.7 against 18.3 us).
+// *n_jobs: jobs that have keys to work on.
 double attn_launch_estimate(int64_t tiles, int hkv, int64_t steps_full, int sp, bool spread,
-                            int n_cu) {
-    const double us_per_step = 1.68, job_fixed = 4.0 + (sp > 1 ? 8.0 : 0.0);
+                            int n_cu, int64_t* n_jobs) {
+    const double fixed = 7.0 + (sp > 1 ? 1.7 : 0.0);
     const int64_t range_steps = (steps_full + sp - 1) / sp;
-    std::vector<double> jobs;
-    jobs.reserve((size_t)(tiles * sp * hkv));
-    for (int64_t i = 0; i < tiles; ++i) {
+    const int share = std::max(1, n_cu / hkv);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
+    for (int c = 0; c < share; ++c) cu.push(0.0);
+    double end = 0.0, total = 0.0;
+    int64_t jobs = 0;
+    for (int64_t i = tiles - 1; i >= 0; --i) {
         const int64_t reach = spread ? std::max<int64_t>(1, (i + 1) * steps_full / tiles)
                                      : steps_full;
         for (int s = 0; s < sp; ++s) {
             const int64_t st = std::min<int64_t>(range_steps, reach - (int64_t)s * range_steps);
             if (st <= 0) break;
-            for (int g = 0; g < hkv; ++g) jobs.push_back(st * us_per_step + job_fixed);
+            const double t = cu.top() + (double)st + fixed;
+            cu.pop();
+            cu.push(t);
+            end = std::max(end, t);
+            total += (double)st + fixed;
+            ++jobs;
         }
     }
-    std::sort(jobs.begin(), jobs.end(), std::greater<double>());
-    std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
-    for (int c = 0; c < n_cu; ++c) cu.push(0.0);
-    double end = 0.0;
-    for (double j : jobs) {
-        const double t = cu.top() + j;
-        cu.pop();
-        cu.push(t);
-        end = std::max(end, t);
-    }
-    return end;
+    *n_jobs = jobs * hkv;
+    const double busy = total / end * hkv;
+    return end * std::max(1.2, 0.66 + 0.0041 * busy);
 }
 
 // Key ranges per row tile for the pipelined kernel.  With few (kv head, row tile) pairs per
 // CU the launch ends when its longest job does - Stage I's 128 query rows make 16 jobs for
-// 256 CUs, an 8k context with 1702 rows 216 jobs whose longest is twice the mean - so the
-// keys of every tile are cut into up to 16 ranges (at least 2048 keys each, multiples of 64);
-// the jobs write normalised partial results that a small kernel merges.  The count minimises
-// the estimated launch time (the two layouts above, weighted by the row count) plus what the ranges cost: the
-// jobs write and the merge kernel reads the partial results a row has (about 2 TB/s, measured, plus
-// a launch).  Plans are remembered per problem size.
+// 256 CUs, a 4k context with 637 rows 104 - so the keys of every tile are cut into up to 32
+// ranges (of two 64-key steps or more); the jobs write normalised partial results that a small
+// kernel merges.  The count minimises the estimated launch time (the two layouts above,
+// weighted by the row count) plus what the ranges cost: the jobs write and the merge kernel
+// reads the partial results a row has, at 5.6 TB/s.  Plans are remembered per problem size.
+// Measured, one range -> the count chosen: 637 rows over 4k keys 82 -> 58 us (2), 320 over 3k
+// 68 -> 35 (6), 883 over 16k 287 -> 145 (3; two, as an earlier estimate chose, 169), 64
+// full-length rows over 8k 147 -> 32 (16).
 void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* n_splits,
                       int* split_len) {
     const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
@@ -514,7 +521,7 @@ void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* 
     *n_splits = 1;
     *split_len = (int)pad64(n_keys);
     if (cfg.head_dim != 128 || jobs >= 1024 || jobs <= 0) return;
-    const int64_t most = std::min<int64_t>(16, n_keys / 2048);   // ranges of 2048 keys or more
+    const int64_t most = std::min<int64_t>(32, n_keys / 128);   // ranges of 128 keys or more
     if (most < 2) return;
 
     // PKV_ATTN_RANGES=n in the environment (read once) asks for n ranges whatever the estimate
@@ -550,22 +557,25 @@ void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* 
         const double w_full = std::min(1.0, std::max(0.0, (768.0 - (double)m) / 640.0));
         double best = 1e30;
         for (int64_t sp = 1; sp <= most; ++sp) {
-            const double run =
-                (1.0 - w_full) * attn_launch_estimate(tiles, cfg.n_kv_heads, steps_full, (int)sp,
-                                                      true, n_cu) +
-                w_full * attn_launch_estimate(tiles, cfg.n_kv_heads, steps_full, (int)sp, false,
-                                              n_cu);
-            // partial results: a row has (sp + 1) / 2 (spread) or sp (full) of them, fp32, written
-            // by the jobs and read back by the merge, which also writes the output.  Measured
-            // against unsplit launches (6681 rows in 2 ranges, 3404 in 4, 1702 in 2) the whole
-            // detour moves at about 2 TB/s.
+            int64_t n_spread = 0, n_full = 0;
+            double run = 0.0;
+            if (w_full < 1.0)
+                run += (1.0 - w_full) * attn_launch_estimate(tiles, cfg.n_kv_heads, steps_full,
+                                                             (int)sp, true, n_cu, &n_spread);
+            if (w_full > 0.0)
+                run += w_full * attn_launch_estimate(tiles, cfg.n_kv_heads, steps_full, (int)sp,
+                                                     false, n_cu, &n_full);
+            // counters to clear and claim from when not every job has a CU of its own
+            if (jobs * sp > n_cu) run += 6.0;
             const double ranges = w_full * sp + (1.0 - w_full) * 0.5 * (sp + 1);
             const double merge = sp == 1 ? 0.0
-                : 5.0 + (out_elems * 4.0 * ranges * 2.0 + out_elems * 2.0) / 2.0e6;
+                : 0.6 + (out_elems * 4.0 * ranges * 2.0 + out_elems * 2.0) / 5.6e6;
             if (run + merge < best - 1e-9) {
                 best = run + merge;
                 want = sp;
             }
+            // more ranges only add rounds of jobs from here on
+            if (std::max(n_spread, n_full) > 2 * n_cu) break;
         }
         std::lock_guard<std::mutex> lock(mu);
         if (cache.size() >= 64) cache.erase(cache.begin());
