@@ -21,7 +21,8 @@ LIB_PATH = os.path.join(HERE, "libpkv.so")
 SOURCES = ["pkv_api.hip", "rope_restore.hip", "query_score.hip", "query_score_dma.hip",
            "topk_select.hip", "gather_qkv_proj.hip", "gather_qkv_proj_dma.hip",
            "scatter_kv.hip", "layer_glue.hip", "static_scratch.hip",
-           "sparse_row_attn.hip", "sparse_row_attn_dma.hip", "sparse_row_attn_w8.hip"]
+           "sparse_row_attn.hip", "sparse_row_attn_dma.hip", "sparse_row_attn_w8.hip",
+           "sparse_row_attn_w8n.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -33,8 +34,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # better with the results in ordinary VGPRs than with copies out of the accumulation
 # registers
 SOURCE_FLAGS = {
-    "sparse_row_attn_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "sparse_row_attn_w8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "sparse_row_attn_w8n.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "query_score_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 

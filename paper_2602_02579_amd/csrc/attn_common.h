@@ -36,11 +36,12 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// head_dim 128 attention proper: the software-pipelined kernel (sparse_row_attn_w8.hip), K / V
-// tiles brought into LDS by direct global->LDS loads, and the merge of its key ranges
-// (sparse_row_attn_dma.hip)
+// head_dim 128 attention proper: the software-pipelined kernels (sparse_row_attn_w8.hip,
+// sparse_row_attn_w8n.hip), K / V tiles brought into LDS by direct global->LDS loads, and the
+// merge of their key ranges (sparse_row_attn_dma.hip)
 pkv_status launch_attn_dma128(const AttnParams& p, hipStream_t st);
-pkv_status launch_attn_w8_main(const AttnParams& p, int n_cu, hipStream_t st);
+pkv_status launch_attn_w8_main(const AttnParams& p, hipStream_t st);
+pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st);
 // compute units of the current device (0: could not be asked)
 int attn_cu_count();
 // Where the pipelined kernel can take the values from: 1 = from a V^T copy made by a pre-pass

@@ -706,14 +706,13 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         int* queue = nullptr;
         if (d == 128 && !attn_one_job_per_cu(cfg, m, n_splits))
             queue = reinterpret_cast<int*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys));
-        // The pipelined kernel can transpose the values on their way out of LDS instead of
-        // reading a V^T copy made here.  Its loop then issues half as many bytes per LDS
-        // instruction and needs ~2 % more clocks (about 1 % more time at the clock the part
-        // grants: 131k keys x 26470 rows 21.6 -> 21.8 ms); the copy costs its bytes at
-        // ~5.5 TB/s plus a launch.  The copy is skipped when that is the cheaper side, which it
-        // is for everything but the largest launches (measured, copy -> no copy: 128 rows over
-        // 32k keys 106 -> 85 us, 1766 rows 487 -> 470 us, 6681 rows 1496 -> 1486 us, 13235
-        // rows 2785 -> 2784 us).
+        // The pipelined kernels can transpose the values on their way out of LDS instead of
+        // reading a V^T copy made here.  The loop then issues half as many bytes per LDS
+        // instruction and takes 2.0 % more time; the copy costs its bytes at ~5.5 TB/s plus a
+        // launch (with a work queue it also clears the counters, a launch that is needed
+        // anyway).  The copy is skipped when that is the cheaper side (measured, no copy ->
+        // copy: 3404 rows over 32k keys 801 -> 809 us, 6681 over 16k 745 -> 739, 6681 over
+        // 32k 1444 -> 1438, 13235 over 32k 2722 -> 2691, 26470 over 131k 21.5 -> 21.1 ms).
         bool nat_v = false;
         if (d == 128) {
             const int src = attn_dma128_v_source();
@@ -722,7 +721,7 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                 const double copy_us = 3.0 + (double)n_pad * cfg.n_kv_heads * d * 4.0 / 5.5e6;
                 const double main_us = 1.68 * (double)ceil_div(m, bm) * cfg.n_kv_heads *
                                        (double)(n_pad / 64) * (m > 768 ? 0.5 : 1.0) / 256.0;
-                nat_v = copy_us - (queue ? 4.0 : 0.0) > 0.012 * main_us;
+                nat_v = copy_us - (queue ? 4.0 : 0.0) > 0.020 * main_us;
             } else {
                 nat_v = src == 0;
             }

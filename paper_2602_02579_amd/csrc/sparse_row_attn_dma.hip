@@ -1,5 +1,5 @@
-// Step 5, head_dim 128, bf16: the launch of the pipelined attention kernel
-// (sparse_row_attn_w8.hip) and the merge of its key ranges.
+// Step 5, head_dim 128, bf16: the launch of the pipelined attention kernels
+// (sparse_row_attn_w8.hip, sparse_row_attn_w8n.hip) and the merge of their key ranges.
 #include <atomic>
 #include <cstdlib>
 
@@ -94,7 +94,8 @@ pkv_status launch_attn_dma128(const AttnParams& p, hipStream_t st) {
     if (n_cu == 0) return PKV_ERR_LAUNCH;
     // without counters every workgroup is one job, and all of them have to be launched
     if (!p.queue && (int64_t)p.n_tiles * p.dma_splits * p.hkv > n_cu) return PKV_ERR_LAUNCH;
-    const pkv_status rc = launch_attn_w8_main(p, n_cu, st);
+    // one job per workgroup, or a queue of them for one workgroup per CU: see the two kernels
+    const pkv_status rc = p.queue ? launch_attn_w8n_main(p, n_cu, st) : launch_attn_w8_main(p, st);
     if (rc != PKV_OK) return rc;
     if (p.dma_splits > 1)
         hipLaunchKernelGGL(attn_merge_splits_kernel,

@@ -1,4 +1,5 @@
-// Step 5, head_dim 128, bf16, eight waves per workgroup.
+// Step 5, head_dim 128, bf16, eight waves per workgroup, for launches with at most one job per
+// CU (more: sparse_row_attn_w8n.hip).
 // (Paper: Sec. 4.3 Stage II - complete recomputation, but only for the selected
 // tokens; Sec. 5.3 - this attention over the long cache dominates the cost.)
 //
@@ -48,7 +49,6 @@ constexpr int kThreads = NW * 64;
 constexpr int kStageK = kBN * D * 2;   // bytes: 64 keys x 256 B
 constexpr int kStageV = D * kBN * 2;   // bytes: 128 d-rows x 128 B
 constexpr int kLdsBytes = NS * (kStageK + kStageV);
-constexpr int kStealLag = 2;   // tiles another kv head must be behind before a workgroup helps it
 
 // 16 bytes per lane from global memory straight into LDS: lane i of the wave
 // writes LDS bytes [lds_base + 16 i, +16); lds_base must be wave-uniform.
@@ -88,7 +88,6 @@ template <bool kNatV>
 __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_red[NW];
-    __shared__ int s_job;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -96,44 +95,10 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     const int hh = lane >> 5;
     const int l32 = lane & 31;
 
-    // Work distribution: one workgroup per CU claims (kv head, row tile[, key range]) jobs,
-    // heaviest first, from one counter per kv head; it prefers its home head (whose K/V its
-    // XCD's L2 holds) unless another head is kStealLag or more jobs behind.  A launch with no
-    // more jobs than CUs has no counters (p.queue null): every workgroup is one job.
-    const int home = blockIdx.x % p.hkv;
+    // one (kv head, row tile[, key range]) job per workgroup, the heavier ones first; the kv head
+    // is the fastest index, so that with eight of them a head's K/V stays in one XCD's L2
     const int jobs_per_head = p.n_tiles * p.dma_splits;
-    bool first = true;
-  for (;;) {
-    if (p.queue == nullptr) {
-        if (tid == 0) s_job = first ? home * jobs_per_head + blockIdx.x / p.hkv : -1;
-        first = false;
-    } else if (tid == 0) {
-        int job = -1;
-        // at most hkv failed claims: each one finds a head exhausted for good
-        for (int attempt = 0; attempt <= p.hkv && job < 0; ++attempt) {
-            int best = home;
-            int best_c = __hip_atomic_load(&p.queue[home], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-            if (best_c < jobs_per_head) best_c -= kStealLag;
-            for (int q = 1; q < p.hkv; ++q) {
-                int y = home + q;
-                if (y >= p.hkv) y -= p.hkv;
-                const int c = __hip_atomic_load(&p.queue[y], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-                if (c < best_c) {
-                    best_c = c;
-                    best = y;
-                }
-            }
-            if (best_c >= jobs_per_head) break;   // nothing left anywhere
-            const int j = atomicAdd(&p.queue[best], 1);
-            if (j < jobs_per_head) job = best * jobs_per_head + j;
-        }
-        s_job = job;
-    }
-    __syncthreads();
-    const int job = __builtin_amdgcn_readfirstlane(s_job);
-    if (job < 0) break;   // block-uniform: every head is exhausted
+    const int job = (int)(blockIdx.x % p.hkv) * jobs_per_head + (int)(blockIdx.x / p.hkv);
     const int g = job / jobs_per_head;
     const int within = job - g * jobs_per_head;
     const int tile = p.n_tiles - 1 - within / p.dma_splits;
@@ -164,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     for (int w = 0; w < NW; ++w) tile_max = max(tile_max, s_red[w]);
     const int key_end = min(tile_max + 1, n_keys_job);
     const int n_iter = __builtin_amdgcn_readfirstlane((key_end + kBN - 1) / kBN);
-    if (n_iter <= 0) continue;   // block-uniform: no valid row, or no row reaches this range
+    if (n_iter <= 0) return;   // block-uniform: no valid row, or no row reaches this range
     // sub-steps [0, u_unm) lie entirely at or below every limit of this wave; a wave without
     // a valid column has nothing to mask
     const int u_unm = __builtin_amdgcn_readfirstlane(lmin == 0x7fffffff ? 0x3fffffff
@@ -574,12 +539,11 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
             }
         }
     }
-  }   // next job
 }
 
 }  // namespace
 
-pkv_status launch_attn_w8_main(const AttnParams& p, int n_cu, hipStream_t st) {
+pkv_status launch_attn_w8_main(const AttnParams& p, hipStream_t st) {
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_w8_kernel<false>),
@@ -591,8 +555,7 @@ pkv_status launch_attn_w8_main(const AttnParams& p, int n_cu, hipStream_t st) {
             return PKV_ERR_LAUNCH;
         configured.store(true, std::memory_order_release);
     }
-    // one workgroup per CU (its LDS admits no second one), or per job if there are fewer
-    const int64_t grid = std::min<int64_t>((int64_t)p.n_tiles * p.dma_splits * p.hkv, n_cu);
+    const int64_t grid = (int64_t)p.n_tiles * p.dma_splits * p.hkv;
     if (p.v)   // the values as the cache holds them; p.vt is then not used
         hipLaunchKernelGGL(attn_w8_kernel<true>, dim3((unsigned)grid), dim3(kThreads), kLdsBytes,
                            st, p);
