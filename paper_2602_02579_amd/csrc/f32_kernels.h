@@ -1,0 +1,47 @@
+// Declarations of the fp32 matrix-core kernels (f32_kernels.hip).
+#pragma once
+
+#include "pkv_common.h"
+
+namespace pkv {
+
+enum F32Mode { kF32Rope = 0, kF32Plain = 1, kF32Gated = 2 };
+
+struct F32GemmParams {
+    const float* x;            // [rows, k]
+    const int32_t* row_idx;    // [m] or null
+    const float* w[3];         // wq, wk, wv; or w; or w_gate, w_up
+    float* out[3];             // q, k, v; or y
+    int m, k;
+    int n_out;                 // plain and gated
+    const float* residual;     // plain: [m, n_out] or null
+    // projection: tiles of 16 rotary pairs, first tile of Q, K, V, end
+    int tile_begin[4];
+    int hq, hkv, d;
+    const int32_t* row_pos;    // [m]
+    const int32_t* dst_row;    // [m] or null: rows of K and V
+    const float* bias[3];      // or null
+};
+pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& tab,
+                           hipStream_t st);
+// pointers of a linear layer allow 16-byte accesses (null counts as aligned), rows fit the grid
+bool linear_f32_supported(const void* x, const void* w0, const void* w1, const void* residual,
+                          const void* y, int64_t m);
+
+// fp32 with head_dim 32, 64 or 128: score and attention below
+bool f32_tiles_supported(const pkv_layer_cfg& cfg);
+pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
+                           const float* v, const int32_t* row_pos, float* out, float* lse,
+                           int64_t m, float scale, hipStream_t st);
+
+struct F32ScorePlan {
+    int n_splits, split_len;
+};
+F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq);
+// lse null: both passes, ws holds n_splits * nq * hq float2; else pass 2 with these normalisers
+pkv_status launch_score_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
+                            const float* lse, const int32_t* row_pos, float* score, int64_t nq,
+                            int64_t n_ctx, float scale, int accumulate, void* ws,
+                            hipStream_t st);
+
+}  // namespace pkv

@@ -1,0 +1,550 @@
+// Single precision on the matrix cores: projection and linear layers, query score, attention.
+// (The same steps as the bf16 kernels: Algorithm 1, both stages; Appendix E.)
+//
+// v_mfma_f32_16x16x4_f32 multiplies and adds in fp32, so nothing is given up against the plain
+// FMA kernels; what is gained is that one instruction does 1024 multiply-adds without moving
+// operands.  fp32 problems here are small (a 1k-token request is 0.2 GFLOP, 2 us of the fp32
+// matrix rate), so all of these kernels are bound by latency: the launch, and the chain of
+// memory round trips inside it.  Each is therefore cut so that a wave makes few round trips,
+// all operands of one requested together, and enough waves run at once to cover the chip.
+//
+// Operand layout of the instruction: A lane l holds row l % 16, contraction index l / 16; B
+// likewise with columns; the accumulator of lane l holds column l % 16, rows 4 (l / 16) + r.
+// The contraction may run in any order as long as A and B agree, so lane group g = l / 16 takes
+// indices 4 g .. 4 g + 3 of every 16 (one 16-byte load) and step j uses element j of all.
+//
+// Measured, 1024 context tokens, 16 query tokens, 4 heads of 64 (us, plain kernels -> these):
+// attention of 220 rows 105 -> 23, column sums 158 -> 5.7, normalisers 13 -> 4.3,
+// projection of 220 rows 37 -> 8; linear layers of 151 rows, 256 -> 512 gated 20 -> 7.
+#include <algorithm>
+#include <atomic>
+
+#include "f32_kernels.h"
+
+namespace pkv {
+
+namespace {
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+// ---- projection and linear layers ----------------------------------------------------------
+// A workgroup (4 waves) computes 64 rows x 32 output columns, a wave 16 rows x 32 columns as
+// two accumulators.  The 32 columns are two sets of 16 whose members meet in one lane and
+// register: rotary partners (i, i + D/2), gate and up of one output, or simply the next 16
+// outputs.  The contraction runs in chunks of 128 through LDS; the next chunk is on its way in
+// registers while one is multiplied.  Rows of LDS are 132 floats apart: the 16 rows of an
+// operand read start 4 banks apart and cover all 64 once.
+constexpr int kTM = 64, kTN = 32, kTK = 128;
+constexpr int kRow = kTK + 4;
+
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTable tab) {
+    __shared__ __align__(16) float lds[(kTM + kTN) * kRow];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
+    const int row0 = blockIdx.y * kTM;
+
+    // weight row of column c of this tile (c < 16: first set, else its partner)
+    int mat = 0, ct = blockIdx.x;
+    if (MODE == kF32Rope) {
+        if (ct >= p.tile_begin[1]) mat = 1;
+        if (ct >= p.tile_begin[2]) mat = 2;
+        ct -= p.tile_begin[mat];
+    }
+    const int half = p.d / 2;
+    // index of the first set's column c: pair index, output index
+    auto col_of = [&](int c) { return ct * (MODE == kF32Plain ? 32 : 16) + c; };
+    const int n_cols = MODE == kF32Rope ? (mat == 0 ? p.hq : p.hkv) * half : p.n_out;
+    auto w_row = [&](int c) -> const float* {
+        int j = col_of(c & 15);
+        if (MODE == kF32Plain) {
+            j = min(j + (c & 16), n_cols - 1);
+            return p.w[0] + (int64_t)j * p.k;
+        }
+        j = min(j, n_cols - 1);
+        if (MODE == kF32Gated) return (c & 16 ? p.w[1] : p.w[0]) + (int64_t)j * p.k;
+        const int head = j / half, i = j % half;
+        return p.w[mat] + (int64_t)(head * p.d + i + (c & 16 ? half : 0)) * p.k;
+    };
+
+    // loader: 96 rows of 32 16-byte pieces; thread t takes piece t % 32 of rows t / 32 + 8 n
+    const int piece = tid & 31, r0 = tid >> 5;
+    const float* src[12];
+#pragma unroll
+    for (int n = 0; n < 12; ++n) {
+        const int r = r0 + 8 * n;
+        if (r < kTM) {
+            const int row = min(row0 + r, p.m - 1);
+            src[n] = p.x + (int64_t)(p.row_idx ? p.row_idx[row] : row) * p.k;
+        } else {
+            src[n] = w_row(r - kTM);
+        }
+    }
+    f32x4 st[12];
+    auto load = [&](int k0) {
+        const int k = k0 + piece * 4;
+#pragma unroll
+        for (int n = 0; n < 12; ++n)
+            st[n] = k < p.k ? ld4(src[n] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    load(0);
+    for (int k0 = 0; k0 < p.k; k0 += kTK) {
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 12; ++n)
+            *reinterpret_cast<f32x4*>(lds + (r0 + 8 * n) * kRow + piece * 4) = st[n];
+        __syncthreads();
+        if (k0 + kTK < p.k) load(k0 + kTK);
+        const float* xb = lds + (wave * 16 + l16) * kRow + g4 * 4;
+        const float* wb = lds + (kTM + l16) * kRow + g4 * 4;
+#pragma unroll
+        for (int c = 0; c < kTK / 16; ++c) {
+            const f32x4 b = ld4(xb + c * 16), a0 = ld4(wb + c * 16),
+                        a1 = ld4(wb + 16 * kRow + c * 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[0] = mfma_f32(a0[j], b[j], acc[0]);
+                acc[1] = mfma_f32(a1[j], b[j], acc[1]);
+            }
+        }
+    }
+
+    // a lane holds row l16 of the wave, columns 4 g4 + r of both sets
+    const int row = row0 + wave * 16 + l16;
+    if (row >= p.m) return;
+    const int c0 = col_of(4 * g4);
+    if (MODE == kF32Plain) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int f = c0 + 16 * s;
+            if (f >= n_cols) continue;             // n_out is a multiple of 8
+            const int64_t o = (int64_t)row * p.n_out + f;
+            f32x4 v = acc[s];
+            if (p.residual) v += ld4(p.residual + o);
+            *reinterpret_cast<f32x4*>(p.out[0] + o) = v;
+        }
+    } else if (MODE == kF32Gated) {
+        if (c0 >= n_cols) return;
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = acc[0][r] / (1.f + expf(-acc[0][r])) * acc[1][r];
+        *reinterpret_cast<f32x4*>(p.out[0] + (int64_t)row * p.n_out + c0) = v;
+    } else {
+        if (c0 >= n_cols) return;                  // half is a multiple of 8
+        const int head = c0 / half, i0 = c0 % half;
+        const int heads = mat == 0 ? p.hq : p.hkv;
+        const int64_t orow = mat != 0 && p.dst_row ? p.dst_row[row] : row;
+        float* o = p.out[mat] + (orow * heads + head) * p.d + i0;
+        f32x4 a = acc[0], b = acc[1];
+        if (p.bias[mat]) {
+            a += ld4(p.bias[mat] + head * p.d + i0);
+            b += ld4(p.bias[mat] + head * p.d + i0 + half);
+        }
+        if (mat != 2) {
+            const double pos = (double)p.row_pos[row];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float sn, cs;
+                rope_sincos(pos, tab.inv_freq[i0 + r], &sn, &cs);
+                const float ra = a[r] * cs - b[r] * sn, rb = b[r] * cs + a[r] * sn;
+                a[r] = ra;
+                b[r] = rb;
+            }
+        }
+        *reinterpret_cast<f32x4*>(o) = a;
+        *reinterpret_cast<f32x4*>(o + half) = b;
+    }
+}
+
+// ---- shared by score and attention -----------------------------------------------------------
+// S of 16 keys x 16 columns: k4[c] = key (lane % 16), elements 16 c + 4 g4 ..; q4 likewise
+template <int D>
+__device__ __forceinline__ f32x4 dot_tile(const f32x4 (&k4)[D / 16], const f32x4 (&q4)[D / 16]) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (c & 1) s2 = mfma_f32(k4[c][j], q4[c][j], s2);   // two chains: half the latency
+            else s = mfma_f32(k4[c][j], q4[c][j], s);
+        }
+    return s + s2;
+}
+template <int D>
+__device__ __forceinline__ void load_row(f32x4 (&dst)[D / 16], const float* row, int g4) {
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) dst[c] = ld4(row + c * 16 + 4 * g4);
+}
+__device__ __forceinline__ float col_max(float v) {   // over the lane groups of a column
+    v = fmaxf(v, __shfl_xor(v, 16, 64));
+    return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+__device__ __forceinline__ float col_sum(float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+// ---- attention ---------------------------------------------------------------------------------
+// A workgroup owns 16 (row, head) columns of one kv head; its NW waves take every NW-th tile of
+// 16 keys, each with a running maximum of its own, and meet in LDS at the end.  The scores of a
+// lane (keys 4 g4 + r of its column) are the B operand of the second product as they are: step
+// j multiplies key 4 g4 + j of every lane group.  Row i of output block e is element C i + e of
+// the head, so that a lane's piece of a value row is C = D / 16 consecutive floats (one element
+// per load instead took 16 loads per tile and as long as the multiplications).  K and V of the
+// next tile are requested before the current one is used.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
+    const int32_t* __restrict__ row_pos, float* __restrict__ out, float* __restrict__ lse_out,
+    int m, int hq, int hkv, float scale) {
+    constexpr int C = D / 16;
+    extern __shared__ __align__(16) float smem[];      // [NW][D][16] partial outputs
+    __shared__ float s_m[NW][16], s_l[NW][16];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
+    const int g = blockIdx.y, group = hq / hkv;
+    const int tile = gridDim.x - 1 - blockIdx.x;       // rows in position order: heavy ones first
+    const int col = tile * 16 + l16;
+    const int row = col / group, head = g * group + col % group;
+    const bool valid = row < m;
+    const int limit = valid ? row_pos[row] : -1;
+    int last = limit;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+
+    f32x4 q4[C];
+    load_row<D>(q4, q + ((int64_t)(valid ? row : 0) * hq + head) * D, g4);
+    const int64_t krow = (int64_t)hkv * D;
+    const float* kb = kc + (int64_t)g * D;
+    const float* vb = vc + (int64_t)g * D + C * l16;
+    typedef float vrow_t __attribute__((ext_vector_type(C)));
+    f32x4 k4[C], kn[C], o_acc[C];
+    vrow_t v4[4], vn[4];
+#pragma unroll
+    for (int c = 0; c < C; ++c) o_acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mx = -INFINITY, sum = 0.f;
+    // keys beyond the tile's last visible one are never needed: re-read that one instead
+    auto load_kv = [&](int t0) {
+        load_row<D>(kn, kb + (int64_t)min(t0 + l16, last) * krow, g4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            vn[j] = *reinterpret_cast<const vrow_t*>(vb + (int64_t)min(t0 + 4 * g4 + j, last) * krow);
+    };
+    int t0 = wave * 16;
+    if (t0 <= last) load_kv(t0);
+    for (; t0 <= last; t0 += NW * 16) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) k4[c] = kn[c];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v4[j] = vn[j];
+        if (t0 + NW * 16 <= last) load_kv(t0 + NW * 16);
+        f32x4 s = dot_tile<D>(k4, q4);
+        float tm = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = t0 + 4 * g4 + r <= limit ? s[r] * scale : -INFINITY;
+            tm = fmaxf(tm, s[r]);
+        }
+        const float mn = fmaxf(mx, col_max(tm));
+        const float ref = mn == -INFINITY ? 0.f : mn;
+        const float corr = expf(mx - ref);
+        float ts = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = expf(s[r] - ref);
+            ts += s[r];
+        }
+        sum = sum * corr + ts;       // this lane group's keys only
+        mx = mn;
+#pragma unroll
+        for (int c = 0; c < C; ++c) o_acc[c] *= corr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int c = 0; c < C; ++c) o_acc[c] = mfma_f32(v4[j][c], s[j], o_acc[c]);
+    }
+    sum = col_sum(sum);
+    if (g4 == 0) {
+        s_m[wave][l16] = mx;
+        s_l[wave][l16] = sum;
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            smem[(wave * D + C * (4 * g4 + r) + c) * 16 + l16] = o_acc[c][r];
+    __syncthreads();
+    for (int e = tid; e < D * 16; e += NW * 64) {
+        const int cc = e / D, dd = e % D;
+        const int ecol = tile * 16 + cc;
+        const int erow = ecol / group;
+        if (erow >= m) break;                          // later elements have later columns
+        float mm = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_m[w][cc]);
+        float acc = 0.f, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = expf(s_m[w][cc] - mm);
+            acc += f * smem[(w * D + dd) * 16 + cc];
+            l += f * s_l[w][cc];
+        }
+        const int64_t oc = (int64_t)erow * hq + g * group + ecol % group;
+        out[oc * D + dd] = acc / l;
+        if (lse_out && dd == 0) lse_out[oc] = mm + logf(l);
+    }
+}
+
+// ---- query score ---------------------------------------------------------------------------------
+// Columns of a kv head are numbered (query token, head of the group), in tiles of 16.
+// Pass 1: per column the (maximum, sum) over a range of keys; four waves per workgroup take
+// every fourth tile of 16 keys and meet in LDS.
+template <int D>
+__global__ __launch_bounds__(256) void score_part_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, float2* __restrict__ part, int nq,
+    int n_ctx, int hq, int hkv, int split_len, float scale) {
+    constexpr int C = D / 16;
+    __shared__ float s_m[4][16], s_l[4][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
+    const int g = blockIdx.y, group = hq / hkv;
+    const int col = blockIdx.x * 16 + l16;
+    const int n_col = nq * group;
+    const int cc = min(col, n_col - 1);
+    const int64_t qcol = (int64_t)(cc / group) * hq + g * group + cc % group;
+    const int begin = blockIdx.z * split_len, end = min(n_ctx, begin + split_len);
+    f32x4 q4[C], k4[C];
+    load_row<D>(q4, q + qcol * D, g4);
+    const float* kb = k + (int64_t)g * D;
+    const int64_t krow = (int64_t)hkv * D;
+    float mx = -INFINITY, sum = 0.f;
+    int t0 = begin + wave * 16;
+    if (t0 < end) load_row<D>(k4, kb + (int64_t)min(t0 + l16, end - 1) * krow, g4);
+    for (; t0 < end; t0 += 64) {
+        f32x4 s = dot_tile<D>(k4, q4);
+        if (t0 + 64 < end)
+            load_row<D>(k4, kb + (int64_t)min(t0 + 64 + l16, end - 1) * krow, g4);
+        float mn = mx;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = t0 + 4 * g4 + r < end ? s[r] * scale : -INFINITY;
+            mn = fmaxf(mn, s[r]);
+        }
+        const float ref = mn == -INFINITY ? 0.f : mn;   // this lane's own reference
+        float ts = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ts += expf(s[r] - ref);
+        sum = sum * expf(mx - ref) + ts;
+        mx = mn;
+    }
+    const float m = col_max(mx);
+    sum = col_sum(m == -INFINITY ? 0.f : sum * expf(mx - m));
+    if (g4 == 0) {
+        s_m[wave][l16] = m;
+        s_l[wave][l16] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x < 16 && col < n_col) {
+        float mm = -INFINITY, l = 0.f;
+        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, s_m[w][l16]);   // finite: the range has keys
+        for (int w = 0; w < 4; ++w) l += s_l[w][l16] * expf(s_m[w][l16] - mm);
+        part[(int64_t)blockIdx.z * nq * hq + qcol] = make_float2(mm, l);
+    }
+}
+
+// Pass 2: the sum over all columns per key.  A workgroup owns 16 keys; its four waves take every
+// fourth tile of columns and meet in LDS.  Columns come in blocks of 256 whose normalisers the
+// workgroup folds (part) or reads (lse) into LDS first.  Fixed order, no atomics.
+// With row_pos a query row counts for the keys up to row_pos[row] only.
+template <int D>
+__global__ __launch_bounds__(256) void score_sum_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float2* __restrict__ part,
+    int n_splits, const float* __restrict__ lse, const int32_t* __restrict__ row_pos,
+    float* __restrict__ score, int nq, int n_ctx, int hq, int hkv, float scale, int accumulate) {
+    constexpr int C = D / 16;
+    __shared__ float s_lse[256];
+    __shared__ float s_sum[4][16];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
+    const int group = hq / hkv, n_col = nq * group, ncol = nq * hq;
+    const int tiles_g = (n_col + 15) / 16, tiles = tiles_g * hkv;
+    const int t0 = blockIdx.x * 16;
+    auto qcol_of = [&](int tile, int c) -> int {      // -1 past the last column of the kv head
+        const int cc = (tile % tiles_g) * 16 + c;
+        return cc < n_col ? (cc / group) * hq + (tile / tiles_g) * group + cc % group : -1;
+    };
+    const float* krow = k + (int64_t)min(t0 + l16, n_ctx - 1) * hkv * D;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 k4[C], q4[C];
+    for (int tb = 0; tb < tiles; tb += 16) {
+        if (tb) __syncthreads();
+        // operands of the wave's first tile, requested before the fold below
+        const bool any = tb + wave < tiles;
+        if (any) {
+            load_row<D>(k4, krow + (int64_t)((tb + wave) / tiles_g) * D, g4);
+            load_row<D>(q4, q + (int64_t)max(qcol_of(tb + wave, l16), 0) * D, g4);
+        }
+        {
+            const int tile = tb + (tid >> 4);
+            const int qc = tile < tiles ? qcol_of(tile, tid & 15) : -1;
+            float v = INFINITY;                       // switches the column off
+            if (qc >= 0) {
+                if (lse) {
+                    v = lse[qc];
+                } else {
+                    float m = -INFINITY, l = 0.f;
+                    for (int s = 0; s < n_splits; s += 8) {
+                        float2 ml[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)   // past the end: the last one, weight 0
+                            ml[e] = part[(int64_t)min(s + e, n_splits - 1) * ncol + qc];
+                        float mn = m;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) mn = fmaxf(mn, ml[e].x);
+                        l *= expf(m - mn);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            l += s + e < n_splits ? ml[e].y * expf(ml[e].x - mn) : 0.f;
+                        m = mn;
+                    }
+                    v = m + logf(l);
+                }
+            }
+            s_lse[tid] = v;
+        }
+        __syncthreads();
+        const int te = min(tiles, tb + 16);
+        for (int tile = tb + wave; tile < te; tile += 4) {
+            const f32x4 s = dot_tile<D>(k4, q4);
+            const float norm = s_lse[(tile - tb) * 16 + l16];
+            const int lim = row_pos ? row_pos[max(qcol_of(tile, l16), 0) / hq] : n_ctx;
+            if (tile + 4 < te) {
+                if ((tile + 4) / tiles_g != tile / tiles_g)
+                    load_row<D>(k4, krow + (int64_t)((tile + 4) / tiles_g) * D, g4);
+                load_row<D>(q4, q + (int64_t)max(qcol_of(tile + 4, l16), 0) * D, g4);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (t0 + 4 * g4 + r <= lim) acc[r] += expf(s[r] * scale - norm);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float v = acc[r];
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
+        if (l16 == 0) s_sum[wave][4 * g4 + r] = v;
+    }
+    __syncthreads();
+    const int t = t0 + tid;
+    if (tid < 16 && t < n_ctx) {
+        const float v = ((s_sum[0][tid] + s_sum[1][tid]) + (s_sum[2][tid] + s_sum[3][tid])) /
+                        (float)ncol;
+        score[t] = accumulate ? score[t] + v : v;
+    }
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+template <int D, int NW>
+pkv_status attn_f32_launch(dim3 grid, const float* q, const float* k, const float* v,
+                           const int32_t* row_pos, float* out, float* lse, int64_t m, int hq,
+                           int hkv, float scale, hipStream_t st) {
+    constexpr size_t kBytes = (size_t)NW * D * 16 * sizeof(float);
+    static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
+    if (!configured.load(std::memory_order_acquire)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, NW>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kBytes) != hipSuccess)
+            return PKV_ERR_LAUNCH;
+        configured.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((attn_f32_kernel<D, NW>), grid, dim3(NW * 64), kBytes, st, q, k, v, row_pos,
+                       out, lse, (int)m, hq, hkv, scale);
+    return launch_status();
+}
+
+}  // namespace
+
+bool f32_tiles_supported(const pkv_layer_cfg& cfg) {
+    return cfg.dtype == PKV_F32 &&
+           (cfg.head_dim == 32 || cfg.head_dim == 64 || cfg.head_dim == 128);
+}
+
+pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& tab, hipStream_t st) {
+    int n_ct;
+    if (mode == kF32Rope) n_ct = p.tile_begin[3];
+    else n_ct = (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
+    const int64_t rows = ceil_div(p.m, kTM);
+    if (rows > 65535) return PKV_ERR_SHAPE;
+    const dim3 grid((unsigned)n_ct, (unsigned)rows);
+    if (mode == kF32Rope) hipLaunchKernelGGL(gemm_f32_kernel<kF32Rope>, grid, dim3(256), 0, st, p, tab);
+    else if (mode == kF32Plain)
+        hipLaunchKernelGGL(gemm_f32_kernel<kF32Plain>, grid, dim3(256), 0, st, p, tab);
+    else hipLaunchKernelGGL(gemm_f32_kernel<kF32Gated>, grid, dim3(256), 0, st, p, tab);
+    return launch_status();
+}
+
+bool linear_f32_supported(const void* x, const void* w0, const void* w1, const void* residual,
+                          const void* y, int64_t m) {
+    return ceil_div(m, kTM) <= 65535 && aligned16(x) && aligned16(w0) && aligned16(w1) &&
+           aligned16(residual) && aligned16(y);
+}
+
+pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
+                           const float* v, const int32_t* row_pos, float* out, float* lse,
+                           int64_t m, float scale, hipStream_t st) {
+    const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads;
+    const dim3 grid((unsigned)ceil_div(m * (hq / hkv), 16), (unsigned)hkv);
+    // as many waves as their registers allow: 16 up to head_dim 64, 8 with 128
+    if (cfg.head_dim == 32) return attn_f32_launch<32, 16>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
+    if (cfg.head_dim == 64) return attn_f32_launch<64, 16>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
+    return attn_f32_launch<128, 8>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
+}
+
+F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {
+    // about one workgroup per CU; the fold at the head of pass 2 reads splits x columns values
+    // per workgroup, which is kept below 8192
+    const int group = cfg.n_q_heads / cfg.n_kv_heads;
+    const int64_t tiles = ceil_div(nq * group, 16) * cfg.n_kv_heads;
+    int64_t want = std::min(ceil_div(256, tiles), ceil_div(n_ctx, 64));
+    want = std::max<int64_t>(1, std::min(want, 8192 / std::max<int64_t>(1, nq * cfg.n_q_heads)));
+    F32ScorePlan p;
+    p.split_len = (int)(ceil_div(ceil_div(n_ctx, want), 64) * 64);
+    p.n_splits = (int)ceil_div(n_ctx, p.split_len);
+    return p;
+}
+
+pkv_status launch_score_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
+                            const float* lse, const int32_t* row_pos, float* score, int64_t nq,
+                            int64_t n_ctx, float scale, int accumulate, void* ws,
+                            hipStream_t st) {
+    const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads, d = cfg.head_dim;
+    const F32ScorePlan p = plan_score_f32(cfg, n_ctx, nq);
+    float2* part = (float2*)ws;
+    const dim3 g1((unsigned)ceil_div(nq * (hq / hkv), 16), (unsigned)hkv, (unsigned)p.n_splits);
+    const dim3 g2((unsigned)ceil_div(n_ctx, 16));
+#define PKV_SCORE_F32(DD)                                                                   \
+    {                                                                                       \
+        if (!lse)                                                                           \
+            hipLaunchKernelGGL(score_part_f32_kernel<DD>, g1, dim3(256), 0, st, q, k, part, \
+                               (int)nq, (int)n_ctx, hq, hkv, p.split_len, scale);           \
+        hipLaunchKernelGGL(score_sum_f32_kernel<DD>, g2, dim3(256), 0, st, q, k, part,      \
+                           p.n_splits, lse, row_pos, score, (int)nq, (int)n_ctx, hq, hkv,   \
+                           scale, accumulate);                                              \
+    }
+    if (d == 32) PKV_SCORE_F32(32)
+    else if (d == 64) PKV_SCORE_F32(64)
+    else PKV_SCORE_F32(128)
+#undef PKV_SCORE_F32
+    return launch_status();
+}
+
+}  // namespace pkv

@@ -7,6 +7,7 @@
 // out[i, head, :] = R(row_pos[i]) (W_head x_i),  x_i = hidden[row_idx[i]]
 // for the Hq query heads, the Hkv key heads, and (without R) the Hkv value
 // heads; fp32 accumulation; one rounding after the rotation.
+#include "f32_kernels.h"
 #include "proj_common.h"
 
 namespace pkv {
@@ -352,6 +353,27 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
         if (d == 128) hipLaunchKernelGGL(qkv_proj_mfma<128>, grid, dim3(256), 0, st, p);
         else hipLaunchKernelGGL(qkv_proj_mfma<64>, grid, dim3(256), 0, st, p);
         return launch_status();
+    }
+    // fp32: the matrix-core kernel, unless heads are normalised (that needs whole heads) or the
+    // row count exceeds the grid
+    if (cfg.dtype == PKV_F32 && !ex.gain[0] && !ex.gain[1] && ceil_div(m, 64) <= 65535) {
+        F32GemmParams p = {};
+        p.x = (const float*)hidden;
+        p.row_idx = row_idx;
+        p.w[0] = (const float*)wq; p.w[1] = (const float*)wk; p.w[2] = (const float*)wv;
+        p.out[0] = (float*)q_out; p.out[1] = (float*)k_out; p.out[2] = (float*)v_out;
+        p.m = (int)m; p.k = cfg.hidden;
+        p.hq = hq; p.hkv = hkv; p.d = cfg.head_dim;
+        p.row_pos = row_pos;
+        p.dst_row = dst_row;
+        for (int i = 0; i < 3; ++i) p.bias[i] = (const float*)ex.bias[i];
+        const int tq = q_out ? (int)ceil_div(hq * cfg.head_dim / 2, 16) : 0;
+        const int tkv = k_out ? (int)ceil_div(hkv * cfg.head_dim / 2, 16) : 0;
+        p.tile_begin[0] = 0;
+        p.tile_begin[1] = tq;
+        p.tile_begin[2] = tq + tkv;
+        p.tile_begin[3] = tq + 2 * tkv;
+        return launch_gemm_f32(kF32Rope, p, tab, st);
     }
     const dim3 grid((unsigned)ceil_div(m, 16), (unsigned)(hq + 2 * hkv));
     if (cfg.dtype == PKV_BF16) {

@@ -5,9 +5,10 @@
 // MLP.  The block is the public Llama one; the paper does not restate it.
 //
 // bf16 linear layers of MFMA-friendly sizes run on the 256 x 256 tile kernel of the
-// Q/K/V projection with a different epilogue (gather_qkv_proj_dma.hip); everything else
-// (fp32, odd sizes, unaligned pointers) takes the simple kernels below, one wave per
-// output element.
+// Q/K/V projection with a different epilogue (gather_qkv_proj_dma.hip), fp32 ones on the fp32
+// matrix-core kernel (f32_kernels.hip); everything else (odd bf16 sizes, unaligned pointers)
+// takes the simple kernels below, one wave per output element.
+#include "f32_kernels.h"
 #include "proj_common.h"
 
 namespace pkv {
@@ -216,6 +217,15 @@ pkv_status launch_linear_rows(int dtype, bool gated, const void* x, const void* 
         return launch_linear_dma(mode, (const bf16_t*)x, (const bf16_t*)w0, (const bf16_t*)w1,
                                  (const bf16_t*)residual, (bf16_t*)y, m, k_in, n_out, (float*)ws,
                                  st);
+    if (dtype == PKV_F32 && linear_f32_supported(x, w0, w1, residual, y, m)) {
+        F32GemmParams p = {};
+        p.x = (const float*)x;
+        p.w[0] = (const float*)w0; p.w[1] = (const float*)w1;
+        p.out[0] = (float*)y;
+        p.m = (int)m; p.k = (int)k_in; p.n_out = (int)n_out;
+        p.residual = (const float*)residual;
+        return launch_gemm_f32(gated ? kF32Gated : kF32Plain, p, RopeTable{}, st);
+    }
     return dtype == PKV_BF16
                ? linear_simple<bf16_t>(gated, x, w0, w1, residual, y, m, k_in, n_out, st)
                : linear_simple<float>(gated, x, w0, w1, residual, y, m, k_in, n_out, st);

@@ -11,6 +11,7 @@
 //   pass 1  lse per (query token, head) column;
 //   pass 2  per key, the sum over all columns of exp(s - lse), written once
 //           per key (no atomics, so the result is deterministic).
+#include "f32_kernels.h"
 #include "score_common.h"
 
 namespace pkv {
@@ -328,6 +329,8 @@ pkv_status launch_attn_lse_partials(const pkv_layer_cfg& cfg, const void* q,
 
 size_t query_score_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {
     const size_t ncol = (size_t)(nq * cfg.n_q_heads);
+    if (f32_tiles_supported(cfg))
+        return (size_t)plan_score_f32(cfg, n_ctx, nq).n_splits * ncol * 2 * sizeof(float);
     if (!mfma_score_supported(cfg)) return ncol * sizeof(float);
     // the key-blocked kernels (other geometries, and the column sums with row limits)
     const SplitPlan sp = plan_splits(cfg, n_ctx, nq);
@@ -407,6 +410,9 @@ pkv_status launch_query_score(const pkv_layer_cfg& cfg, const void* q,
                            1.0f / (float)ncol, accumulate);
         return launch_status();
     }
+    if (f32_tiles_supported(cfg))
+        return launch_score_f32(cfg, (const float*)q, (const float*)k, nullptr, nullptr, score, nq,
+                                n_ctx, scale, accumulate, ws, st);
     const unsigned kb = (unsigned)ceil_div(n_ctx, 256);
     if (cfg.dtype == PKV_BF16) {
         hipLaunchKernelGGL(score_lse_generic<bf16_t>, dim3(ncol), dim3(256), 0, st,
@@ -436,6 +442,9 @@ pkv_status launch_query_score_lse(const pkv_layer_cfg& cfg, const void* q, const
     const int ncol = (int)(nq * cfg.n_q_heads);
     const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads, d = cfg.head_dim;
     const float scale_log2 = scale * 1.4426950408889634f;
+    if (f32_tiles_supported(cfg))
+        return launch_score_f32(cfg, (const float*)q, (const float*)k, lse, row_pos, score, nq,
+                                n_ctx, scale, accumulate, ws, st);
     if (!mfma_score_supported(cfg)) {
         const unsigned kb = (unsigned)ceil_div(n_ctx, 256);
         if (cfg.dtype == PKV_BF16)
