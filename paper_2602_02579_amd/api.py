@@ -11,7 +11,8 @@ from __future__ import annotations
 
 import ctypes
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, fields
+from functools import cached_property
 from typing import Optional
 
 import torch
@@ -70,9 +71,19 @@ class LayerCfg:
     rope_theta: float
     dtype: str  # "f32" or "bf16"
 
-    @property
+    # The binding costs a few microseconds per call, of the order of a small kernel: what a
+    # call needs of its configuration is made once per object (it is frozen) and kept with it.
+    @cached_property
     def torch_dtype(self) -> torch.dtype:
         return {"f32": torch.float32, "bf16": torch.bfloat16}[self.dtype]
+
+    @cached_property
+    def _ref(self):
+        """Reference to the C structure, which it keeps alive."""
+        return ctypes.byref(self._c())
+
+    def __getstate__(self):   # copies and pickles carry the fields, not what was derived
+        return {f.name: getattr(self, f.name) for f in fields(self)}
 
     def _c(self) -> _CCfg:
         return _CCfg(self.n_q_heads, self.n_kv_heads, self.head_dim, self.hidden,
@@ -177,11 +188,17 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype], name: str):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    return torch.cuda.current_stream().cuda_stream
+
+
+# the same number without building a Stream object, where torch offers it
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream() -> int:   # noqa: F811
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ws(ws: Optional[torch.Tensor]):
@@ -189,24 +206,22 @@ def _ws(ws: Optional[torch.Tensor]):
         return None, 0
     if not ws.is_cuda or not ws.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
 def pkv_workspace_bytes(which_call: int, cfg: LayerCfg, n: int, m: int) -> int:
-    c = cfg._c()
-    return int(load_library().pkv_workspace_bytes(which_call, ctypes.byref(c), n, m))
+    return int(load_library().pkv_workspace_bytes(which_call, cfg._ref, n, m))
 
 
 def pkv_rope_restore(cfg: LayerCfg, k_in: torch.Tensor, k_out: torch.Tensor,
                      pos: Optional[torch.Tensor] = None, pos_base: int = 0) -> None:
     n = k_in.shape[0]
-    if tuple(k_in.shape) != (n, cfg.n_kv_heads, cfg.head_dim) or k_out.shape != k_in.shape:
+    if k_in.shape != (n, cfg.n_kv_heads, cfg.head_dim) or k_out.shape != k_in.shape:
         raise ValueError("k_in/k_out must be [n, Hkv, D]")
-    if pos is not None and tuple(pos.shape) != (n,):
+    if pos is not None and pos.shape != (n,):
         raise ValueError("pos must be [n]")
-    c = cfg._c()
     _check("pkv_rope_restore", load_library().pkv_rope_restore(
-        ctypes.byref(c), _ptr(k_in, cfg.torch_dtype, "k_in"),
+        cfg._ref, _ptr(k_in, cfg.torch_dtype, "k_in"),
         _ptr(k_out, cfg.torch_dtype, "k_out"), _ptr(pos, torch.int32, "pos"),
         int(pos_base), n, _stream()))
 
@@ -216,16 +231,15 @@ def pkv_query_score(cfg: LayerCfg, q: torch.Tensor, k: torch.Tensor,
                     softmax_scale: float = 0.0,
                     ws: Optional[torch.Tensor] = None) -> None:
     nq, n_ctx = q.shape[0], k.shape[0]
-    if tuple(q.shape) != (nq, cfg.n_q_heads, cfg.head_dim):
+    if q.shape != (nq, cfg.n_q_heads, cfg.head_dim):
         raise ValueError("q must be [nq, Hq, D]")
-    if tuple(k.shape) != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
+    if k.shape != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
         raise ValueError("k must be [n_ctx, Hkv, D]")
-    if tuple(score.shape) != (n_ctx,):
+    if score.shape != (n_ctx,):
         raise ValueError("score must be [n_ctx]")
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_query_score", load_library().pkv_query_score(
-        ctypes.byref(c), _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
+        cfg._ref, _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
         _ptr(score, torch.float32, "score"), nq, n_ctx, float(softmax_scale),
         int(bool(accumulate)), wp, wb, _stream()))
 
@@ -235,15 +249,14 @@ def pkv_query_score_static(cfg: LayerCfg, q: torch.Tensor, k: torch.Tensor,
                            softmax_scale: float = 0.0) -> None:
     """pkv_query_score without a workspace (scratch inside the library)."""
     nq, n_ctx = q.shape[0], k.shape[0]
-    if tuple(q.shape) != (nq, cfg.n_q_heads, cfg.head_dim):
+    if q.shape != (nq, cfg.n_q_heads, cfg.head_dim):
         raise ValueError("q must be [nq, Hq, D]")
-    if tuple(k.shape) != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
+    if k.shape != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
         raise ValueError("k must be [n_ctx, Hkv, D]")
-    if tuple(score.shape) != (n_ctx,):
+    if score.shape != (n_ctx,):
         raise ValueError("score must be [n_ctx]")
-    c = cfg._c()
     _check("pkv_query_score_static", load_library().pkv_query_score_static(
-        ctypes.byref(c), _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
+        cfg._ref, _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
         _ptr(score, torch.float32, "score"), nq, n_ctx, float(softmax_scale),
         int(bool(accumulate)), _stream()))
 
@@ -263,17 +276,17 @@ def _check_proj_args(cfg, hidden, row_idx, row_pos, wq, wk, wv, q_out, k_out, v_
     m = row_pos.shape[0]
     if hidden.dim() != 2 or hidden.shape[1] != cfg.hidden:
         raise ValueError("hidden must be [rows, hidden]")
-    if row_idx is not None and tuple(row_idx.shape) != (m,):
+    if row_idx is not None and row_idx.shape != (m,):
         raise ValueError("row_idx must be [m]")
     if row_idx is None and hidden.shape[0] < m:
         raise ValueError("hidden has fewer than m rows")
     for t, heads, name in ((q_out, cfg.n_q_heads, "q_out"), (k_out, cfg.n_kv_heads, "k_out"),
                            (v_out, cfg.n_kv_heads, "v_out")):
-        if t is not None and tuple(t.shape) != (m, heads, cfg.head_dim):
+        if t is not None and t.shape != (m, heads, cfg.head_dim):
             raise ValueError(f"{name} must be [m, heads, D]")
     for t, heads, name in ((wq, cfg.n_q_heads, "wq"), (wk, cfg.n_kv_heads, "wk"),
                            (wv, cfg.n_kv_heads, "wv")):
-        if t is not None and tuple(t.shape) != (heads * cfg.head_dim, cfg.hidden):
+        if t is not None and t.shape != (heads * cfg.head_dim, cfg.hidden):
             raise ValueError(f"{name} must be [heads*D, hidden]")
     return m
 
@@ -288,9 +301,8 @@ def pkv_gather_qkv_proj(cfg: LayerCfg, hidden: torch.Tensor,
     m = _check_proj_args(cfg, hidden, row_idx, row_pos, wq, wk, wv, q_out, k_out, v_out)
     dt = cfg.torch_dtype
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_gather_qkv_proj", load_library().pkv_gather_qkv_proj(
-        ctypes.byref(c), _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
+        cfg._ref, _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
         _ptr(row_pos, torch.int32, "row_pos"), _ptr(wq, dt, "wq"), _ptr(wk, dt, "wk"),
         _ptr(wv, dt, "wv"), _ptr(q_out, dt, "q_out"), _ptr(k_out, dt, "k_out"),
         _ptr(v_out, dt, "v_out"), m, wp, wb, _stream()))
@@ -312,21 +324,19 @@ def pkv_gather_qkv_proj_ex(cfg: LayerCfg, hidden: torch.Tensor,
     dt = cfg.torch_dtype
     for t, n, name in ((bq, cfg.n_q_heads, "bq"), (bk, cfg.n_kv_heads, "bk"),
                        (bv, cfg.n_kv_heads, "bv")):
-        if t is not None and tuple(t.shape) != (n * cfg.head_dim,):
+        if t is not None and t.shape != (n * cfg.head_dim,):
             raise ValueError(f"{name} must be [heads*D]")
     for t, name in ((q_norm, "q_norm"), (k_norm, "k_norm")):
-        if t is not None and tuple(t.shape) != (cfg.head_dim,):
+        if t is not None and t.shape != (cfg.head_dim,):
             raise ValueError(f"{name} must be [D]")
 
     def raw(t, name):
-        p = _ptr(t, dt, name)
-        return None if p is None else p.value
+        return _ptr(t, dt, name)
     var = _CVariant(raw(bq, "bq"), raw(bk, "bk"), raw(bv, "bv"), raw(q_norm, "q_norm"),
                     raw(k_norm, "k_norm"), float(norm_eps))
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_gather_qkv_proj_ex", load_library().pkv_gather_qkv_proj_ex(
-        ctypes.byref(c), _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
+        cfg._ref, _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
         _ptr(row_pos, torch.int32, "row_pos"), _ptr(wq, dt, "wq"), _ptr(wk, dt, "wk"),
         _ptr(wv, dt, "wv"), ctypes.byref(var), _ptr(q_out, dt, "q_out"),
         _ptr(k_out, dt, "k_out"), _ptr(v_out, dt, "v_out"), m, wp, wb, _stream()))
@@ -347,21 +357,19 @@ def pkv_gather_qkv_proj_scatter(cfg: LayerCfg, hidden: torch.Tensor,
     m = _check_proj_args(cfg, hidden, row_idx, row_pos, wq, wk, wv, q_out, None, None)
     dt = cfg.torch_dtype
     n_cache = k_cache.shape[0]
-    if tuple(k_cache.shape) != (n_cache, cfg.n_kv_heads, cfg.head_dim) or \
+    if k_cache.shape != (n_cache, cfg.n_kv_heads, cfg.head_dim) or \
             v_cache.shape != k_cache.shape:
         raise ValueError("caches must be [n_cache, Hkv, D]")
-    if tuple(dst_row.shape) != (m,):
+    if dst_row.shape != (m,):
         raise ValueError("dst_row must be [m]")
 
     def raw(t, name):
-        p = _ptr(t, dt, name)
-        return None if p is None else p.value
+        return _ptr(t, dt, name)
     var = _CVariant(raw(bq, "bq"), raw(bk, "bk"), raw(bv, "bv"), raw(q_norm, "q_norm"),
                     raw(k_norm, "k_norm"), float(norm_eps))
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_gather_qkv_proj_scatter", load_library().pkv_gather_qkv_proj_scatter(
-        ctypes.byref(c), _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
+        cfg._ref, _ptr(hidden, dt, "hidden"), _ptr(row_idx, torch.int32, "row_idx"),
         _ptr(row_pos, torch.int32, "row_pos"), _ptr(wq, dt, "wq"), _ptr(wk, dt, "wk"),
         _ptr(wv, dt, "wv"), ctypes.byref(var), _ptr(q_out, dt, "q_out"),
         _ptr(k_cache, dt, "k_cache"), _ptr(v_cache, dt, "v_cache"),
@@ -374,13 +382,12 @@ def pkv_scatter_kv(cfg: LayerCfg, k_new: torch.Tensor, v_new: torch.Tensor,
     m, n_cache = dst_row.shape[0], k_cache.shape[0]
     dt = cfg.torch_dtype
     row = (cfg.n_kv_heads, cfg.head_dim)
-    if tuple(k_new.shape) != (m, *row) or tuple(v_new.shape) != (m, *row):
+    if k_new.shape != (m, *row) or v_new.shape != (m, *row):
         raise ValueError("k_new/v_new must be [m, Hkv, D]")
-    if tuple(k_cache.shape) != (n_cache, *row) or v_cache.shape != k_cache.shape:
+    if k_cache.shape != (n_cache, *row) or v_cache.shape != k_cache.shape:
         raise ValueError("caches must be [n_cache, Hkv, D]")
-    c = cfg._c()
     _check("pkv_scatter_kv", load_library().pkv_scatter_kv(
-        ctypes.byref(c), _ptr(k_new, dt, "k_new"), _ptr(v_new, dt, "v_new"),
+        cfg._ref, _ptr(k_new, dt, "k_new"), _ptr(v_new, dt, "v_new"),
         _ptr(dst_row, torch.int32, "dst_row"), _ptr(k_cache, dt, "k_cache"),
         _ptr(v_cache, dt, "v_cache"), m, n_cache, _stream()))
 
@@ -392,17 +399,16 @@ def pkv_sparse_row_attn(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.Tensor,
                         ws: Optional[torch.Tensor] = None) -> None:
     m, n_keys = row_pos.shape[0], k_cache.shape[0]
     dt = cfg.torch_dtype
-    if tuple(q.shape) != (m, cfg.n_q_heads, cfg.head_dim) or out.shape != q.shape:
+    if q.shape != (m, cfg.n_q_heads, cfg.head_dim) or out.shape != q.shape:
         raise ValueError("q/out must be [m, Hq, D]")
-    if tuple(k_cache.shape) != (n_keys, cfg.n_kv_heads, cfg.head_dim) or \
+    if k_cache.shape != (n_keys, cfg.n_kv_heads, cfg.head_dim) or \
             v_cache.shape != k_cache.shape:
         raise ValueError("caches must be [n_keys, Hkv, D]")
-    if lse_out is not None and tuple(lse_out.shape) != (m, cfg.n_q_heads):
+    if lse_out is not None and lse_out.shape != (m, cfg.n_q_heads):
         raise ValueError("lse_out must be [m, Hq]")
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_sparse_row_attn", load_library().pkv_sparse_row_attn(
-        ctypes.byref(c), _ptr(q, dt, "q"), _ptr(k_cache, dt, "k_cache"),
+        cfg._ref, _ptr(q, dt, "q"), _ptr(k_cache, dt, "k_cache"),
         _ptr(v_cache, dt, "v_cache"), _ptr(row_pos, torch.int32, "row_pos"),
         _ptr(out, dt, "out"), _ptr(lse_out, torch.float32, "lse_out"), m, n_keys,
         float(softmax_scale), wp, wb, _stream()))
@@ -411,9 +417,8 @@ def pkv_sparse_row_attn(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.Tensor,
 def pkv_sparse_row_attn_ctx_lse_workspace_bytes(cfg: LayerCfg, n_keys: int, n_ctx: int,
                                                 m: int) -> int:
     """Scratch of pkv_sparse_row_attn_ctx_lse; 0 when the geometry is not supported."""
-    c = cfg._c()
     return int(load_library().pkv_sparse_row_attn_ctx_lse_workspace_bytes(
-        ctypes.byref(c), int(n_keys), int(n_ctx), int(m)))
+        cfg._ref, int(n_keys), int(n_ctx), int(m)))
 
 
 def pkv_sparse_row_attn_ctx_lse(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.Tensor,
@@ -424,18 +429,17 @@ def pkv_sparse_row_attn_ctx_lse(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.T
                                 ws: Optional[torch.Tensor] = None) -> None:
     m, n_keys = row_pos.shape[0], k_cache.shape[0]
     dt = cfg.torch_dtype
-    if tuple(q.shape) != (m, cfg.n_q_heads, cfg.head_dim) or out.shape != q.shape:
+    if q.shape != (m, cfg.n_q_heads, cfg.head_dim) or out.shape != q.shape:
         raise ValueError("q/out must be [m, Hq, D]")
-    if tuple(k_cache.shape) != (n_keys, cfg.n_kv_heads, cfg.head_dim) or \
+    if k_cache.shape != (n_keys, cfg.n_kv_heads, cfg.head_dim) or \
             v_cache.shape != k_cache.shape:
         raise ValueError("caches must be [n_keys, Hkv, D]")
     for name, t in (("lse_out", lse_out), ("lse_ctx_out", lse_ctx_out)):
-        if t is not None and tuple(t.shape) != (m, cfg.n_q_heads):
+        if t is not None and t.shape != (m, cfg.n_q_heads):
             raise ValueError(f"{name} must be [m, Hq]")
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_sparse_row_attn_ctx_lse", load_library().pkv_sparse_row_attn_ctx_lse(
-        ctypes.byref(c), _ptr(q, dt, "q"), _ptr(k_cache, dt, "k_cache"),
+        cfg._ref, _ptr(q, dt, "q"), _ptr(k_cache, dt, "k_cache"),
         _ptr(v_cache, dt, "v_cache"), _ptr(row_pos, torch.int32, "row_pos"),
         _ptr(out, dt, "out"), _ptr(lse_out, torch.float32, "lse_out"),
         _ptr(lse_ctx_out, torch.float32, "lse_ctx_out"), m, n_keys, int(n_ctx),
@@ -447,20 +451,19 @@ def pkv_query_score_lse(cfg: LayerCfg, q: torch.Tensor, k: torch.Tensor, lse: to
                         accumulate: bool = False, softmax_scale: float = 0.0,
                         ws: Optional[torch.Tensor] = None) -> None:
     nq, n_ctx = q.shape[0], k.shape[0]
-    if tuple(q.shape) != (nq, cfg.n_q_heads, cfg.head_dim):
+    if q.shape != (nq, cfg.n_q_heads, cfg.head_dim):
         raise ValueError("q must be [nq, Hq, D]")
-    if tuple(k.shape) != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
+    if k.shape != (n_ctx, cfg.n_kv_heads, cfg.head_dim):
         raise ValueError("k must be [n_ctx, Hkv, D]")
-    if tuple(lse.shape) != (nq, cfg.n_q_heads):
+    if lse.shape != (nq, cfg.n_q_heads):
         raise ValueError("lse must be [nq, Hq]")
-    if row_pos is not None and tuple(row_pos.shape) != (nq,):
+    if row_pos is not None and row_pos.shape != (nq,):
         raise ValueError("row_pos must be [nq]")
-    if tuple(score.shape) != (n_ctx,):
+    if score.shape != (n_ctx,):
         raise ValueError("score must be [n_ctx]")
     wp, wb = _ws(ws)
-    c = cfg._c()
     _check("pkv_query_score_lse", load_library().pkv_query_score_lse(
-        ctypes.byref(c), _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
+        cfg._ref, _ptr(q, cfg.torch_dtype, "q"), _ptr(k, cfg.torch_dtype, "k"),
         _ptr(lse, torch.float32, "lse"), _ptr(row_pos, torch.int32, "row_pos"),
         _ptr(score, torch.float32, "score"), nq, n_ctx, float(softmax_scale),
         int(bool(accumulate)), wp, wb, _stream()))
@@ -484,9 +487,9 @@ def pkv_rmsnorm_rows(h: torch.Tensor, row_idx: Optional[torch.Tensor],
                      weight: torch.Tensor, eps: float, y: torch.Tensor) -> None:
     m, hidden = y.shape
     dt = h.dtype
-    if h.dim() != 2 or h.shape[1] != hidden or tuple(weight.shape) != (hidden,):
+    if h.dim() != 2 or h.shape[1] != hidden or weight.shape != (hidden,):
         raise ValueError("h must be [rows, hidden], weight [hidden], y [m, hidden]")
-    if row_idx is not None and tuple(row_idx.shape) != (m,):
+    if row_idx is not None and row_idx.shape != (m,):
         raise ValueError("row_idx must be [m]")
     if row_idx is None and h.shape[0] < m:
         raise ValueError("h has fewer than m rows")
@@ -497,7 +500,7 @@ def pkv_rmsnorm_rows(h: torch.Tensor, row_idx: Optional[torch.Tensor],
 
 def pkv_gather_rows(src: torch.Tensor, row_idx: torch.Tensor, dst: torch.Tensor) -> None:
     m, width = dst.shape
-    if src.dim() != 2 or src.shape[1] != width or tuple(row_idx.shape) != (m,):
+    if src.dim() != 2 or src.shape[1] != width or row_idx.shape != (m,):
         raise ValueError("src must be [rows, width], row_idx [m], dst [m, width]")
     _check("pkv_gather_rows", load_library().pkv_gather_rows(
         _dtype_code(src), _ptr(src, src.dtype, "src"), _ptr(row_idx, torch.int32, "row_idx"),
@@ -509,9 +512,9 @@ def pkv_linear_rows(x: torch.Tensor, w: torch.Tensor, residual: Optional[torch.T
     m, k_in = x.shape
     n_out = w.shape[0]
     dt = x.dtype
-    if tuple(w.shape) != (n_out, k_in) or tuple(y.shape) != (m, n_out):
+    if w.shape != (n_out, k_in) or y.shape != (m, n_out):
         raise ValueError("w must be [n_out, k_in] and y [m, n_out]")
-    if residual is not None and tuple(residual.shape) != (m, n_out):
+    if residual is not None and residual.shape != (m, n_out):
         raise ValueError("residual must be [m, n_out]")
     wp, wb = _ws(ws)
     _check("pkv_linear_rows", load_library().pkv_linear_rows(
@@ -524,8 +527,8 @@ def pkv_swiglu_rows(x: torch.Tensor, w_gate: torch.Tensor, w_up: torch.Tensor,
     m, k_in = x.shape
     n_out = w_gate.shape[0]
     dt = x.dtype
-    if tuple(w_gate.shape) != (n_out, k_in) or w_up.shape != w_gate.shape or \
-            tuple(y.shape) != (m, n_out):
+    if w_gate.shape != (n_out, k_in) or w_up.shape != w_gate.shape or \
+            y.shape != (m, n_out):
         raise ValueError("w_gate/w_up must be [n_out, k_in] and y [m, n_out]")
     wp, wb = _ws(ws)
     _check("pkv_swiglu_rows", load_library().pkv_swiglu_rows(
