@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 #pragma unroll
             for (int j = 0; j < 2; ++j) issue_x(par, i, j, adv);
     }
-    wait_vm<22>();     // W0..W3 and X0 of step 0 (the first ten of 32 instructions) landed
+    wait_vm<20>();     // W0..W3, X0 and X1 of step 0 (the first twelve of 32: quarter 0 reads X1)
     __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) {
