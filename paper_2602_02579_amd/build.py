@@ -20,7 +20,8 @@ LIB_PATH = os.path.join(HERE, "libpkv.so")
 
 SOURCES = ["pkv_api.hip", "rope_restore.hip", "query_score.hip", "query_score_dma.hip",
            "topk_select.hip", "gather_qkv_proj.hip", "gather_qkv_proj_dma.hip",
-           "scatter_kv.hip", "layer_glue.hip", "static_scratch.hip", "f32_kernels.hip",
+           "gather_qkv_proj_tiles.hip", "scatter_kv.hip", "layer_glue.hip",
+           "static_scratch.hip", "f32_kernels.hip",
            "sparse_row_attn.hip", "sparse_row_attn_dma.hip", "sparse_row_attn_w8.hip",
            "sparse_row_attn_w8n.hip"]
 

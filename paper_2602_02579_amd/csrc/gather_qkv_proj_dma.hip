@@ -31,13 +31,13 @@
 // contiguous run of tiles, 8 token tiles deep, and its L2 sees few distinct
 // operand panels at a time.
 //
-// A launch with few rows (the user-query projection of the scoring stage: 128 rows,
-// 16 tiles) cannot fill 256 CUs with tiles alone, so its contraction is split: every
-// split writes fp32 partial tiles, and a second small kernel adds them in a fixed
-// order, rotates and rounds (deterministic: no atomics).
+// A launch that cannot fill 256 CUs with such tiles takes lower or smaller ones
+// (plan_tiles) and, with very few rows (the user-query projection of the scoring stage),
+// splits its contraction: every split writes fp32 partial tiles, and a second small
+// kernel adds them in a fixed order, rotates and rounds (deterministic: no atomics).
 #include <atomic>
 
-#include "proj_common.h"
+#include "proj_tile.h"
 
 namespace pkv {
 
@@ -51,39 +51,8 @@ constexpr int kRowBytes = BK * 2;                // 64
 constexpr int kOperandBytes = T * kRowBytes;     // 16 KB: 256 rows of one operand
 constexpr int kStageBytes = 2 * kOperandBytes;   // token rows, then feature rows
 constexpr int kLdsBytes = NS * kStageBytes;      // 160 KB, all of a CU's LDS
-constexpr int kEpiStride = 272;                  // bytes per token of the store staging
 constexpr int kEpiStrideF32 = 528;               // same for fp32 partial tiles (32 tokens)
 constexpr int kGroup = 8;                        // token tiles per group
-
-// 16 bytes per lane from global memory straight into LDS: lane i of the wave
-// writes LDS bytes [lds_base + 16 i, +16); lds_base must be wave-uniform.
-__device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, off"
-        :
-        : "s"(lds_base), "v"(gptr)
-        : "memory", "m0");
-}
-// c += a . b on a 16 x 16 tile, 32 of the contraction.  Written out so that the accumulator
-// stays where it is: left to itself the register allocator rotates the 64 accumulators of a
-// wave through copies (584 of them per two steps) once they are four registers each.  The
-// compiler does not see the result's latency: acc_settle() before the first reader.
-__device__ __forceinline__ void mfma_16x16x32(f32x4& c, bf16x8 a, bf16x8 b) {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// silu(a) = a / (1 + e^-a) with the hardware reciprocal (1 ulp): the result is rounded to
-// bf16 right away, and a full-precision division would cost ten instructions per element
-__device__ __forceinline__ float silu_f32(float a) {
-    return a * __builtin_amdgcn_rcpf(1.f + __expf(-a));
-}
 
 // EXTRA (Q | K | V mode only): the launch has projection biases, per-head norm gains and/or
 // a fused cache update (K/V rows stored at dst_row)
@@ -98,8 +67,8 @@ struct TileCtx {
 // rotate pairs in registers / add the residual / gate, round, stage through LDS, store
 // 16 B per lane; or store the fp32 partial tile of a split contraction.  Called after the
 // main loop, when nothing is still writing the LDS stages.
-template <int MODE, bool EXTRA>
-__device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[8][8],
+template <int MODE, bool EXTRA, int NQ>
+__device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[8][2 * NQ],
                                               const TileCtx& c, unsigned char* smem) {
     const int lane = c.lane, wave = c.wave, g4 = c.g4, l16 = c.l16, wt = c.wt, wf = c.wf;
     const int split = c.split, ft = c.ft, mat = c.mat, feat0 = c.feat0, row0 = c.row0;
@@ -114,8 +83,8 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
         unsigned char* epf = smem + wave * (32 * kEpiStrideF32);
         const int f_total = T * p.tile_begin[3];
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb) {
-            const int rbase = row0 + wt * 128 + tb * 32;
+        for (int tb = 0; tb < NQ; ++tb) {
+            const int rbase = row0 + wt * (32 * NQ) + tb * 32;
             if (rbase >= p.m) break;   // wave-uniform
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
@@ -136,28 +105,28 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
         }
         return;
     }
-    unsigned char* epi = smem + wave * (64 * kEpiStride);
+    unsigned char* epi = smem + wave * (16 * NQ * kEpiStride);
     if (MODE == kProjPlain) {
-        // the wave's 128 tokens x 128 outputs: round the products, stage, then add the
+        // the wave's 32 NQ tokens x 128 outputs: round the products, stage, then add the
         // residual (if any) 16 B per lane and round again
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
+            for (int nt = 0; nt < NQ; ++nt) {
                 unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
                 for (int mt = 0; mt < 8; ++mt) {
                     bf16x4 v;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)acc[mt][half * 4 + nt][e];
+                    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)acc[mt][half * NQ + nt][e];
                     *reinterpret_cast<bf16x4*>(erow + (mt * 16 + 4 * g4) * 2) = v;
                 }
             }
 #pragma unroll
-            for (int it = 0; it < 16; ++it) {
+            for (int it = 0; it < 4 * NQ; ++it) {
                 const int idx = it * 64 + lane;
                 const int tok = idx >> 4, ch = idx & 15;
-                const int row = row0 + wt * 128 + half * 64 + tok;
+                const int row = row0 + wt * (32 * NQ) + half * (16 * NQ) + tok;
                 bf16x8 v = *reinterpret_cast<const bf16x8*>(epi + tok * kEpiStride + ch * 16);
                 if (row < p.m) {
                     const int64_t o = (int64_t)row * p.n_out + feat0 + wf * 128 + ch * 8;
@@ -173,12 +142,12 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
         return;
     }
     if (MODE == kProjGated) {
-        // the wave's 128 tokens x 64 outputs: gate in feature blocks 0..3 and up in 4..7
+        // the wave's 32 NQ tokens x 64 outputs: gate in feature blocks 0..3 and up in 4..7
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int tt = half * 4 + nt;
+            for (int nt = 0; nt < NQ; ++nt) {
+                const int tt = half * NQ + nt;
                 unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt) {
@@ -194,10 +163,10 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
                 }
             }
 #pragma unroll
-            for (int it = 0; it < 8; ++it) {
+            for (int it = 0; it < 2 * NQ; ++it) {
                 const int idx = it * 64 + lane;
                 const int tok = idx >> 3, ch = idx & 7;
-                const int row = row0 + wt * 128 + half * 64 + tok;
+                const int row = row0 + wt * (32 * NQ) + half * (16 * NQ) + tok;
                 const uint4 v = *reinterpret_cast<const uint4*>(epi + tok * kEpiStride + ch * 16);
                 if (row < p.m)
                     *reinterpret_cast<uint4*>(out + (int64_t)row * p.n_out + ft * 128 + wf * 64 +
@@ -214,9 +183,9 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int tt = half * 4 + nt;
-            const int row = min(row0 + wt * 128 + tt * 16 + l16, p.m - 1);
+        for (int nt = 0; nt < NQ; ++nt) {
+            const int tt = half * NQ + nt;
+            const int row = min(row0 + wt * (32 * NQ) + tt * 16 + l16, p.m - 1);
             const float4* cs = reinterpret_cast<const float4*>(p.cs + (int64_t)row * (D / 2));
             unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
             float rnorm = 1.f;
@@ -283,12 +252,12 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
                 *reinterpret_cast<bf16x4*>(erow + (i0 + D / 2) * 2) = vb;
             }
         }
-        // the wave's own 64 tokens x 256 B, now 16 B per lane and 256 B per row
+        // the wave's own 16 NQ tokens x 256 B, now 16 B per lane and 256 B per row
 #pragma unroll
-        for (int it = 0; it < 16; ++it) {
+        for (int it = 0; it < 4 * NQ; ++it) {
             const int idx = it * 64 + lane;
             const int tok = idx >> 4, ch = idx & 15;
-            const int row = row0 + wt * 128 + half * 64 + tok;
+            const int row = row0 + wt * (32 * NQ) + half * (16 * NQ) + tok;
             const uint4 v = *reinterpret_cast<const uint4*>(epi + tok * kEpiStride + ch * 16);
             if (row < p.m) {
                 const int64_t orow = (EXTRA && mat != 0 && p.dst_row) ? p.dst_row[row] : row;
@@ -456,35 +425,37 @@ __global__ __launch_bounds__(256) void proj_dma_kernel(ProjParams p, int n_tok_t
     ctx.lane = lane; ctx.wave = wave; ctx.g4 = g4; ctx.l16 = l16; ctx.wt = wt; ctx.wf = wf;
     ctx.split = split; ctx.ft = ft; ctx.mat = mat; ctx.feat0 = feat0; ctx.row0 = row0;
     ctx.heads_out = heads_out; ctx.out = out;
-    tile_epilogue<MODE, EXTRA>(p, acc, ctx, smem);
+    tile_epilogue<MODE, EXTRA, 4>(p, acc, ctx, smem);
 }
 
 // ---------------------------------------------------------------------------------------
-// The same tile with the contraction in steps of 64 ("slabs"): every fill instruction
+// The same tile, or one of 64 NQ = 192 tokens, with the contraction in steps of 64 ("slabs"): every fill instruction
 // fetches whole 128-byte lines (8 rows x 128 B), which the memory pipeline serves at
 // 1.7 x the rate of the 64-byte row pieces of the kernel above and at a higher clock.
 //
-// LDS: a ring of 16 units of 8 KB; a unit is 64 rows x 128 B of one operand.  A step T
-// needs four feature units W0..W3 (tile rows 64 i ..) and four token units X0..X3, where
-// X_q holds the rows both token halves consume in quarter q of the step: tile rows
-// 32 q .. + 32 and 128 + 32 q .. + 32.  Units of step T sit in slots 8 (T & 1) + (0..7).
+// LDS: two steps' worth of units of 8 KB; a unit is 64 rows x 128 B of one operand.  A step T
+// needs four feature units W0..W3 (tile rows 64 i ..) and NQ token units X0.., where
+// X_q holds the rows both token halves consume in part q of the step: tile rows
+// 32 q .. + 32 and 32 NQ + 32 q .. + 32.  Step T uses the units of its parity.
 // The 16-byte chunk c of unit row r is stored at position c ^ ((r >> 1) & 7): two 128-byte
 // rows span the 64 banks, so the sixteen lanes that an operand read serves per clock (rows
 // r .. r + 15, one logical chunk) must differ in (r & 1, position) - with c ^ (r & 7) rows r
 // and r + 8 met in one bank group and every read took two passes (SQ_LDS_BANK_CONFLICT).
 //
-// A step is 128 MFMAs per wave in four quarters; quarter q multiplies the wave's eight
-// feature blocks by its token blocks 2 q, 2 q + 1 for both 32-wide sub-steps.  The feature
-// operands of a whole step live in registers (loaded during the second half of the
-// previous step), so the W units of step T are free again when T begins and are refilled
-// with step T + 2 during its first two quarters; X_q is free after quarter q - 1 and is
-// refilled in quarters 2 and 3.  One barrier per quarter, two fill instructions per wave
-// and unit, one fill instruction every eight MFMAs, as in the kernel above.
+// A step is NQ quarters (of the 256-token tile's 128 MFMAs per wave) of 32 MFMAs; quarter q
+// multiplies the wave's eight feature blocks by its token blocks 2 q, 2 q + 1 for both 32-wide
+// sub-steps.  The feature operands of a whole step live in registers (loaded during the last
+// two quarters of the previous step), so the W units of step T are free again when T begins and
+// are refilled with step T + 2 from its first quarter on; X_q is free after quarter q - 1 and is
+// refilled behind them.  One barrier per quarter, two fill instructions per wave
+// and unit, one fill instruction every eight MFMAs where there are four quarters; with three the
+// features' fills all go out in the first, so that they have three quarters to land.
 // Needs an even number (>= 2) of steps per split.
 constexpr int kUnitBytes = 64 * 128;
-constexpr int kSlabLdsBytes = 16 * kUnitBytes;
+template <int NQ>
+constexpr int kSlabLdsBytes = 2 * (4 + NQ) * kUnitBytes;
 
-template <int MODE, bool EXTRA = false>
+template <int MODE, bool EXTRA, int NQ>
 __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_tiles,
                                                         int n_tiles, int per_xcd) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -516,7 +487,7 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     const bf16_t* w = p.w[mat];
     bf16_t* out = p.out[mat];
     const int heads_out = mat == 0 ? p.hq : p.hkv;
-    const int row0 = tok_tile * T;
+    const int row0 = tok_tile * (64 * NQ);
 
     const int n_T = p.hid / 64 / p.n_ksplit;   // steps of this split: even, >= 2 (launcher)
     const int k_begin = split * n_T * 64;
@@ -524,9 +495,10 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     // ---- fill side: wave w issues instructions j = 0, 1 of every unit: unit rows
     // 8 (2 w + j) .. + 8; lane = (row in the eight, position), fetching the chunk that
     // belongs at that position: pos ^ ((unit row >> 1) & 7) = pos ^ (4 j + (row >> 1))
+    constexpr int kFills = 8 + 2 * NQ;   // fill instructions of a wave per step
     const int rl = lane >> 3;
     const bf16_t* wptr[4][2];
-    const bf16_t* xptr[4][2];
+    const bf16_t* xptr[NQ][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -540,7 +512,8 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
             } else {
                 wptr[i][j] = w + (int64_t)(feat0 + r) * p.hid + k_begin + gchunk * 8;
             }
-            const int xr = ur < 32 ? 32 * i + ur : 96 + 32 * i + ur;   // token row of the tile
+            if (i >= NQ) continue;
+            const int xr = 32 * i + (ur < 32 ? ur : 32 * NQ - 32 + ur);   // token row of the tile
             const int gr = min(row0 + xr, p.m - 1);
             const int64_t src_row = p.row_idx ? p.row_idx[gr] : gr;
             xptr[i][j] = p.hidden + src_row * p.hid + k_begin + gchunk * 8;
@@ -550,11 +523,11 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     // unit i of the feature (which = 1) or token (which = 0) operand of a step with
     // parity par; adv is 64, or 0 once the last step has been requested
     auto issue_w = [&](int par, int i, int j, int adv) {
-        dma16(wptr[i][j], lds_fill + (par * 8 + i) * kUnitBytes + j * 1024);
+        dma16(wptr[i][j], lds_fill + (par * (4 + NQ) + i) * kUnitBytes + j * 1024);
         wptr[i][j] += adv;
     };
     auto issue_x = [&](int par, int i, int j, int adv) {
-        dma16(xptr[i][j], lds_fill + (par * 8 + 4 + i) * kUnitBytes + j * 1024);
+        dma16(xptr[i][j], lds_fill + (par * (4 + NQ) + 4 + i) * kUnitBytes + j * 1024);
         xptr[i][j] += adv;
     };
 
@@ -567,8 +540,8 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const uint32_t swz = (uint32_t)(((4 * ks + g4) ^ (l16 >> 1)) * 16);
-            base_w[par][ks] = par * 8 * kUnitBytes + 2 * wf * kUnitBytes + l16 * 128 + swz;
-            base_x[par][ks] = par * 8 * kUnitBytes + 4 * kUnitBytes + (wt * 32 + l16) * 128 + swz;
+            base_w[par][ks] = par * (4 + NQ) * kUnitBytes + 2 * wf * kUnitBytes + l16 * 128 + swz;
+            base_x[par][ks] = par * (4 + NQ) * kUnitBytes + 4 * kUnitBytes + (wt * 32 + l16) * 128 + swz;
         }
     auto ld = [&](uint32_t off) { return *reinterpret_cast<const bf16x8*>(smem + off); };
 
@@ -576,11 +549,11 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     bf16x8 fw1[8];      // [feature block], sub-step 1
     bf16x8 fx[2][2][2]; // [quarter parity][sub-step][token block]
 
-    f32x4 acc[8][8];   // [feature block][token block]
+    f32x4 acc[8][2 * NQ];   // [feature block][token block]
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
+        for (int nt = 0; nt < 2 * NQ; ++nt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[mt][nt][r] = 0.f;
 
@@ -593,11 +566,11 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 #pragma unroll
             for (int j = 0; j < 2; ++j) issue_w(par, i, j, adv);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NQ; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) issue_x(par, i, j, adv);
     }
-    wait_vm<20>();     // W0..W3, X0 and X1 of step 0 (the first twelve of 32: quarter 0 reads X1)
+    wait_vm<2 * kFills - 12>();   // W0..W3, X0 and X1 of step 0 (the first twelve) landed
     __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) {
@@ -620,29 +593,40 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 #define PKV_QUARTER(PAR, Q, ADV)                                                          \
     {                                                                                     \
         _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_) {                                \
-            const int ks = (Q) == 3 ? 1 - (g_ >> 1) : g_ >> 1;                            \
+            const int ks = (Q) == NQ - 1 ? 1 - (g_ >> 1) : g_ >> 1;                       \
             const int nt = g_ & 1;                                                        \
+            constexpr int qp_ = (PAR) * (NQ & 1);   /* an odd NQ flips the parity */      \
             _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                            \
                 const bf16x8 a_ = ks == 0 ? fw0[PAR][mt] : fw1[mt];                       \
-                mfma_16x16x32(acc[mt][2 * (Q) + nt], a_, fx[(Q) & 1][ks][nt]);            \
-                if ((Q) == 3 && g_ == 1)   /* last use: take step T + 1's operand */      \
+                mfma_16x16x32(acc[mt][2 * (Q) + nt], a_, fx[((Q) + qp_) & 1][ks][nt]);    \
+                if ((Q) == NQ - 1 && g_ == 1)   /* last use: take step T + 1's operand */ \
                     fw1[mt] = ld(base_w[(PAR) ^ 1][1] + mt * 2048);                       \
             }                                                                             \
             __builtin_amdgcn_sched_barrier(0);                                            \
-            /* fill: quarters 0, 1 -> feature units 2 Q, 2 Q + 1; 2, 3 -> token units */  \
-            if ((Q) < 2) issue_w(PAR, 2 * (Q) + (g_ >> 1), g_ & 1, ADV);                  \
-            else issue_x(PAR, 2 * ((Q) - 2) + (g_ >> 1), g_ & 1, ADV);                    \
+            /* fill, 4 quarters: feature units 2 Q, 2 Q + 1, then token units in twos; */ \
+            /* 3 quarters: all feature units, token units 0 and 1, token unit 2        */ \
+            if (NQ == 4) {                                                                \
+                if ((Q) < 2) issue_w(PAR, 2 * (Q) + (g_ >> 1), g_ & 1, ADV);              \
+                else issue_x(PAR, 2 * ((Q) - 2) + (g_ >> 1), g_ & 1, ADV);                \
+            } else if ((Q) == 0) {                                                        \
+                issue_w(PAR, g_, 0, ADV);                                                 \
+                issue_w(PAR, g_, 1, ADV);                                                 \
+            } else if ((Q) == 1) {                                                        \
+                issue_x(PAR, g_ >> 1, g_ & 1, ADV);                                       \
+            } else if (g_ < 2) {                                                          \
+                issue_x(PAR, 2, g_, ADV);                                                 \
+            }                                                                             \
             /* token operands of the next quarter: 2, 1, 1, 0 per group */                \
             _Pragma("unroll") for (int n_ = 0; n_ < 4; ++n_) {                            \
                 if ((n_ < 2 ? 0 : n_ - 1) != g_) continue;                                \
                 const int k2 = n_ >> 1, t2 = n_ & 1;                                      \
-                if ((Q) < 3)                                                              \
-                    fx[((Q) + 1) & 1][k2][t2] =                                           \
+                if ((Q) < NQ - 1)                                                         \
+                    fx[((Q) + qp_ + 1) & 1][k2][t2] =                                     \
                         ld(base_x[PAR][k2] + ((Q) + 1) * 8192 + t2 * 2048);               \
-                else fx[0][k2][t2] = ld(base_x[(PAR) ^ 1][k2] + t2 * 2048);               \
+                else fx[((Q) + qp_ + 1) & 1][k2][t2] = ld(base_x[(PAR) ^ 1][k2] + t2 * 2048); \
             }                                                                             \
-            /* quarter 2: sub-step 0 feature operands of the next step: 2, 4, 2, 0 */     \
-            if ((Q) == 2) {                                                               \
+            /* last quarter but one: sub-step 0 feature operands of the next step */      \
+            if ((Q) == NQ - 2) {                                                          \
                 _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                        \
                     if ((mt < 2 ? 0 : mt < 6 ? 1 : 2) != g_) continue;                    \
                     fw0[(PAR) ^ 1][mt] = ld(base_w[(PAR) ^ 1][0] + mt * 2048);            \
@@ -651,13 +635,19 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
             __builtin_amdgcn_sched_barrier(0);                                            \
         }                                                                                 \
     }
-    // outstanding fills allowed at the barrier that ends quarter 0, 1, 2, 3 (see above):
-    // what the next quarter reads was requested at least 22 / 16 / 18 / 20 instructions ago
+    // Outstanding fills allowed at the barrier before a quarter.  Quarter q reads token unit
+    // q + 1 of its step (the last one unit 0 of the next step), the last two quarters the
+    // feature units of the next step; a wave's fills land in order, so what may be outstanding
+    // is what was issued behind the youngest of those: the rest of its step's kFills, all of
+    // the step after, and this step's fills so far (0, 4, 8, 12 with four quarters; 0, 8, 12
+    // with three).
 #define PKV_STEP(PAR, ADV)                                                                \
-    PKV_QUARTER(PAR, 0, ADV) wait_vm<22>(); __syncthreads();                              \
+    PKV_QUARTER(PAR, 0, ADV) wait_vm<(NQ == 4 ? 22 : 14)>(); __syncthreads();             \
     PKV_QUARTER(PAR, 1, ADV) wait_vm<16>(); __syncthreads();                              \
-    PKV_QUARTER(PAR, 2, ADV) wait_vm<18>(); __syncthreads();                              \
-    PKV_QUARTER(PAR, 3, ADV) wait_vm<20>(); __syncthreads();
+    if constexpr (NQ == 4) {                                                              \
+        PKV_QUARTER(PAR, 2, ADV) wait_vm<18>(); __syncthreads();                          \
+    }                                                                                     \
+    PKV_QUARTER(PAR, NQ - 1, ADV) wait_vm<(NQ == 4 ? 20 : 16)>(); __syncthreads();
 
     for (int t = 0; t < n_T; t += 2) {
         const int adv0 = t + 3 < n_T ? 64 : 0;   // step t fetches step t + 2
@@ -674,7 +664,7 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     ctx.lane = lane; ctx.wave = wave; ctx.g4 = g4; ctx.l16 = l16; ctx.wt = wt; ctx.wf = wf;
     ctx.split = split; ctx.ft = ft; ctx.mat = mat; ctx.feat0 = feat0; ctx.row0 = row0;
     ctx.heads_out = heads_out; ctx.out = out;
-    tile_epilogue<MODE, EXTRA>(p, acc, ctx, smem);
+    tile_epilogue<MODE, EXTRA, NQ>(p, acc, ctx, smem);
 }
 
 // adds the splits of the contraction in a fixed order, rotates, rounds once, stores.
@@ -764,8 +754,68 @@ __global__ __launch_bounds__(256) void linear_splitk_finish_kernel(ProjParams p)
     *reinterpret_cast<bf16x4*>(p.out[0] + o) = v;
 }
 
-// splits of the contraction for a launch of n_tiles tiles over n_k stages: the largest
-// power of two that keeps the launch within ~256 workgroups and a split >= NS stages
+// ---- which tile, how many splits ---------------------------------------------------------
+// Four tiles: 64 or 128 tokens x 128 features (gather_qkv_proj_tiles.hip), 192 or 256 tokens x
+// 256 features (the slab kernel; contractions that are no multiple of 128 take the 32-wide
+// ring).  The large ones have the better rate once the chip is full (8192^3: 1467 TFLOP/s), the
+// small ones fill it with fewer rows and without splitting the contraction, whose fp32 partial
+// tiles cost a round trip through memory and a second launch.  The choice minimises an estimate
+// of the launch time:
+//     rounds of the CUs x (fixed + step cost x steps)  against  bytes / 7 TB/s  (+ partials)
+// where a partly filled round costs between a full one and its share (the CUs that work clock
+// higher).  The constants are fitted to 2661 launches (1024 to 14336 inputs, 1024 to 28672
+// outputs, 16 to 6681 rows, 1 to 16 splits; rms error 5 %).  Over those 228 shapes the choice is
+// within 1 % of the fastest tile on average and 1.46 x faster than 256 x 256 tiles alone were:
+// 64 rows x 4096 x 4096 24 -> 15 us, x 28672 gated 64 -> 45; 512 rows x 4096 x 4096 39 -> 30;
+// 1702 rows x 6144 x 4096 84 -> 70; 256 rows x 1536 x 1024 21 -> 8.  The present plan's
+// 256-token tile is left only for one that is estimated 5 % faster.
+struct TileCost {
+    float fixed, step;      // us per tile and per 64 of the contraction
+    float part;             // share of a full round that an almost empty one costs
+    float overlap;          // how badly the loop and the memory traffic overlap
+};
+constexpr int kTileTokens[4] = {64, 128, 192, 256};
+constexpr TileCost kTileCost[4] = {{0.855f, 0.401f, 0.744f, 0.597f},
+                                   {2.217f, 0.512f, 0.759f, 0.378f},
+                                   {5.207f, 1.044f, 0.742f, 0.253f},
+                                   {6.630f, 1.348f, 0.721f, 0.179f}};
+
+struct TilePlan { int tokens, ksplit; };
+
+// features of a launch x splits of its contraction that the fp32 partials have room for
+// (256 tiles' worth of 256 x 256; nothing for launches of more than 128 token tiles)
+int64_t partial_features(int64_t m) {
+    const int64_t n_tok_tiles = ceil_div(m, T);
+    return n_tok_tiles > 128 ? 0 : (int64_t)T * 256 / n_tok_tiles;
+}
+
+float estimate_us(int kind, int64_t m, int64_t features, int64_t k_in, int ks) {
+    const TileCost& c = kTileCost[kind];
+    const int64_t tiles =
+        ceil_div(m, kTileTokens[kind]) * (features / (kind < 2 ? 128 : 256)) * ks;
+    const float steps = (float)k_in / (64.f * ks);
+    const float r = (float)tiles / 256.f;
+    const float full = (float)(tiles / 256), up = (float)ceil_div(tiles, 256);
+    float loop;
+    if (kind == 0) {
+        // two workgroups share a CU: a second tile costs 0.84 of a first one's steps
+        const float more = r <= 1.f ? 0.f : 0.564f * (up - 1.f) + 0.436f * (r - 1.f);
+        const float rounds = r <= 1.f ? c.part + (1.f - c.part) * r : 1.f + 0.844f * more;
+        loop = c.step * steps * rounds + c.fixed * (1.f + 0.603f * more);
+    } else {
+        const float rounds = full + (up > full ? c.part + (1.f - c.part) * (r - full) : 0.f);
+        loop = c.step * steps * rounds + c.fixed * up;
+    }
+    const float mb = 2e-6f * ((float)features * k_in + (float)m * k_in + (float)m * features);
+    const float mem = mb / 7.094f;
+    const float hi = loop > mem ? loop : mem, lo = loop > mem ? mem : loop;
+    float t = 1.671f + hi + c.overlap * lo * lo / hi;
+    if (ks > 1) t += 3.956f + 8e-6f * (float)ks * (float)m * (float)features / 6.419f;
+    return t;
+}
+
+// what 256 x 256 tiles take: the largest power of two that keeps the launch within 256
+// workgroups and a split >= NS stages
 int plan_ksplit(int64_t n_tiles, int n_k) {
     int ks = 1;
     while (ks < 16 && n_tiles * (ks * 2) <= 256 && n_k % (ks * 2) == 0 && n_k / (ks * 2) >= NS)
@@ -773,14 +823,31 @@ int plan_ksplit(int64_t n_tiles, int n_k) {
     return ks;
 }
 
+TilePlan plan_tiles(int64_t m, int64_t features, int64_t k_in) {
+    const int64_t n_tiles = ceil_div(m, T) * (features / T);
+    TilePlan best = {256, plan_ksplit(n_tiles, (int)(k_in / BK))};
+    const float now = estimate_us(3, m, features, k_in, best.ksplit);
+    float t_best = 0.95f * now;
+    const int64_t room = partial_features(m);
+    for (int kind = n_tiles <= 2048 ? 0 : 2; kind < 4; ++kind)
+        for (int ks = 1; ks <= 16; ks *= 2) {
+            if (ks > 1 && ks * features > room) break;
+            if (k_in < 256 * ks || k_in % ((kind < 2 ? 64 : 128) * ks)) break;
+            const float t = estimate_us(kind, m, features, k_in, ks);
+            if (t < t_best) {
+                t_best = t;
+                best.tokens = kTileTokens[kind];
+                best.ksplit = ks;
+            }
+        }
+    return best;
+}
+
 }  // namespace
 
 size_t proj_dma128_partial_bytes(const pkv_layer_cfg& cfg, int64_t m) {
-    // n_ksplit * (features of the launch) <= 256 * 256 / (token tiles): see plan_ksplit
-    const int64_t n_tok_tiles = ceil_div(m, T);
-    if (n_tok_tiles > 128) return 0;
     (void)cfg;
-    return (size_t)m * (size_t)(T * 256 / n_tok_tiles) * sizeof(float);
+    return (size_t)m * (size_t)partial_features(m) * sizeof(float);
 }
 
 bool proj_dma128_supported(const pkv_layer_cfg& cfg, int64_t m) {
@@ -798,27 +865,40 @@ pkv_status launch_tiles(const ProjParams& p, hipStream_t st) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(proj_dma_kernel<MODE, EXTRA>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_kernel<MODE, EXTRA>),
+            hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_kernel<MODE, EXTRA, 4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kSlabLdsBytes) != hipSuccess)
+                                kSlabLdsBytes<4>) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_kernel<MODE, EXTRA, 3>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kSlabLdsBytes<3>) != hipSuccess)
             return PKV_ERR_LAUNCH;
         configured.store(true, std::memory_order_release);
     }
-    const int n_tok_tiles = (int)ceil_div(p.m, T);
-    const int64_t n_tiles = (int64_t)n_tok_tiles * p.tile_begin[3];
-    if (n_tiles == 0) return PKV_OK;
-    if (n_tiles > (1 << 30)) return PKV_ERR_SHAPE;
+    if (p.tile_begin[3] == 0) return PKV_OK;
+    if (ceil_div(p.m, T) * p.tile_begin[3] > (1 << 29)) return PKV_ERR_SHAPE;
+    const TilePlan plan = plan_tiles(p.m, (int64_t)p.tile_begin[3] * T, p.hid);
     ProjParams q = p;
-    q.n_ksplit = plan_ksplit(n_tiles, p.hid / BK);
+    q.n_ksplit = plan.ksplit;
     if (q.n_ksplit > 1 && q.partial == nullptr) return PKV_ERR_WORKSPACE;
-    const int per_xcd = (int)ceil_div(n_tiles * q.n_ksplit, 8);
-    // contraction in slabs of 64 when every split has an even number of them
-    if (p.hid % (128 * q.n_ksplit) == 0)
-        hipLaunchKernelGGL((proj_slab_kernel<MODE, EXTRA>), dim3((unsigned)(per_xcd * 8)),
-                           dim3(256), kSlabLdsBytes, st, q, n_tok_tiles, (int)n_tiles, per_xcd);
-    else
-        hipLaunchKernelGGL((proj_dma_kernel<MODE, EXTRA>), dim3((unsigned)(per_xcd * 8)),
-                           dim3(256), kLdsBytes, st, q, n_tok_tiles, (int)n_tiles, per_xcd);
+    if (plan.tokens < 192) {
+        const pkv_status rc = launch_proj_small<MODE, EXTRA>(plan.tokens, q, st);
+        if (rc != PKV_OK) return rc;
+    } else {
+        const int n_tok_tiles = (int)ceil_div(p.m, plan.tokens);
+        const int n_tiles = n_tok_tiles * p.tile_begin[3];
+        const int per_xcd = (int)ceil_div((int64_t)n_tiles * q.n_ksplit, 8);
+        const dim3 grid((unsigned)(per_xcd * 8)), block(256);
+        // contraction in slabs of 64 when every split has an even number of them
+        if (plan.tokens == 192)
+            hipLaunchKernelGGL((proj_slab_kernel<MODE, EXTRA, 3>), grid, block, kSlabLdsBytes<3>,
+                               st, q, n_tok_tiles, n_tiles, per_xcd);
+        else if (p.hid % (128 * q.n_ksplit) == 0)
+            hipLaunchKernelGGL((proj_slab_kernel<MODE, EXTRA, 4>), grid, block, kSlabLdsBytes<4>,
+                               st, q, n_tok_tiles, n_tiles, per_xcd);
+        else
+            hipLaunchKernelGGL((proj_dma_kernel<MODE, EXTRA>), grid, block, kLdsBytes, st, q,
+                               n_tok_tiles, n_tiles, per_xcd);
+    }
     if (q.n_ksplit > 1) {
         if (MODE == kProjRope) {
             const int64_t total = (int64_t)p.m * (T * p.tile_begin[3] / 2);
@@ -848,10 +928,7 @@ bool linear_dma_supported(int mode, int64_t m, int64_t k_in, int64_t n_out) {
 }
 
 size_t linear_dma_partial_bytes(int64_t m) {
-    // as for the Q/K/V launch: splits x features <= 256 tiles' worth
-    const int64_t n_tok_tiles = ceil_div(m, T);
-    if (m <= 0 || n_tok_tiles > 128) return 0;
-    return (size_t)m * (size_t)(T * 256 / n_tok_tiles) * sizeof(float);
+    return m <= 0 ? 0 : (size_t)m * (size_t)partial_features(m) * sizeof(float);
 }
 
 pkv_status launch_linear_dma(int mode, const bf16_t* x, const bf16_t* w0, const bf16_t* w1,
