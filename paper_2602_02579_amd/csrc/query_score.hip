@@ -373,8 +373,14 @@ pkv_status launch_query_score(const pkv_layer_cfg& cfg, const void* q,
         sp_.scale_log2 = scale * 1.4426950408889634f;
         pkv_status stt = launch_score_dma128(1, sp_, st);
         if (stt != PKV_OK) return stt;
-        hipLaunchKernelGGL(merge_lse_kernel, dim3((unsigned)ceil_div(ncol, 64)), dim3(256),
-                           0, st, part_ml, lse2, ncol, sp.n_splits, sp_.scale_log2);
+        // Up to 64 splits pass 2 folds them itself (32 loads per thread in four round trips,
+        // beside the first key tiles' own); with more (one or two kv heads) the launch that does
+        // it once for all workgroups is the shorter way
+        if (sp.n_splits <= 64)
+            sp_.n_fold = sp.n_splits;
+        else
+            hipLaunchKernelGGL(merge_lse_kernel, dim3((unsigned)ceil_div(ncol, 64)), dim3(256),
+                               0, st, part_ml, lse2, ncol, sp.n_splits, sp_.scale_log2);
         stt = launch_score_dma128(2, sp_, st);
         if (stt != PKV_OK) return stt;
         hipLaunchKernelGGL(finish_score_kernel, dim3((unsigned)ceil_div(n_ctx, 64)),

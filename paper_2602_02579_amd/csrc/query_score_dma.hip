@@ -180,6 +180,7 @@ __global__ __launch_bounds__(64 * NW) void score_dma128_kernel(ScoreParams p) {
         for (int r = 0; r < 16; ++r) {
             const int col = acc_col(cb, r);
             if (PASS == 2) {
+                if (p.n_fold) continue;   // below, from the partial normalisers
                 const bool valid = col < ncol_g;
                 const int qi = valid ? col / p.group : 0;
                 const int h = g * p.group + (valid ? col % p.group : 0);
@@ -196,6 +197,53 @@ __global__ __launch_bounds__(64 * NW) void score_dma128_kernel(ScoreParams p) {
     // ---- prologue --------------------------------------------------------------------------
 #pragma unroll
     for (int T = 0; T < NS - 1; ++T) dma_tile(T);
+    if (PASS == 2 && p.n_fold) {
+        // The normalisers of the workgroup's 256 columns from pass 1's partial ones: two
+        // threads per column, every other split each, eight loads together; they meet in the
+        // ring's last stage, which is not filled before the main loop.  Here the loads' latency
+        // runs beside that of the first key tiles, where a launch of its own cost 5 us.
+        float2* const fold = reinterpret_cast<float2*>(smem + (NS - 1) * kStage);   // [2][256]
+        const int c = tid & 255, part = tid >> 8;
+        const int col = cblk * 256 + c;
+        float m = -INFINITY, l = 0.f;
+        if (col < ncol_g) {
+            const int64_t ncol = (int64_t)p.nq * p.hq;
+            const float2* src = reinterpret_cast<const float2*>(p.part_ml) +
+                                (int64_t)(col / p.group) * p.hq + g * p.group + col % p.group;
+            for (int s0 = part; s0 < p.n_fold; s0 += 16) {
+                float2 ml[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)   // past the end: the last one, weight 0
+                    ml[e] = src[min(s0 + 2 * e, p.n_fold - 1) * ncol];
+                float mn = m;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) mn = fmaxf(mn, ml[e].x);
+                const float ref = mn == -INFINITY ? 0.f : mn;
+                l *= __builtin_amdgcn_exp2f((m - ref) * c2);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float w = __builtin_amdgcn_exp2f((ml[e].x - ref) * c2);
+                    l += s0 + 2 * e < p.n_fold && ml[e].x != -INFINITY ? ml[e].y * w : 0.f;
+                }
+                m = mn;
+            }
+        }
+        fold[tid] = make_float2(m, l);
+        __syncthreads();
+        float* const s_norm = reinterpret_cast<float*>(fold + 512);
+        if (part == 0) {
+            const float2 o = fold[256 + c];
+            const float mm = fmaxf(m, o.x), ref = mm == -INFINITY ? 0.f : mm;
+            l = l * __builtin_amdgcn_exp2f((m - ref) * c2) +
+                o.y * __builtin_amdgcn_exp2f((o.x - ref) * c2);
+            s_norm[c] = col < ncol_g ? mm * c2 + log2f(l) : INFINITY;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) norm[cb][r] = s_norm[acc_col(cb, r) - cblk * 256];
+    }
     wait_vm<FILLS * (NS - 2)>();   // tile 0
     __syncthreads();
     {
@@ -476,7 +524,7 @@ pkv_status launch_score_dma128(int pass, const ScoreParams& p, hipStream_t st) {
             return PKV_ERR_LAUNCH;
         configured.store(true, std::memory_order_release);
     }
-    if (!p.q || !p.k || (pass == 1 ? !p.part_ml : (!p.lse2 || !p.part_score)))
+    if (!p.q || !p.k || (pass == 1 ? !p.part_ml : (!(p.n_fold ? p.part_ml : p.lse2) || !p.part_score)))
         return PKV_ERR_NULL;
     const int64_t grid = (int64_t)p.n_cblk * p.n_splits * p.hkv;
     if (pass == 1)

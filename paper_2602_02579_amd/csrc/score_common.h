@@ -11,6 +11,8 @@ struct ScoreParams {
     float* part_ml;         // pass 1 out: [n_splits, nq * hq, 2] (max in raw logits, sum)
     const float* lse2;      // pass 2 in:  [nq * hq] normaliser, times lse_factor = its log2-domain
     float lse_factor;       //             value (1, or log2(e) for a natural-log normaliser)
+    int n_fold;             // pass 2: > 0 = fold the normalisers from this many splits of part_ml
+                            //         instead of reading lse2
     float* part_score;      // pass 2 out: [n_parts, n_ctx]
     int nq, n_ctx, hq, hkv, group;
     int n_cblk;             // blocks of 256 columns per kv group
