@@ -6,17 +6,16 @@
 // One workgroup of 1024 lanes (16 waves).  The score vector is small (128 KB
 // at 32k context) and stays in L2, so the kernel is latency-bound.
 //
-// Up to 64 scores per lane (n <= 65536) the keys live in registers, each lane
-// owning a contiguous run of indices (topk_bisect_kernel):
-//   1. the key tau of the k-th largest score is built bit by bit from the top:
-//      up to 32 rounds of "how many keys are >= candidate" (it stops at the round
-//      that leaves exactly k keys), each a compare-and-count
-//      over the lane's registers, a DPP row reduction and one barrier - no
-//      atomics, so the skewed digit distribution of real scores (all in two or
-//      three binades) costs nothing;
-//   2. two block-wide exclusive scans (keys > tau, keys == tau) give every
-//      lane the output offset of its run; equal keys are taken in index order
-//      until the need is met - the lower-index tie rule.
+// Up to 64 scores per lane (n <= 65536) the keys live in registers (topk_radix_kernel):
+//   1. the smallest and the largest key; 2048 bins of equal width between them are counted
+//      with LDS atomics and searched from the top for the k-th largest key, then the bin that
+//      holds it is divided again, until the whole bin is wanted or it is one key wide (two or
+//      three times; keys are spread over the bins by the span of the actual scores, so the
+//      few binades that real scores occupy do not meet in a few bins);
+//   2. an index-ordered compaction by ballots; of keys equal to the threshold those at the
+//      lowest indices are taken - the lower-index tie rule.
+// Built bit by bit instead, with a count over all keys and a barrier per bit, the threshold
+// took up to 32 rounds.
 // Longer vectors use the radix kernel below:
 //   1. radix select, 4 passes of 8 bits over order-preserving uint32 keys,
 //      finds the key tau of the k-th largest score and how many scores equal
@@ -154,122 +153,178 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(
     }
 }
 
-// sum over the wave of a small per-lane count, returned wave-uniform
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-    // inclusive scan inside each row of 16 lanes (row_shr 1, 2, 4, 8; lanes shifted in
-    // from outside the row read 0), then the four row totals
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 15) +
-           (uint32_t)__builtin_amdgcn_readlane((int)v, 31) +
-           (uint32_t)__builtin_amdgcn_readlane((int)v, 47) +
-           (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
+// One workgroup, the keys in registers: wave w owns scores [64 ITEMS w, 64 ITEMS (w + 1)),
+// a lane four consecutive ones of every 256.
 template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void topk_bisect_kernel(
+__global__ __launch_bounds__(kThreads) void topk_radix_kernel(
     const float* __restrict__ score, int n, int k, int32_t* __restrict__ idx_out) {
-    __shared__ uint32_t s_wave[2][kWaves];
-    __shared__ uint32_t s_scan[2][kWaves];
+    constexpr int kBins = 2048, kBits = 11;
+    __shared__ uint32_t hist[kBins];
+    __shared__ uint32_t s_a[kWaves], s_b[kWaves], s_res[3];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
+    const int base = wave * 64 * ITEMS + lane * 4;   // + 256 (j / 4) + j % 4 for element j
 
-    // lane tid owns indices [tid * ITEMS, tid * ITEMS + ITEMS); indices >= n get key 0,
-    // which is below the key of every float (order_key(-inf) = 0x007fffff)
     uint32_t key[ITEMS];
-    const int base = tid * ITEMS;
+    uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
     for (int j = 0; j < ITEMS; j += 4) {
-        if (base + j + 3 < n) {
-            const float4 v = *reinterpret_cast<const float4*>(score + base + j);
+        const int i0 = base + j * 64;
+        if (i0 + 3 < n) {
+            const float4 v = *reinterpret_cast<const float4*>(score + i0);
             key[j] = order_key(v.x);
             key[j + 1] = order_key(v.y);
             key[j + 2] = order_key(v.z);
             key[j + 3] = order_key(v.w);
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                key[j + e] = base + j + e < n ? order_key(score[base + j + e]) : 0u;
+            for (int e = 0; e < 4; ++e) key[j + e] = i0 + e < n ? order_key(score[i0 + e]) : 0u;
         }
     }
+#define PKV_IN(J) (base + ((J) / 4) * 256 + (J) % 4 < n)
 
-    // block-wide count of keys for which PRED holds (one barrier; s_wave is double
-    // buffered so that a fast wave cannot overwrite what a slow one still reads)
-    int round = 0;
-#define PKV_BLOCK_COUNT(PRED, RESULT)                                                    \
-    {                                                                                    \
-        uint32_t c_ = 0;                                                                 \
-        _Pragma("unroll") for (int j = 0; j < ITEMS; ++j) c_ += (PRED) ? 1u : 0u;        \
-        c_ = wave_sum(c_);                                                               \
-        if (lane == 0) s_wave[round & 1][wave] = c_;                                     \
-        __syncthreads();                                                                 \
-        uint32_t t_ = 0;                                                                 \
-        _Pragma("unroll") for (int w = 0; w < kWaves; ++w) t_ += s_wave[round & 1][w];   \
-        RESULT = t_;                                                                     \
-        ++round;                                                                         \
+    // ---- 1. the span of the keys ----------------------------------------------------------
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        if (PKV_IN(j)) {
+            mn = min(mn, key[j]);
+            mx = max(mx, key[j]);
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mn = min(mn, __shfl_xor(mn, o, 64));
+        mx = max(mx, __shfl_xor(mx, o, 64));
+    }
+    if (lane == 0) {
+        s_a[wave] = mn;
+        s_b[wave] = mx;
+    }
+    hist[tid] = 0u;
+    hist[tid + kThreads] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        mn = min(mn, s_a[w]);
+        mx = max(mx, s_b[w]);
     }
 
-    // ---- 1. tau = the k-th largest key, bit by bit ---------------------------------
-    uint32_t tau = 0;
-    for (int b = 31; b >= 0; --b) {
-        const uint32_t cand = tau | (1u << b);
-        uint32_t cnt;
-        PKV_BLOCK_COUNT(key[j] >= cand, cnt)
-        if (cnt >= (uint32_t)k) tau = cand;
-        // exactly k keys at or above the candidate: they are the selection, the lower bits
-        // of the k-th key do not matter (block-uniform; with distinct scores this happens
-        // at the highest bit in which the k-th and the (k+1)-th key differ)
-        if (cnt == (uint32_t)k) break;
+    // ---- 2. lo = lower end of the bin with the k-th largest key, ever finer ----------------
+    uint32_t lo = mn, span = mx - mn;   // keys [lo, lo + span] are counted
+    uint32_t rest = (uint32_t)k, cnt = 0u;
+    int shift = span ? max(0, 32 - __clz(span) - kBits) : 0;
+    for (;;) {
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t d = key[j] - lo;   // wraps to the far end below lo
+            if (PKV_IN(j) && d <= span) atomicAdd(&hist[d >> shift], 1u);
+        }
+        __syncthreads();
+        // thread t owns the bins 2047 - 2 t and 2046 - 2 t; counts above them
+        const uint32_t c0 = hist[kBins - 1 - 2 * tid], c1 = hist[kBins - 2 - 2 * tid];
+        uint32_t inc = c0 + c1;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += o;
+        }
+        if (lane == 63) s_a[wave] = inc;
+        __syncthreads();
+        uint32_t above = inc - c0 - c1;
+        for (int w = 0; w < wave; ++w) above += s_a[w];
+        if (above < rest && rest <= above + c0) {
+            s_res[0] = kBins - 1 - 2 * tid;
+            s_res[1] = rest - above;
+            s_res[2] = c0;
+        } else if (above + c0 < rest && rest <= above + c0 + c1) {
+            s_res[0] = kBins - 2 - 2 * tid;
+            s_res[1] = rest - above - c0;
+            s_res[2] = c1;
+        }
+        hist[kBins - 1 - 2 * tid] = 0u;
+        hist[kBins - 2 - 2 * tid] = 0u;
+        __syncthreads();
+        lo += s_res[0] << shift;
+        rest = s_res[1];
+        cnt = s_res[2];
+        // the whole bin is wanted: the selection is everything from lo on; or the bin is one
+        // key wide and `rest` of its equals are wanted
+        if (rest == cnt || shift == 0) break;
+        span = (1u << shift) - 1u;
+        shift = max(0, shift - kBits);
     }
-    uint32_t n_gt;
-    PKV_BLOCK_COUNT(key[j] > tau, n_gt)
-    const uint32_t need = (uint32_t)k - n_gt;   // keys == tau still to take
-#undef PKV_BLOCK_COUNT
 
-    // ---- 2. output offsets: exclusive scans over the lanes in index order -------------
-    uint32_t my_gt = 0, my_eq = 0;
+    // ---- 3. compaction in index order -------------------------------------------------------
+    const uint64_t lt = lanemask_lt();
+    if (rest == cnt) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) mine += __popcll(__ballot(PKV_IN(j) && key[j] >= lo));
+        if (lane == 0) s_b[wave] = mine;
+        __syncthreads();
+        uint32_t out = 0;
+        for (int w = 0; w < wave; ++w) out += s_b[w];
+#pragma unroll
+        for (int j = 0; j < ITEMS; j += 4) {
+            uint32_t at = out;
+            bool take[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                take[e] = PKV_IN(j + e) && key[j + e] >= lo;
+                const uint64_t b = __ballot(take[e]);
+                at += __popcll(b & lt);
+                out += __popcll(b);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (take[e]) idx_out[at++] = base + j * 64 + e;
+        }
+        return;
+    }
+    // `rest` of the cnt keys equal to lo, those at the lowest indices
+    uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-        my_gt += key[j] > tau ? 1u : 0u;
-        my_eq += key[j] == tau ? 1u : 0u;
+        gt += __popcll(__ballot(PKV_IN(j) && key[j] > lo));
+        eq += __popcll(__ballot(PKV_IN(j) && key[j] == lo));
     }
-    uint32_t in_gt = my_gt, in_eq = my_eq;   // inclusive scans inside the wave
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t og = __shfl_up(in_gt, d, 64), oe = __shfl_up(in_eq, d, 64);
-        if (lane >= d) {
-            in_gt += og;
-            in_eq += oe;
-        }
-    }
-    if (lane == 63) {
-        s_scan[0][wave] = in_gt;
-        s_scan[1][wave] = in_eq;
+    if (lane == 0) {
+        s_a[wave] = gt;
+        s_b[wave] = eq;
     }
     __syncthreads();
-    uint32_t gt_before = in_gt - my_gt, eq_before = in_eq - my_eq;
+    gt = eq = 0;       // of the waves before mine, then of the groups as well
     for (int w = 0; w < wave; ++w) {
-        gt_before += s_scan[0][w];
-        eq_before += s_scan[1][w];
+        gt += s_a[w];
+        eq += s_b[w];
     }
-    // equal keys at lower indices are taken first, until `need` of them are
-    uint32_t out = gt_before + (eq_before < need ? eq_before : need);
-    uint32_t eq_seen = eq_before;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const bool is_eq = key[j] == tau;
-        const bool take = key[j] > tau || (is_eq && eq_seen < need);
-        if (take) idx_out[out++] = base + j;
-        eq_seen += is_eq ? 1u : 0u;
+    for (int j = 0; j < ITEMS; j += 4) {
+        uint32_t g_at = gt, e_at = eq;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t bg = __ballot(PKV_IN(j + e) && key[j + e] > lo);
+            const uint64_t be = __ballot(PKV_IN(j + e) && key[j + e] == lo);
+            g_at += __popcll(bg & lt);
+            e_at += __popcll(be & lt);
+            gt += __popcll(bg);
+            eq += __popcll(be);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = PKV_IN(j + e);
+            const bool is_gt = in && key[j + e] > lo, is_eq = in && key[j + e] == lo;
+            if (is_gt || (is_eq && e_at < rest)) idx_out[g_at + min(e_at, rest)] = base + j * 64 + e;
+            g_at += is_gt ? 1u : 0u;
+            e_at += is_eq ? 1u : 0u;
+        }
     }
+#undef PKV_IN
 }
 
 
 // ---------------------------------------------------------------------------
-// Longer vectors (n > 24576) with a workspace: the same radix select spread over many
+// Longer vectors with a workspace: a radix select spread over many
 // workgroups, so that the counting runs at the bandwidth of the whole chip instead of one
 // CU's.  A workgroup of 256 lanes owns 2048 consecutive scores (8 per lane, in registers).
 //   hist<0>  histogram of the top 11 key bits              -> hist0[2048]
@@ -484,9 +539,9 @@ __global__ __launch_bounds__(256) void topk_ws_write_kernel(const float* __restr
 
 }  // namespace
 
-// Shortest vector that takes the many-workgroup kernels when a workspace is given: their six
-// launches cost a flat ~20 us, the one-workgroup register kernel 10 us at 4k scores, 16 us
-// at 16k, 29 us at 32k and 46 us at 64k.
+// Shortest vector that takes the many-workgroup kernels when a workspace is given (and, up to
+// 32768 scores, only if its address is not a multiple of 16): their six launches cost a flat
+// 17.5 us, one workgroup without register keys 43 us at 24k.
 constexpr int64_t kWsMin = 24 * 1024 + 1;
 
 size_t topk_select_ws_bytes(int64_t n) {
@@ -499,6 +554,25 @@ pkv_status launch_topk_select(const float* score, int64_t n, int64_t k,
     if (n == 0 || k == 0) return PKV_OK;
     // the register kernels read 16 bytes at a time
     const bool aligned = (reinterpret_cast<uintptr_t>(score) & 15) == 0;
+    // every pass walks over all register keys, so short vectors take the instantiation with
+    // the fewest keys per lane that holds them.  From 1024 to 32768 scores 5.2, 6.7 (4k), 7.0
+    // (8k), 9.0 (16k) and 15.4 us; the many-workgroup kernels take 17.5 at any length (with the
+    // threshold built bit by bit 9, 10, 14, 15 and 26)
+    if (aligned && n <= 8 * kThreads) {
+        hipLaunchKernelGGL(topk_radix_kernel<8>, dim3(1), dim3(kThreads), 0, st, score,
+                           (int)n, (int)k, idx_out);
+        return launch_status();
+    }
+    if (aligned && n <= 16 * kThreads) {
+        hipLaunchKernelGGL(topk_radix_kernel<16>, dim3(1), dim3(kThreads), 0, st, score,
+                           (int)n, (int)k, idx_out);
+        return launch_status();
+    }
+    if (aligned && n <= 32 * kThreads) {
+        hipLaunchKernelGGL(topk_radix_kernel<32>, dim3(1), dim3(kThreads), 0, st, score,
+                           (int)n, (int)k, idx_out);
+        return launch_status();
+    }
     const size_t need = topk_select_ws_bytes(n);
     if (need && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 3) == 0) {
         uint32_t* w = (uint32_t*)ws;
@@ -512,25 +586,8 @@ pkv_status launch_topk_select(const float* score, int64_t n, int64_t k,
         hipLaunchKernelGGL(topk_ws_write_kernel, grid, block, 0, st, score, (int)n, w, idx_out, al);
         return launch_status();
     }
-    // a round costs one vector compare-and-count per register key, so short vectors take
-    // the instantiation with the fewest keys per lane that holds them
-    if (aligned && n <= 8 * kThreads) {
-        hipLaunchKernelGGL(topk_bisect_kernel<8>, dim3(1), dim3(kThreads), 0, st, score,
-                           (int)n, (int)k, idx_out);
-        return launch_status();
-    }
-    if (aligned && n <= 16 * kThreads) {
-        hipLaunchKernelGGL(topk_bisect_kernel<16>, dim3(1), dim3(kThreads), 0, st, score,
-                           (int)n, (int)k, idx_out);
-        return launch_status();
-    }
-    if (aligned && n <= 32 * kThreads) {
-        hipLaunchKernelGGL(topk_bisect_kernel<32>, dim3(1), dim3(kThreads), 0, st, score,
-                           (int)n, (int)k, idx_out);
-        return launch_status();
-    }
     if (aligned && n <= 64 * kThreads) {
-        hipLaunchKernelGGL(topk_bisect_kernel<64>, dim3(1), dim3(kThreads), 0, st, score,
+        hipLaunchKernelGGL(topk_radix_kernel<64>, dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);
         return launch_status();
     }
