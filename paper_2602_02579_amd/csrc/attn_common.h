@@ -42,6 +42,10 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 pkv_status launch_attn_dma128(const AttnParams& p, hipStream_t st);
 pkv_status launch_attn_w8_main(const AttnParams& p, hipStream_t st);
 pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st);
+// sparse_row_attn_short.hip: up to 1024 keys, at most one job of 128 columns per CU; n_splits is
+// what the pipelined kernel would cut the keys into
+bool attn_short_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int n_splits);
+pkv_status launch_attn_short(AttnParams p, hipStream_t st);
 // compute units of the current device (0: could not be asked)
 int attn_cu_count();
 // Where the pipelined kernel can take the values from: 1 = from a V^T copy made by a pre-pass

@@ -714,10 +714,13 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         // anyway).  The copy is skipped when that is the cheaper side (measured, no copy ->
         // copy: 3404 rows over 32k keys 801 -> 809 us, 6681 over 16k 745 -> 739, 6681 over
         // 32k 1444 -> 1438, 13235 over 32k 2722 -> 2691, 26470 over 131k 21.5 -> 21.1 ms).
-        bool nat_v = false;
+        bool nat_v = false, short_job = false;
         if (d == 128) {
             const int src = attn_dma128_v_source();
-            if (src < 0) {
+            short_job = src <= 0 && !lse_ctx_out && attn_short_applies(cfg, n_keys, m, n_splits);
+            if (short_job) {
+                nat_v = true;
+            } else if (src < 0) {
                 const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
                 const double copy_us = 3.0 + (double)n_pad * cfg.n_kv_heads * d * 4.0 / 5.5e6;
                 const double main_us = 1.68 * (double)ceil_div(m, bm) * cfg.n_kv_heads *
@@ -728,7 +731,7 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
             }
         }
         if (nat_v) {
-            if (queue)
+            if (queue && !short_job)
                 hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue,
                                    cfg.n_kv_heads);
         } else {
@@ -760,6 +763,7 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         p.scale = scale;
         p.scale_log2 = scale * 1.4426950408889634f;
         if (d != 128) return launch_attn_mfma<64, true>(p, st);
+        if (short_job) return launch_attn_short(p, st);
         p.queue = queue;
         p.dma_splits = n_splits;
         p.dma_split_len = split_len;
