@@ -286,6 +286,12 @@ bool mfma_proj_supported(const pkv_layer_cfg& cfg) {
 
 }  // namespace
 
+void launch_rope_table(const int32_t* row_pos, int64_t m, int half, const RopeTable& tab,
+                       float2* cs, hipStream_t st) {
+    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div(m * half, 256)), dim3(256), 0,
+                       st, row_pos, (int)m, half, tab, cs);
+}
+
 size_t gather_qkv_proj_ws_bytes(const pkv_layer_cfg& cfg, int64_t m) {
     if (!mfma_proj_supported(cfg)) return 0;
     size_t b = (size_t)m * (cfg.head_dim / 2) * sizeof(float2);
@@ -317,9 +323,6 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
     if (mfma_proj_supported(cfg) && (!extra || proj_dma128_supported(cfg, m))) {
         const int d = cfg.head_dim, half = d / 2;
         float2* cs = (float2*)ws;
-        const int64_t n_tab = m * half;
-        hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div(n_tab, 256)), dim3(256),
-                           0, st, row_pos, (int)m, half, tab, cs);
         ProjParams p = {};
         p.hidden = (const bf16_t*)hidden;
         p.row_idx = row_idx;
@@ -340,8 +343,9 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
             p.tile_begin[3] = tq + 2 * tkv;
             const size_t cs_bytes = ((size_t)m * half * sizeof(float2) + 255) & ~(size_t)255;
             p.partial = reinterpret_cast<float*>((unsigned char*)ws + cs_bytes);
-            return launch_proj_dma128(p, st);
+            return launch_proj_dma128(p, row_pos, tab, st);
         }
+        launch_rope_table(row_pos, m, half, tab, cs, st);
         // column tiles: only the matrices whose outputs were asked for
         const int tq = q_out ? hq * d / kGN : 0;
         const int tkv = k_out ? hkv * d / kGN : 0;

@@ -668,53 +668,77 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
 }
 
 // adds the splits of the contraction in a fixed order, rotates, rounds once, stores.
-// One thread per (row, head slot, pair index i): elements i and i + 64 of the head.
-__global__ __launch_bounds__(256) void proj_splitk_finish_kernel(ProjParams p) {
+// Sixteen lanes per (row, head), four pairs per lane: elements i .. i + 3 and i + 64 .. of the
+// head, 16 bytes per load.  The lane works out the sines and cosines of its pairs itself and
+// then walks over every gridDim.y-th head slot, so that no table has to be made and read
+// (883 rows x 6144 outputs in two splits: 18 us and 5 for the table -> 12; with one
+// pair per lane the sums alone moved 3 TB/s).
+__global__ __launch_bounds__(256) void proj_splitk_finish_kernel(ProjParams p,
+                                                                 const int32_t* __restrict__ row_pos,
+                                                                 RopeTable tab) {
     const int f_total = T * p.tile_begin[3];
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = (int64_t)p.m * (f_total / 2);
-    if (idx >= total) return;
-    const int i = (int)(idx % (D / 2));
-    const int hs = (int)((idx / (D / 2)) % (f_total / D));   // head slot over Q | K | V
-    const int row = (int)(idx / ((int64_t)(D / 2) * (f_total / D)));
-    const int ft = hs / 2;
-    int mat = 0;
-    if (ft >= p.tile_begin[1]) mat = 1;
-    if (ft >= p.tile_begin[2]) mat = 2;
-    bf16_t* out = p.out[mat];
-    if (out == nullptr) return;
-    const int head = (ft - p.tile_begin[mat]) * 2 + (hs & 1);
-    const int heads_out = mat == 0 ? p.hq : p.hkv;
-    float a = 0.f, b = 0.f;
-    for (int s = 0; s < p.n_ksplit; ++s) {
-        const float* src = p.partial + ((int64_t)s * p.m + row) * f_total + hs * D + i;
-        a += src[0];
-        b += src[D / 2];
-    }
-    if (p.bias[mat]) {
-        a += (float)p.bias[mat][head * D + i];
-        b += (float)p.bias[mat][head * D + i + D / 2];
-    }
-    if (mat != 2 && p.norm_w[mat]) {
-        // a wave is exactly one (row, head): its 64 lanes hold the head's 128 features
-        float ss = a * a + b * b;
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    const int row = idx >> 4;
+    if (row >= p.m) return;                     // a row's lanes leave together
+    const int i = (idx & 15) * 4;
+    float sn[4], cs[4];
+    const double pos = (double)row_pos[row];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-        const float r = 1.0f / sqrtf(ss * (1.0f / D) + p.norm_eps);
-        a = a * r * (float)p.norm_w[mat][i];
-        b = b * r * (float)p.norm_w[mat][i + D / 2];
+    for (int e = 0; e < 4; ++e) rope_sincos(pos, tab.inv_freq[i + e], &sn[e], &cs[e]);
+    for (int hs = blockIdx.y; hs < f_total / D; hs += gridDim.y) {   // head slot over Q | K | V
+        const int ft = hs / 2;
+        int mat = 0;
+        if (ft >= p.tile_begin[1]) mat = 1;
+        if (ft >= p.tile_begin[2]) mat = 2;
+        bf16_t* out = p.out[mat];
+        if (out == nullptr) continue;
+        const int head = (ft - p.tile_begin[mat]) * 2 + (hs & 1);
+        const int heads_out = mat == 0 ? p.hq : p.hkv;
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+        const float* src = p.partial + (int64_t)row * f_total + hs * D + i;
+#pragma unroll 4
+        for (int s = 0; s < p.n_ksplit; ++s) {
+            a += *reinterpret_cast<const f32x4*>(src);
+            b += *reinterpret_cast<const f32x4*>(src + D / 2);
+            src += (int64_t)p.m * f_total;
+        }
+        if (p.bias[mat]) {
+            const bf16x4 ba = *reinterpret_cast<const bf16x4*>(p.bias[mat] + head * D + i);
+            const bf16x4 bb = *reinterpret_cast<const bf16x4*>(p.bias[mat] + head * D + i + D / 2);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[e] += (float)ba[e];
+                b[e] += (float)bb[e];
+            }
+        }
+        if (mat != 2 && p.norm_w[mat]) {
+            float ss = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ss += a[e] * a[e] + b[e] * b[e];
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+            const float r = 1.0f / sqrtf(ss * (1.0f / D) + p.norm_eps);
+            const bf16x4 ga = *reinterpret_cast<const bf16x4*>(p.norm_w[mat] + i);
+            const bf16x4 gb = *reinterpret_cast<const bf16x4*>(p.norm_w[mat] + i + D / 2);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[e] = a[e] * r * (float)ga[e];
+                b[e] = b[e] * r * (float)gb[e];
+            }
+        }
+        bf16x4 va, vb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float ra = mat != 2 ? a[e] * cs[e] - b[e] * sn[e] : a[e];
+            const float rb = mat != 2 ? b[e] * cs[e] + a[e] * sn[e] : b[e];
+            va[e] = (bf16_t)ra;
+            vb[e] = (bf16_t)rb;
+        }
+        const int64_t orow = (mat != 0 && p.dst_row) ? p.dst_row[row] : row;
+        bf16_t* o = out + (orow * heads_out + head) * D + i;
+        *reinterpret_cast<bf16x4*>(o) = va;
+        *reinterpret_cast<bf16x4*>(o + D / 2) = vb;
     }
-    if (mat != 2) {
-        const float2 t = p.cs[(int64_t)row * (D / 2) + i];
-        const float ra = a * t.x - b * t.y;
-        const float rb = b * t.x + a * t.y;
-        a = ra;
-        b = rb;
-    }
-    const int64_t orow = (mat != 0 && p.dst_row) ? p.dst_row[row] : row;
-    bf16_t* o = out + (orow * heads_out + head) * D + i;
-    o[0] = (bf16_t)a;
-    o[D / 2] = (bf16_t)b;
 }
 
 // the same for the plain and the gated linear layers: one thread per (row, 4 outputs)
@@ -729,6 +753,7 @@ __global__ __launch_bounds__(256) void linear_splitk_finish_kernel(ProjParams p)
     // column of output f in the tile order of the partials
     const int col = MODE == kProjGated ? (f >> 7) * T + ((f >> 6) & 1) * 128 + (f & 63) : f;
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
     for (int s = 0; s < p.n_ksplit; ++s) {
         const float* src = p.partial + ((int64_t)s * p.m + row) * f_total + col;
         a += *reinterpret_cast<const f32x4*>(src);
@@ -858,8 +883,10 @@ bool proj_dma128_supported(const pkv_layer_cfg& cfg, int64_t m) {
 
 namespace {
 
+// row_pos, tab: the angles of a Q | K | V launch (p.cs: room for their table)
 template <int MODE, bool EXTRA = false>
-pkv_status launch_tiles(const ProjParams& p, hipStream_t st) {
+pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
+                        hipStream_t st) {
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(proj_dma_kernel<MODE, EXTRA>),
@@ -880,6 +907,9 @@ pkv_status launch_tiles(const ProjParams& p, hipStream_t st) {
     ProjParams q = p;
     q.n_ksplit = plan.ksplit;
     if (q.n_ksplit > 1 && q.partial == nullptr) return PKV_ERR_WORKSPACE;
+    // a split launch's finishing kernel works the angles out by itself
+    if (MODE == kProjRope && q.n_ksplit == 1)
+        launch_rope_table(row_pos, p.m, D / 2, tab, const_cast<float2*>(p.cs), st);
     if (plan.tokens < 192) {
         const pkv_status rc = launch_proj_small<MODE, EXTRA>(plan.tokens, q, st);
         if (rc != PKV_OK) return rc;
@@ -901,9 +931,14 @@ pkv_status launch_tiles(const ProjParams& p, hipStream_t st) {
     }
     if (q.n_ksplit > 1) {
         if (MODE == kProjRope) {
-            const int64_t total = (int64_t)p.m * (T * p.tile_begin[3] / 2);
-            hipLaunchKernelGGL(proj_splitk_finish_kernel, dim3((unsigned)ceil_div(total, 256)),
-                               dim3(256), 0, st, q);
+            // enough workgroups to hide the loads, as few head groups as that allows
+            const int64_t blocks = ceil_div((int64_t)p.m * 16, 256);
+            const int64_t heads = 2 * p.tile_begin[3];
+            int64_t groups = ceil_div(1024, blocks);
+            if (groups > heads) groups = heads;
+            hipLaunchKernelGGL(proj_splitk_finish_kernel,
+                               dim3((unsigned)blocks, (unsigned)groups), dim3(256), 0, st, q,
+                               row_pos, tab);
         } else {
             const int64_t total = (int64_t)p.m * (p.n_out / 4);
             hipLaunchKernelGGL(linear_splitk_finish_kernel<MODE>,
@@ -915,10 +950,12 @@ pkv_status launch_tiles(const ProjParams& p, hipStream_t st) {
 
 }  // namespace
 
-pkv_status launch_proj_dma128(const ProjParams& p, hipStream_t st) {
+pkv_status launch_proj_dma128(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
+                              hipStream_t st) {
     const bool extra = p.bias[0] || p.bias[1] || p.bias[2] || p.norm_w[0] || p.norm_w[1] ||
                        p.dst_row;
-    return extra ? launch_tiles<kProjRope, true>(p, st) : launch_tiles<kProjRope, false>(p, st);
+    return extra ? launch_tiles<kProjRope, true>(p, row_pos, tab, st)
+                 : launch_tiles<kProjRope, false>(p, row_pos, tab, st);
 }
 
 bool linear_dma_supported(int mode, int64_t m, int64_t k_in, int64_t n_out) {
@@ -950,7 +987,8 @@ pkv_status launch_linear_dma(int mode, const bf16_t* x, const bf16_t* w0, const 
     p.n_ksplit = 1;
     p.residual = residual;
     p.n_out = (int)n_out;
-    return mode == kProjGated ? launch_tiles<kProjGated>(p, st) : launch_tiles<kProjPlain>(p, st);
+    return mode == kProjGated ? launch_tiles<kProjGated>(p, nullptr, RopeTable{}, st)
+                              : launch_tiles<kProjPlain>(p, nullptr, RopeTable{}, st);
 }
 
 }  // namespace pkv

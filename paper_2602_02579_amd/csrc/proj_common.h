@@ -10,7 +10,8 @@ struct ProjParams {
     const int32_t* row_idx;
     const bf16_t* w[3];   // wq, wk, wv
     bf16_t* out[3];       // q_out, k_out, v_out (may be null)
-    const float2* cs;     // [m, D/2] (cos, sin) of every output row's position
+    const float2* cs;     // [m, D/2] (cos, sin) of every output row's position (a split
+                          // launch of head_dim 128 leaves it unwritten)
     int m, hid, hq, hkv;
     int tile_begin[4];    // first feature tile of Q, K, V, end
     float* partial;       // [n_ksplit, m, 256 * tile_begin[3]] fp32, used when n_ksplit > 1
@@ -45,7 +46,11 @@ bool proj_dma128_supported(const pkv_layer_cfg& cfg, int64_t m);
 // bytes of fp32 partials that a launch with m rows may need (0 when the launch is large
 // enough to fill the chip without splitting the contraction)
 size_t proj_dma128_partial_bytes(const pkv_layer_cfg& cfg, int64_t m);
-pkv_status launch_proj_dma128(const ProjParams& p, hipStream_t st);
+pkv_status launch_proj_dma128(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
+                              hipStream_t st);
+// cs [m, half] = (cos, sin) of every row's angles (gather_qkv_proj.hip)
+void launch_rope_table(const int32_t* row_pos, int64_t m, int half, const RopeTable& tab,
+                       float2* cs, hipStream_t st);
 
 // The same tile kernel as a plain or gated linear layer over m rows of k_in inputs.
 // mode kProjPlain: n_out % 256 == 0; kProjGated: n_out % 128 == 0 (a tile then holds
