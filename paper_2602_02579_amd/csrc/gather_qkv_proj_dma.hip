@@ -35,6 +35,7 @@
 // (plan_tiles) and, with very few rows (the user-query projection of the scoring stage),
 // splits its contraction: every split writes fp32 partial tiles, and a second small
 // kernel adds them in a fixed order, rotates and rounds (deterministic: no atomics).
+#include <algorithm>
 #include <atomic>
 
 #include "proj_tile.h"
@@ -456,28 +457,14 @@ template <int NQ>
 constexpr int kSlabLdsBytes = 2 * (4 + NQ) * kUnitBytes;
 
 template <int MODE, bool EXTRA, int NQ>
-__global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_tiles,
-                                                        int n_tiles, int per_xcd) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void slab_tile(const ProjParams& p, unsigned char* smem, int row0,
+                                          int ft, int split) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, l16 = lane & 15;
     const int wt = wave >> 1, wf = wave & 1;
 
-    // ---- which tile (as above) ---------------------------------------------------------
-    int logical = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (logical >= n_tiles * p.n_ksplit) return;
-    const int split = logical / n_tiles;
-    logical -= split * n_tiles;
-    const int n_feat_tiles = p.tile_begin[3];
-    const int per_group = kGroup * n_feat_tiles;
-    const int group = logical / per_group;
-    const int first_tok = group * kGroup;
-    const int rows_in_group = min(kGroup, n_tok_tiles - first_tok);
-    const int within = logical - group * per_group;
-    const int tok_tile = first_tok + within % rows_in_group;
-    const int ft = within / rows_in_group;
     int mat = 0;
     if (MODE == kProjRope) {
         if (ft >= p.tile_begin[1]) mat = 1;
@@ -487,7 +474,6 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     const bf16_t* w = p.w[mat];
     bf16_t* out = p.out[mat];
     const int heads_out = mat == 0 ? p.hq : p.hkv;
-    const int row0 = tok_tile * (64 * NQ);
 
     const int n_T = p.hid / 64 / p.n_ksplit;   // steps of this split: even, >= 2 (launcher)
     const int k_begin = split * n_T * 64;
@@ -667,6 +653,52 @@ __global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_
     tile_epilogue<MODE, EXTRA, NQ>(p, acc, ctx, smem);
 }
 
+// tile number -> (token tile, feature tile) of a run of n_tok token tiles, kGroup deep
+__device__ __forceinline__ void tile_of(int logical, int n_tok, int n_feat, int* tok, int* ft) {
+    const int per_group = kGroup * n_feat;
+    const int group = logical / per_group;
+    const int first_tok = group * kGroup;
+    const int rows_in_group = min(kGroup, n_tok - first_tok);
+    const int within = logical - group * per_group;
+    *tok = first_tok + within % rows_in_group;
+    *ft = within / rows_in_group;
+}
+
+template <int MODE, bool EXTRA, int NQ>
+__global__ __launch_bounds__(256) void proj_slab_kernel(ProjParams p, int n_tok_tiles,
+                                                        int n_tiles, int per_xcd) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int logical = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (logical >= n_tiles * p.n_ksplit) return;
+    const int split = logical / n_tiles;
+    int tok, ft;
+    tile_of(logical - split * n_tiles, n_tok_tiles, p.tile_begin[3], &tok, &ft);
+    slab_tile<MODE, EXTRA, NQ>(p, smem, tok * (64 * NQ), ft, split);
+}
+
+// Both heights in one launch: n_hi token tiles of 256 rows, which fill whole rounds of the CUs,
+// then n_lo of 192 for the last, partly filled round: the tail ends sooner than with a round of
+// full tiles of which a part of the CUs has none.  No splits of the contraction.
+template <int MODE, bool EXTRA>
+__global__ __launch_bounds__(256) void proj_slab_mix_kernel(ProjParams p, int n_hi, int n_lo,
+                                                            int per_xcd_hi, int per_xcd_lo) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int xcd = (int)(blockIdx.x & 7), nth = (int)(blockIdx.x >> 3);
+    const int nf = p.tile_begin[3];
+    int tok, ft;
+    if (nth < per_xcd_hi) {
+        const int logical = xcd * per_xcd_hi + nth;
+        if (logical >= n_hi * nf) return;
+        tile_of(logical, n_hi, nf, &tok, &ft);
+        slab_tile<MODE, EXTRA, 4>(p, smem, tok * 256, ft, 0);
+    } else {
+        const int logical = xcd * per_xcd_lo + nth - per_xcd_hi;
+        if (logical >= n_lo * nf) return;
+        tile_of(logical, n_lo, nf, &tok, &ft);
+        slab_tile<MODE, EXTRA, 3>(p, smem, n_hi * 256 + tok * 192, ft, 0);
+    }
+}
+
 // adds the splits of the contraction in a fixed order, rotates, rounds once, stores.
 // Sixteen lanes per (row, head), four pairs per lane: elements i .. i + 3 and i + 64 .. of the
 // head, 16 bytes per load.  The lane works out the sines and cosines of its pairs itself and
@@ -805,7 +837,10 @@ constexpr TileCost kTileCost[4] = {{0.855f, 0.401f, 0.744f, 0.597f},
                                    {5.207f, 1.044f, 0.742f, 0.253f},
                                    {6.630f, 1.348f, 0.721f, 0.179f}};
 
-struct TilePlan { int tokens, ksplit; };
+struct TilePlan {
+    int tokens, ksplit;   // tokens 256 with n_hi > 0: that many tiles of 256, the rest of 192
+    int n_hi;
+};
 
 // features of a launch x splits of its contraction that the fp32 partials have room for
 // (256 tiles' worth of 256 x 256; nothing for launches of more than 128 token tiles)
@@ -839,6 +874,22 @@ float estimate_us(int kind, int64_t m, int64_t features, int64_t k_in, int ks) {
     return t;
 }
 
+// `rounds` full rounds of 256-token tiles and `left` 192-token tiles behind them
+float estimate_mix_us(int64_t m, int64_t features, int64_t k_in, int64_t rounds, int64_t left) {
+    const TileCost &h = kTileCost[3], &l = kTileCost[2];
+    const float steps = (float)k_in / 64.f;
+    float loop = (float)rounds * (h.step * steps + h.fixed);
+    if (left > 0) {
+        const float full = (float)(left / 256), up = (float)ceil_div(left, 256);
+        const float part = up > full ? l.part + (1.f - l.part) * ((float)left / 256.f - full) : 0.f;
+        loop += l.step * steps * (full + part) + l.fixed * up;
+    }
+    const float mem =
+        2e-6f * ((float)features * k_in + (float)m * k_in + (float)m * features) / 7.094f;
+    const float hi = loop > mem ? loop : mem, lo = loop > mem ? mem : loop;
+    return 1.671f + hi + h.overlap * lo * lo / hi;
+}
+
 // what 256 x 256 tiles take: the largest power of two that keeps the launch within 256
 // workgroups and a split >= NS stages
 int plan_ksplit(int64_t n_tiles, int n_k) {
@@ -850,7 +901,7 @@ int plan_ksplit(int64_t n_tiles, int n_k) {
 
 TilePlan plan_tiles(int64_t m, int64_t features, int64_t k_in) {
     const int64_t n_tiles = ceil_div(m, T) * (features / T);
-    TilePlan best = {256, plan_ksplit(n_tiles, (int)(k_in / BK))};
+    TilePlan best = {256, plan_ksplit(n_tiles, (int)(k_in / BK)), 0};
     const float now = estimate_us(3, m, features, k_in, best.ksplit);
     float t_best = 0.95f * now;
     const int64_t room = partial_features(m);
@@ -865,6 +916,18 @@ TilePlan plan_tiles(int64_t m, int64_t features, int64_t k_in) {
                 best.ksplit = ks;
             }
         }
+    // whole rounds of 256-token tiles, what is left of the rows on 192-token ones
+    const int64_t nf = features / T;
+    const int64_t rounds = n_tiles / 256, hi = 256 * rounds / nf;
+    if (rounds >= 1 && n_tiles % 256 != 0 && hi >= 1 && k_in % 128 == 0) {
+        const int64_t left = ceil_div(m - hi * T, 192) * nf - (256 * rounds - hi * nf);
+        const float t = estimate_mix_us(m, features, k_in, rounds, left);
+        if (t < 0.97f * (best.tokens == 256 ? now : t_best)) {
+            best.tokens = 256;
+            best.ksplit = 1;
+            best.n_hi = (int)hi;
+        }
+    }
     return best;
 }
 
@@ -895,6 +958,9 @@ pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeT
             hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_kernel<MODE, EXTRA, 4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kSlabLdsBytes<4>) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_mix_kernel<MODE, EXTRA>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kSlabLdsBytes<4>) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void*>(proj_slab_kernel<MODE, EXTRA, 3>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kSlabLdsBytes<3>) != hipSuccess)
@@ -919,7 +985,14 @@ pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeT
         const int per_xcd = (int)ceil_div((int64_t)n_tiles * q.n_ksplit, 8);
         const dim3 grid((unsigned)(per_xcd * 8)), block(256);
         // contraction in slabs of 64 when every split has an even number of them
-        if (plan.tokens == 192)
+        if (plan.n_hi > 0) {
+            const int n_lo = (int)ceil_div(p.m - plan.n_hi * T, 192);
+            const int px_hi = (int)ceil_div((int64_t)plan.n_hi * p.tile_begin[3], 8);
+            const int px_lo = (int)ceil_div((int64_t)n_lo * p.tile_begin[3], 8);
+            hipLaunchKernelGGL((proj_slab_mix_kernel<MODE, EXTRA>),
+                               dim3((unsigned)(8 * (px_hi + px_lo))), block, kSlabLdsBytes<4>, st,
+                               q, plan.n_hi, n_lo, px_hi, px_lo);
+        } else if (plan.tokens == 192)
             hipLaunchKernelGGL((proj_slab_kernel<MODE, EXTRA, 3>), grid, block, kSlabLdsBytes<3>,
                                st, q, n_tok_tiles, n_tiles, per_xcd);
         else if (p.hid % (128 * q.n_ksplit) == 0)

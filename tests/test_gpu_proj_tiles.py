@@ -30,6 +30,8 @@ SHAPES = [
     (883, 5120, 5120),    # 192 x 2
     (961, 256, 12288),    # 256, four steps
     (300, 160, 512),      # 256, contraction no multiple of 64
+    (769, 256, 28672),    # 512 rows on 256-token tiles, 257 on 192-token ones, in one launch
+    (1921, 256, 12288),   # 1280 and 641
 ]
 
 
