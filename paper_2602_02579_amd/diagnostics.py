@@ -81,9 +81,12 @@ class Diagnostics:
         layers = []
         for b in blocks:
             L = {name: b[name] for name in BLOCK_WEIGHTS + VARIANT_WEIGHTS if name in b}
-            L["k_cache"], L["v_cache"] = self._cache_pair(t)
+            # every one of the T rows is written before anything reads it
+            shape = (t, self.cfg.n_kv_heads, self.cfg.head_dim)
+            L["k_cache"] = torch.empty(shape, dtype=self.dt, device=self.device)
+            L["v_cache"] = torch.empty_like(L["k_cache"])
             layers.append(L)
-        cr.stage2(embed_rows.contiguous(), layers)
+        cr._stage2(embed_rows.contiguous(), layers, caches_only=True)
         k_nope = []
         for L in layers:
             out = torch.empty_like(L["k_cache"])

@@ -90,9 +90,10 @@ class CarriedRows:
                        api.pkv_workspace_bytes(api.CALL_TOPK_SELECT, self.lc, n, 0), ctx_ws)
         self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device=device)
 
-    # one decoder layer for the first ``cnt`` rows of the buffers, at positions ``rows``
+    # one decoder layer for the first ``cnt`` rows of the buffers, at positions ``rows``;
+    # caches_only: its normalisation and K/V projection, nothing of the rows themselves
     def _layer(self, L: Dict[str, torch.Tensor], rows: torch.Tensor, cnt: int,
-               score: Optional[bool]) -> None:
+               score: Optional[bool], caches_only: bool = False) -> None:
         lc, ws = self.lc, self.ws
         h, x = self.h[:cnt], self.x[:cnt]
         q = self.q[:cnt]
@@ -101,10 +102,13 @@ class CarriedRows:
         # Q/K/V of the rows; K and V go straight to their cache rows (steps 4a + 4b).  The
         # score of Stage I reads only the context rows of the key cache, which the query
         # rows' own keys (stored behind the context) do not touch.
-        api.pkv_gather_qkv_proj_scatter(lc, x, None, rows, L["wq"], L["wk"], L["wv"], q,
+        api.pkv_gather_qkv_proj_scatter(lc, x, None, rows, L["wq"], L["wk"], L["wv"],
+                                        None if caches_only else q,
                                         L["k_cache"], L["v_cache"], rows, ws=ws,
                                         norm_eps=self.eps,
                                         **{v: L[v] for v in VARIANT_WEIGHTS if v in L})
+        if caches_only:
+            return
         if score is not None and self.fuse_stage1:
             api.pkv_sparse_row_attn_ctx_lse(lc, q, L["k_cache"], L["v_cache"], rows, attn, None,
                                             self.lse_ctx[:cnt], self.n, ws=ws)
@@ -121,26 +125,54 @@ class CarriedRows:
         api.pkv_swiglu_rows(x, L["w_gate"], L["w_up"], g, ws=ws)
         api.pkv_linear_rows(g, L["w_down"], h, h, ws=ws)
 
+    # the last scoring layer where only its scores are wanted: queries and both passes of the
+    # score, which cost less than the attention that would spare one of them
+    def _score_only(self, L: Dict[str, torch.Tensor], accumulate: bool) -> None:
+        qn = self.qn
+        api.pkv_rmsnorm_rows(self.h[:qn], None, L["w_in"], self.eps, self.x[:qn])
+        api.pkv_gather_qkv_proj_ex(self.lc, self.x[:qn], None, self.q_rows, L["wq"], None, None,
+                                   self.q[:qn], None, None, ws=self.ws, norm_eps=self.eps,
+                                   **{v: L[v] for v in VARIANT_WEIGHTS if v in L})
+        api.pkv_query_score(self.lc, self.q[:qn], L["k_cache"][:self.n], self.score,
+                            accumulate=accumulate, ws=self.ws)
+
     def stage1(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]],
                n_score_layers: Optional[int] = None) -> None:
         """Restores every layer's context keys, scores with the query rows over the first
-        ``n_score_layers`` layers and writes the selection into ``self.rows[:k]``."""
+        ``n_score_layers`` layers and writes the selection into ``self.rows[:k]``.  The query
+        rows' hidden states after those layers stay in ``self.h``, their K/V in the caches."""
+        self._stage1(embed, layers, n_score_layers, keep_rows=True)
+
+    # keep_rows=False: Stage II follows, which gathers the query rows anew and replaces their
+    # cache rows in every layer - the last scoring layer then stops at its scores
+    def _stage1(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]],
+                n_score_layers: Optional[int], keep_rows: bool) -> None:
         ls = self.cfg.n_score_layers if n_score_layers is None else n_score_layers
+        last = min(ls, len(layers)) - 1
         api.pkv_gather_rows(embed, self.q_rows, self.h[:self.qn])
         for li, L in enumerate(layers):
             api.pkv_rope_restore(self.lc, L["k_nope"], L["k_cache"][:self.n], None, 0)
-            if li < ls:
+            if li == last and not keep_rows:
+                self._score_only(L, accumulate=li > 0)
+            elif li < ls:
                 self._layer(L, self.q_rows, self.qn, score=li > 0)
         api.pkv_topk_select(self.score, self.k, self.rows, ws=self.ws)
 
     def stage2(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]]) -> torch.Tensor:
         """The rows ``self.rows`` through every layer; returns their final hidden states
         (a view of the work buffer).  Caches are updated in place."""
-        api.pkv_gather_rows(embed, self.rows, self.h[:self.m])
-        for L in layers:
-            self._layer(L, self.rows, self.m, score=None)
+        self._stage2(embed, layers)
         return self.h[:self.m]
 
+    # caches_only: nobody reads the rows' final hidden states - the last layer stops at its
+    # cache rows
+    def _stage2(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]],
+                caches_only: bool = False) -> None:
+        api.pkv_gather_rows(embed, self.rows, self.h[:self.m])
+        for li, L in enumerate(layers):
+            self._layer(L, self.rows, self.m, score=None,
+                        caches_only=caches_only and li == len(layers) - 1)
+
     def run(self, embed, layers, n_score_layers: Optional[int] = None) -> torch.Tensor:
-        self.stage1(embed, layers, n_score_layers)
+        self._stage1(embed, layers, n_score_layers, keep_rows=False)
         return self.stage2(embed, layers)
