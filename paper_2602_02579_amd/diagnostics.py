@@ -68,6 +68,16 @@ class Diagnostics:
                       blocks: Sequence[Block]) -> Tuple[List[torch.Tensor], List[torch.Tensor]]:
         """Ordinary causal prefill of ``embed_rows [T, hid]`` at positions 0..T-1; returns
         per layer the keys in their stored, position-free form and the values."""
+        shape = (embed_rows.shape[0], self.cfg.n_kv_heads, self.cfg.head_dim)
+        k, v = ([torch.empty(shape, dtype=self.dt, device=self.device) for _ in blocks]
+                for _ in range(2))
+        self._prefill_into(embed_rows, blocks, k, v)
+        return k, v
+
+    # the same into given tensors: every one of their T rows is written before anything reads
+    # it, and the inverse rotation runs in place
+    def _prefill_into(self, embed_rows: torch.Tensor, blocks: Sequence[Block],
+                      k: List[torch.Tensor], v: List[torch.Tensor]) -> None:
         t = embed_rows.shape[0]
         if t < 2:
             raise ValueError("a chunk needs at least two tokens")
@@ -79,33 +89,27 @@ class Diagnostics:
             cr.neg_pos = -torch.arange(t, dtype=torch.int32, device=self.device)
             self._prefill[t] = cr
         layers = []
-        for b in blocks:
+        for li, b in enumerate(blocks):
             L = {name: b[name] for name in BLOCK_WEIGHTS + VARIANT_WEIGHTS if name in b}
-            # every one of the T rows is written before anything reads it
-            shape = (t, self.cfg.n_kv_heads, self.cfg.head_dim)
-            L["k_cache"] = torch.empty(shape, dtype=self.dt, device=self.device)
-            L["v_cache"] = torch.empty_like(L["k_cache"])
+            L["k_cache"], L["v_cache"] = k[li], v[li]
             layers.append(L)
         cr._stage2(embed_rows.contiguous(), layers, caches_only=True)
-        k_nope = []
-        for L in layers:
-            out = torch.empty_like(L["k_cache"])
-            api.pkv_rope_restore(self.lc, L["k_cache"], out, cr.neg_pos)   # inverse rotation
-            k_nope.append(out)
-        return k_nope, [L["v_cache"] for L in layers]
+        for kk in k:
+            api.pkv_rope_restore(self.lc, kk, kk, cr.neg_pos)   # inverse rotation
 
     def chunk_isolated_cache(self, embed: torch.Tensor, blocks: Sequence[Block],
                              chunk_len: int):
         """Per-layer ``(k_nope, v) [n_ctx, Hkv, D]`` with every chunk prefilled alone."""
         n = self.cfg.n_ctx
-        ks = [[] for _ in blocks]
-        vs = [[] for _ in blocks]
-        for a in range(0, n, chunk_len):
-            k, v = self.prefill_cache(embed[a:min(a + chunk_len, n)], blocks)
-            for li in range(len(blocks)):
-                ks[li].append(k[li])
-                vs[li].append(v[li])
-        return [torch.cat(x) for x in ks], [torch.cat(x) for x in vs]
+        shape = (n, self.cfg.n_kv_heads, self.cfg.head_dim)
+        ks, vs = ([torch.empty(shape, dtype=self.dt, device=self.device) for _ in blocks]
+                  for _ in range(2))
+        end = 0
+        for a in range(0, n, chunk_len):   # straight into the chunk's rows of the whole
+            rows = embed[a:min(a + chunk_len, n)]
+            end = a + rows.shape[0]
+            self._prefill_into(rows, blocks, [x[a:end] for x in ks], [x[a:end] for x in vs])
+        return [x[:end] for x in ks], [x[:end] for x in vs]
 
     def full_prefill_cache(self, embed: torch.Tensor, blocks: Sequence[Block]):
         return self.chunk_isolated_cache(embed, blocks, self.cfg.n_ctx)
