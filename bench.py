@@ -693,9 +693,8 @@ def main():
                      "traffic_source": TRAFFIC_SOURCE,
                      "flops_per_launch": flops, "avg_launch_s": t_attn,
                      "launch": "pkv_sparse_row_attn = a small first kernel (clears the work "
-                               "counters; at the largest sizes it also makes a V^T copy) + "
-                               "attn_w8_kernel + repair pass, timed with events on the launch "
-                               "stream"},
+                               "counters; at the larger sizes it also makes a V^T copy) + "
+                               "attn_w8n_kernel, timed with events on the launch stream"},
         "breakdown": breakdown,
     }
     # the same pass with steps 4a + 4b fused into one call (outside `value`)
