@@ -93,6 +93,61 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const T* __restrict__
     }
 }
 
+// The same with a workgroup per row, the row in registers (up to 2048 pieces of 16 bytes): few
+// rows are a chain of one load, one sum over the row and one store, and four waves make it a
+// quarter as long.
+template <typename T>
+__global__ __launch_bounds__(256) void rmsnorm_few_kernel(const T* __restrict__ h,
+                                                          const int32_t* __restrict__ row_idx,
+                                                          const T* __restrict__ weight, float eps,
+                                                          T* __restrict__ y, int hidden) {
+    typedef typename Vec16<T>::type vec_t;
+    constexpr int N = Vec16<T>::N;
+    __shared__ float s_sum[4];
+    const int tid = threadIdx.x;
+    const int row = blockIdx.x;
+    const int64_t src = row_idx ? row_idx[row] : row;
+    const vec_t* hp = reinterpret_cast<const vec_t*>(h + src * hidden);
+    const vec_t* wp = reinterpret_cast<const vec_t*>(weight);
+    vec_t* yp = reinterpret_cast<vec_t*>(y + (int64_t)row * hidden);
+    const int n_chunks = hidden / N;
+    vec_t v[8], w[8];
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = i * 256 + tid;
+        if (c < n_chunks) {
+            v[i] = hp[c];
+            w[i] = wp[c];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (i * 256 + tid < n_chunks) {
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const float f = Elem<T>::to_f32(v[i][e]);
+                ss += f * f;
+            }
+        }
+    ss = wave_sum_f32(ss);
+    if ((tid & 63) == 0) s_sum[tid >> 6] = ss;
+    __syncthreads();
+    ss = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    const float r = 1.0f / sqrtf(ss / (float)hidden + eps);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = i * 256 + tid;
+        if (c < n_chunks) {
+            vec_t o;
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+                o[e] = Elem<T>::from_f32(Elem<T>::to_f32(v[i][e]) * r * Elem<T>::to_f32(w[i][e]));
+            yp[c] = o;
+        }
+    }
+}
+
 // ---- row gather: 16 bytes per lane ------------------------------------------------------
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restrict__ src,
                                                           const int32_t* __restrict__ row_idx,
@@ -145,9 +200,23 @@ __global__ __launch_bounds__(256) void linear_simple_kernel(const T* __restrict_
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// Whether a workgroup per row is the faster way: the row must give a wave more than one piece
+// per lane, and a workgroup more than it has lanes where there are many rows.  Measured, wave per
+// row -> workgroup per row (us): 4096 bf16, 64 rows 4.9 -> 2.8, 512 7.4 -> 3.4, 2048 9.6 -> 8.2, 3000
+// 11.7 -> 12.4; 5120, 50 rows 5.7 -> 2.9, 870 8.9 -> 5.5; 1024, 256 rows 2.8 -> 2.5, 1500 3.8 -> 4.5; 256
+// fp32 (one piece per lane), 883 rows 2.5 -> 2.9.
+bool few_rows(int64_t m, int64_t chunks) {
+    return chunks <= 2048 && (chunks >= 256 ? m <= 2048 : chunks > 64 && m <= 1024);
+}
+
 template <typename T>
 pkv_status rmsnorm_typed(const void* h, const int32_t* row_idx, const void* weight, float eps,
                          void* y, int64_t m, int64_t hidden, hipStream_t st) {
+    if (few_rows(m, hidden * (int64_t)sizeof(T) / 16)) {
+        hipLaunchKernelGGL(rmsnorm_few_kernel<T>, dim3((unsigned)m), dim3(256), 0, st,
+                           (const T*)h, row_idx, (const T*)weight, eps, (T*)y, (int)hidden);
+        return launch_status();
+    }
     const unsigned blocks = (unsigned)ceil_div(m, 4);
     const bool in_regs = hidden * (int64_t)sizeof(T) <= 8 * 64 * 16;
     if (in_regs)
