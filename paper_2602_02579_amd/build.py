@@ -31,14 +31,15 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-# per-source additions: kernels whose MFMA results are read by the VALU right away do
-# better with the results in ordinary VGPRs than with copies out of the accumulation
-# registers
+# per-source additions: kernels whose MFMA results are read by the VALU right away, or whose
+# accumulators are few, do better with the results in ordinary VGPRs than with copies out of
+# the accumulation registers
 SOURCE_FLAGS = {
     "sparse_row_attn_w8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "sparse_row_attn_w8n.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "sparse_row_attn_short.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "query_score_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "gather_qkv_proj_tiles.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

@@ -13,6 +13,12 @@
 // The operands of step t + 1 are read into registers while step t is multiplied, so a stage is
 // free again one barrier after its reads and S - 1 steps are in flight.
 //
+// The accumulators (32 or 64 registers) fit the ordinary vector registers beside the operands,
+// and the matrix instructions are the compiler's own, so that it keeps the distance between a
+// result and its reader.  Written out in assembly, as the large tiles need them, they left it
+// free to put the register copies of the odd last step one slot behind the instruction whose
+// result they copy (eight are needed).
+//
 // What bounds it: few rows stream the weights (64 rows x 28672 outputs x 4096: 235 MB in 45 us,
 // 5.2 TB/s, against 64 us on 256 x 256 tiles whose matrix work is three quarters padding); on a
 // small model the latency of one tile's chain of steps (256 rows x 1536 x 1024: 21 -> 8 us with
@@ -174,7 +180,8 @@ __global__ __launch_bounds__(256, (SmallTile<NT, S>::kPerCu)) void proj_small_ke
             const int ks = g >> 2, mt = g & 3;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-                mfma_16x16x32(acc[mt][nt], fw[PAR][ks][mt], fx[PAR][ks][nt]);
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    fw[PAR][ks][mt], fx[PAR][ks][nt], acc[mt][nt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if (g < FILLS) issue(off_cur, g, adv);
             if (g < 6) {                         // 8 feature and 2 NT token operands
@@ -197,7 +204,6 @@ __global__ __launch_bounds__(256, (SmallTile<NT, S>::kPerCu)) void proj_small_ke
     }
     if (t < n_T) step(t, std::integral_constant<int, 0>());
     wait_vm<0>();                 // the ring's trailing fills must not land in the staging
-    acc_settle();
     __syncthreads();
 
     // ---- epilogue: the tile meets in LDS, whole rows leave 16 B per lane --------------------
