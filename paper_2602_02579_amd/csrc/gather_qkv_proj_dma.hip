@@ -90,9 +90,11 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                for (int mt = 0; mt < 8; ++mt)
+                for (int mt = 0; mt < 8; ++mt) {
+                    acc_take(acc[mt][tb * 2 + nt]);
                     *reinterpret_cast<f32x4*>(epf + (nt * 16 + l16) * kEpiStrideF32 +
                                               (mt * 16 + 4 * g4) * 4) = acc[mt][tb * 2 + nt];
+                }
 #pragma unroll
             for (int it = 0; it < 16; ++it) {
                 const int idx = it * 64 + lane;
@@ -117,6 +119,7 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
                 unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
                 for (int mt = 0; mt < 8; ++mt) {
+                    acc_take(acc[mt][half * NQ + nt]);
                     bf16x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = (bf16_t)acc[mt][half * NQ + nt][e];
@@ -152,6 +155,8 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
                 unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt) {
+                    acc_take(acc[mt][tt]);
+                    acc_take(acc[mt + 4][tt]);
                     bf16x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -189,6 +194,8 @@ __device__ __forceinline__ void tile_epilogue(const ProjParams& p, f32x4 (&acc)[
             const int row = min(row0 + wt * (32 * NQ) + tt * 16 + l16, p.m - 1);
             const float4* cs = reinterpret_cast<const float4*>(p.cs + (int64_t)row * (D / 2));
             unsigned char* erow = epi + (nt * 16 + l16) * kEpiStride;
+#pragma unroll
+            for (int mt = 0; mt < 8; ++mt) acc_take(acc[mt][tt]);
             float rnorm = 1.f;
             if (EXTRA) {
                 if (bias) {

@@ -21,11 +21,20 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
 // c += a . b on a 16 x 16 tile, 32 of the contraction.  Written out so that the accumulator
 // stays where it is: left to itself the register allocator rotates the 64 accumulators of a
 // wave through copies (584 of them per two steps) once they are four registers each.  The
-// compiler does not see the result's latency: acc_settle() before the first reader.
+// compiler does not see the result's latency: acc_settle(), then acc_take() before a read.  (What it
+// adds by itself, such as copies at the end of a loop, can still come before that:
+// test_matrix_result_waits.py looks for it in the built code.)
 __device__ __forceinline__ void mfma_16x16x32(f32x4& c, bf16x8 a, bf16x8 b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+// the wait behind the last product, which nothing is moved across
+__device__ __forceinline__ void acc_settle() {
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+// an accumulator on its way to its readers: they depend on this statement, and this one comes
+// behind the wait
+__device__ __forceinline__ void acc_take(f32x4& c) { asm volatile("" : "+v"(c)); }
 template <int N>
 __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -442,8 +442,10 @@ __global__ __launch_bounds__(kThreads) void attn_w8_kernel(AttnParams p) {
     }
     wait_vm<0>();   // nothing may still be writing LDS when the workgroup moves on
     // the last O^T MFMAs were issued behind the compiler's back: let them retire before the
-    // accumulators are read
+    // accumulators are read (which the statements behind the wait keep behind it)
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(o_acc[db]));
 
     l_tot = l_run + __shfl_xor(l_run, 32, 64);
     {

@@ -484,7 +484,10 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
         }
         msc[ct] = (m_run[ct] == -INFINITY ? 0.f : m_run[ct]) * c2;
     }
-    asm volatile("s_nop 15" ::: "memory");   // s_b is read by statements of our own
+    // the scores are read by statements of our own: made before this wait, read behind it
+    asm volatile("s_nop 15"
+                 : "+v"(s_a[0][0]), "+v"(s_a[0][1]), "+v"(s_a[1][0]), "+v"(s_a[1][1]),
+                   "+v"(s_b[0][0]), "+v"(s_b[0][1]), "+v"(s_b[1][0]), "+v"(s_b[1][1]));
     // P(0); its last pair is packed and summed by the first sub-step
     W8_SM_PREP(s_a, 0, 0, true)
 #pragma unroll
@@ -519,8 +522,12 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
     }
     wait_vm<0>();   // nothing may still be writing LDS when the workgroup moves on
     // the last O^T MFMAs were issued behind the compiler's back: let them retire before the
-    // accumulators are read
+    // accumulators are read (which the statements behind the wait keep behind it)
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) asm volatile("" : "+v"(o_acc[db][ct]));
 
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
