@@ -516,9 +516,10 @@ F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq)
     const int64_t tiles = ceil_div(nq * group, 16) * cfg.n_kv_heads;
     int64_t want = std::min(ceil_div(256, tiles), ceil_div(n_ctx, 64));
     want = std::max<int64_t>(1, std::min(want, 8192 / std::max<int64_t>(1, nq * cfg.n_q_heads)));
+    const int64_t len = ceil_div(ceil_div(n_ctx, want), 64) * 64;
     F32ScorePlan p;
-    p.split_len = (int)(ceil_div(ceil_div(n_ctx, want), 64) * 64);
-    p.n_splits = (int)ceil_div(n_ctx, p.split_len);
+    p.split_len = (int)len;
+    p.n_splits = (int)ceil_div(n_ctx, len);
     return p;
 }
 

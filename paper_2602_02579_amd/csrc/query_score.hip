@@ -328,6 +328,9 @@ pkv_status launch_attn_lse_partials(const pkv_layer_cfg& cfg, const void* q,
                                     float* part_ml, hipStream_t st);
 
 size_t query_score_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {
+    // the plans below divide by what they are asked to split
+    if (nq <= 0) return 0;
+    if (n_ctx < 1) n_ctx = 1;
     const size_t ncol = (size_t)(nq * cfg.n_q_heads);
     if (f32_tiles_supported(cfg))
         return (size_t)plan_score_f32(cfg, n_ctx, nq).n_splits * ncol * 2 * sizeof(float);
