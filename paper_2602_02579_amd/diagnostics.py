@@ -101,11 +101,14 @@ class Diagnostics:
                              chunk_len: int):
         """Per-layer ``(k_nope, v) [n_ctx, Hkv, D]`` with every chunk prefilled alone."""
         n = self.cfg.n_ctx
+        starts = range(0, n, chunk_len)
+        if blocks and not starts:
+            raise ValueError(f"no chunks of {chunk_len} tokens in {n}")
         shape = (n, self.cfg.n_kv_heads, self.cfg.head_dim)
         ks, vs = ([torch.empty(shape, dtype=self.dt, device=self.device) for _ in blocks]
                   for _ in range(2))
         end = 0
-        for a in range(0, n, chunk_len):   # straight into the chunk's rows of the whole
+        for a in starts:   # straight into the chunk's rows of the whole
             rows = embed[a:min(a + chunk_len, n)]
             end = a + rows.shape[0]
             self._prefill_into(rows, blocks, [x[a:end] for x in ks], [x[a:end] for x in vs])
