@@ -8,8 +8,8 @@
 #include <atomic>
 #include <cstdlib>
 #include <functional>
+#include <functional>
 #include <mutex>
-#include <queue>
 #include <vector>
 
 #include "attn_common.h"
@@ -464,6 +464,8 @@ constexpr int kMaxCtxRanges = 32;   // ranges per tile when a boundary is forced
 bool attn_plan_splits_at(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int64_t ctx_keys,
                          int* n_splits, int* split_len);
 
+constexpr int kPlanCus = 256;       // CUs that the plans reckon with
+
 // Estimated time (us) of the pipelined launch when every row tile's keys are cut into `sp`
 // ranges, without the merge, for one layout of the row limits (the limits live on the device;
 // the host weighs two layouts): `spread` = rows in position order with limits evenly over the
@@ -481,8 +483,7 @@ double attn_launch_estimate(int64_t tiles, int hkv, int64_t steps_full, int sp, 
     const double fixed = 7.0 + (sp > 1 ? 1.7 : 0.0);
     const int64_t range_steps = (steps_full + sp - 1) / sp;
     const int share = std::max(1, n_cu / hkv);
-    std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
-    for (int c = 0; c < share; ++c) cu.push(0.0);
+    double cu[kPlanCus];      // when each of them is free; a heap once all have a job
     double end = 0.0, total = 0.0;
     int64_t jobs = 0;
     for (int64_t i = tiles - 1; i >= 0; --i) {
@@ -491,11 +492,17 @@ double attn_launch_estimate(int64_t tiles, int hkv, int64_t steps_full, int sp, 
         for (int s = 0; s < sp; ++s) {
             const int64_t st = std::min<int64_t>(range_steps, reach - (int64_t)s * range_steps);
             if (st <= 0) break;
-            const double t = cu.top() + (double)st + fixed;
-            cu.pop();
-            cu.push(t);
+            double t = (double)st + fixed;
+            total += t;
+            if (jobs < share) {
+                cu[jobs] = t;
+                if (jobs == share - 1) std::make_heap(cu, cu + share, std::greater<double>());
+            } else {
+                std::pop_heap(cu, cu + share, std::greater<double>());
+                t = cu[share - 1] = cu[share - 1] + (double)st + fixed;
+                std::push_heap(cu, cu + share, std::greater<double>());
+            }
             end = std::max(end, t);
-            total += (double)st + fixed;
             ++jobs;
         }
     }
@@ -510,7 +517,8 @@ double attn_launch_estimate(int64_t tiles, int hkv, int64_t steps_full, int sp, 
 // ranges (of two 64-key steps or more); the jobs write normalised partial results that a small
 // kernel merges.  The count minimises the estimated launch time (the two layouts above,
 // weighted by the row count) plus what the ranges cost: the jobs write and the merge kernel
-// reads the partial results a row has, at 5.6 TB/s.  Plans are remembered per problem size.
+// reads the partial results a row has, at 5.6 TB/s.  Plans are remembered per problem size (the
+// last 64); a size not seen before costs 3 us on the host with eight kv heads, 18 with one.
 // Measured, one range -> the count chosen: 637 rows over 4k keys 82 -> 58 us (2), 320 over 3k
 // 68 -> 35 (6), 883 over 16k 287 -> 145 (3; two, as an earlier estimate chose, 169), 64
 // full-length rows over 8k 147 -> 32 (16).
@@ -550,7 +558,7 @@ void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* 
                 want = c.want;
     }
     if (want == 0) {
-        const int n_cu = 256;
+        const int n_cu = kPlanCus;
         const int64_t steps_full = ceil_div(n_keys, 64);
         const double out_elems = (double)m * cfg.n_q_heads * cfg.head_dim;
         // a handful of rows are the user query, which sees the whole cache; thousands of rows
