@@ -554,6 +554,8 @@ def carried_model(cfg, device, n_layers, inter=14336, eps=1e-5, steps=3):
             "recomputed_tokens_per_s": round(m * n_layers / per_pass, 1),
             "output_finite": finite, "same_selection_every_pass": same_selection,
             "fused_stage1": cr.fuse_stage1,
+            # a whole run scores its last scoring layer without the attention
+            "fused_scoring_layers": cfg.n_score_layers - 1 if cr.fuse_stage1 else 0,
             "data": "synthetic (device-side seeded normal draws)",
             "glue": glue}
 

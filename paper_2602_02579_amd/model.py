@@ -52,10 +52,12 @@ class CarriedRows:
         self.lc = layer_cfg(cfg)
         n, qn = cfg.n_ctx, cfg.n_query
         # Stage I with one key stream less: the query rows' attention emits the
-        # normaliser over the context keys and the score only sums the columns
-        # (None = whenever the library has it for this geometry)
+        # normaliser over the context keys and the score only sums the columns.
+        # None = whenever the library has it for this geometry, but for the last scoring layer
+        # of a whole run, whose attention nobody reads; True = there too
         ctx_ws = api.pkv_sparse_row_attn_ctx_lse_workspace_bytes(self.lc, n + qn, n, qn)
         self.fuse_stage1 = ctx_ws > 0 if fuse_stage1 is None else bool(fuse_stage1)
+        self._fuse_last = bool(fuse_stage1)
         if self.fuse_stage1 and ctx_ws == 0:
             raise ValueError("fused Stage I is not available for this geometry")
         self.n, self.qn = n, qn
@@ -91,9 +93,11 @@ class CarriedRows:
         self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device=device)
 
     # one decoder layer for the first ``cnt`` rows of the buffers, at positions ``rows``;
-    # caches_only: its normalisation and K/V projection, nothing of the rows themselves
+    # caches_only: its normalisation and K/V projection, nothing of the rows themselves;
+    # scores_only: up to the scores
     def _layer(self, L: Dict[str, torch.Tensor], rows: torch.Tensor, cnt: int,
-               score: Optional[bool], caches_only: bool = False) -> None:
+               score: Optional[bool], caches_only: bool = False,
+               scores_only: bool = False) -> None:
         lc, ws = self.lc, self.ws
         h, x = self.h[:cnt], self.x[:cnt]
         q = self.q[:cnt]
@@ -120,6 +124,8 @@ class CarriedRows:
                                     accumulate=score, ws=ws)
             api.pkv_sparse_row_attn(lc, q, L["k_cache"], L["v_cache"], rows, attn, None,
                                     ws=ws)
+        if scores_only:
+            return
         api.pkv_linear_rows(attn.view(cnt, -1), L["wo"], h, h, ws=ws)
         api.pkv_rmsnorm_rows(h, None, L["w_post"], self.eps, x)
         api.pkv_swiglu_rows(x, L["w_gate"], L["w_up"], g, ws=ws)
@@ -152,7 +158,9 @@ class CarriedRows:
         api.pkv_gather_rows(embed, self.q_rows, self.h[:self.qn])
         for li, L in enumerate(layers):
             api.pkv_rope_restore(self.lc, L["k_nope"], L["k_cache"][:self.n], None, 0)
-            if li == last and not keep_rows:
+            if li == last and not keep_rows and self._fuse_last:
+                self._layer(L, self.q_rows, self.qn, score=li > 0, scores_only=True)
+            elif li == last and not keep_rows:
                 self._score_only(L, accumulate=li > 0)
             elif li < ls:
                 self._layer(L, self.q_rows, self.qn, score=li > 0)
