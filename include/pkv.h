@@ -181,8 +181,8 @@ pkv_status pkv_query_score_static(const pkv_layer_cfg* cfg,
  * writes 0..n-1.  Scores must be finite.  The workspace is optional: vectors of
  * up to 24576 scores need none; longer ones (up to 2^22) are selected by many
  * workgroups when `ws` holds pkv_workspace_bytes(PKV_CALL_TOPK_SELECT, cfg, n, 0)
- * bytes (from 32769 scores on if they are 16-byte aligned), and by one workgroup (2x
- * slower at 64k scores, 10x at 128k) when it is NULL or smaller.  The result is the same either way.
+ * bytes (from 32769 scores on if they are 16-byte aligned), and by one workgroup (1.5x
+ * slower at 64k scores, 9x at 128k) when it is NULL or smaller.  The result is the same either way.
  */
 pkv_status pkv_topk_select(const float* score, /* [n] */
                            int64_t n, int64_t k,

@@ -153,14 +153,30 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(
     }
 }
 
+// Keys of the kernel below: past the end of the vector 0, scores from 1 to 0xffdfffff (which
+// touches NaNs only).  So a key of 0 lies below every bin, also where it wraps: the largest bin is
+// 2^21 keys wide and ends short of 2^32.
+__device__ __forceinline__ uint32_t inner_key(float x) {
+    return min(max(order_key(x), 1u), 0xffdfffffu);
+}
+
+// Updates of one LDS counter by c lanes of an instruction take about 6 c cycles, so a key that many
+// scores share (zeros of an underflow, masks, ties) is kept out of the bins: every wave looks
+// whether kOften of 64 of its keys are one, the block takes two such keys, and their number goes
+// to the bin they belong to in one update per wave.  And a bin that holds a sixteenth of all keys
+// is divided by the span of the keys in it, not by its width: often it is one key, and done.
+// Vectors of kOftenMin or fewer scores do without the former.
+constexpr int kOften = 4, kOftenMin = 2048;
+
 // One workgroup, the keys in registers: wave w owns scores [64 ITEMS w, 64 ITEMS (w + 1)),
 // a lane four consecutive ones of every 256.
-template <int ITEMS>
+template <int ITEMS, bool OFTEN>
 __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
     const float* __restrict__ score, int n, int k, int32_t* __restrict__ idx_out) {
     constexpr int kBins = 2048, kBits = 11;
     __shared__ uint32_t hist[kBins];
     __shared__ uint32_t s_a[kWaves], s_b[kWaves], s_res[3];
+    __shared__ uint32_t s_often[2 * kWaves];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
@@ -173,51 +189,102 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
         const int i0 = base + j * 64;
         if (i0 + 3 < n) {
             const float4 v = *reinterpret_cast<const float4*>(score + i0);
-            key[j] = order_key(v.x);
-            key[j + 1] = order_key(v.y);
-            key[j + 2] = order_key(v.z);
-            key[j + 3] = order_key(v.w);
+            key[j] = inner_key(v.x);
+            key[j + 1] = inner_key(v.y);
+            key[j + 2] = inner_key(v.z);
+            key[j + 3] = inner_key(v.w);
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) key[j + e] = i0 + e < n ? order_key(score[i0 + e]) : 0u;
+            for (int e = 0; e < 4; ++e) key[j + e] = i0 + e < n ? inner_key(score[i0 + e]) : 0u;
         }
     }
-#define PKV_IN(J) (base + ((J) / 4) * 256 + (J) % 4 < n)
-
-    // ---- 1. the span of the keys ----------------------------------------------------------
+    // ---- 1. the span of the keys: mn + 1 to mx ---------------------------------------------
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-        if (PKV_IN(j)) {
-            mn = min(mn, key[j]);
-            mx = max(mx, key[j]);
-        }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        mn = min(mn, __shfl_xor(mn, o, 64));
-        mx = max(mx, __shfl_xor(mx, o, 64));
+    for (int j = 0; j < ITEMS; ++j) {
+        mn = min(mn, key[j] - 1u);   // no score: wraps to the largest
+        mx = max(mx, key[j]);
     }
-    if (lane == 0) {
-        s_a[wave] = mn;
-        s_b[wave] = mx;
+    // up to two keys that kOften or more of 64 of the wave's keys are (0: none)
+    uint32_t often[2] = {0u, 0u};
+    if (OFTEN) {
+        uint64_t left = __ballot(key[0] != 0u);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (left == 0) break;
+            const uint32_t k0 = __builtin_amdgcn_readlane(key[0], (int)__builtin_ctzll(left));
+            const uint64_t same = __ballot(key[0] == k0) & left;
+            left &= ~same;
+            if (__popcll(same) >= kOften) often[r] = k0;
+        }
+    }
+    if (OFTEN && lane == 0) {
+        s_often[2 * wave] = often[0];
+        s_often[2 * wave + 1] = often[1];
     }
     hist[tid] = 0u;
     hist[tid + kThreads] = 0u;
-    __syncthreads();
+    // smallest and largest of the block's values; a barrier inside
+    auto block_span = [&](uint32_t& lo_, uint32_t& hi_) {
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        mn = min(mn, s_a[w]);
-        mx = max(mx, s_b[w]);
+        for (int o = 32; o > 0; o >>= 1) {
+            lo_ = min(lo_, __shfl_xor(lo_, o, 64));
+            hi_ = max(hi_, __shfl_xor(hi_, o, 64));
+        }
+        if (lane == 0) {
+            s_a[wave] = lo_;
+            s_b[wave] = hi_;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            lo_ = min(lo_, s_a[w]);
+            hi_ = max(hi_, s_b[w]);
+        }
+    };
+    block_span(mn, mx);
+    // the block's two, the same in every wave
+    bool crowded = false;
+    if (OFTEN) {
+        const uint32_t v = s_often[lane & (2 * kWaves - 1)];
+        const uint64_t some = __ballot(v != 0u);
+        crowded = some != 0;
+        often[0] = often[1] = 0u;
+        if (crowded) {
+            often[0] = __builtin_amdgcn_readlane(v, (int)__builtin_ctzll(some));
+            const uint64_t more = __ballot(v != 0u && v != often[0]);
+            if (more) often[1] = __builtin_amdgcn_readlane(v, (int)__builtin_ctzll(more));
+        }
+    }
+    // how many of the wave's keys are those
+    uint32_t own[2] = {0u, 0u};
+    if (crowded) {
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            own[0] += __popcll(__ballot(key[j] == often[0]));
+            own[1] += __popcll(__ballot(key[j] == often[1]));
+        }
     }
 
     // ---- 2. lo = lower end of the bin with the k-th largest key, ever finer ----------------
-    uint32_t lo = mn, span = mx - mn;   // keys [lo, lo + span] are counted
+    uint32_t lo = mn + 1u, span = mx - lo;   // keys [lo, lo + span] are counted
     uint32_t rest = (uint32_t)k, cnt = 0u;
     int shift = span ? max(0, 32 - __clz(span) - kBits) : 0;
     for (;;) {
+        if (!crowded) {
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t d = key[j] - lo;   // wraps to the far end below lo
-            if (PKV_IN(j) && d <= span) atomicAdd(&hist[d >> shift], 1u);
+            for (int j = 0; j < ITEMS; ++j) {
+                const uint32_t d = key[j] - lo;   // wraps to the far end below lo
+                if (d <= span) atomicAdd(&hist[d >> shift], 1u);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) {
+                const uint32_t d = key[j] - lo;
+                if (d <= span && key[j] != often[0] && key[j] != often[1])
+                    atomicAdd(&hist[d >> shift], 1u);
+            }
+            const uint32_t d = (lane == 0 ? often[0] : often[1]) - lo;
+            if (lane < 2 && d <= span) atomicAdd(&hist[d >> shift], lane == 0 ? own[0] : own[1]);
         }
         __syncthreads();
         // thread t owns the bins 2047 - 2 t and 2046 - 2 t; counts above them
@@ -251,7 +318,27 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
         // key wide and `rest` of its equals are wanted
         if (rest == cnt || shift == 0) break;
         span = (1u << shift) - 1u;
-        shift = max(0, shift - kBits);
+        if (cnt <= (uint32_t)n / 16u) {
+            shift = max(0, shift - kBits);
+            continue;
+        }
+        // the span that the bin's keys really take
+        mn = 0xffffffffu;
+        mx = 0u;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t d = key[j] - lo;
+            mn = min(mn, d <= span ? d : 0xffffffffu);
+            mx = max(mx, d <= span ? d : 0u);
+        }
+        block_span(mn, mx);
+        lo += mn;
+        span = mx - mn;
+        if (span == 0u) {
+            __syncthreads();   // s_a and s_b are written again below
+            break;
+        }
+        shift = max(0, 32 - __clz(span) - kBits);
     }
 
     // ---- 3. compaction in index order -------------------------------------------------------
@@ -259,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
     if (rest == cnt) {
         uint32_t mine = 0;
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) mine += __popcll(__ballot(PKV_IN(j) && key[j] >= lo));
+        for (int j = 0; j < ITEMS; ++j) mine += __popcll(__ballot(key[j] >= lo));
         if (lane == 0) s_b[wave] = mine;
         __syncthreads();
         uint32_t out = 0;
@@ -270,7 +357,7 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
             bool take[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                take[e] = PKV_IN(j + e) && key[j + e] >= lo;
+                take[e] = key[j + e] >= lo;
                 const uint64_t b = __ballot(take[e]);
                 at += __popcll(b & lt);
                 out += __popcll(b);
@@ -285,8 +372,8 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-        gt += __popcll(__ballot(PKV_IN(j) && key[j] > lo));
-        eq += __popcll(__ballot(PKV_IN(j) && key[j] == lo));
+        gt += __popcll(__ballot(key[j] > lo));
+        eq += __popcll(__ballot(key[j] == lo));
     }
     if (lane == 0) {
         s_a[wave] = gt;
@@ -303,8 +390,8 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
         uint32_t g_at = gt, e_at = eq;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint64_t bg = __ballot(PKV_IN(j + e) && key[j + e] > lo);
-            const uint64_t be = __ballot(PKV_IN(j + e) && key[j + e] == lo);
+            const uint64_t bg = __ballot(key[j + e] > lo);
+            const uint64_t be = __ballot(key[j + e] == lo);
             g_at += __popcll(bg & lt);
             e_at += __popcll(be & lt);
             gt += __popcll(bg);
@@ -312,14 +399,12 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const bool in = PKV_IN(j + e);
-            const bool is_gt = in && key[j + e] > lo, is_eq = in && key[j + e] == lo;
+            const bool is_gt = key[j + e] > lo, is_eq = key[j + e] == lo;
             if (is_gt || (is_eq && e_at < rest)) idx_out[g_at + min(e_at, rest)] = base + j * 64 + e;
             g_at += is_gt ? 1u : 0u;
             e_at += is_eq ? 1u : 0u;
         }
     }
-#undef PKV_IN
 }
 
 
@@ -555,21 +640,28 @@ pkv_status launch_topk_select(const float* score, int64_t n, int64_t k,
     // the register kernels read 16 bytes at a time
     const bool aligned = (reinterpret_cast<uintptr_t>(score) & 15) == 0;
     // every pass walks over all register keys, so short vectors take the instantiation with
-    // the fewest keys per lane that holds them.  From 1024 to 32768 scores 5.2, 6.7 (4k), 7.0
-    // (8k), 9.0 (16k) and 15.4 us; the many-workgroup kernels take 17.5 at any length (with the
-    // threshold built bit by bit 9, 10, 14, 15 and 26)
+    // the fewest keys per lane that holds them.  From 1000 to 32768 scores 4.9, 6.8 (4k), 7.2
+    // (8k), 9.2 (16k) and 14.4 us; the many-workgroup kernels take 17.5 at any length (with the
+    // threshold built bit by bit 9, 10, 14, 15 and 26).  Scores that share a few values: 98 %
+    // zeros 7.6, 7.9, 8.0, 10.8 and 19.2 (many workgroups 21.5), 25 values 6.8, 7.9, 8.7, 12.2 and
+    // 21.9 (17.1; bit by bit 16, 16, 16, 22 and 33)
+    if (aligned && n <= kOftenMin) {
+        hipLaunchKernelGGL((topk_radix_kernel<8, false>), dim3(1), dim3(kThreads), 0, st, score,
+                           (int)n, (int)k, idx_out);
+        return launch_status();
+    }
     if (aligned && n <= 8 * kThreads) {
-        hipLaunchKernelGGL(topk_radix_kernel<8>, dim3(1), dim3(kThreads), 0, st, score,
+        hipLaunchKernelGGL((topk_radix_kernel<8, true>), dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);
         return launch_status();
     }
     if (aligned && n <= 16 * kThreads) {
-        hipLaunchKernelGGL(topk_radix_kernel<16>, dim3(1), dim3(kThreads), 0, st, score,
+        hipLaunchKernelGGL((topk_radix_kernel<16, true>), dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);
         return launch_status();
     }
     if (aligned && n <= 32 * kThreads) {
-        hipLaunchKernelGGL(topk_radix_kernel<32>, dim3(1), dim3(kThreads), 0, st, score,
+        hipLaunchKernelGGL((topk_radix_kernel<32, true>), dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);
         return launch_status();
     }
@@ -587,7 +679,7 @@ pkv_status launch_topk_select(const float* score, int64_t n, int64_t k,
         return launch_status();
     }
     if (aligned && n <= 64 * kThreads) {
-        hipLaunchKernelGGL(topk_radix_kernel<64>, dim3(1), dim3(kThreads), 0, st, score,
+        hipLaunchKernelGGL((topk_radix_kernel<64, true>), dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);
         return launch_status();
     }
