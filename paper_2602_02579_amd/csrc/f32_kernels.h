@@ -27,6 +27,8 @@ pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& ta
 // pointers of a linear layer allow 16-byte accesses (null counts as aligned), rows fit the grid
 bool linear_f32_supported(const void* x, const void* w0, const void* w1, const void* residual,
                           const void* y, int64_t m);
+// whether it beats a wave per output element
+bool linear_f32_pays(bool gated, int64_t m, int64_t k_in, int64_t n_out);
 
 // fp32 with head_dim 32, 64 or 128: score and attention below
 bool f32_tiles_supported(const pkv_layer_cfg& cfg);

@@ -1,9 +1,10 @@
 // Single precision on the matrix cores: projection and linear layers, query score, attention.
 // (The same steps as the bf16 kernels: Algorithm 1, both stages; Appendix E.)
 //
-// v_mfma_f32_16x16x4_f32 multiplies and adds in fp32, so nothing is given up against the plain
-// FMA kernels; what is gained is that one instruction does 1024 multiply-adds without moving
-// operands.  fp32 problems here are small (a 1k-token request is 0.2 GFLOP, 2 us of the fp32
+// v_mfma_f32_16x16x4_f32 multiplies and adds in fp32, so nothing is given up against plain
+// FMA kernels that sum in one chain (against the linear layers', which summed in parts, it is:
+// those take the fp64 instruction, see below); what is gained is that one instruction does 1024
+// multiply-adds without moving operands.  fp32 problems here are small (a 1k-token request is 0.2 GFLOP, 2 us of the fp32
 // matrix rate), so all of these kernels are bound by latency: the launch, and the chain of
 // memory round trips inside it.  Each is therefore cut so that a wave makes few round trips,
 // all operands of one requested together, and enough waves run at once to cover the chip.
@@ -15,9 +16,11 @@
 //
 // Measured, 1024 context tokens, 16 query tokens, 4 heads of 64 (us, plain kernels -> these):
 // attention of 220 rows 105 -> 23, column sums 158 -> 5.7, normalisers 13 -> 4.3,
-// projection of 220 rows 37 -> 8; linear layers of 151 rows, 256 -> 512 gated 20 -> 7.
+// projection of 220 rows 34 -> 6.7; linear layers of 151 rows, 256 -> 512 gated 21 -> 5.9,
+// 512 -> 256 10.3 -> 6.5.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "f32_kernels.h"
 
@@ -27,6 +30,10 @@ namespace {
 
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mfma_f64(float a, float b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0);
 }
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
@@ -40,13 +47,30 @@ __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<
 constexpr int kTM = 64, kTN = 32, kTK = 128;
 constexpr int kRow = kTK + 4;
 
-template <int MODE>
+// Sums.  The projection sums in fp32, one product behind the other, as the plain kernel did, with
+// the same error.  The plain linear layers summed 64 interleaved parts and then these in a tree:
+// 0.6 to 1.2e-7 off the fp64 result (2-norm, 64 to 4096 inputs), where one chain is 0.9 to 8.4e-7
+// off.  So they sum in fp64 here (v_mfma_f64_16x16x4_f64, at half the rate; products of fp32 are
+// exact in it) and round once: 0.3e-7 at any length.  Its accumulator register r of lane group g is
+// row g + 4 r, not 4 g + r, so the weight rows go in permuted and the outputs come out alike.
+//
+// KS = 4, for linear layers whose tiles then all run at once: a tile of 16 rows whose four waves
+// share the contraction and meet in LDS - four times the workgroups, a quarter of the chain
+// (151 rows, 256 -> 512: 8.5 us with KS = 1, 4.4 with 4; 400 rows, 512 -> 1024: 14.8 and 14.1; above
+// 1024 tiles of 16 rows the higher tiles' better use of the weights wins).
+template <int KS>
+constexpr int kTileRows = kTM / KS;
+
+template <int MODE, int KS>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTable tab) {
-    __shared__ __align__(16) float lds[(kTM + kTN) * kRow];
+    constexpr int TM = kTileRows<KS>, kLoads = (TM + kTN) / 8;
+    constexpr bool kWide = MODE != kF32Rope;
+    typedef typename std::conditional<kWide, f64x4, f32x4>::type acc_t;
+    __shared__ __align__(32) float lds[(TM + kTN) * kRow];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int g4 = lane >> 4, l16 = lane & 15;
-    const int row0 = blockIdx.y * kTM;
+    const int row0 = blockIdx.y * TM;
 
     // weight row of column c of this tile (c < 16: first set, else its partner)
     int mat = 0, ct = blockIdx.x;
@@ -71,60 +95,85 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTabl
         return p.w[mat] + (int64_t)(head * p.d + i + (c & 16 ? half : 0)) * p.k;
     };
 
-    // loader: 96 rows of 32 16-byte pieces; thread t takes piece t % 32 of rows t / 32 + 8 n
+    // loader: TM + 32 rows of 32 16-byte pieces; thread t takes piece t % 32 of rows t / 32 + 8 n
     const int piece = tid & 31, r0 = tid >> 5;
-    const float* src[12];
+    const float* src[kLoads];
 #pragma unroll
-    for (int n = 0; n < 12; ++n) {
+    for (int n = 0; n < kLoads; ++n) {
         const int r = r0 + 8 * n;
-        if (r < kTM) {
+        if (r < TM) {
             const int row = min(row0 + r, p.m - 1);
             src[n] = p.x + (int64_t)(p.row_idx ? p.row_idx[row] : row) * p.k;
         } else {
-            src[n] = w_row(r - kTM);
+            src[n] = w_row(r - TM);
         }
     }
-    f32x4 st[12];
+    f32x4 st[kLoads];
     auto load = [&](int k0) {
         const int k = k0 + piece * 4;
 #pragma unroll
-        for (int n = 0; n < 12; ++n)
+        for (int n = 0; n < kLoads; ++n)
             st[n] = k < p.k ? ld4(src[n] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    acc_t acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    const int w16 = kWide ? 4 * (l16 & 3) + (l16 >> 2) : l16;
     load(0);
     for (int k0 = 0; k0 < p.k; k0 += kTK) {
         __syncthreads();
 #pragma unroll
-        for (int n = 0; n < 12; ++n)
+        for (int n = 0; n < kLoads; ++n)
             *reinterpret_cast<f32x4*>(lds + (r0 + 8 * n) * kRow + piece * 4) = st[n];
         __syncthreads();
         if (k0 + kTK < p.k) load(k0 + kTK);
-        const float* xb = lds + (wave * 16 + l16) * kRow + g4 * 4;
-        const float* wb = lds + (kTM + l16) * kRow + g4 * 4;
+        const int part = KS == 1 ? 0 : wave * (kTK / KS);   // of the chunk
+        const float* xb = lds + ((KS == 1 ? wave * 16 : 0) + l16) * kRow + g4 * 4 + part;
+        const float* wb = lds + (TM + w16) * kRow + g4 * 4 + part;
 #pragma unroll
-        for (int c = 0; c < kTK / 16; ++c) {
+        for (int c = 0; c < kTK / KS / 16; ++c) {
             const f32x4 b = ld4(xb + c * 16), a0 = ld4(wb + c * 16),
                         a1 = ld4(wb + 16 * kRow + c * 16);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                acc[0] = mfma_f32(a0[j], b[j], acc[0]);
-                acc[1] = mfma_f32(a1[j], b[j], acc[1]);
+                if constexpr (kWide) {
+                    acc[0] = mfma_f64(a0[j], b[j], acc[0]);
+                    acc[1] = mfma_f64(a1[j], b[j], acc[1]);
+                } else {
+                    acc[0] = mfma_f32(a0[j], b[j], acc[0]);
+                    acc[1] = mfma_f32(a1[j], b[j], acc[1]);
+                }
             }
         }
     }
 
+    if constexpr (KS > 1) {
+        acc_t* const ex = reinterpret_cast<acc_t*>(lds);   // [wave - 1][set][lane]
+        static_assert((KS - 1) * 2 * 64 * sizeof(acc_t) <= sizeof(lds), "");
+        __syncthreads();
+        if (wave > 0) {
+            ex[(wave * 2 - 2) * 64 + lane] = acc[0];
+            ex[(wave * 2 - 1) * 64 + lane] = acc[1];
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int w = 0; w < 2 * (KS - 1); ++w) acc[w & 1] += ex[w * 64 + lane];
+    }
     // a lane holds row l16 of the wave, columns 4 g4 + r of both sets
-    const int row = row0 + wave * 16 + l16;
+    const int row = row0 + (KS == 1 ? wave * 16 : 0) + l16;
     if (row >= p.m) return;
     const int c0 = col_of(4 * g4);
+    f32x4 sum[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[s][r] = (float)acc[s][r];
     if (MODE == kF32Plain) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int f = c0 + 16 * s;
             if (f >= n_cols) continue;             // n_out is a multiple of 8
             const int64_t o = (int64_t)row * p.n_out + f;
-            f32x4 v = acc[s];
+            f32x4 v = sum[s];
             if (p.residual) v += ld4(p.residual + o);
             *reinterpret_cast<f32x4*>(p.out[0] + o) = v;
         }
@@ -132,7 +181,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTabl
         if (c0 >= n_cols) return;
         f32x4 v;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc[0][r] / (1.f + expf(-acc[0][r])) * acc[1][r];
+        for (int r = 0; r < 4; ++r) v[r] = sum[0][r] / (1.f + expf(-sum[0][r])) * sum[1][r];
         *reinterpret_cast<f32x4*>(p.out[0] + (int64_t)row * p.n_out + c0) = v;
     } else {
         if (c0 >= n_cols) return;                  // half is a multiple of 8
@@ -140,7 +189,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTabl
         const int heads = mat == 0 ? p.hq : p.hkv;
         const int64_t orow = mat != 0 && p.dst_row ? p.dst_row[row] : row;
         float* o = p.out[mat] + (orow * heads + head) * p.d + i0;
-        f32x4 a = acc[0], b = acc[1];
+        f32x4 a = sum[0], b = sum[1];
         if (p.bias[mat]) {
             a += ld4(p.bias[mat] + head * p.d + i0);
             b += ld4(p.bias[mat] + head * p.d + i0 + half);
@@ -482,13 +531,19 @@ pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& ta
     int n_ct;
     if (mode == kF32Rope) n_ct = p.tile_begin[3];
     else n_ct = (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
-    const int64_t rows = ceil_div(p.m, kTM);
+    // a linear layer whose tiles of 16 rows all run at once (four workgroups per CU)
+    const bool low = mode != kF32Rope && ceil_div(p.m, kTileRows<4>) * n_ct <= 1024;
+    const int64_t rows = ceil_div(p.m, low ? kTileRows<4> : kTM);
     if (rows > 65535) return PKV_ERR_SHAPE;
     const dim3 grid((unsigned)n_ct, (unsigned)rows);
-    if (mode == kF32Rope) hipLaunchKernelGGL(gemm_f32_kernel<kF32Rope>, grid, dim3(256), 0, st, p, tab);
-    else if (mode == kF32Plain)
-        hipLaunchKernelGGL(gemm_f32_kernel<kF32Plain>, grid, dim3(256), 0, st, p, tab);
-    else hipLaunchKernelGGL(gemm_f32_kernel<kF32Gated>, grid, dim3(256), 0, st, p, tab);
+#define PKV_GEMM_F32(MODE, KS) \
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE, KS>), grid, dim3(256), 0, st, p, tab)
+    if (mode == kF32Rope) PKV_GEMM_F32(kF32Rope, 1);
+    else if (mode == kF32Plain && low) PKV_GEMM_F32(kF32Plain, 4);
+    else if (mode == kF32Plain) PKV_GEMM_F32(kF32Plain, 1);
+    else if (low) PKV_GEMM_F32(kF32Gated, 4);
+    else PKV_GEMM_F32(kF32Gated, 1);
+#undef PKV_GEMM_F32
     return launch_status();
 }
 
@@ -496,6 +551,18 @@ bool linear_f32_supported(const void* x, const void* w0, const void* w1, const v
                           const void* y, int64_t m) {
     return ceil_div(m, kTM) <= 65535 && aligned16(x) && aligned16(w0) && aligned16(w1) &&
            aligned16(residual) && aligned16(y);
+}
+
+// us of a launch: a wave per output takes about 1e-4 + 2.2e-7 k_in per output (and, where the
+// weights no longer stay in a cache, 0.004 per input beyond 1024), the tiles 0.0083 per input
+// while they run at once.  Measured, wave per output against tiles of 16 rows: 256 x 512, 16 rows 3.5
+// / 4.4, 64 rows 7.4 / 4.4; 512 x 256, 64 rows 5.6 / 6.5, 110 rows 8.2 / 6.5; 1024 x 4096, 4 rows
+// 7.4 / 11.1, 16 rows 23 / 11; 4096 x 1024, 7 rows 21 / 36, 32 rows 74 / 36.
+bool linear_f32_pays(bool gated, int64_t m, int64_t k_in, int64_t n_out) {
+    const double k = (double)k_in;
+    const double per_output = (double)m * (double)n_out * (1.0e-4 + 2.2e-7 * k) +
+                              0.004 * std::max(0.0, k - 1024.0);
+    return per_output * (gated ? 2.0 : 1.0) >= 0.45 + 0.0083 * k;
 }
 
 pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,

@@ -286,7 +286,8 @@ pkv_status launch_linear_rows(int dtype, bool gated, const void* x, const void* 
         return launch_linear_dma(mode, (const bf16_t*)x, (const bf16_t*)w0, (const bf16_t*)w1,
                                  (const bf16_t*)residual, (bf16_t*)y, m, k_in, n_out, (float*)ws,
                                  st);
-    if (dtype == PKV_F32 && linear_f32_supported(x, w0, w1, residual, y, m)) {
+    if (dtype == PKV_F32 && linear_f32_supported(x, w0, w1, residual, y, m) &&
+        linear_f32_pays(gated, m, k_in, n_out)) {
         F32GemmParams p = {};
         p.x = (const float*)x;
         p.w[0] = (const float*)w0; p.w[1] = (const float*)w1;
