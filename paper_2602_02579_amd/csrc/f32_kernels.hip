@@ -15,7 +15,7 @@
 // indices 4 g .. 4 g + 3 of every 16 (one 16-byte load) and step j uses element j of all.
 //
 // Measured, 1024 context tokens, 16 query tokens, 4 heads of 64 (us, plain kernels -> these):
-// attention of 220 rows 105 -> 23, column sums 158 -> 5.7, normalisers 13 -> 4.3,
+// attention of 220 rows 105 -> 19, column sums 158 -> 5.7, normalisers 13 -> 4.3,
 // projection of 220 rows 34 -> 6.7; linear layers of 151 rows, 256 -> 512 gated 21 -> 5.9,
 // 512 -> 256 10.3 -> 6.5.
 #include <algorithm>
@@ -246,14 +246,16 @@ __device__ __forceinline__ float col_sum(float v) {
 // the head, so that a lane's piece of a value row is C = D / 16 consecutive floats (one element
 // per load instead took 16 loads per tile and as long as the multiplications).  K and V of the
 // next tile are requested before the current one is used.
+constexpr int kColRow = 17;   // the merge reads down the columns: 16 would be 16 lanes to a bank
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
     const int32_t* __restrict__ row_pos, float* __restrict__ out, float* __restrict__ lse_out,
     int m, int hq, int hkv, float scale) {
     constexpr int C = D / 16;
-    extern __shared__ __align__(16) float smem[];      // [NW][D][16] partial outputs
-    __shared__ float s_m[NW][16], s_l[NW][16];
+    extern __shared__ __align__(16) float smem[];      // [NW][D][16] partial outputs, rows of 17
+    __shared__ float s_m[NW][16], s_l[NW][16], s_f[NW][16], s_top[16];
+    __shared__ int s_out[16];   // (row, head) of a column, -1: none
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int g4 = lane >> 4, l16 = lane & 15;
@@ -327,26 +329,36 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     for (int c = 0; c < C; ++c)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            smem[(wave * D + C * (4 * g4 + r) + c) * 16 + l16] = o_acc[c][r];
+            smem[(wave * D + C * (4 * g4 + r) + c) * kColRow + l16] = o_acc[c][r];
     __syncthreads();
-    for (int e = tid; e < D * 16; e += NW * 64) {
-        const int cc = e / D, dd = e % D;
-        const int ecol = tile * 16 + cc;
-        const int erow = ecol / group;
-        if (erow >= m) break;                          // later elements have later columns
+    if (tid < NW * 16) {        // the weight of every wave's part
+        const int w = tid >> 4, cc = tid & 15;
         float mm = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_m[w][cc]);
+        for (int v = 0; v < NW; ++v) mm = fmaxf(mm, s_m[v][cc]);
+        s_f[w][cc] = expf(s_m[w][cc] - mm);
+        if (w == 0) {                                   // (this lane's own column: cc = l16)
+            s_top[cc] = mm;
+            s_out[cc] = valid ? row * hq + head : -1;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e0 = 0; e0 < D * 16; e0 += NW * 64) {
+        const int e = e0 + tid;
+        if (D * 16 % (NW * 64) && e >= D * 16) break;   // head_dim 32 on 16 waves
+        const int cc = e / D, dd = e % D;
+        const int64_t oc = s_out[cc];
+        if (oc < 0) continue;
         float acc = 0.f, l = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float f = expf(s_m[w][cc] - mm);
-            acc += f * smem[(w * D + dd) * 16 + cc];
+            const float f = s_f[w][cc];
+            acc += f * smem[(w * D + dd) * kColRow + cc];
             l += f * s_l[w][cc];
         }
-        const int64_t oc = (int64_t)erow * hq + g * group + ecol % group;
         out[oc * D + dd] = acc / l;
-        if (lse_out && dd == 0) lse_out[oc] = mm + logf(l);
+        if (lse_out && dd == 0) lse_out[oc] = s_top[cc] + logf(l);
     }
 }
 
@@ -506,7 +518,7 @@ template <int D, int NW>
 pkv_status attn_f32_launch(dim3 grid, const float* q, const float* k, const float* v,
                            const int32_t* row_pos, float* out, float* lse, int64_t m, int hq,
                            int hkv, float scale, hipStream_t st) {
-    constexpr size_t kBytes = (size_t)NW * D * 16 * sizeof(float);
+    constexpr size_t kBytes = (size_t)NW * D * kColRow * sizeof(float);
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, NW>),
@@ -567,13 +579,18 @@ bool linear_f32_pays(bool gated, int64_t m, int64_t k_in, int64_t n_out) {
 
 pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
                            const float* v, const int32_t* row_pos, float* out, float* lse,
-                           int64_t m, float scale, hipStream_t st) {
+                           int64_t m, int64_t n_keys, float scale, hipStream_t st) {
     const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads;
     const dim3 grid((unsigned)ceil_div(m * (hq / hkv), 16), (unsigned)hkv);
-    // as many waves as their registers allow: 16 up to head_dim 64, 8 with 128
-    if (cfg.head_dim == 32) return attn_f32_launch<32, 16>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
-    if (cfg.head_dim == 64) return attn_f32_launch<64, 16>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
-    return attn_f32_launch<128, 8>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st);
+    // as many waves as their registers allow: 16 up to head_dim 64, 8 with 128; four where that
+    // is a tile or two of keys each (head_dim 128: a tile), so that fewer parts have to be merged
+    const bool few = n_keys <= (cfg.head_dim == 128 ? 64 : 128);
+#define PKV_ATTN_F32(D, NW) \
+    attn_f32_launch<D, NW>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st)
+    if (cfg.head_dim == 32) return few ? PKV_ATTN_F32(32, 4) : PKV_ATTN_F32(32, 16);
+    if (cfg.head_dim == 64) return few ? PKV_ATTN_F32(64, 4) : PKV_ATTN_F32(64, 16);
+    return few ? PKV_ATTN_F32(128, 4) : PKV_ATTN_F32(128, 8);
+#undef PKV_ATTN_F32
 }
 
 F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {

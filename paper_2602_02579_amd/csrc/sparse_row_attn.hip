@@ -787,7 +787,7 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
     if (f32_tiles_supported(cfg) && ceil_div(m * (cfg.n_q_heads / cfg.n_kv_heads), 16) < (1 << 30) &&
         cfg.n_kv_heads <= 65535)
         return launch_attn_f32(cfg, (const float*)q, (const float*)k_cache, (const float*)v_cache,
-                               row_pos, (float*)out, lse_out, m, scale, st);
+                               row_pos, (float*)out, lse_out, m, n_keys, scale, st);
     const int block = d <= 64 ? 64 : (d <= 128 ? 128 : 256);
     const dim3 grid((unsigned)m, (unsigned)cfg.n_q_heads);
     if (cfg.dtype == PKV_BF16) {
