@@ -40,7 +40,9 @@ struct F32ScorePlan {
     int n_splits, split_len;
 };
 F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq);
-// lse null: both passes, ws holds n_splits * nq * hq float2; else pass 2 with these normalisers
+// a float per column, or with several splits two per split and column
+size_t score_f32_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq);
+// lse null: both passes, ws holds score_f32_ws_bytes; else pass 2 with these normalisers
 pkv_status launch_score_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
                             const float* lse, const int32_t* row_pos, float* score, int64_t nq,
                             int64_t n_ctx, float scale, int accumulate, void* ws,

@@ -365,10 +365,12 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
 // ---- query score ---------------------------------------------------------------------------------
 // Columns of a kv head are numbered (query token, head of the group), in tiles of 16.
 // Pass 1: per column the (maximum, sum) over a range of keys; four waves per workgroup take
-// every fourth tile of 16 keys and meet in LDS.
+// every fourth tile of 16 keys and meet in LDS.  With one range that is the column's normaliser,
+// and it goes out as such (lse, then part is not used).
 template <int D>
 __global__ __launch_bounds__(256) void score_part_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k, float2* __restrict__ part, int nq,
+    const float* __restrict__ q, const float* __restrict__ k, float2* __restrict__ part,
+    float* __restrict__ lse, int nq,
     int n_ctx, int hq, int hkv, int split_len, float scale) {
     constexpr int C = D / 16;
     __shared__ float s_m[4][16], s_l[4][16];
@@ -415,7 +417,8 @@ __global__ __launch_bounds__(256) void score_part_f32_kernel(
         float mm = -INFINITY, l = 0.f;
         for (int w = 0; w < 4; ++w) mm = fmaxf(mm, s_m[w][l16]);   // finite: the range has keys
         for (int w = 0; w < 4; ++w) l += s_l[w][l16] * expf(s_m[w][l16] - mm);
-        part[(int64_t)blockIdx.z * nq * hq + qcol] = make_float2(mm, l);
+        if (lse) lse[qcol] = mm + logf(l);
+        else part[(int64_t)blockIdx.z * nq * hq + qcol] = make_float2(mm, l);
     }
 }
 
@@ -594,8 +597,9 @@ pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float
 }
 
 F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {
-    // about one workgroup per CU; the fold at the head of pass 2 reads splits x columns values
-    // per workgroup, which is kept below 8192
+    // about one workgroup per CU; every workgroup of pass 2 folds splits x columns partial
+    // normalisers, 8192 at most (above that many columns there is one split, and nothing to fold:
+    // it reads the normalisers)
     const int group = cfg.n_q_heads / cfg.n_kv_heads;
     const int64_t tiles = ceil_div(nq * group, 16) * cfg.n_kv_heads;
     int64_t want = std::min(ceil_div(256, tiles), ceil_div(n_ctx, 64));
@@ -607,6 +611,11 @@ F32ScorePlan plan_score_f32(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq)
     return p;
 }
 
+size_t score_f32_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq) {
+    const int n_splits = plan_score_f32(cfg, n_ctx, nq).n_splits;
+    return (size_t)(nq * cfg.n_q_heads) * sizeof(float) * (n_splits == 1 ? 1 : 2 * n_splits);
+}
+
 pkv_status launch_score_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
                             const float* lse, const int32_t* row_pos, float* score, int64_t nq,
                             int64_t n_ctx, float scale, int accumulate, void* ws,
@@ -614,16 +623,17 @@ pkv_status launch_score_f32(const pkv_layer_cfg& cfg, const float* q, const floa
     const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads, d = cfg.head_dim;
     const F32ScorePlan p = plan_score_f32(cfg, n_ctx, nq);
     float2* part = (float2*)ws;
+    float* one = p.n_splits == 1 ? (float*)ws : nullptr;
     const dim3 g1((unsigned)ceil_div(nq * (hq / hkv), 16), (unsigned)hkv, (unsigned)p.n_splits);
     const dim3 g2((unsigned)ceil_div(n_ctx, 16));
 #define PKV_SCORE_F32(DD)                                                                   \
     {                                                                                       \
         if (!lse)                                                                           \
             hipLaunchKernelGGL(score_part_f32_kernel<DD>, g1, dim3(256), 0, st, q, k, part, \
-                               (int)nq, (int)n_ctx, hq, hkv, p.split_len, scale);           \
+                               one, (int)nq, (int)n_ctx, hq, hkv, p.split_len, scale);      \
         hipLaunchKernelGGL(score_sum_f32_kernel<DD>, g2, dim3(256), 0, st, q, k, part,      \
-                           p.n_splits, lse, row_pos, score, (int)nq, (int)n_ctx, hq, hkv,   \
-                           scale, accumulate);                                              \
+                           p.n_splits, lse ? lse : one, row_pos, score, (int)nq,            \
+                           (int)n_ctx, hq, hkv, scale, accumulate);                         \
     }
     if (d == 32) PKV_SCORE_F32(32)
     else if (d == 64) PKV_SCORE_F32(64)

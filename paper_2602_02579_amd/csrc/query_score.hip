@@ -332,8 +332,7 @@ size_t query_score_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_ctx, int64_t nq)
     if (nq <= 0) return 0;
     if (n_ctx < 1) n_ctx = 1;
     const size_t ncol = (size_t)(nq * cfg.n_q_heads);
-    if (f32_tiles_supported(cfg))
-        return (size_t)plan_score_f32(cfg, n_ctx, nq).n_splits * ncol * 2 * sizeof(float);
+    if (f32_tiles_supported(cfg)) return score_f32_ws_bytes(cfg, n_ctx, nq);
     if (!mfma_score_supported(cfg)) return ncol * sizeof(float);
     // the key-blocked kernels (other geometries, and the column sums with row limits)
     const SplitPlan sp = plan_splits(cfg, n_ctx, nq);
