@@ -40,10 +40,10 @@ if ROOT not in sys.path:
 from paper_2602_02579_amd import api, model, pipeline, synth  # noqa: E402
 
 PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA
-# HBM bytes per pkv_sparse_row_attn launch (its main kernel; the others move nothing), from the
-# FETCH_SIZE / WRITE_SIZE counter runs summarised in profiles/hot_path_cfg3_hbm_traffic.txt
+# HBM bytes per pkv_sparse_row_attn call (its main kernel 1.897e9, the V^T copy before it 0.135e9),
+# from the FETCH_SIZE / WRITE_SIZE counter runs summarised in profiles/hot_path_cfg3_hbm_traffic.txt
 # (counters cannot be read from inside this process; the figure is for that workload only)
-MEASURED_ATTN_TRAFFIC_BYTES = {"cfg3-llama8b-32k": 1.744e9}
+MEASURED_ATTN_TRAFFIC_BYTES = {"cfg3-llama8b-32k": 2.031e9}
 TRAFFIC_SOURCE = ("profiles/hot_path_cfg3_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / "
                   "WRITE_SIZE runs of this program, commands in the file; not read live)")
 PEAK_F32_TFLOPS = 157.3
@@ -694,8 +694,8 @@ def main():
                      "traffic": MEASURED_ATTN_TRAFFIC_BYTES.get(cfg.name),
                      "traffic_source": TRAFFIC_SOURCE,
                      "flops_per_launch": flops, "avg_launch_s": t_attn,
-                     "launch": "pkv_sparse_row_attn = a small first kernel (clears the work "
-                               "counters; at the larger sizes it also makes a V^T copy) + "
+                     "launch": "pkv_sparse_row_attn = a first kernel (a V^T copy that also clears the "
+                               "work counters; with fewer rows the clear alone) + "
                                "attn_w8n_kernel, timed with events on the launch stream"},
         "breakdown": breakdown,
     }

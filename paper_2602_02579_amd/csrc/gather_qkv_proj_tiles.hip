@@ -22,7 +22,9 @@
 // What bounds it: few rows stream the weights (64 rows x 28672 outputs x 4096: 235 MB in 45 us,
 // 5.2 TB/s, against 64 us on 256 x 256 tiles whose matrix work is three quarters padding); on a
 // small model the latency of one tile's chain of steps (256 rows x 1536 x 1024: 21 -> 8 us with
-// its finishing launch gone).  64 tokens: three stages of 24 KB, so that two workgroups share a
+// its finishing launch gone); hundreds of rows the operand bytes through L2, which a small tile
+// multiplies (512 rows x 4096 x 4096: 427 MB of L2 requests in 23 us, 71 bytes per ns and CU,
+// with the matrix pipe 27 % busy).  64 tokens: three stages of 24 KB, so that two workgroups share a
 // CU (six stages for one workgroup measured the same).  128 tokens: four stages of 32 KB and one
 // workgroup; two stages and two workgroups were 1 to 30 % slower below 700 rows.
 #include <atomic>

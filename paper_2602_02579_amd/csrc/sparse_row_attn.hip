@@ -8,7 +8,6 @@
 #include <atomic>
 #include <cstdlib>
 #include <functional>
-#include <functional>
 #include <mutex>
 #include <vector>
 
@@ -123,8 +122,9 @@ __global__ __launch_bounds__(256) void sparse_row_attn_generic(
 // The same kernel with PV switched off and the key range split over
 // blockIdx-encoded splits produces the per-column (max, sum) partials that
 // the query-score call needs for its normalisers.  For head_dim 128 the
-// attention proper runs in the software-pipelined kernel of
-// sparse_row_attn_dma.hip; this one serves head_dim 64 and the partials.
+// attention proper runs in the kernels of sparse_row_attn_w8.hip (jobs up to
+// one per CU), sparse_row_attn_w8n.hip (more jobs) and sparse_row_attn_short.hip
+// (short caches and few rows); this one serves head_dim 64 and the partials.
 // ---------------------------------------------------------------------------
 
 template <int D>
@@ -562,7 +562,10 @@ void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* 
         const int64_t steps_full = ceil_div(n_keys, 64);
         const double out_elems = (double)m * cfg.n_q_heads * cfg.head_dim;
         // a handful of rows are the user query, which sees the whole cache; thousands of rows
-        // are selected context rows, whose positions cannot help being spread
+        // are selected context rows, whose positions cannot help being spread.  The count that
+        // suits spread rows costs 700 to 1300 rows that all sit at the end of the cache 8 to
+        // 15 % (190 -> 218, 157 -> 172, 604 -> 650 us) and gives the same shapes with spread
+        // rows 10 to 26 % (152 -> 112, 113 -> 85, 416 -> 375 us)
         const double w_full = std::min(1.0, std::max(0.0, (768.0 - (double)m) / 640.0));
         double best = 1e30;
         for (int64_t sp = 1; sp <= most; ++sp) {

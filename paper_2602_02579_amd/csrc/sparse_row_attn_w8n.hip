@@ -15,8 +15,8 @@
 // only under the power limit, and only with the softmax arithmetic laid out by hand between
 // the two MFMAs of a pair: a wave that reaches the second one while the pipe is busy issues
 // nothing else.  6681 rows over 32k keys, whole call: 32x32x16 1513 us (72.5 % of the matrix
-// pipe at ~1.64 GHz); 16x16x32 in the compiler's order 1522 us (61 %); laid out 1455 us (65 %
-// at ~1.9 GHz).  1766 rows over 16k 260 -> 249 us, 26470 over 131k 21.9 -> 21.2 ms.  With one
+// pipe at ~1.64 GHz); 16x16x32 in the compiler's order 1522 us (61 %); laid out 1455 us (65
+// to 68 % at ~1.9 GHz).  1766 rows over 16k 260 -> 249 us, 26470 over 131k 21.9 -> 21.2 ms.  With one
 // job per CU, where the clock is not limited, it is the slower one (637 rows over 4k keys
 // in one range 84 -> 92 us): those launches keep attn_w8_kernel.
 //

@@ -506,11 +506,13 @@ def test_sparse_row_attn_closed_forms(gpu_device):
         assert np.abs(got[:, h] - vc[0, h // 4]).max() <= 2e-2 * np.abs(vc[0]).max()
 
 
-@pytest.mark.parametrize("n_keys", [700, 4500])   # 4500: the keys of a tile run as two ranges
+# 700 keys: the running maximum of the short-cache kernel with the values as the cache holds
+# them, the pipelined kernel on the transposed copy; 4500: the keys of a tile run as 18 ranges
+@pytest.mark.parametrize("n_keys", [700, 4500])
 def test_sparse_row_attn_scores_far_above_the_first_keys(gpu_device, n_keys, v_source):
     """Late keys whose scores exceed everything among a row's first 32 keys by
-    hundreds of nats: the fixed-reference fast path of the head_dim-128 kernel
-    cannot represent them and must hand the tile to the exact kernel."""
+    hundreds of nats: the fixed-reference first attempt of the pipelined head_dim-128
+    kernels cannot represent them, and the workgroup must do its job again."""
     dtype, hq, hkv, d, m = "bf16", 8, 2, 128, 150
     cfg = lcfg(dtype, hq, hkv, d)
     g = np.random.default_rng(31)

@@ -83,9 +83,9 @@ def test_context_lse_when_every_key_is_a_context_key(gpu_device, v_source):
     ctx_lse_case(gpu_device, 2048, 0, np.arange(2048 - 70, 2048), 720)
 
 
-def test_context_lse_through_the_exact_kernel(gpu_device, v_source):
-    """A key far above the reference of its column marks the tile; the exact kernel
-    redoes it and must cut its running sums at the context boundary too."""
+def test_context_lse_through_the_second_attempt(gpu_device, v_source):
+    """A key far above the reference of its column makes the workgroup do its job again;
+    the log-sum-exp of the context keys must come out of that attempt too."""
     n_ctx, qn = 2048, 64
     ctx_lse_case(gpu_device, n_ctx, qn, np.arange(n_ctx, n_ctx + qn), 730, q_scale=3.0,
                  spike=1500)
