@@ -4,10 +4,11 @@
 // v_mfma_f32_16x16x4_f32 multiplies and adds in fp32, so nothing is given up against plain
 // FMA kernels that sum in one chain (against the linear layers', which summed in parts, it is:
 // those take the fp64 instruction, see below); what is gained is that one instruction does 1024
-// multiply-adds without moving operands.  fp32 problems here are small (a 1k-token request is 0.2 GFLOP, 2 us of the fp32
-// matrix rate), so all of these kernels are bound by latency: the launch, and the chain of
-// memory round trips inside it.  Each is therefore cut so that a wave makes few round trips,
-// all operands of one requested together, and enough waves run at once to cover the chip.
+// multiply-adds without moving operands.  fp32 problems here are small (a 1k-token request is
+// 0.2 GFLOP, 2 us of the fp32 matrix rate), so all of these kernels are bound by latency: the
+// launch, and the chain of memory round trips inside it.  Each is therefore cut so that a wave
+// makes few round trips, all operands of one requested together, and enough waves run at once to
+// cover the chip.
 //
 // Operand layout of the instruction: A lane l holds row l % 16, contraction index l / 16; B
 // likewise with columns; the accumulator of lane l holds column l % 16, rows 4 (l / 16) + r.

@@ -475,8 +475,11 @@ constexpr int kPlanCus = 256;       // CUs that the plans reckon with
 // set-up worth `fixed` of them (pipeline fill, output; with ranges also the fp32 partials).  A
 // step takes longer the more CUs are busy (memory and the power limit): 1.2 us up to 130 of
 // them, 1.7 us with all 256.  The constants are fitted to 46 launches of 16 to 6681 rows over
-// 256 to 131k keys, each measured in up to 14 range counts (516 in all): the count chosen is
-// within 4 % of the best one everywhere but at 16 rows over 2k keys (19.7 against 18.3 us).
+// 256 to 131k keys, each measured in up to 14 range counts (516 in all), of which the count
+// chosen is within 4 % of the best one but at 16 rows over 2k keys (19.7 against 18.3 us).  Of 40
+// other shapes (700 to 1700 spread rows over 4k to 32k keys, 32 / 8 and 40 / 8 heads) it is within
+// 8 % on 35 and up to 18 % off at 700 to 1000 rows over 16k and 32k (40 / 8, 700 over 16k: 166
+// against 141 us).
 // *n_jobs: jobs that have keys to work on.
 double attn_launch_estimate(int64_t tiles, int hkv, int64_t steps_full, int sp, bool spread,
                             int n_cu, int64_t* n_jobs) {
@@ -562,10 +565,9 @@ void attn_plan_splits(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int* 
         const int64_t steps_full = ceil_div(n_keys, 64);
         const double out_elems = (double)m * cfg.n_q_heads * cfg.head_dim;
         // a handful of rows are the user query, which sees the whole cache; thousands of rows
-        // are selected context rows, whose positions cannot help being spread.  The count that
-        // suits spread rows costs 700 to 1300 rows that all sit at the end of the cache 8 to
-        // 15 % (190 -> 218, 157 -> 172, 604 -> 650 us) and gives the same shapes with spread
-        // rows 10 to 26 % (152 -> 112, 113 -> 85, 416 -> 375 us)
+        // are selected context rows, whose positions cannot help being spread.  No count serves
+        // both: 1300 rows over 8k keys, 32 / 8 heads, one range / two / three: spread 148 / 113 /
+        // 150 us, all at the end of the cache 163 / 216 / 188
         const double w_full = std::min(1.0, std::max(0.0, (768.0 - (double)m) / 640.0));
         double best = 1e30;
         for (int64_t sp = 1; sp <= most; ++sp) {
