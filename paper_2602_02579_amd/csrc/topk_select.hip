@@ -153,11 +153,11 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(
     }
 }
 
-// Keys of the kernel below: past the end of the vector 0, scores from 1 to 0xffdfffff (which
-// touches NaNs only).  So a key of 0 lies below every bin, also where it wraps: the largest bin is
-// 2^21 keys wide and ends short of 2^32.
+// Keys of the kernel below: past the end of the vector 0, of scores order_key, one higher below
+// zero: no score has the key that is free between the two halves, -0.0 being folded.
 __device__ __forceinline__ uint32_t inner_key(float x) {
-    return min(max(order_key(x), 1u), 0xffdfffffu);
+    const uint32_t u = __float_as_uint(x + 0.0f);
+    return (u & 0x80000000u) ? 0u - u : (u | 0x80000000u);
 }
 
 // Updates of one LDS counter by c lanes of an instruction take about 6 c cycles, so a key that many
@@ -266,7 +266,10 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
     }
 
     // ---- 2. lo = lower end of the bin with the k-th largest key, ever finer ----------------
-    uint32_t lo = mn + 1u, span = mx - lo;   // keys [lo, lo + span] are counted
+    // keys [lo, lo + span] are counted; no bin reaches beyond the largest key, so that a key of 0,
+    // which wraps to the far end too, lies in none
+    const uint32_t top = mx;
+    uint32_t lo = mn + 1u, span = top - lo;
     uint32_t rest = (uint32_t)k, cnt = 0u;
     int shift = span ? max(0, 32 - __clz(span) - kBits) : 0;
     for (;;) {
@@ -317,7 +320,7 @@ __global__ __launch_bounds__(kThreads) void topk_radix_kernel(
         // the whole bin is wanted: the selection is everything from lo on; or the bin is one
         // key wide and `rest` of its equals are wanted
         if (rest == cnt || shift == 0) break;
-        span = (1u << shift) - 1u;
+        span = min((1u << shift) - 1u, top - lo);
         if (cnt <= (uint32_t)n / 16u) {
             shift = max(0, shift - kBits);
             continue;
@@ -640,11 +643,11 @@ pkv_status launch_topk_select(const float* score, int64_t n, int64_t k,
     // the register kernels read 16 bytes at a time
     const bool aligned = (reinterpret_cast<uintptr_t>(score) & 15) == 0;
     // every pass walks over all register keys, so short vectors take the instantiation with
-    // the fewest keys per lane that holds them.  From 1000 to 32768 scores 4.9, 6.8 (4k), 7.2
-    // (8k), 9.2 (16k) and 14.4 us; the many-workgroup kernels take 17.5 at any length (with the
+    // the fewest keys per lane that holds them.  From 1000 to 32768 scores 4.9, 6.7 (4k), 7.1
+    // (8k), 9.1 (16k) and 13.9 us; the many-workgroup kernels take 17.5 at any length (with the
     // threshold built bit by bit 9, 10, 14, 15 and 26).  Scores that share a few values: 98 %
-    // zeros 7.6, 7.9, 8.0, 10.8 and 19.2 (many workgroups 21.5), 25 values 6.8, 7.9, 8.7, 12.2 and
-    // 21.9 (17.1; bit by bit 16, 16, 16, 22 and 33)
+    // zeros 7.6, 7.8, 8.0, 10.7 and 18.8 (many workgroups 21.5), 25 values 6.9, 7.8, 8.7, 12.2 and
+    // 21.5 (17.1; bit by bit 16, 16, 16, 22 and 33)
     if (aligned && n <= kOftenMin) {
         hipLaunchKernelGGL((topk_radix_kernel<8, false>), dim3(1), dim3(kThreads), 0, st, score,
                            (int)n, (int)k, idx_out);

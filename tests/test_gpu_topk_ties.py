@@ -1,6 +1,7 @@
 """The one-workgroup top-k on vectors many of whose scores share a value, everywhere or only in a
 part of the vector, and with thresholds in, just above and just below such a value: the indices
-against the oracle bit by bit.  And NaNs: no order is promised, but k different indices."""
+against the oracle bit by bit.  And NaNs: k different indices, in the order of their
+bits."""
 
 import numpy as np
 import pytest
@@ -53,3 +54,28 @@ def test_nan_scores_give_indices_of_the_vector(gpu_device, bits, n):
         got = idx.cpu().numpy()
         assert (got[k:] == -7).all()
         assert got[0] >= 0 and got[k - 1] < n and (np.diff(got[:k]) > 0).all()
+
+
+@pytest.mark.parametrize("n", [100, 5000, 32767])
+def test_nan_payloads_order_as_in_the_kernel_for_any_vector(gpu_device, n):
+    """NaNs of different bits are different keys, also at both ends of their range.  An address
+    that is no multiple of 16 takes the kernel for any vector."""
+    g = np.random.default_rng(n)
+    s = g.standard_normal(n).astype(np.float32)
+    bits = np.uint32([0x7fc00000, 0x7fdfffff, 0x7fe00000, 0x7ffffffe, 0x7fffffff,
+                      0xffc00000, 0xfffffffe, 0xffffffff])
+    at = g.random(n) < 0.6
+    s[at] = g.choice(bits, int(at.sum())).view(np.float32)
+    plain = torch.from_numpy(s).to(gpu_device)
+    moved = torch.empty(n + 1, dtype=torch.float32, device=gpu_device)[1:].copy_(plain)
+    assert plain.data_ptr() % 16 == 0 and moved.data_ptr() % 16 != 0
+    u = s.view(np.uint32).astype(np.int64)
+    keys = np.where(u & 0x80000000, u ^ 0xffffffff, u | 0x80000000)
+    for k in sorted({1, n // 20, n // 10, n // 5, n // 3, n // 2, (3 * n) // 4, n - 2, n}):
+        got = []
+        for score in (plain, moved):
+            idx = torch.empty(k, dtype=torch.int32, device=gpu_device)
+            api.pkv_topk_select(score, k, idx)
+            got.append(idx.cpu().numpy())
+        want = np.sort(np.lexsort((np.arange(n), -keys))[:k])
+        assert np.array_equal(got[0], want) and np.array_equal(got[1], want), k
