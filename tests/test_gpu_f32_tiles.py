@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 matrix-core kernels at the edges of their tiles: 64-row and 32-column
+"""GPU parity of the fp32 matrix-core kernels at the edges of their tiles: 64-row, 16-row and 32-column
 (16-pair) tiles and 128-wide contraction chunks of the projection and the linear layers, 16-key
 tiles and 16-column tiles of score and attention, fewer keys than waves, ranges of keys.
 
@@ -50,8 +50,12 @@ def test_projection(gpu_device, m, hq, hkv, d, hid):
     assert not host(kc)[rest].any() and not host(vc)[rest].any()
 
 
+# the first five are little work and take a wave per output, the next four tiles of 16 rows, the
+# last three tiles of 64
 @pytest.mark.parametrize("m,k,n", [(1, 8, 8), (63, 128, 24), (65, 136, 40), (64, 256, 72),
-                                   (17, 520, 104)])
+                                   (17, 520, 104), (130, 8, 72), (97, 24, 520), (64, 128, 264),
+                                   (321, 136, 200), (1025, 24, 520), (1088, 128, 512),
+                                   (1100, 520, 504)])
 def test_linear_layers(gpu_device, m, k, n):
     x, w, u = rnd(1, (m, k), "f32"), rnd(2, (n, k), "f32", k ** -0.5), rnd(3, (n, k), "f32", k ** -0.5)
     res = rnd(4, (m, n), "f32")
