@@ -310,6 +310,25 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg,
                                void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * Attention of rows inside their own chunks (paper: Sec. 2 - the method's input are chunks
+ * prefilled one by one).  The m rows, and the m cache rows, are consecutive chunks of
+ * chunk_len, the last one with what is left; row i attends the rows of its chunk up to
+ * row_pos[i], which is counted from the chunk's first row: pkv_sparse_row_attn chunk by
+ * chunk, in one launch where the chunks are short.  row_pos[i] must lie in [0, length of
+ * the chunk).  Scratch: pkv_chunk_attn_workspace_bytes.  m == 0 is a no-op.
+ */
+pkv_status pkv_chunk_attn(const pkv_layer_cfg* cfg,
+                          const void* q,          /* [m, Hq, D] */
+                          const void* k,          /* [m, Hkv, D] */
+                          const void* v,          /* [m, Hkv, D] */
+                          const int32_t* row_pos, /* [m] */
+                          void* out,              /* [m, Hq, D] */
+                          int64_t m, int64_t chunk_len, float softmax_scale,
+                          void* ws, size_t ws_bytes, void* stream);
+
+size_t pkv_chunk_attn_workspace_bytes(const pkv_layer_cfg* cfg, int64_t m, int64_t chunk_len);
+
+/*
  * Fused variants for the first stage (paper: Sec. 4.2 - the user query is run through
  * the model against the imprecise cache, and its attention to the context is the value
  * function; Algorithm 1, first stage).  The query rows' attention pass and the score

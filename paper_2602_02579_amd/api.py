@@ -23,7 +23,8 @@ __all__ = ["LayerCfg", "PkvError", "load_library", "library_path",
            "pkv_sparse_row_attn_ctx_lse_workspace_bytes",
            "pkv_topk_select", "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
            "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
-           "pkv_sparse_row_attn", "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
+           "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_chunk_attn_workspace_bytes",
+           "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
            "pkv_glue_workspace_bytes",
            "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
            "EXPORTED_SYMBOLS"]
@@ -39,7 +40,8 @@ EXPORTED_SYMBOLS = [
     "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex", "pkv_gather_qkv_proj_scatter",
     "pkv_scatter_kv", "pkv_sparse_row_attn", "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
     "pkv_glue_workspace_bytes", "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
-    "pkv_sparse_row_attn_ctx_lse_workspace_bytes",
+    "pkv_sparse_row_attn_ctx_lse_workspace_bytes", "pkv_chunk_attn",
+    "pkv_chunk_attn_workspace_bytes",
     "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
 ]
 
@@ -140,6 +142,10 @@ def load_library() -> ctypes.CDLL:
     lib.pkv_scatter_kv.argtypes = [cfgp, vp, vp, i32p, vp, vp, i64, i64, vp]
     lib.pkv_sparse_row_attn.argtypes = [cfgp, vp, vp, vp, i32p, vp, f32p, i64, i64,
                                         ctypes.c_float, vp, ctypes.c_size_t, vp]
+    lib.pkv_chunk_attn.argtypes = [cfgp, vp, vp, vp, i32p, vp, i64, i64, ctypes.c_float, vp,
+                                   ctypes.c_size_t, vp]
+    lib.pkv_chunk_attn_workspace_bytes.argtypes = [cfgp, i64, i64]
+    lib.pkv_chunk_attn_workspace_bytes.restype = ctypes.c_size_t
     i32 = ctypes.c_int32
     lib.pkv_rmsnorm_rows.argtypes = [i32, vp, i32p, vp, ctypes.c_float, vp, i64, i64, vp]
     lib.pkv_gather_rows.argtypes = [i32, vp, i32p, vp, i64, i64, vp]
@@ -153,8 +159,8 @@ def load_library() -> ctypes.CDLL:
                  "pkv_topk_select", "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
                  "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
                  "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
-                 "pkv_sparse_row_attn", "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows",
-                 "pkv_swiglu_rows"):
+                 "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_rmsnorm_rows", "pkv_gather_rows",
+                 "pkv_linear_rows", "pkv_swiglu_rows"):
         getattr(lib, name).restype = ctypes.c_int
     lib.pkv_workspace_bytes.argtypes = [ctypes.c_int, cfgp, i64, i64]
     lib.pkv_workspace_bytes.restype = ctypes.c_size_t
@@ -411,6 +417,26 @@ def pkv_sparse_row_attn(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.Tensor,
         cfg._ref, _ptr(q, dt, "q"), _ptr(k_cache, dt, "k_cache"),
         _ptr(v_cache, dt, "v_cache"), _ptr(row_pos, torch.int32, "row_pos"),
         _ptr(out, dt, "out"), _ptr(lse_out, torch.float32, "lse_out"), m, n_keys,
+        float(softmax_scale), wp, wb, _stream()))
+
+
+def pkv_chunk_attn_workspace_bytes(cfg: LayerCfg, m: int, chunk_len: int) -> int:
+    return int(load_library().pkv_chunk_attn_workspace_bytes(cfg._ref, int(m), int(chunk_len)))
+
+
+def pkv_chunk_attn(cfg: LayerCfg, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
+                   row_pos: torch.Tensor, out: torch.Tensor, chunk_len: int,
+                   softmax_scale: float = 0.0, ws: Optional[torch.Tensor] = None) -> None:
+    m = row_pos.shape[0]
+    dt = cfg.torch_dtype
+    if q.shape != (m, cfg.n_q_heads, cfg.head_dim) or out.shape != q.shape:
+        raise ValueError("q/out must be [m, Hq, D]")
+    if k.shape != (m, cfg.n_kv_heads, cfg.head_dim) or v.shape != k.shape:
+        raise ValueError("k/v must be [m, Hkv, D]")
+    wp, wb = _ws(ws)
+    _check("pkv_chunk_attn", load_library().pkv_chunk_attn(
+        cfg._ref, _ptr(q, dt, "q"), _ptr(k, dt, "k"), _ptr(v, dt, "v"),
+        _ptr(row_pos, torch.int32, "row_pos"), _ptr(out, dt, "out"), m, int(chunk_len),
         float(softmax_scale), wp, wb, _stream()))
 
 

@@ -28,6 +28,8 @@ struct AttnParams {
     int dma_splits, dma_split_len;   // key ranges per row tile in the pipelined kernel
     int m, n_keys, n_pad, hq, hkv, group, bm, n_tiles, n_splits, split_len;
     int fixed_limit;         // >= 0: every row sees keys 0..fixed_limit
+    int n_chunks, chunk_len; // sparse_row_attn_short.hip, n_chunks > 1: the m rows and the m keys
+                             // are runs of chunk_len, each attending within itself
     float scale_log2;        // softmax scale * log2(e)
     float scale;
 };
@@ -46,6 +48,8 @@ pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st);
 // what the pipelined kernel would cut the keys into
 bool attn_short_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int n_splits);
 pkv_status launch_attn_short(AttnParams p, hipStream_t st);
+// most keys of a chunk that the same kernel takes when many chunks share a launch
+constexpr int kShortChunk = 1024;
 // compute units of the current device (0: could not be asked)
 int attn_cu_count();
 // Where the pipelined kernel can take the values from: 1 = from a V^T copy made by a pre-pass

@@ -34,7 +34,9 @@ bool linear_f32_pays(bool gated, int64_t m, int64_t k_in, int64_t n_out);
 bool f32_tiles_supported(const pkv_layer_cfg& cfg);
 pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
                            const float* v, const int32_t* row_pos, float* out, float* lse,
-                           int64_t m, int64_t n_keys, float scale, hipStream_t st);
+                           int64_t m, int64_t n_keys, float scale, hipStream_t st,
+                           int64_t chunk_len = 0);   // > 0: rows and keys are runs of that
+                                                     // length, each attending within itself
 
 struct F32ScorePlan {
     int n_splits, split_len;

@@ -252,7 +252,7 @@ template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
     const int32_t* __restrict__ row_pos, float* __restrict__ out, float* __restrict__ lse_out,
-    int m, int hq, int hkv, float scale) {
+    int m_all, int hq, int hkv, float scale, int chunk_len) {
     constexpr int C = D / 16;
     extern __shared__ __align__(16) float smem[];      // [NW][D][16] partial outputs, rows of 17
     __shared__ float s_m[NW][16], s_l[NW][16], s_f[NW][16], s_top[16];
@@ -262,8 +262,11 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     const int g4 = lane >> 4, l16 = lane & 15;
     const int g = blockIdx.y, group = hq / hkv;
     const int tile = gridDim.x - 1 - blockIdx.x;       // rows in position order: heavy ones first
+    // rows and keys of chunk blockIdx.z start at row0 (one chunk: the keys are a cache of their own)
+    const int row0 = (int)blockIdx.z * chunk_len;
+    const int m = min(m_all, row0 + chunk_len);
     const int col = tile * 16 + l16;
-    const int row = col / group, head = g * group + col % group;
+    const int row = row0 + col / group, head = g * group + col % group;
     const bool valid = row < m;
     const int limit = valid ? row_pos[row] : -1;
     int last = limit;
@@ -273,8 +276,8 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     f32x4 q4[C];
     load_row<D>(q4, q + ((int64_t)(valid ? row : 0) * hq + head) * D, g4);
     const int64_t krow = (int64_t)hkv * D;
-    const float* kb = kc + (int64_t)g * D;
-    const float* vb = vc + (int64_t)g * D + C * l16;
+    const float* kb = kc + row0 * krow + (int64_t)g * D;
+    const float* vb = vc + row0 * krow + (int64_t)g * D + C * l16;
     typedef float vrow_t __attribute__((ext_vector_type(C)));
     f32x4 k4[C], kn[C], o_acc[C];
     vrow_t v4[4], vn[4];
@@ -521,7 +524,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 template <int D, int NW>
 pkv_status attn_f32_launch(dim3 grid, const float* q, const float* k, const float* v,
                            const int32_t* row_pos, float* out, float* lse, int64_t m, int hq,
-                           int hkv, float scale, hipStream_t st) {
+                           int hkv, float scale, int chunk_len, hipStream_t st) {
     constexpr size_t kBytes = (size_t)NW * D * kColRow * sizeof(float);
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
@@ -532,7 +535,7 @@ pkv_status attn_f32_launch(dim3 grid, const float* q, const float* k, const floa
         configured.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL((attn_f32_kernel<D, NW>), grid, dim3(NW * 64), kBytes, st, q, k, v, row_pos,
-                       out, lse, (int)m, hq, hkv, scale);
+                       out, lse, (int)m, hq, hkv, scale, chunk_len);
     return launch_status();
 }
 
@@ -583,14 +586,17 @@ bool linear_f32_pays(bool gated, int64_t m, int64_t k_in, int64_t n_out) {
 
 pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float* k,
                            const float* v, const int32_t* row_pos, float* out, float* lse,
-                           int64_t m, int64_t n_keys, float scale, hipStream_t st) {
+                           int64_t m, int64_t n_keys, float scale, hipStream_t st,
+                           int64_t chunk_len) {
     const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads;
-    const dim3 grid((unsigned)ceil_div(m * (hq / hkv), 16), (unsigned)hkv);
+    if (chunk_len <= 0) chunk_len = m;
+    const dim3 grid((unsigned)ceil_div(chunk_len * (hq / hkv), 16), (unsigned)hkv,
+                    (unsigned)ceil_div(m, chunk_len));
     // as many waves as their registers allow: 16 up to head_dim 64, 8 with 128; four where that
     // is a tile or two of keys each (head_dim 128: a tile), so that fewer parts have to be merged
     const bool few = n_keys <= (cfg.head_dim == 128 ? 64 : 128);
 #define PKV_ATTN_F32(D, NW) \
-    attn_f32_launch<D, NW>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, st)
+    attn_f32_launch<D, NW>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, (int)chunk_len, st)
     if (cfg.head_dim == 32) return few ? PKV_ATTN_F32(32, 4) : PKV_ATTN_F32(32, 16);
     if (cfg.head_dim == 64) return few ? PKV_ATTN_F32(64, 4) : PKV_ATTN_F32(64, 16);
     return few ? PKV_ATTN_F32(128, 4) : PKV_ATTN_F32(128, 8);

@@ -2,6 +2,7 @@
 // launchers.  Nothing here touches device memory or synchronises.
 #include "pkv_common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -187,6 +188,35 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg, const void* q,
     return launch_sparse_row_attn(*cfg, q, k_cache, v_cache, row_pos, out, lse_out, m,
                                   n_keys, resolve_scale(softmax_scale, cfg->head_dim),
                                   ws, (hipStream_t)stream);
+}
+
+pkv_status pkv_chunk_attn(const pkv_layer_cfg* cfg, const void* q, const void* k, const void* v,
+                          const int32_t* row_pos, void* out, int64_t m, int64_t chunk_len,
+                          float softmax_scale, void* ws, size_t ws_bytes, void* stream) {
+    pkv_status st = check_cfg(cfg);
+    if (st != PKV_OK) return st;
+    if (m < 0 || m > kMaxTokens || chunk_len <= 0 || chunk_len > kMaxTokens) return PKV_ERR_SHAPE;
+    // as pkv_sparse_row_attn, for the longest chunk
+    if (cfg->dtype == PKV_BF16 &&
+        (int64_t)cfg->head_dim * ((std::min(m, chunk_len) + 63) / 64 * 64) * 2 >=
+            ((int64_t)1 << 32))
+        return PKV_ERR_UNSUPPORTED;
+    if (m * (int64_t)cfg->n_q_heads > INT32_MAX) return PKV_ERR_UNSUPPORTED;
+    if (m == 0) return PKV_OK;
+    if (!q || !k || !v || !row_pos || !out) return PKV_ERR_NULL;
+    if (!std::isfinite(softmax_scale) || softmax_scale < 0.f) return PKV_ERR_SHAPE;
+    const size_t need = align256(chunk_attn_ws_bytes(*cfg, m, chunk_len));
+    if (need && (!ws || ws_bytes < need)) return PKV_ERR_WORKSPACE;
+    return launch_chunk_attn(*cfg, q, k, v, row_pos, out, m, chunk_len,
+                             resolve_scale(softmax_scale, cfg->head_dim), ws,
+                             (hipStream_t)stream);
+}
+
+size_t pkv_chunk_attn_workspace_bytes(const pkv_layer_cfg* cfg, int64_t m, int64_t chunk_len) {
+    if (check_cfg(cfg) != PKV_OK || m <= 0 || chunk_len <= 0 || m > kMaxTokens ||
+        chunk_len > kMaxTokens)
+        return 0;
+    return align256(chunk_attn_ws_bytes(*cfg, m, chunk_len));
 }
 
 pkv_status pkv_sparse_row_attn_ctx_lse(const pkv_layer_cfg* cfg, const void* q,

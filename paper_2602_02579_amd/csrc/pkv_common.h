@@ -116,6 +116,11 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                                   float scale, void* ws, hipStream_t st,
                                   int64_t ctx_keys = 0, float* lse_ctx_out = nullptr);
 
+size_t chunk_attn_ws_bytes(const pkv_layer_cfg& cfg, int64_t m, int64_t chunk_len);
+pkv_status launch_chunk_attn(const pkv_layer_cfg& cfg, const void* q, const void* k,
+                             const void* v, const int32_t* row_pos, void* out, int64_t m,
+                             int64_t chunk_len, float scale, void* ws, hipStream_t st);
+
 // layer glue (layer_glue.hip); dtype is a pkv_dtype
 pkv_status launch_rmsnorm_rows(int dtype, const void* h, const int32_t* row_idx,
                                const void* weight, float eps, void* y, int64_t m,

@@ -809,4 +809,61 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
     return launch_status();
 }
 
+// The rows of chunk_len tokens each, every chunk through its own keys.  Chunks of a document are
+// alike and small (a chunk of 256 tokens makes 16 to 64 jobs for 256 CUs), so they share a launch
+// where a kernel takes them by a grid of chunks; others go one by one.
+bool chunk_attn_batched(const pkv_layer_cfg& cfg, int64_t m, int64_t chunk_len) {
+    if (m <= chunk_len) return false;
+    const int group = cfg.n_q_heads / cfg.n_kv_heads;
+    if (mfma_attn_supported(cfg))
+        return cfg.head_dim == 128 && chunk_len <= kShortChunk && attn_dma128_v_source() <= 0;
+    // the rules of the fp32 kernel, and chunks in the third dimension of its grid
+    return f32_tiles_supported(cfg) && ceil_div(chunk_len * group, 16) < (1 << 30) &&
+           cfg.n_kv_heads <= 65535 && ceil_div(m, chunk_len) <= 65535;
+}
+
+size_t chunk_attn_ws_bytes(const pkv_layer_cfg& cfg, int64_t m, int64_t chunk_len) {
+    const int64_t one = std::min(m, chunk_len), tail = m % chunk_len;
+    return std::max(sparse_row_attn_ws_bytes(cfg, one, one),
+                    tail ? sparse_row_attn_ws_bytes(cfg, tail, tail) : 0);
+}
+
+pkv_status launch_chunk_attn(const pkv_layer_cfg& cfg, const void* q, const void* k,
+                             const void* v, const int32_t* row_pos, void* out, int64_t m,
+                             int64_t chunk_len, float scale, void* ws, hipStream_t st) {
+    if (chunk_attn_batched(cfg, m, chunk_len)) {
+        if (cfg.dtype == PKV_F32)
+            return launch_attn_f32(cfg, (const float*)q, (const float*)k, (const float*)v, row_pos,
+                                   (float*)out, nullptr, m, chunk_len, scale, st, chunk_len);
+        AttnParams p = {};
+        p.q = (const bf16_t*)q;
+        p.k = (const bf16_t*)k;
+        p.v = (const bf16_t*)v;
+        p.row_pos = row_pos;
+        p.out = (bf16_t*)out;
+        p.m = (int)m;
+        p.n_keys = (int)m;
+        p.hq = cfg.n_q_heads;
+        p.hkv = cfg.n_kv_heads;
+        p.group = cfg.n_q_heads / cfg.n_kv_heads;
+        p.n_chunks = (int)ceil_div(m, chunk_len);
+        p.chunk_len = (int)chunk_len;
+        p.scale = scale;
+        p.scale_log2 = scale * 1.4426950408889634f;
+        return launch_attn_short(p, st);
+    }
+    const size_t elt = cfg.dtype == PKV_F32 ? 4 : 2;
+    const size_t q_row = (size_t)cfg.n_q_heads * cfg.head_dim * elt;
+    const size_t kv_row = (size_t)cfg.n_kv_heads * cfg.head_dim * elt;
+    for (int64_t a = 0; a < m; a += chunk_len) {
+        const int64_t rows = std::min(chunk_len, m - a);
+        const pkv_status s = launch_sparse_row_attn(
+            cfg, (const char*)q + a * q_row, (const char*)k + a * kv_row,
+            (const char*)v + a * kv_row, row_pos + a, (char*)out + a * q_row, nullptr, rows, rows,
+            scale, ws, st);
+        if (s != PKV_OK) return s;
+    }
+    return PKV_OK;
+}
+
 }  // namespace pkv

@@ -12,6 +12,12 @@
 // Arithmetic and LDS layouts are those of sparse_row_attn_w8.hip:
 //     S^T = K Q^T,   O^T += V^T P^T     (v_mfma_f32_32x32x16_bf16)
 // with value rows as the cache holds them, transposed by the LDS read.
+//
+// Many chunks of one document share a launch (pkv_chunk_attn): a job is then a tile of one
+// chunk, the tiles that see most keys first over all chunks.  A launch per chunk -> one for all
+// (32 / 8 heads, us): 8 chunks of 64 keys 64 -> 18, 8 of 256 83 -> 26, 4 of 512 62 -> 30, 8 of 1024
+// (two jobs per CU each, which took the pipelined kernels one by one) 204 -> 136; the same at 40 / 8
+// and 8 / 2 heads and up to 64 chunks, so every chunk length of this kernel shares.
 #include <atomic>
 
 #include "attn_common.h"
@@ -60,7 +66,14 @@ __global__ __launch_bounds__(kThreads) void attn_short_kernel(AttnParams p) {
     const int half = wave >> 2, cw = wave & 3;   // key half, column block
     const int hh = lane >> 5, l32 = lane & 31;
     const int g = blockIdx.x % p.hkv;
-    const int tile = p.n_tiles - 1 - (int)(blockIdx.x / p.hkv);   // the longer ones first
+    // the longer tiles first; rows and keys of a chunk start at row0
+    int job = (int)(blockIdx.x / p.hkv), row0 = 0, n_rows = p.m, n_keys = p.n_keys;
+    if (p.n_chunks > 1) {
+        row0 = job % p.n_chunks * p.chunk_len;
+        job /= p.n_chunks;
+        n_rows = n_keys = min(p.chunk_len, p.m - row0);
+    }
+    const int tile = p.n_tiles - 1 - job;
 
     // ---- global -> LDS: this wave fills rows 16 cw .. + 16 of its half's key tile ----------
     // K row r at byte r*256, 16-byte chunk c at c ^ (r & 15); V row r likewise at c ^ (4 (r & 3))
@@ -72,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void attn_short_kernel(AttnParams p) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 16 * cw + 4 * i + (lane >> 4);
-            const int64_t off = (int64_t)min(key0 + r, p.n_keys - 1) * row_elems + g * D;
+            const int64_t off = (int64_t)(row0 + min(key0 + r, n_keys - 1)) * row_elems + g * D;
             const uint32_t dst = lds_fill + (pair & 1) * kPair + i * 1024;
             dma16(p.k + off + ((lane & 15) ^ (r & 15)) * 8, dst);
             dma16(p.v + off + ((lane & 15) ^ (4 * (r & 3))) * 8, dst + kTileBytes);
@@ -83,10 +96,10 @@ __global__ __launch_bounds__(kThreads) void attn_short_kernel(AttnParams p) {
     // ---- this lane's column ---------------------------------------------------------------
     const int col = cw * 32 + l32;
     const int rl = col / p.group;
-    const int row = tile * p.bm + rl;
+    const int row_in = tile * p.bm + rl, row = row0 + row_in;
     const int head = g * p.group + col % p.group;
-    const bool valid = rl < p.bm && row < p.m;
-    const int limit = valid ? min(p.row_pos[row], p.n_keys - 1) : -1;
+    const bool valid = rl < p.bm && row_in < n_rows;
+    const int limit = valid ? min(p.row_pos[row], n_keys - 1) : -1;
     bf16x8 qreg[KC];
     {
         const bf16_t* qp = p.q + ((int64_t)row * p.hq + head) * D + hh * 8;
@@ -269,9 +282,10 @@ pkv_status launch_attn_short(AttnParams p, hipStream_t st) {
         configured.store(true, std::memory_order_release);
     }
     p.bm = kCols / p.group;
-    p.n_tiles = (int)ceil_div(p.m, p.bm);
-    hipLaunchKernelGGL(attn_short_kernel, dim3((unsigned)(p.n_tiles * p.hkv)), dim3(kThreads),
-                       kLdsBytes, st, p);
+    p.n_tiles = (int)ceil_div(p.n_chunks > 1 ? p.chunk_len : p.m, p.bm);
+    const int64_t grid = (int64_t)p.n_tiles * p.hkv * (p.n_chunks > 1 ? p.n_chunks : 1);
+    if (grid > INT32_MAX) return PKV_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(attn_short_kernel, dim3((unsigned)grid), dim3(kThreads), kLdsBytes, st, p);
     return launch_status();
 }
 

@@ -94,10 +94,11 @@ class CarriedRows:
 
     # one decoder layer for the first ``cnt`` rows of the buffers, at positions ``rows``;
     # caches_only: its normalisation and K/V projection, nothing of the rows themselves;
-    # scores_only: up to the scores
+    # scores_only: up to the scores; chunks = (rows of the caches, chunk length): the rows are
+    # all of the caches, in chunks that attend within themselves, ``rows`` counting inside them
     def _layer(self, L: Dict[str, torch.Tensor], rows: torch.Tensor, cnt: int,
                score: Optional[bool], caches_only: bool = False,
-               scores_only: bool = False) -> None:
+               scores_only: bool = False, chunks=None) -> None:
         lc, ws = self.lc, self.ws
         h, x = self.h[:cnt], self.x[:cnt]
         q = self.q[:cnt]
@@ -108,12 +109,15 @@ class CarriedRows:
         # rows' own keys (stored behind the context) do not touch.
         api.pkv_gather_qkv_proj_scatter(lc, x, None, rows, L["wq"], L["wk"], L["wv"],
                                         None if caches_only else q,
-                                        L["k_cache"], L["v_cache"], rows, ws=ws,
+                                        L["k_cache"], L["v_cache"],
+                                        rows if chunks is None else chunks[0], ws=ws,
                                         norm_eps=self.eps,
                                         **{v: L[v] for v in VARIANT_WEIGHTS if v in L})
         if caches_only:
             return
-        if score is not None and self.fuse_stage1:
+        if chunks is not None:
+            api.pkv_chunk_attn(lc, q, L["k_cache"], L["v_cache"], rows, attn, chunks[1], ws=ws)
+        elif score is not None and self.fuse_stage1:
             api.pkv_sparse_row_attn_ctx_lse(lc, q, L["k_cache"], L["v_cache"], rows, attn, None,
                                             self.lse_ctx[:cnt], self.n, ws=ws)
             api.pkv_query_score_lse(lc, q, L["k_cache"][:self.n], self.lse_ctx[:cnt], None,
@@ -172,14 +176,10 @@ class CarriedRows:
         self._stage2(embed, layers)
         return self.h[:self.m]
 
-    # caches_only: nobody reads the rows' final hidden states - the last layer stops at its
-    # cache rows
-    def _stage2(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]],
-                caches_only: bool = False) -> None:
+    def _stage2(self, embed: torch.Tensor, layers: List[Dict[str, torch.Tensor]]) -> None:
         api.pkv_gather_rows(embed, self.rows, self.h[:self.m])
-        for li, L in enumerate(layers):
-            self._layer(L, self.rows, self.m, score=None,
-                        caches_only=caches_only and li == len(layers) - 1)
+        for L in layers:
+            self._layer(L, self.rows, self.m, score=None)
 
     def run(self, embed, layers, n_score_layers: Optional[int] = None) -> torch.Tensor:
         self._stage1(embed, layers, n_score_layers, keep_rows=False)
