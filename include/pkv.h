@@ -480,6 +480,41 @@ pkv_status pkv_swiglu_rows(int32_t dtype,
 size_t pkv_glue_workspace_bytes(int32_t dtype, int64_t m, int64_t k_in,
                                 int64_t n_out);
 
+/*
+ * A whole decoder layer for the carried rows in one call: the calls above in the order that
+ * their comments give, with the same checks, rounding points and no-op rules -
+ *     x = rmsnorm(h, w_in);  Q, and K/V into rows dst_row of the caches
+ *     [score; attention of the rows]
+ *     h += a Wo^T;  x = rmsnorm(h, w_post);  g = swiglu(x);  h += g Wd^T.
+ * A model's layers are tens of small launches, and a caller in an interpreted language spends
+ * more on marshalling each than the launch costs.  `call` is a HOST struct read during the
+ * call.  The first call that fails ends it with its status; what was enqueued before stays.
+ *   score == NULL:     no score.
+ *   lse_ctx == NULL:   pkv_query_score over cache rows 0 .. n_ctx - 1, then the attention;
+ *   otherwise:         pkv_sparse_row_attn_ctx_lse with it, then pkv_query_score_lse.
+ *   chunk_len == 0:    pkv_sparse_row_attn over the n_cache rows of the caches;
+ *   otherwise:         pkv_chunk_attn (m rows, m == n_cache, score must be NULL).
+ *   stop:              what is left out - nothing, everything behind the attention and the
+ *                      score, or everything behind the caches (q is then not written).
+ */
+enum { PKV_LAYER_WHOLE = 0, PKV_LAYER_TO_SCORES = 1, PKV_LAYER_TO_CACHES = 2 };
+
+typedef struct {
+    void *h, *x, *q, *attn, *g;   /* [m, hidden] twice, [m, Hq, D] twice, [m, inter] */
+    const int32_t *row_pos, *dst_row;                  /* [m] */
+    const void *w_in, *wq, *wk, *wv, *wo, *w_post, *w_gate, *w_up, *w_down;
+    pkv_proj_variant variant;     /* its norm_eps is not used: eps is */
+    void *k_cache, *v_cache;      /* [n_cache, Hkv, D] */
+    float *score, *lse_ctx;       /* [n_ctx], [m, Hq] or NULL */
+    void* ws;
+    size_t ws_bytes;
+    int64_t m, n_cache, n_ctx, inter, chunk_len;
+    float eps;
+    int32_t accumulate, stop;
+} pkv_layer_call;
+
+pkv_status pkv_layer_rows(const pkv_layer_cfg* cfg, const pkv_layer_call* call, void* stream);
+
 /* Static, never-NULL description of a status code. */
 const char* pkv_status_string(pkv_status status);
 

@@ -25,7 +25,7 @@ __all__ = ["LayerCfg", "PkvError", "load_library", "library_path",
            "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
            "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_chunk_attn_workspace_bytes",
            "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
-           "pkv_glue_workspace_bytes",
+           "LayerCall", "pkv_layer_rows", "pkv_glue_workspace_bytes",
            "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
            "EXPORTED_SYMBOLS"]
 
@@ -41,7 +41,7 @@ EXPORTED_SYMBOLS = [
     "pkv_scatter_kv", "pkv_sparse_row_attn", "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
     "pkv_glue_workspace_bytes", "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
     "pkv_sparse_row_attn_ctx_lse_workspace_bytes", "pkv_chunk_attn",
-    "pkv_chunk_attn_workspace_bytes",
+    "pkv_chunk_attn_workspace_bytes", "pkv_layer_rows",
     "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
 ]
 
@@ -56,6 +56,21 @@ class _CVariant(ctypes.Structure):
     _fields_ = [("bq", ctypes.c_void_p), ("bk", ctypes.c_void_p), ("bv", ctypes.c_void_p),
                 ("q_norm", ctypes.c_void_p), ("k_norm", ctypes.c_void_p),
                 ("norm_eps", ctypes.c_float)]
+
+
+LAYER_WHOLE, LAYER_TO_SCORES, LAYER_TO_CACHES = 0, 1, 2
+
+
+class LayerCall(ctypes.Structure):
+    """``pkv_layer_call``: raw pointers, for one call of ``pkv_layer_rows``."""
+    _fields_ = [(name, ctypes.c_void_p) for name in (
+        "h", "x", "q", "attn", "g", "row_pos", "dst_row", "w_in", "wq", "wk", "wv", "wo",
+        "w_post", "w_gate", "w_up", "w_down")] + [
+        ("variant", _CVariant), ("k_cache", ctypes.c_void_p), ("v_cache", ctypes.c_void_p),
+        ("score", ctypes.c_void_p), ("lse_ctx", ctypes.c_void_p), ("ws", ctypes.c_void_p),
+        ("ws_bytes", ctypes.c_size_t)] + [
+        (name, ctypes.c_int64) for name in ("m", "n_cache", "n_ctx", "inter", "chunk_len")] + [
+        ("eps", ctypes.c_float), ("accumulate", ctypes.c_int32), ("stop", ctypes.c_int32)]
 
 
 class _CCfg(ctypes.Structure):
@@ -144,6 +159,7 @@ def load_library() -> ctypes.CDLL:
                                         ctypes.c_float, vp, ctypes.c_size_t, vp]
     lib.pkv_chunk_attn.argtypes = [cfgp, vp, vp, vp, i32p, vp, i64, i64, ctypes.c_float, vp,
                                    ctypes.c_size_t, vp]
+    lib.pkv_layer_rows.argtypes = [cfgp, ctypes.POINTER(LayerCall), vp]
     lib.pkv_chunk_attn_workspace_bytes.argtypes = [cfgp, i64, i64]
     lib.pkv_chunk_attn_workspace_bytes.restype = ctypes.c_size_t
     i32 = ctypes.c_int32
@@ -160,7 +176,7 @@ def load_library() -> ctypes.CDLL:
                  "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
                  "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
                  "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_rmsnorm_rows", "pkv_gather_rows",
-                 "pkv_linear_rows", "pkv_swiglu_rows"):
+                 "pkv_linear_rows", "pkv_swiglu_rows", "pkv_layer_rows"):
         getattr(lib, name).restype = ctypes.c_int
     lib.pkv_workspace_bytes.argtypes = [ctypes.c_int, cfgp, i64, i64]
     lib.pkv_workspace_bytes.restype = ctypes.c_size_t
@@ -560,3 +576,55 @@ def pkv_swiglu_rows(x: torch.Tensor, w_gate: torch.Tensor, w_up: torch.Tensor,
     _check("pkv_swiglu_rows", load_library().pkv_swiglu_rows(
         _dtype_code(x), _ptr(x, dt, "x"), _ptr(w_gate, dt, "w_gate"), _ptr(w_up, dt, "w_up"),
         _ptr(y, dt, "y"), m, k_in, n_out, wp, wb, _stream()))
+
+
+def pkv_layer_rows(cfg: LayerCfg, h: torch.Tensor, x: torch.Tensor, q: torch.Tensor,
+                   attn: torch.Tensor, g: torch.Tensor, m: int, weights, variant,
+                   k_cache: torch.Tensor, v_cache: torch.Tensor, row_pos: torch.Tensor,
+                   dst_row: torch.Tensor, eps: float, ws: torch.Tensor, *,
+                   score: Optional[torch.Tensor] = None,
+                   lse_ctx: Optional[torch.Tensor] = None, n_ctx: int = 0,
+                   accumulate: bool = False, chunk_len: int = 0,
+                   stop: int = LAYER_WHOLE) -> None:
+    """One decoder layer for the first ``m`` rows of the buffers ``h, x, q, attn, g``.
+    ``weights`` maps the nine weight names to tensors, and the names ``variant`` of block variants
+    that it also holds."""
+    hid, hq, hkv, d = cfg.hidden, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim
+    inter, n_cache = g.shape[-1], k_cache.shape[0]
+    dt = cfg.torch_dtype
+    c = LayerCall()
+
+    def put(obj, name, t, shape, dtype, rows=None):
+        # rows: the first of a buffer that may hold more
+        if (t.shape if rows is None else (min(rows, t.shape[0]), *t.shape[1:])) != shape:
+            raise ValueError(f"{name} must be {list(shape)}, got {list(t.shape)}")
+        setattr(obj, name, _ptr(t, dtype, name))
+    put(c, "h", h, (m, hid), dt, m)
+    put(c, "x", x, (m, hid), dt, m)
+    put(c, "q", q, (m, hq, d), dt, m)
+    put(c, "attn", attn, (m, hq, d), dt, m)
+    put(c, "g", g, (m, inter), dt, m)
+    put(c, "row_pos", row_pos, (m,), torch.int32)
+    put(c, "dst_row", dst_row, (m,), torch.int32)
+    put(c, "k_cache", k_cache, (n_cache, hkv, d), dt)
+    put(c, "v_cache", v_cache, (n_cache, hkv, d), dt)
+    shapes = {"w_in": (hid,), "wq": (hq * d, hid), "wk": (hkv * d, hid), "wv": (hkv * d, hid)}
+    if stop == LAYER_WHOLE:
+        shapes.update(wo=(hid, hq * d), w_post=(hid,), w_gate=(inter, hid), w_up=(inter, hid),
+                      w_down=(hid, inter))
+    for name, shape in shapes.items():
+        put(c, name, weights[name], shape, dt)
+    for name in variant:
+        if weights.get(name) is not None:
+            heads = hq if name == "bq" else hkv
+            put(c.variant, name, weights[name], (d,) if "norm" in name else (heads * d,), dt)
+    if score is not None:
+        put(c, "score", score, (n_ctx,), torch.float32)
+        if n_ctx > n_cache:
+            raise ValueError("the caches hold fewer than n_ctx rows")
+        if lse_ctx is not None:
+            put(c, "lse_ctx", lse_ctx, (m, hq), torch.float32, m)
+    c.ws, c.ws_bytes = _ws(ws)
+    c.m, c.n_cache, c.n_ctx, c.inter, c.chunk_len = m, n_cache, n_ctx, inter, chunk_len
+    c.eps, c.accumulate, c.stop = eps, bool(accumulate), stop
+    _check("pkv_layer_rows", load_library().pkv_layer_rows(cfg._ref, ctypes.byref(c), _stream()))

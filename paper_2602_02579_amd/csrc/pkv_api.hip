@@ -308,6 +308,54 @@ pkv_status pkv_swiglu_rows(int32_t dtype, const void* x, const void* w_gate, con
                           ws_bytes, stream);
 }
 
+pkv_status pkv_layer_rows(const pkv_layer_cfg* cfg, const pkv_layer_call* call, void* stream) {
+    pkv_status st = check_cfg(cfg);
+    if (st != PKV_OK) return st;
+    if (!call) return PKV_ERR_NULL;
+    const pkv_layer_call& c = *call;
+    if (c.stop < PKV_LAYER_WHOLE || c.stop > PKV_LAYER_TO_CACHES || c.chunk_len < 0)
+        return PKV_ERR_SHAPE;
+    if (c.chunk_len && (c.score || c.m != c.n_cache)) return PKV_ERR_SHAPE;
+    const int32_t dt = cfg->dtype;
+    const int64_t hid = cfg->hidden, q_row = (int64_t)cfg->n_q_heads * cfg->head_dim;
+    pkv_proj_variant var = c.variant;
+    var.norm_eps = c.eps;
+#define PKV_TRY(EXPR) \
+    if ((st = (EXPR)) != PKV_OK) return st
+    PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_in, c.eps, c.x, c.m, hid, stream));
+    PKV_TRY(pkv_gather_qkv_proj_scatter(
+        cfg, c.x, nullptr, c.row_pos, c.wq, c.wk, c.wv, &var,
+        c.stop == PKV_LAYER_TO_CACHES ? nullptr : c.q, c.k_cache, c.v_cache, c.dst_row, c.m,
+        c.n_cache, c.ws, c.ws_bytes, stream));
+    if (c.stop == PKV_LAYER_TO_CACHES) return PKV_OK;
+    if (c.chunk_len) {
+        PKV_TRY(pkv_chunk_attn(cfg, c.q, c.k_cache, c.v_cache, c.row_pos, c.attn, c.m,
+                               c.chunk_len, 0.f, c.ws, c.ws_bytes, stream));
+    } else if (c.score && c.lse_ctx) {
+        PKV_TRY(pkv_sparse_row_attn_ctx_lse(cfg, c.q, c.k_cache, c.v_cache, c.row_pos, c.attn,
+                                            nullptr, c.lse_ctx, c.m, c.n_cache, c.n_ctx, 0.f,
+                                            c.ws, c.ws_bytes, stream));
+        PKV_TRY(pkv_query_score_lse(cfg, c.q, c.k_cache, c.lse_ctx, nullptr, c.score, c.m,
+                                    c.n_ctx, 0.f, c.accumulate, c.ws, c.ws_bytes, stream));
+    } else {
+        if (c.score)
+            PKV_TRY(pkv_query_score(cfg, c.q, c.k_cache, c.score, c.m, c.n_ctx, 0.f,
+                                    c.accumulate, c.ws, c.ws_bytes, stream));
+        PKV_TRY(pkv_sparse_row_attn(cfg, c.q, c.k_cache, c.v_cache, c.row_pos, c.attn, nullptr,
+                                    c.m, c.n_cache, 0.f, c.ws, c.ws_bytes, stream));
+    }
+    if (c.stop == PKV_LAYER_TO_SCORES) return PKV_OK;
+    PKV_TRY(pkv_linear_rows(dt, c.attn, c.wo, c.h, c.h, c.m, q_row, hid, c.ws, c.ws_bytes,
+                            stream));
+    PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_post, c.eps, c.x, c.m, hid, stream));
+    PKV_TRY(pkv_swiglu_rows(dt, c.x, c.w_gate, c.w_up, c.g, c.m, hid, c.inter, c.ws, c.ws_bytes,
+                            stream));
+    PKV_TRY(pkv_linear_rows(dt, c.g, c.w_down, c.h, c.h, c.m, c.inter, hid, c.ws, c.ws_bytes,
+                            stream));
+#undef PKV_TRY
+    return PKV_OK;
+}
+
 size_t pkv_glue_workspace_bytes(int32_t dtype, int64_t m, int64_t k_in, int64_t n_out) {
     if ((dtype != PKV_F32 && dtype != PKV_BF16) || m <= 0 || k_in <= 0 || n_out <= 0 ||
         m > kMaxTokens || k_in > kMaxTokens || n_out > kMaxTokens)

@@ -99,41 +99,18 @@ class CarriedRows:
     def _layer(self, L: Dict[str, torch.Tensor], rows: torch.Tensor, cnt: int,
                score: Optional[bool], caches_only: bool = False,
                scores_only: bool = False, chunks=None) -> None:
-        lc, ws = self.lc, self.ws
-        h, x = self.h[:cnt], self.x[:cnt]
-        q = self.q[:cnt]
-        attn, g = self.attn[:cnt], self.g[:cnt]
-        api.pkv_rmsnorm_rows(h, None, L["w_in"], self.eps, x)
-        # Q/K/V of the rows; K and V go straight to their cache rows (steps 4a + 4b).  The
-        # score of Stage I reads only the context rows of the key cache, which the query
-        # rows' own keys (stored behind the context) do not touch.
-        api.pkv_gather_qkv_proj_scatter(lc, x, None, rows, L["wq"], L["wk"], L["wv"],
-                                        None if caches_only else q,
-                                        L["k_cache"], L["v_cache"],
-                                        rows if chunks is None else chunks[0], ws=ws,
-                                        norm_eps=self.eps,
-                                        **{v: L[v] for v in VARIANT_WEIGHTS if v in L})
-        if caches_only:
-            return
-        if chunks is not None:
-            api.pkv_chunk_attn(lc, q, L["k_cache"], L["v_cache"], rows, attn, chunks[1], ws=ws)
-        elif score is not None and self.fuse_stage1:
-            api.pkv_sparse_row_attn_ctx_lse(lc, q, L["k_cache"], L["v_cache"], rows, attn, None,
-                                            self.lse_ctx[:cnt], self.n, ws=ws)
-            api.pkv_query_score_lse(lc, q, L["k_cache"][:self.n], self.lse_ctx[:cnt], None,
-                                    self.score, accumulate=score, ws=ws)
-        else:
-            if score is not None:
-                api.pkv_query_score(lc, q, L["k_cache"][:self.n], self.score,
-                                    accumulate=score, ws=ws)
-            api.pkv_sparse_row_attn(lc, q, L["k_cache"], L["v_cache"], rows, attn, None,
-                                    ws=ws)
-        if scores_only:
-            return
-        api.pkv_linear_rows(attn.view(cnt, -1), L["wo"], h, h, ws=ws)
-        api.pkv_rmsnorm_rows(h, None, L["w_post"], self.eps, x)
-        api.pkv_swiglu_rows(x, L["w_gate"], L["w_up"], g, ws=ws)
-        api.pkv_linear_rows(g, L["w_down"], h, h, ws=ws)
+        # K and V go straight to their cache rows.  The score of Stage I reads only the context
+        # rows of the key cache, which the query rows' own keys (stored behind the context) do
+        # not touch.
+        fused = score is not None and self.fuse_stage1 and chunks is None
+        api.pkv_layer_rows(
+            self.lc, self.h, self.x, self.q, self.attn, self.g, cnt, L, VARIANT_WEIGHTS,
+            L["k_cache"], L["v_cache"], rows, rows if chunks is None else chunks[0], self.eps,
+            self.ws, score=None if score is None else self.score,
+            lse_ctx=self.lse_ctx if fused else None, n_ctx=self.n, accumulate=bool(score),
+            chunk_len=0 if chunks is None else chunks[1],
+            stop=api.LAYER_TO_CACHES if caches_only else
+            api.LAYER_TO_SCORES if scores_only else api.LAYER_WHOLE)
 
     # the last scoring layer where only its scores are wanted: queries and both passes of the
     # score, which cost less than the attention that would spare one of them
