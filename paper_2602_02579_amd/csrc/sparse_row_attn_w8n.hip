@@ -122,32 +122,39 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
     const int g4 = lane >> 4;    // key octet of a 32-key sub-step this lane holds scores of
     const int l16 = lane & 15;   // its column in each of the wave's two 16-column blocks
 
-    // Work distribution: one workgroup per CU claims (kv head, row tile[, key range]) jobs,
-    // heaviest first, from one counter per kv head; it prefers its home head (whose K/V its
-    // XCD's L2 holds) unless another head is kStealLag or more jobs behind.
+    // Work distribution: one workgroup per CU takes (kv head, row tile[, key range]) jobs,
+    // heaviest first.  Its first one goes by its own number (256 workgroups at eight counters
+    // took 4 to 5 us to claim them: 1702 rows over 8k keys 132 -> 128 us); further ones it claims from one counter per kv head,
+    // preferring its home head (whose K/V its XCD's L2 holds) unless another head is kStealLag or
+    // more jobs behind.
     const int home = blockIdx.x % p.hkv;
     const int jobs_per_head = p.n_tiles * p.dma_splits;
-  for (;;) {
+    // jobs of head h that went by number, and those claimed
+    auto taken = [&](int h) {
+        return ((int)gridDim.x - h + p.hkv - 1) / p.hkv +
+               __hip_atomic_load(&p.queue[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+  for (bool first = true;; first = false) {
     if (tid == 0) {
-        int job = -1;
+        // (the grid is no larger than the number of jobs, so there is one)
+        int job = first ? home * jobs_per_head + (int)(blockIdx.x / p.hkv) : -1;
         // at most hkv failed claims: each one finds a head exhausted for good
         for (int attempt = 0; attempt <= p.hkv && job < 0; ++attempt) {
             int best = home;
-            int best_c = __hip_atomic_load(&p.queue[home], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
+            int best_c = taken(home);
             if (best_c < jobs_per_head) best_c -= kStealLag;
             for (int q = 1; q < p.hkv; ++q) {
                 int y = home + q;
                 if (y >= p.hkv) y -= p.hkv;
-                const int c = __hip_atomic_load(&p.queue[y], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
+                const int c = taken(y);
                 if (c < best_c) {
                     best_c = c;
                     best = y;
                 }
             }
             if (best_c >= jobs_per_head) break;   // nothing left anywhere
-            const int j = atomicAdd(&p.queue[best], 1);
+            const int j = ((int)gridDim.x - best + p.hkv - 1) / p.hkv +
+                          atomicAdd(&p.queue[best], 1);
             if (j < jobs_per_head) job = best * jobs_per_head + j;
         }
         s_job = job;
