@@ -48,17 +48,19 @@ __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<
 constexpr int kTM = 64, kTN = 32, kTK = 128;
 constexpr int kRow = kTK + 4;
 
-// Sums.  The projection sums in fp32, one product behind the other, as the plain kernel did, with
-// the same error.  The plain linear layers summed 64 interleaved parts and then these in a tree:
+// Sums.  The projection sums in fp32, one product behind the other in each of its KS parts of the
+// contraction (3e-7 off the fp64 result at 256 inputs with one, 1.5e-7 with four).  The plain linear layers summed 64 interleaved parts and then these in a tree:
 // 0.6 to 1.2e-7 off the fp64 result (2-norm, 64 to 4096 inputs), where one chain is 0.9 to 8.4e-7
 // off.  So they sum in fp64 here (v_mfma_f64_16x16x4_f64, at half the rate; products of fp32 are
 // exact in it) and round once: 0.3e-7 at any length.  Its accumulator register r of lane group g is
 // row g + 4 r, not 4 g + r, so the weight rows go in permuted and the outputs come out alike.
 //
-// KS = 4, for linear layers whose tiles then all run at once: a tile of 16 rows whose four waves
-// share the contraction and meet in LDS - four times the workgroups, a quarter of the chain
-// (151 rows, 256 -> 512: 8.5 us with KS = 1, 4.4 with 4; 400 rows, 512 -> 1024: 14.8 and 14.1; above
-// 1024 tiles of 16 rows the higher tiles' better use of the weights wins).
+// KS = 4, where all tiles then run at once: a tile of 16 rows whose four waves share the
+// contraction and meet in LDS - four times the workgroups, a quarter of the chain (linear layers,
+// 151 rows, 256 -> 512: 8.5 us with KS = 1, 4.4 with 4; 400 rows, 512 -> 1024: 14.8 and 14.1;
+// projection, 4 heads of 64, 256 inputs: 16 rows 6.4 and 4.4, 220 rows 6.7 and 5.3; 8 heads of 64,
+// 1024 inputs, 64 rows: 16.5 and 8.3; above 1024 tiles of 16 rows the higher tiles' better use of
+// the weights wins).
 template <int KS>
 constexpr int kTileRows = kTM / KS;
 
@@ -550,14 +552,15 @@ pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& ta
     int n_ct;
     if (mode == kF32Rope) n_ct = p.tile_begin[3];
     else n_ct = (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
-    // a linear layer whose tiles of 16 rows all run at once (four workgroups per CU)
-    const bool low = mode != kF32Rope && ceil_div(p.m, kTileRows<4>) * n_ct <= 1024;
+    // tiles of 16 rows that all run at once (four workgroups per CU)
+    const bool low = ceil_div(p.m, kTileRows<4>) * n_ct <= 1024;
     const int64_t rows = ceil_div(p.m, low ? kTileRows<4> : kTM);
     if (rows > 65535) return PKV_ERR_SHAPE;
     const dim3 grid((unsigned)n_ct, (unsigned)rows);
 #define PKV_GEMM_F32(MODE, KS) \
     hipLaunchKernelGGL((gemm_f32_kernel<MODE, KS>), grid, dim3(256), 0, st, p, tab)
-    if (mode == kF32Rope) PKV_GEMM_F32(kF32Rope, 1);
+    if (mode == kF32Rope && low) PKV_GEMM_F32(kF32Rope, 4);
+    else if (mode == kF32Rope) PKV_GEMM_F32(kF32Rope, 1);
     else if (mode == kF32Plain && low) PKV_GEMM_F32(kF32Plain, 4);
     else if (mode == kF32Plain) PKV_GEMM_F32(kF32Plain, 1);
     else if (low) PKV_GEMM_F32(kF32Gated, 4);
