@@ -21,6 +21,9 @@ struct F32GemmParams {
     const int32_t* row_pos;    // [m]
     const int32_t* dst_row;    // [m] or null: rows of K and V
     const float* bias[3];      // or null
+    // projection and gated: gains [k] of an RMS norm of the rows of x before the product, or null
+    const float* norm_w;
+    float norm_eps;
 };
 pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& tab,
                            hipStream_t st);

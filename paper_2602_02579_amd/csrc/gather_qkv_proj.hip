@@ -7,6 +7,8 @@
 // out[i, head, :] = R(row_pos[i]) (W_head x_i),  x_i = hidden[row_idx[i]]
 // for the Hq query heads, the Hkv key heads, and (without R) the Hkv value
 // heads; fp32 accumulation; one rounding after the rotation.
+#include <cmath>
+
 #include "f32_kernels.h"
 #include "proj_common.h"
 
@@ -284,6 +286,30 @@ bool mfma_proj_supported(const pkv_layer_cfg& cfg) {
     return cfg.head_dim == 64 && cfg.n_q_heads % 2 == 0 && cfg.n_kv_heads % 2 == 0;
 }
 
+F32GemmParams f32_proj_params(const pkv_layer_cfg& cfg, const void* hidden, const int32_t* row_idx,
+                              const int32_t* row_pos, const void* wq, const void* wk,
+                              const void* wv, const ProjExtra& ex, const int32_t* dst_row,
+                              void* q_out, void* k_out, void* v_out, int64_t m) {
+    const int hq = cfg.n_q_heads, hkv = cfg.n_kv_heads;
+    F32GemmParams p = {};
+    p.x = (const float*)hidden;
+    p.row_idx = row_idx;
+    p.w[0] = (const float*)wq; p.w[1] = (const float*)wk; p.w[2] = (const float*)wv;
+    p.out[0] = (float*)q_out; p.out[1] = (float*)k_out; p.out[2] = (float*)v_out;
+    p.m = (int)m; p.k = cfg.hidden;
+    p.hq = hq; p.hkv = hkv; p.d = cfg.head_dim;
+    p.row_pos = row_pos;
+    p.dst_row = dst_row;
+    for (int i = 0; i < 3; ++i) p.bias[i] = (const float*)ex.bias[i];
+    const int tq = q_out ? (int)ceil_div(hq * cfg.head_dim / 2, 16) : 0;
+    const int tkv = k_out ? (int)ceil_div(hkv * cfg.head_dim / 2, 16) : 0;
+    p.tile_begin[0] = 0;
+    p.tile_begin[1] = tq;
+    p.tile_begin[2] = tq + tkv;
+    p.tile_begin[3] = tq + 2 * tkv;
+    return p;
+}
+
 }  // namespace
 
 void launch_rope_table(const int32_t* row_pos, int64_t m, int half, const RopeTable& tab,
@@ -361,23 +387,10 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
     // fp32: the matrix-core kernel, unless heads are normalised (that needs whole heads) or the
     // row count exceeds the grid
     if (cfg.dtype == PKV_F32 && !ex.gain[0] && !ex.gain[1] && ceil_div(m, 64) <= 65535) {
-        F32GemmParams p = {};
-        p.x = (const float*)hidden;
-        p.row_idx = row_idx;
-        p.w[0] = (const float*)wq; p.w[1] = (const float*)wk; p.w[2] = (const float*)wv;
-        p.out[0] = (float*)q_out; p.out[1] = (float*)k_out; p.out[2] = (float*)v_out;
-        p.m = (int)m; p.k = cfg.hidden;
-        p.hq = hq; p.hkv = hkv; p.d = cfg.head_dim;
-        p.row_pos = row_pos;
-        p.dst_row = dst_row;
-        for (int i = 0; i < 3; ++i) p.bias[i] = (const float*)ex.bias[i];
-        const int tq = q_out ? (int)ceil_div(hq * cfg.head_dim / 2, 16) : 0;
-        const int tkv = k_out ? (int)ceil_div(hkv * cfg.head_dim / 2, 16) : 0;
-        p.tile_begin[0] = 0;
-        p.tile_begin[1] = tq;
-        p.tile_begin[2] = tq + tkv;
-        p.tile_begin[3] = tq + 2 * tkv;
-        return launch_gemm_f32(kF32Rope, p, tab, st);
+        return launch_gemm_f32(kF32Rope,
+                               f32_proj_params(cfg, hidden, row_idx, row_pos, wq, wk, wv, ex, dst_row,
+                                               q_out, k_out, v_out, m),
+                               tab, st);
     }
     const dim3 grid((unsigned)ceil_div(m, 16), (unsigned)(hq + 2 * hkv));
     if (cfg.dtype == PKV_BF16) {
@@ -394,6 +407,30 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
                            hkv, cfg.head_dim, cfg.hidden, tab, ex);
     }
     return launch_status();
+}
+
+bool norm_proj_f32(const pkv_layer_cfg& cfg, const void* hidden, const void* norm_w, float eps,
+                   const int32_t* row_pos, const void* wq, const void* wk, const void* wv,
+                   const pkv_proj_variant* var, const int32_t* dst_row, void* q_out, void* k_out,
+                   void* v_out, int64_t m, hipStream_t st, pkv_status* status) {
+    // what the two calls refuse goes to them, as do heads that are normalised
+    auto bad = [](const void* q) { return !q || (reinterpret_cast<uintptr_t>(q) & 15) != 0; };
+    if (cfg.dtype != PKV_F32 || m <= 0 || ceil_div(m, 64) > 65535 || cfg.hidden > 16384 ||
+        !(eps >= 0.f) || !std::isfinite(eps) || bad(hidden) || bad(norm_w) || !row_pos || !wk ||
+        !wv || !k_out || !v_out || !dst_row || (q_out && !wq) || (var && (var->q_norm || var->k_norm)))
+        return false;
+    ProjExtra ex = {};
+    if (var) {
+        ex.bias[0] = var->bq; ex.bias[1] = var->bk; ex.bias[2] = var->bv;
+    }
+    RopeTable tab;
+    fill_rope_table(&tab, cfg.head_dim, (double)cfg.rope_theta);
+    F32GemmParams p = f32_proj_params(cfg, hidden, nullptr, row_pos, wq, wk, wv, ex, dst_row,
+                                      q_out, k_out, v_out, m);
+    p.norm_w = (const float*)norm_w;
+    p.norm_eps = eps;
+    *status = launch_gemm_f32(kF32Rope, p, tab, st);
+    return true;
 }
 
 }  // namespace pkv

@@ -8,6 +8,8 @@
 // Q/K/V projection with a different epilogue (gather_qkv_proj_dma.hip), fp32 ones on the fp32
 // matrix-core kernel (f32_kernels.hip); everything else (odd bf16 sizes, unaligned pointers)
 // takes the simple kernels below, one wave per output element.
+#include <cmath>
+
 #include "f32_kernels.h"
 #include "proj_common.h"
 
@@ -299,6 +301,27 @@ pkv_status launch_linear_rows(int dtype, bool gated, const void* x, const void* 
     return dtype == PKV_BF16
                ? linear_simple<bf16_t>(gated, x, w0, w1, residual, y, m, k_in, n_out, st)
                : linear_simple<float>(gated, x, w0, w1, residual, y, m, k_in, n_out, st);
+}
+
+bool norm_swiglu_f32(const void* x, const void* norm_w, float eps, const void* w_gate,
+                     const void* w_up, void* y, int64_t m, int64_t k_in, int64_t n_out,
+                     hipStream_t st, pkv_status* status) {
+    // what the two calls refuse goes to them; few rows over many inputs have the wave per output,
+    // which is the faster one there by more than the launch that is saved
+    if (m <= 0 || k_in <= 0 || n_out <= 0 || k_in % 8 || n_out % 8 || k_in > 16384 ||
+        n_out > (1 << 30) || !(eps >= 0.f) || !std::isfinite(eps) || !x || !norm_w || !w_gate ||
+        !w_up || !y || !aligned16(norm_w) || !linear_f32_supported(x, w_gate, w_up, nullptr, y, m) ||
+        !(k_in <= 512 || linear_f32_pays(true, m, k_in, n_out)))
+        return false;
+    F32GemmParams p = {};
+    p.x = (const float*)x;
+    p.w[0] = (const float*)w_gate; p.w[1] = (const float*)w_up;
+    p.out[0] = (float*)y;
+    p.m = (int)m; p.k = (int)k_in; p.n_out = (int)n_out;
+    p.norm_w = (const float*)norm_w;
+    p.norm_eps = eps;
+    *status = launch_gemm_f32(kF32Gated, p, RopeTable{}, st);
+    return true;
 }
 
 }  // namespace pkv

@@ -322,11 +322,19 @@ pkv_status pkv_layer_rows(const pkv_layer_cfg* cfg, const pkv_layer_call* call, 
     var.norm_eps = c.eps;
 #define PKV_TRY(EXPR) \
     if ((st = (EXPR)) != PKV_OK) return st
-    PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_in, c.eps, c.x, c.m, hid, stream));
-    PKV_TRY(pkv_gather_qkv_proj_scatter(
-        cfg, c.x, nullptr, c.row_pos, c.wq, c.wk, c.wv, &var,
-        c.stop == PKV_LAYER_TO_CACHES ? nullptr : c.q, c.k_cache, c.v_cache, c.dst_row, c.m,
-        c.n_cache, c.ws, c.ws_bytes, stream));
+    void* const q = c.stop == PKV_LAYER_TO_CACHES ? nullptr : c.q;
+    const bool x_ok = c.x && (reinterpret_cast<uintptr_t>(c.x) & 15) == 0;   // else refused below
+    if (c.m > 0 && c.m <= c.n_cache && c.n_cache <= kMaxTokens && x_ok &&
+        (q || c.stop == PKV_LAYER_TO_CACHES) &&
+        norm_proj_f32(*cfg, c.h, c.w_in, c.eps, c.row_pos, c.wq, c.wk, c.wv, &var, c.dst_row, q,
+                      c.k_cache, c.v_cache, c.m, (hipStream_t)stream, &st)) {
+        if (st != PKV_OK) return st;
+    } else {
+        PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_in, c.eps, c.x, c.m, hid, stream));
+        PKV_TRY(pkv_gather_qkv_proj_scatter(cfg, c.x, nullptr, c.row_pos, c.wq, c.wk, c.wv, &var, q,
+                                            c.k_cache, c.v_cache, c.dst_row, c.m, c.n_cache, c.ws,
+                                            c.ws_bytes, stream));
+    }
     if (c.stop == PKV_LAYER_TO_CACHES) return PKV_OK;
     if (c.chunk_len) {
         PKV_TRY(pkv_chunk_attn(cfg, c.q, c.k_cache, c.v_cache, c.row_pos, c.attn, c.m,
@@ -347,9 +355,15 @@ pkv_status pkv_layer_rows(const pkv_layer_cfg* cfg, const pkv_layer_call* call, 
     if (c.stop == PKV_LAYER_TO_SCORES) return PKV_OK;
     PKV_TRY(pkv_linear_rows(dt, c.attn, c.wo, c.h, c.h, c.m, q_row, hid, c.ws, c.ws_bytes,
                             stream));
-    PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_post, c.eps, c.x, c.m, hid, stream));
-    PKV_TRY(pkv_swiglu_rows(dt, c.x, c.w_gate, c.w_up, c.g, c.m, hid, c.inter, c.ws, c.ws_bytes,
-                            stream));
+    if (dt == PKV_F32 && x_ok &&
+        norm_swiglu_f32(c.h, c.w_post, c.eps, c.w_gate, c.w_up, c.g, c.m, hid, c.inter,
+                        (hipStream_t)stream, &st)) {
+        if (st != PKV_OK) return st;
+    } else {
+        PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_post, c.eps, c.x, c.m, hid, stream));
+        PKV_TRY(pkv_swiglu_rows(dt, c.x, c.w_gate, c.w_up, c.g, c.m, hid, c.inter, c.ws,
+                                c.ws_bytes, stream));
+    }
     PKV_TRY(pkv_linear_rows(dt, c.g, c.w_down, c.h, c.h, c.m, c.inter, hid, c.ws, c.ws_bytes,
                             stream));
 #undef PKV_TRY

