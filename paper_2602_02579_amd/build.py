@@ -23,7 +23,7 @@ SOURCES = ["pkv_api.hip", "rope_restore.hip", "query_score.hip", "query_score_dm
            "gather_qkv_proj_tiles.hip", "scatter_kv.hip", "layer_glue.hip",
            "static_scratch.hip", "f32_kernels.hip",
            "sparse_row_attn.hip", "sparse_row_attn_dma.hip", "sparse_row_attn_w8.hip",
-           "sparse_row_attn_w8n.hip", "sparse_row_attn_short.hip"]
+           "sparse_row_attn_w8n.hip", "sparse_row_attn_pair.hip", "sparse_row_attn_short.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -37,6 +37,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 SOURCE_FLAGS = {
     "sparse_row_attn_w8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "sparse_row_attn_w8n.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "sparse_row_attn_pair.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "sparse_row_attn_short.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "query_score_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "gather_qkv_proj_tiles.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],

@@ -50,6 +50,9 @@ bool attn_short_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int
 pkv_status launch_attn_short(AttnParams p, hipStream_t st);
 // most keys of a chunk that the same kernel takes when many chunks share a launch
 constexpr int kShortChunk = 1024;
+// sparse_row_attn_pair.hip: jobs of 128 columns whose two groups of waves share the keys
+bool attn_pair_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m);
+pkv_status launch_attn_pair(AttnParams p, hipStream_t st);
 // compute units of the current device (0: could not be asked)
 int attn_cu_count();
 // Where the pipelined kernel can take the values from: 1 = from a V^T copy made by a pre-pass

@@ -123,8 +123,8 @@ __global__ __launch_bounds__(256) void sparse_row_attn_generic(
 // blockIdx-encoded splits produces the per-column (max, sum) partials that
 // the query-score call needs for its normalisers.  For head_dim 128 the
 // attention proper runs in the kernels of sparse_row_attn_w8.hip (jobs up to
-// one per CU), sparse_row_attn_w8n.hip (more jobs) and sparse_row_attn_short.hip
-// (short caches and few rows); this one serves head_dim 64 and the partials.
+// one per CU), sparse_row_attn_w8n.hip (more jobs), sparse_row_attn_pair.hip (a few
+// thousand keys) and sparse_row_attn_short.hip (short caches and few rows); this one serves head_dim 64 and the partials.
 // ---------------------------------------------------------------------------
 
 template <int D>
@@ -743,8 +743,10 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                 nat_v = src == 0;
             }
         }
+        const bool pair_job = d == 128 && nat_v && !short_job && !lse_ctx_out &&
+                              attn_pair_applies(cfg, n_keys, m);
         if (nat_v) {
-            if (queue && !short_job)
+            if (queue && !short_job && !pair_job)
                 hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue,
                                    cfg.n_kv_heads);
         } else {
@@ -777,6 +779,7 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         p.scale_log2 = scale * 1.4426950408889634f;
         if (d != 128) return launch_attn_mfma<64, true>(p, st);
         if (short_job) return launch_attn_short(p, st);
+        if (pair_job) return launch_attn_pair(p, st);
         p.queue = queue;
         p.dma_splits = n_splits;
         p.dma_split_len = split_len;
