@@ -127,6 +127,16 @@ pkv_status pkv_rope_restore(const pkv_layer_cfg* cfg,
                             int64_t pos_base, int64_t n, void* stream);
 
 /*
+ * The same for the caches of n_layers layers, each of n tokens at the same positions, in
+ * one launch (per eight of them).  k_in and k_out are HOST arrays of device pointers, read
+ * during the call; k_out[l] may alias k_in[l] exactly, and no other cache of the call.
+ */
+pkv_status pkv_rope_restore_layers(const pkv_layer_cfg* cfg, const void* const* k_in,
+                                   void* const* k_out, int32_t n_layers,
+                                   const int32_t* pos, int64_t pos_base, int64_t n,
+                                   void* stream);
+
+/*
  * Step 2 - query-driven value function (paper: Algorithm 1, first stage:
  * alpha_l = Softmax(Q_s K'^T / sqrt(d_k)); Sec. 4.2: average over the query
  * tokens; Appendix E: mean over heads; Algorithm 1 second stage / Eq. 7:

@@ -18,7 +18,8 @@ from typing import Optional
 import torch
 
 __all__ = ["LayerCfg", "PkvError", "load_library", "library_path",
-           "pkv_rope_restore", "pkv_query_score", "pkv_query_score_static",
+           "pkv_rope_restore", "pkv_rope_restore_layers", "pkv_query_score",
+           "pkv_query_score_static",
            "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
            "pkv_sparse_row_attn_ctx_lse_workspace_bytes",
            "pkv_topk_select", "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
@@ -41,7 +42,7 @@ EXPORTED_SYMBOLS = [
     "pkv_scatter_kv", "pkv_sparse_row_attn", "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
     "pkv_glue_workspace_bytes", "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
     "pkv_sparse_row_attn_ctx_lse_workspace_bytes", "pkv_chunk_attn",
-    "pkv_chunk_attn_workspace_bytes", "pkv_layer_rows",
+    "pkv_chunk_attn_workspace_bytes", "pkv_layer_rows", "pkv_rope_restore_layers",
     "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
 ]
 
@@ -159,6 +160,7 @@ def load_library() -> ctypes.CDLL:
                                         ctypes.c_float, vp, ctypes.c_size_t, vp]
     lib.pkv_chunk_attn.argtypes = [cfgp, vp, vp, vp, i32p, vp, i64, i64, ctypes.c_float, vp,
                                    ctypes.c_size_t, vp]
+    lib.pkv_rope_restore_layers.argtypes = [cfgp, vp, vp, ctypes.c_int32, i32p, i64, i64, vp]
     lib.pkv_layer_rows.argtypes = [cfgp, ctypes.POINTER(LayerCall), vp]
     lib.pkv_chunk_attn_workspace_bytes.argtypes = [cfgp, i64, i64]
     lib.pkv_chunk_attn_workspace_bytes.restype = ctypes.c_size_t
@@ -176,7 +178,8 @@ def load_library() -> ctypes.CDLL:
                  "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
                  "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
                  "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_rmsnorm_rows", "pkv_gather_rows",
-                 "pkv_linear_rows", "pkv_swiglu_rows", "pkv_layer_rows"):
+                 "pkv_linear_rows", "pkv_swiglu_rows", "pkv_layer_rows",
+                 "pkv_rope_restore_layers"):
         getattr(lib, name).restype = ctypes.c_int
     lib.pkv_workspace_bytes.argtypes = [ctypes.c_int, cfgp, i64, i64]
     lib.pkv_workspace_bytes.restype = ctypes.c_size_t
@@ -245,6 +248,35 @@ def pkv_rope_restore(cfg: LayerCfg, k_in: torch.Tensor, k_out: torch.Tensor,
     _check("pkv_rope_restore", load_library().pkv_rope_restore(
         cfg._ref, _ptr(k_in, cfg.torch_dtype, "k_in"),
         _ptr(k_out, cfg.torch_dtype, "k_out"), _ptr(pos, torch.int32, "pos"),
+        int(pos_base), n, _stream()))
+
+
+def caches_apart(k_in, k_out) -> bool:
+    """Whether no layer's keys (equal shapes, contiguous) overlap those of another layer."""
+    size = k_in[0].numel() * k_in[0].element_size() if len(k_in) else 0
+    spans = sorted({(t.data_ptr(), i) for ts in (k_in, k_out) for i, t in enumerate(ts)})
+    return all(a[1] == b[1] or b[0] - a[0] >= size for a, b in zip(spans, spans[1:]))
+
+
+def pkv_rope_restore_layers(cfg: LayerCfg, k_in, k_out, pos: Optional[torch.Tensor] = None,
+                            pos_base: int = 0) -> None:
+    """``pkv_rope_restore`` for lists of caches, all of one length, in one launch.  A layer's k_out
+    may be its k_in; between layers nothing overlaps (``caches_apart``)."""
+    layers = len(k_in)
+    if len(k_out) != layers:
+        raise ValueError("as many k_out as k_in")
+    if not layers:
+        return
+    n, dt = k_in[0].shape[0], cfg.torch_dtype
+    shape = (n, cfg.n_kv_heads, cfg.head_dim)
+    if any(t.shape != shape for t in (*k_in, *k_out)):
+        raise ValueError("k_in/k_out must be [n, Hkv, D]")
+    if pos is not None and pos.shape != (n,):
+        raise ValueError("pos must be [n]")
+    ptrs = ctypes.c_void_p * layers
+    _check("pkv_rope_restore_layers", load_library().pkv_rope_restore_layers(
+        cfg._ref, ptrs(*(_ptr(t, dt, "k_in") for t in k_in)),
+        ptrs(*(_ptr(t, dt, "k_out") for t in k_out)), layers, _ptr(pos, torch.int32, "pos"),
         int(pos_base), n, _stream()))
 
 

@@ -36,16 +36,24 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 extern "C" {
 
+pkv_status pkv_rope_restore_layers(const pkv_layer_cfg* cfg, const void* const* k_in,
+                                   void* const* k_out, int32_t n_layers, const int32_t* pos,
+                                   int64_t pos_base, int64_t n, void* stream) {
+    pkv_status st = check_cfg(cfg);
+    if (st != PKV_OK) return st;
+    if (n < 0 || n > kMaxTokens || n_layers < 0) return PKV_ERR_SHAPE;
+    if (n == 0 || n_layers == 0) return PKV_OK;
+    if (!k_in || !k_out) return PKV_ERR_NULL;
+    for (int32_t l = 0; l < n_layers; ++l)
+        if (!k_in[l] || !k_out[l]) return PKV_ERR_NULL;
+    if (!pos && (pos_base < -kMaxTokens || pos_base > kMaxTokens)) return PKV_ERR_SHAPE;
+    return launch_rope_restore(*cfg, k_in, k_out, n_layers, pos, pos_base, n, (hipStream_t)stream);
+}
+
 pkv_status pkv_rope_restore(const pkv_layer_cfg* cfg, const void* k_in,
                             void* k_out, const int32_t* pos, int64_t pos_base,
                             int64_t n, void* stream) {
-    pkv_status st = check_cfg(cfg);
-    if (st != PKV_OK) return st;
-    if (n < 0 || n > kMaxTokens) return PKV_ERR_SHAPE;
-    if (n == 0) return PKV_OK;
-    if (!k_in || !k_out) return PKV_ERR_NULL;
-    if (!pos && (pos_base < -kMaxTokens || pos_base > kMaxTokens)) return PKV_ERR_SHAPE;
-    return launch_rope_restore(*cfg, k_in, k_out, pos, pos_base, n, (hipStream_t)stream);
+    return pkv_rope_restore_layers(cfg, &k_in, &k_out, 1, pos, pos_base, n, stream);
 }
 
 pkv_status pkv_query_score(const pkv_layer_cfg* cfg, const void* q, const void* k,

@@ -72,8 +72,8 @@ inline pkv_status launch_status() {
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- kernel launchers (one per source file) ---------------------------------
-pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* k_in,
-                               void* k_out, const int32_t* pos,
+pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* const* k_in,
+                               void* const* k_out, int n_layers, const int32_t* pos,
                                int64_t pos_base, int64_t n, hipStream_t st);
 
 pkv_status launch_scatter_kv(const pkv_layer_cfg& cfg, const void* k_new,

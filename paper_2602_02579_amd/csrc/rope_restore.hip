@@ -9,9 +9,13 @@
 // whole 128-byte (bf16, D=128) half-head segments of consecutive tokens.
 #include "pkv_common.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace pkv {
+
+constexpr int kRopeLayers = 8;    // caches of a launch (its arguments grow with them)
+constexpr int kRopeFull = 256;    // workgroups that a launch is brought to, see below
 
 void fill_rope_table(RopeTable* t, int head_dim, double theta) {
     const int half = head_dim / 2;
@@ -19,11 +23,24 @@ void fill_rope_table(RopeTable* t, int head_dim, double theta) {
         t->inv_freq[i] = i < half ? std::pow(theta, -2.0 * i / head_dim) : 0.0;
 }
 
+// The caches of several layers share a launch (blockIdx.y): one chunk of 512 tokens is 16 workgroups
+// and as long as their chain of loads, sines and stores.  Where even that leaves the chip idle the
+// heads of a token are dealt out too (blockIdx.z, heads_each of them): 512 tokens of 8 heads 4.7 ->
+// 3.8 us, 4001 5.9 -> 5.3; past one workgroup per CU the sines made again cost more than the shorter
+// chain gives (8192 tokens on 256, 512 and 1024 workgroups: 7.3, 7.5 and 7.8).  The launch itself
+// costs a single large cache 0.1 us more than one without layers (32768 tokens: 21.6 -> 21.7).
+struct RopeCaches {
+    const void* in[kRopeLayers];
+    void* out[kRopeLayers];
+};
+
 template <typename T>
 __global__ __launch_bounds__(256) void rope_restore_kernel(
-    const T* k_in, T* k_out,
-    const int32_t* __restrict__ pos, int64_t pos_base, int64_t n, int n_heads,
-    int head_dim, RopeTable tab) {
+    RopeCaches caches, const int32_t* __restrict__ pos, int64_t pos_base, int64_t n, int n_heads,
+    int heads_each, int head_dim, RopeTable tab) {
+    const T* const k_in = static_cast<const T*>(caches.in[blockIdx.y]);
+    T* const k_out = static_cast<T*>(caches.out[blockIdx.y]);
+    const int head0 = blockIdx.z * heads_each, head_end = min(n_heads, head0 + heads_each);
     constexpr int V = Vec16<T>::N;
     typedef typename Vec16<T>::type vec_t;
     const int half = head_dim / 2;
@@ -47,7 +64,7 @@ __global__ __launch_bounds__(256) void rope_restore_kernel(
         auto load_batch = [&](int h0) {
 #pragma unroll
             for (int u = 0; u < HB; ++u) {
-                if (h0 + u < n_heads) {
+                if (h0 + u < head_end) {
                     // streamed once: non-temporal, so that the lines do not displace what the
                     // caches hold for the kernels around this one
                     a[u] = __builtin_nontemporal_load(
@@ -57,15 +74,15 @@ __global__ __launch_bounds__(256) void rope_restore_kernel(
                 }
             }
         };
-        load_batch(0);
+        load_batch(head0);
         float sn[V], cs[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) rope_sincos(p, tab.inv_freq[i0 + j], &sn[j], &cs[j]);
-        for (int h0 = 0; h0 < n_heads; h0 += HB) {
-            if (h0 > 0) load_batch(h0);
+        for (int h0 = head0; h0 < head_end; h0 += HB) {
+            if (h0 > head0) load_batch(h0);
 #pragma unroll
             for (int u = 0; u < HB; ++u) {
-                if (h0 + u < n_heads) {
+                if (h0 + u < head_end) {
                     vec_t ra, rb;
 #pragma unroll
                     for (int j = 0; j < V; ++j) {
@@ -83,10 +100,10 @@ __global__ __launch_bounds__(256) void rope_restore_kernel(
     }
 }
 
-pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* k_in,
-                               void* k_out, const int32_t* pos,
+pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* const* k_in,
+                               void* const* k_out, int n_layers, const int32_t* pos,
                                int64_t pos_base, int64_t n, hipStream_t st) {
-    if (n == 0) return PKV_OK;
+    if (n == 0 || n_layers == 0) return PKV_OK;
     RopeTable tab;
     fill_rope_table(&tab, cfg.head_dim, (double)cfg.rope_theta);
     const int half = cfg.head_dim / 2;
@@ -95,16 +112,25 @@ pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* k_in,
     const int block = 256;
     int64_t grid = ceil_div(total, block);
     if (grid > 256 * 64) grid = 256 * 64;  // grid-stride beyond 64 blocks per CU
-    if (cfg.dtype == PKV_BF16) {
-        hipLaunchKernelGGL(rope_restore_kernel<bf16_t>, dim3((unsigned)grid),
-                           dim3(block), 0, st, (const bf16_t*)k_in,
-                           (bf16_t*)k_out, pos, pos_base, n, cfg.n_kv_heads,
-                           cfg.head_dim, tab);
-    } else {
-        hipLaunchKernelGGL(rope_restore_kernel<float>, dim3((unsigned)grid),
-                           dim3(block), 0, st, (const float*)k_in,
-                           (float*)k_out, pos, pos_base, n, cfg.n_kv_heads,
-                           cfg.head_dim, tab);
+    // heads in as many parts as bring the launch to kRopeFull workgroups
+    const int layers = n_layers < kRopeLayers ? n_layers : kRopeLayers;
+    const int64_t parts = std::min<int64_t>(
+        cfg.n_kv_heads, std::max<int64_t>(1, kRopeFull / (grid * layers)));
+    const int heads_each = (int)ceil_div(cfg.n_kv_heads, parts);
+    for (int l0 = 0; l0 < n_layers; l0 += kRopeLayers) {
+        RopeCaches caches = {};
+        const int cnt = n_layers - l0 < kRopeLayers ? n_layers - l0 : kRopeLayers;
+        for (int l = 0; l < cnt; ++l) {
+            caches.in[l] = k_in[l0 + l];
+            caches.out[l] = k_out[l0 + l];
+        }
+        const dim3 g((unsigned)grid, (unsigned)cnt, (unsigned)ceil_div(cfg.n_kv_heads, heads_each));
+        if (cfg.dtype == PKV_BF16)
+            hipLaunchKernelGGL(rope_restore_kernel<bf16_t>, g, dim3(block), 0, st, caches, pos,
+                               pos_base, n, cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
+        else
+            hipLaunchKernelGGL(rope_restore_kernel<float>, g, dim3(block), 0, st, caches, pos,
+                               pos_base, n, cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
     }
     return launch_status();
 }

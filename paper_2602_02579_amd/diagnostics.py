@@ -113,8 +113,7 @@ class Diagnostics:
             L["k_cache"], L["v_cache"] = k[li], v[li]
             cr._layer(L, cr.pos, t, score=None, caches_only=li == len(blocks) - 1,
                       chunks=(cr.rows, chunk_len))
-        for kk in k:
-            api.pkv_rope_restore(self.lc, kk, kk, cr.neg_pos)   # inverse rotation
+        api.pkv_rope_restore_layers(self.lc, k, k, cr.neg_pos)   # inverse rotation
 
     def chunk_isolated_cache(self, embed: torch.Tensor, blocks: Sequence[Block],
                              chunk_len: int):

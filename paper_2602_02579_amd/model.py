@@ -18,7 +18,7 @@ import numpy as np
 import torch
 
 from . import api
-from .pipeline import layer_cfg
+from .pipeline import layer_cfg, restore_together
 from .synth import Config, select_count
 
 BLOCK_WEIGHTS = ("w_in", "wq", "wk", "wv", "wo", "w_post", "w_gate", "w_up", "w_down")
@@ -137,8 +137,10 @@ class CarriedRows:
         ls = self.cfg.n_score_layers if n_score_layers is None else n_score_layers
         last = min(ls, len(layers)) - 1
         api.pkv_gather_rows(embed, self.q_rows, self.h[:self.qn])
+        together = restore_together(self.lc, layers, self.n)
         for li, L in enumerate(layers):
-            api.pkv_rope_restore(self.lc, L["k_nope"], L["k_cache"][:self.n], None, 0)
+            if not together:
+                api.pkv_rope_restore(self.lc, L["k_nope"], L["k_cache"][:self.n], None, 0)
             if li == last and not keep_rows and self._fuse_last:
                 self._layer(L, self.q_rows, self.qn, score=li > 0, scores_only=True)
             elif li == last and not keep_rows:

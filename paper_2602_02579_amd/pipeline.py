@@ -39,6 +39,20 @@ def upload_layer(cfg: Config, layer: Dict[str, np.ndarray],
     return out
 
 
+def restore_together(lc: api.LayerCfg, layers: List[Dict[str, torch.Tensor]], n: int) -> bool:
+    """Restore the keys of all ``layers`` in one launch, unless some share memory: then the caller
+    restores each layer right before it uses it, as it does with a single layer, where the lists
+    would only add to the host's time (4 us of a pass of 52)."""
+    if len(layers) == 1:
+        return False
+    k_in = [L["k_nope"] for L in layers]
+    k_out = [L["k_cache"][:n] for L in layers]
+    if not api.caches_apart(k_in, k_out):
+        return False
+    api.pkv_rope_restore_layers(lc, k_in, k_out)
+    return True
+
+
 class SelectiveRecompute:
     """Work buffers and the per-layer call sequence for one configuration."""
 
@@ -110,8 +124,10 @@ class SelectiveRecompute:
         """One pass of the whole hot path over ``layers`` (outputs of the last
         layer stay in ``self.out`` / ``self.lse``; caches are updated in place)."""
         ls = self.cfg.n_score_layers if n_score_layers is None else n_score_layers
+        together = restore_together(self.lc, layers, self.n)
         for li, L in enumerate(layers):
-            self.restore(L)
+            if not together:
+                self.restore(L)
             if li < ls:
                 self.score_layer(L, accumulate=li > 0)
         self.select()
