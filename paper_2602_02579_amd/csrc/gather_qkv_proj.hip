@@ -331,7 +331,7 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
                                   const void* wq, const void* wk, const void* wv,
                                   const pkv_proj_variant* var, const int32_t* dst_row,
                                   void* q_out, void* k_out, void* v_out, int64_t m, void* ws,
-                                  hipStream_t st) {
+                                  hipStream_t st, bool angles_ready) {
     if (m == 0) return PKV_OK;
     ProjExtra ex = {};
     ex.dst_row = dst_row;
@@ -369,9 +369,9 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
             p.tile_begin[3] = tq + 2 * tkv;
             const size_t cs_bytes = ((size_t)m * half * sizeof(float2) + 255) & ~(size_t)255;
             p.partial = reinterpret_cast<float*>((unsigned char*)ws + cs_bytes);
-            return launch_proj_dma128(p, row_pos, tab, st);
+            return launch_proj_dma128(p, row_pos, tab, st, angles_ready);
         }
-        launch_rope_table(row_pos, m, half, tab, cs, st);
+        if (!angles_ready) launch_rope_table(row_pos, m, half, tab, cs, st);
         // column tiles: only the matrices whose outputs were asked for
         const int tq = q_out ? hq * d / kGN : 0;
         const int tkv = k_out ? hkv * d / kGN : 0;
@@ -407,6 +407,16 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
                            hkv, cfg.head_dim, cfg.hidden, tab, ex);
     }
     return launch_status();
+}
+
+bool proj_reads_angles(const pkv_layer_cfg& cfg, const pkv_proj_variant* var, bool with_q,
+                       bool with_kv, int64_t m) {
+    if (m <= 0 || !mfma_proj_supported(cfg)) return false;
+    if (proj_dma128_supported(cfg, m))
+        return proj_dma128_reads_angles(
+            m, ((with_q ? cfg.n_q_heads : 0) + (with_kv ? 2 * cfg.n_kv_heads : 0)) * cfg.head_dim,
+            cfg.hidden);
+    return !(var && (var->bq || var->bk || var->bv || var->q_norm || var->k_norm));
 }
 
 bool norm_proj_f32(const pkv_layer_cfg& cfg, const void* hidden, const void* norm_w, float eps,

@@ -953,10 +953,10 @@ bool proj_dma128_supported(const pkv_layer_cfg& cfg, int64_t m) {
 
 namespace {
 
-// row_pos, tab: the angles of a Q | K | V launch (p.cs: room for their table)
+// row_pos, tab: the angles of a Q | K | V launch (p.cs: room for their table, or the table)
 template <int MODE, bool EXTRA = false>
 pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
-                        hipStream_t st) {
+                        hipStream_t st, bool angles_ready = false) {
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(proj_dma_kernel<MODE, EXTRA>),
@@ -981,7 +981,7 @@ pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeT
     q.n_ksplit = plan.ksplit;
     if (q.n_ksplit > 1 && q.partial == nullptr) return PKV_ERR_WORKSPACE;
     // a split launch's finishing kernel works the angles out by itself
-    if (MODE == kProjRope && q.n_ksplit == 1)
+    if (MODE == kProjRope && q.n_ksplit == 1 && !angles_ready)
         launch_rope_table(row_pos, p.m, D / 2, tab, const_cast<float2*>(p.cs), st);
     if (plan.tokens < 192) {
         const pkv_status rc = launch_proj_small<MODE, EXTRA>(plan.tokens, q, st);
@@ -1030,12 +1030,16 @@ pkv_status launch_tiles(const ProjParams& p, const int32_t* row_pos, const RopeT
 
 }  // namespace
 
+bool proj_dma128_reads_angles(int64_t m, int64_t features, int64_t k_in) {
+    return features > 0 && plan_tiles(m, features, k_in).ksplit == 1;
+}
+
 pkv_status launch_proj_dma128(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
-                              hipStream_t st) {
+                              hipStream_t st, bool angles_ready) {
     const bool extra = p.bias[0] || p.bias[1] || p.bias[2] || p.norm_w[0] || p.norm_w[1] ||
                        p.dst_row;
-    return extra ? launch_tiles<kProjRope, true>(p, row_pos, tab, st)
-                 : launch_tiles<kProjRope, false>(p, row_pos, tab, st);
+    return extra ? launch_tiles<kProjRope, true>(p, row_pos, tab, st, angles_ready)
+                 : launch_tiles<kProjRope, false>(p, row_pos, tab, st, angles_ready);
 }
 
 bool linear_dma_supported(int mode, int64_t m, int64_t k_in, int64_t n_out) {

@@ -127,13 +127,13 @@ pkv_status pkv_gather_qkv_proj_ex(const pkv_layer_cfg* cfg, const void* hidden,
                                   q_out, k_out, v_out, m, ws, (hipStream_t)stream);
 }
 
-pkv_status pkv_gather_qkv_proj_scatter(const pkv_layer_cfg* cfg, const void* hidden,
+static pkv_status proj_scatter_checked(const pkv_layer_cfg* cfg, const void* hidden,
                                        const int32_t* row_idx, const int32_t* row_pos,
                                        const void* wq, const void* wk, const void* wv,
                                        const pkv_proj_variant* variant, void* q_out,
                                        void* k_cache, void* v_cache, const int32_t* dst_row,
                                        int64_t m, int64_t n_cache, void* ws, size_t ws_bytes,
-                                       void* stream) {
+                                       void* stream, bool angles_ready) {
     pkv_status st = check_cfg(cfg);
     if (st != PKV_OK) return st;
     if (m < 0 || m > kMaxTokens || n_cache < 0 || n_cache > kMaxTokens || m > n_cache)
@@ -150,7 +150,19 @@ pkv_status pkv_gather_qkv_proj_scatter(const pkv_layer_cfg* cfg, const void* hid
     const size_t need = align256(gather_qkv_proj_ws_bytes(*cfg, m));
     if (need && (!ws || ws_bytes < need)) return PKV_ERR_WORKSPACE;
     return launch_gather_qkv_proj(*cfg, hidden, row_idx, row_pos, wq, wk, wv, variant, dst_row,
-                                  q_out, k_cache, v_cache, m, ws, (hipStream_t)stream);
+                                  q_out, k_cache, v_cache, m, ws, (hipStream_t)stream,
+                                  angles_ready);
+}
+
+pkv_status pkv_gather_qkv_proj_scatter(const pkv_layer_cfg* cfg, const void* hidden,
+                                       const int32_t* row_idx, const int32_t* row_pos,
+                                       const void* wq, const void* wk, const void* wv,
+                                       const pkv_proj_variant* variant, void* q_out,
+                                       void* k_cache, void* v_cache, const int32_t* dst_row,
+                                       int64_t m, int64_t n_cache, void* ws, size_t ws_bytes,
+                                       void* stream) {
+    return proj_scatter_checked(cfg, hidden, row_idx, row_pos, wq, wk, wv, variant, q_out, k_cache,
+                                v_cache, dst_row, m, n_cache, ws, ws_bytes, stream, false);
 }
 
 pkv_status pkv_gather_qkv_proj(const pkv_layer_cfg* cfg, const void* hidden,
@@ -262,17 +274,23 @@ size_t pkv_sparse_row_attn_ctx_lse_workspace_bytes(const pkv_layer_cfg* cfg, int
     return align256(sparse_row_attn_ws_bytes(*cfg, n_keys, m, n_ctx));
 }
 
-pkv_status pkv_rmsnorm_rows(int32_t dtype, const void* h, const int32_t* row_idx,
-                            const void* weight, float eps, void* y, int64_t m,
-                            int64_t hidden, void* stream) {
+static pkv_status rmsnorm_checked(int32_t dtype, const void* h, const int32_t* row_idx,
+                                  const void* weight, float eps, void* y, int64_t m,
+                                  int64_t hidden, void* stream, const RowAngles* angles) {
     if (dtype != PKV_F32 && dtype != PKV_BF16) return PKV_ERR_UNSUPPORTED;
     if (m < 0 || m > kMaxTokens || hidden <= 0) return PKV_ERR_SHAPE;
     if (hidden % 8 || hidden > 16384) return PKV_ERR_UNSUPPORTED;
     if (!(eps >= 0.f) || !std::isfinite(eps)) return PKV_ERR_SHAPE;
     if (m == 0) return PKV_OK;
     if (!h || !weight || !y) return PKV_ERR_NULL;
-    return launch_rmsnorm_rows(dtype, h, row_idx, weight, eps, y, m, hidden,
-                               (hipStream_t)stream);
+    return launch_rmsnorm_rows(dtype, h, row_idx, weight, eps, y, m, hidden, (hipStream_t)stream,
+                               angles);
+}
+
+pkv_status pkv_rmsnorm_rows(int32_t dtype, const void* h, const int32_t* row_idx,
+                            const void* weight, float eps, void* y, int64_t m,
+                            int64_t hidden, void* stream) {
+    return rmsnorm_checked(dtype, h, row_idx, weight, eps, y, m, hidden, stream, nullptr);
 }
 
 pkv_status pkv_gather_rows(int32_t dtype, const void* src, const int32_t* row_idx, void* dst,
@@ -338,10 +356,17 @@ pkv_status pkv_layer_rows(const pkv_layer_cfg* cfg, const pkv_layer_call* call, 
                       c.k_cache, c.v_cache, c.m, (hipStream_t)stream, &st)) {
         if (st != PKV_OK) return st;
     } else {
-        PKV_TRY(pkv_rmsnorm_rows(dt, c.h, nullptr, c.w_in, c.eps, c.x, c.m, hid, stream));
-        PKV_TRY(pkv_gather_qkv_proj_scatter(cfg, c.x, nullptr, c.row_pos, c.wq, c.wk, c.wv, &var, q,
-                                            c.k_cache, c.v_cache, c.dst_row, c.m, c.n_cache, c.ws,
-                                            c.ws_bytes, stream));
+        // the table of angles, where the projection reads one, comes out of the norm's launch
+        const bool angles = c.m > 0 && c.m <= kMaxTokens && c.row_pos && c.ws &&
+                            c.ws_bytes >= align256(gather_qkv_proj_ws_bytes(*cfg, c.m)) &&
+                            proj_reads_angles(*cfg, &var, q != nullptr, true, c.m);
+        RowAngles ra = {c.row_pos, static_cast<float2*>(c.ws), cfg->head_dim / 2, {}};
+        if (angles) fill_rope_table(&ra.tab, cfg->head_dim, (double)cfg->rope_theta);
+        PKV_TRY(rmsnorm_checked(dt, c.h, nullptr, c.w_in, c.eps, c.x, c.m, hid, stream,
+                                angles ? &ra : nullptr));
+        PKV_TRY(proj_scatter_checked(cfg, c.x, nullptr, c.row_pos, c.wq, c.wk, c.wv, &var, q,
+                                     c.k_cache, c.v_cache, c.dst_row, c.m, c.n_cache, c.ws,
+                                     c.ws_bytes, stream, angles));
     }
     if (c.stop == PKV_LAYER_TO_CACHES) return PKV_OK;
     if (c.chunk_len) {

@@ -101,8 +101,18 @@ pkv_status launch_gather_qkv_proj(const pkv_layer_cfg& cfg, const void* hidden,
                                   const void* wq, const void* wk, const void* wv,
                                   const pkv_proj_variant* var, const int32_t* dst_row,
                                   void* q_out, void* k_out, void* v_out, int64_t m, void* ws,
-                                  hipStream_t st);
+                                  hipStream_t st, bool angles_ready = false);
 size_t gather_qkv_proj_ws_bytes(const pkv_layer_cfg& cfg, int64_t m);
+// Whether that launch reads the table of its rows' angles, float2 [m, head_dim / 2] at ws: it makes
+// the table itself unless told that an earlier launch did (RowAngles)
+bool proj_reads_angles(const pkv_layer_cfg& cfg, const pkv_proj_variant* var, bool with_q,
+                       bool with_kv, int64_t m);
+struct RowAngles {
+    const int32_t* row_pos;
+    float2* cs;
+    int half;
+    RopeTable tab;
+};
 // fp32: the same of rmsnorm(hidden, norm_w, eps) in one launch; false: not for these arguments
 bool norm_proj_f32(const pkv_layer_cfg& cfg, const void* hidden, const void* norm_w, float eps,
                    const int32_t* row_pos, const void* wq, const void* wk, const void* wv,
@@ -129,7 +139,7 @@ pkv_status launch_chunk_attn(const pkv_layer_cfg& cfg, const void* q, const void
 // layer glue (layer_glue.hip); dtype is a pkv_dtype
 pkv_status launch_rmsnorm_rows(int dtype, const void* h, const int32_t* row_idx,
                                const void* weight, float eps, void* y, int64_t m,
-                               int64_t hidden, hipStream_t st);
+                               int64_t hidden, hipStream_t st, const RowAngles* angles = nullptr);
 pkv_status launch_gather_rows(int dtype, const void* src, const int32_t* row_idx, void* dst,
                               int64_t m, int64_t width, hipStream_t st);
 size_t glue_ws_bytes(int dtype, int64_t m, int64_t k_in, int64_t n_out);

@@ -47,7 +47,9 @@ bool proj_dma128_supported(const pkv_layer_cfg& cfg, int64_t m);
 // enough to fill the chip without splitting the contraction)
 size_t proj_dma128_partial_bytes(const pkv_layer_cfg& cfg, int64_t m);
 pkv_status launch_proj_dma128(const ProjParams& p, const int32_t* row_pos, const RopeTable& tab,
-                              hipStream_t st);
+                              hipStream_t st, bool angles_ready);
+// whether that launch reads the table of angles: one that splits its contraction does not
+bool proj_dma128_reads_angles(int64_t m, int64_t features, int64_t k_in);
 // cs [m, half] = (cos, sin) of every row's angles (gather_qkv_proj.hip)
 void launch_rope_table(const int32_t* row_pos, int64_t m, int half, const RopeTable& tab,
                        float2* cs, hipStream_t st);

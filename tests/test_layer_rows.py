@@ -120,3 +120,37 @@ def test_same_bits_as_the_calls(gpu_device, dtype, variant, form):
             # rows, another kernel's: a few units of 2^-24 of sums of at most 128 terms of order
             # one, twice (x is then not written)
             assert (a[name] - b[name]).abs().max() <= 2e-5 * max(1.0, b[name].abs().max()), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,d,hid,m", [(8, 8, 128, 1024, 500), (2, 2, 128, 5120, 2100),
+                                            (2, 2, 128, 256, 1), (4, 4, 64, 256, 33)])
+def test_angles_out_of_the_norms_launch(gpu_device, hq, hkv, d, hid, m):
+    """A workgroup per row, a wave per row in registers and not, and the 256 x 128 kernel: Q, K and V
+    are those of the two calls, which make the table in a launch of its own."""
+    cfg = api.LayerCfg(hq, hkv, d, hid, 1e4, "bf16")
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(m)
+
+    def mat(*shape, scale=1.0):
+        return (torch.randn(shape, generator=gen, device=gpu_device) * scale).to(torch.bfloat16)
+    L = dict(w_in=mat(hid), w_post=mat(hid), wq=mat(hq * d, hid, scale=.05),
+             wk=mat(hkv * d, hid, scale=.05), wv=mat(hkv * d, hid, scale=.05),
+             wo=mat(hid, hq * d), w_gate=mat(64, hid), w_up=mat(64, hid), w_down=mat(hid, 64))
+    h = mat(m, hid)
+    pos = torch.randperm(3 * m, generator=gen, device=gpu_device)[:m].to(torch.int32)
+    rows = torch.randperm(m, generator=gen, device=gpu_device).to(torch.int32)
+    ws = torch.empty(256 << 20, dtype=torch.uint8, device=gpu_device)
+    new = lambda *s: torch.zeros((m,) + s, dtype=torch.bfloat16, device=gpu_device)   # noqa: E731
+    out = [(new(hid), new(hq, d), new(hkv, d), new(hkv, d)) for _ in range(2)]
+    x, q, k, v = out[0]
+    api.pkv_layer_rows(cfg, h, x, q, new(hq, d), new(64), m, L, (), k, v, pos, rows, EPS, ws,
+                       score=torch.zeros(m, device=gpu_device), n_ctx=m,
+                       stop=api.LAYER_TO_SCORES)
+    x, q, k, v = out[1]
+    api.pkv_rmsnorm_rows(h, None, L["w_in"], EPS, x)
+    ws.fill_(255)
+    api.pkv_gather_qkv_proj_scatter(cfg, x, None, pos, L["wq"], L["wk"], L["wv"], q, k, v, rows,
+                                    ws=ws)
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
