@@ -18,6 +18,7 @@ struct AttnParams {
     bf16_t* out;             // [m, hq, D]
     float* lse;              // [m, hq] or nullptr
     float* part_ml;          // [n_splits, m*hq, 2] (max in raw logits, sum) or nullptr
+    const int* order;        // [n_tiles * dma_splits] or null: a kv head's jobs, the heaviest first
     int* queue;              // [hkv] next unclaimed row tile per kv head, zero before the
                              // launch, or nullptr: one job per workgroup (pipelined kernel)
     float* part_o;           // [dma_splits, m, hq, D] normalised partial outputs, and

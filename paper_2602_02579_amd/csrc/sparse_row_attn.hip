@@ -437,6 +437,37 @@ __global__ __launch_bounds__(64) void attn_clear_kernel(int* zero, int n_zero) {
     for (int i = threadIdx.x; i < n_zero; i += 64) zero[i] = 0;
 }
 
+// The same, and the order of the jobs of a kv head where the keys are cut into ranges: a job's weight
+// is what the last row of its tile sees of its range (for rows in ascending order the most that any
+// sees; another order of rows only makes the list a worse one).  Tile by tile, as they are numbered,
+// heavy jobs of short tiles queue up behind empty ones of long tiles.
+constexpr int kOrderJobs = 512;
+__global__ __launch_bounds__(256) void attn_order_kernel(AttnParams p, int* zero, int* order) {
+    __shared__ __align__(16) int s_weight[kOrderJobs];
+    const int jobs = p.n_tiles * p.dma_splits;   // <= kOrderJobs
+    for (int i = threadIdx.x; i < p.hkv; i += 256) zero[i] = 0;
+    for (int j = threadIdx.x; j < kOrderJobs; j += 256) {
+        int w = -1;
+        if (j < jobs) {
+            const int tile = p.n_tiles - 1 - j / p.dma_splits;
+            const int seen = min(p.row_pos[min((tile + 1) * p.bm, p.m) - 1] + 1, p.n_keys);
+            w = max(0, min(seen - j % p.dma_splits * p.dma_split_len, p.dma_split_len));
+        }
+        s_weight[j] = w;
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < jobs; j += 256) {
+        const int w = s_weight[j];
+        int rank = 0;   // equal weights in their own order: the ranks are a permutation
+        for (int i = 0; i < jobs; i += 4) {
+            const int4 o = *reinterpret_cast<const int4*>(&s_weight[i]);
+            rank += (o.x > w || (o.x == w && i < j)) + (o.y > w || (o.y == w && i + 1 < j)) +
+                    (o.z > w || (o.z == w && i + 2 < j)) + (o.w > w || (o.w == w && i + 3 < j));
+        }
+        order[rank] = j;
+    }
+}
+
 bool mfma_attn_supported(const pkv_layer_cfg& cfg) {
     const int group = cfg.n_q_heads / cfg.n_kv_heads;
     return cfg.dtype == PKV_BF16 && (cfg.head_dim == 64 || cfg.head_dim == 128) &&
@@ -670,6 +701,22 @@ bool sparse_row_attn_ctx_lse_supported(const pkv_layer_cfg& cfg, int64_t n_keys,
            attn_plan_splits_at(cfg, n_keys, m, ctx_keys, &a, &b);
 }
 
+// Jobs of several ranges through the queue by weight instead of tile by tile (us, rows spread over
+// the keys / all at their end; 32 / 8 heads, 883 rows over 24.6k keys, 4 ranges: 224 -> 204 / 348 ->
+// 332, over 32.9k 280 -> 251 / 443 -> 437, 1300 over 32.9k, 5 ranges, 383 -> 365, 2500 over 65.5k, 3
+// ranges, 1229 -> 1147 / 2227 -> 2154; 40 / 8, 883 over 32.9k 310 -> 288).  Up to one and a half jobs
+// per CU nothing is gained (883 over 16.5k, 336 jobs, 137 -> 138), and two ranges of up to two jobs
+// per CU are dealt out well as they are: the first of a short tile falls to who had the second of a
+// middling one (1766 over 13k 182 -> 205).  With fewer kv heads than XCDs neighbouring jobs are on
+// different XCDs, whose L2s then hold another range each as long as the numbering is kept (8 / 2
+// heads, 2500 at the end of 16.5k: 187 -> 197).
+bool attn_order_pays(const pkv_layer_cfg& cfg, int64_t m, int n_splits) {
+    const int64_t per_head = ceil_div(m, 256 / (cfg.n_q_heads / cfg.n_kv_heads)) * n_splits;
+    const int64_t jobs = per_head * cfg.n_kv_heads, n_cu = attn_cu_count();
+    return n_splits > 1 && cfg.n_kv_heads % 8 == 0 && per_head <= kOrderJobs &&
+           2 * jobs > 3 * n_cu && (n_splits > 2 || jobs > 2 * n_cu);
+}
+
 // Per-column (max, sum) partials of softmax(q k^T * scale) over keys
 // 0 .. n_ctx-1, split over the keys; used by the query-score call.
 // part_ml: [n_splits, nq*hq, 2].
@@ -745,8 +792,10 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         }
         const bool pair_job = d == 128 && nat_v && !short_job && !lse_ctx_out &&
                               attn_pair_applies(cfg, n_keys, m);
+        const bool ordered = nat_v && queue && !short_job && !pair_job &&
+                             attn_order_pays(cfg, m, n_splits);
         if (nat_v) {
-            if (queue && !short_job && !pair_job)
+            if (queue && !short_job && !pair_job && !ordered)
                 hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue,
                                    cfg.n_kv_heads);
         } else {
@@ -785,6 +834,12 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         p.dma_split_len = split_len;
         p.lse_ctx = lse_ctx_out;
         p.ctx_keys = (int)ctx_keys;
+        if (ordered) {
+            int* const order = reinterpret_cast<int*>(vt);   // no V^T copy is made: its room is free
+            hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(256), 0, st, p, queue, order);
+            if (launch_status() != PKV_OK) return PKV_ERR_LAUNCH;
+            p.order = order;
+        }
         if (n_splits > 1) {
             p.part_o = reinterpret_cast<float*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys) +
                                                 attn_queue_bytes(cfg));

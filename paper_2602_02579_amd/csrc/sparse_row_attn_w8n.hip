@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
     const int l16 = lane & 15;   // its column in each of the wave's two 16-column blocks
 
     // Work distribution: one workgroup per CU takes (kv head, row tile[, key range]) jobs,
-    // heaviest first.  Its first one goes by its own number (256 workgroups at eight counters
+    // heaviest first (tiles from the last one on, or by p.order).  Its first one goes by its own number (256 workgroups at eight counters
     // took 4 to 5 us to claim them: 1702 rows over 8k keys 132 -> 128 us); further ones it claims from one counter per kv head,
     // preferring its home head (whose K/V its XCD's L2 holds) unless another head is kStealLag or
     // more jobs behind.
@@ -157,6 +157,7 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
                           atomicAdd(&p.queue[best], 1);
             if (j < jobs_per_head) job = best * jobs_per_head + j;
         }
+        if (p.order && job >= 0) job += p.order[job % jobs_per_head] - job % jobs_per_head;
         s_job = job;
     }
     __syncthreads();
