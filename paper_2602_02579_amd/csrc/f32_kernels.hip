@@ -25,6 +25,8 @@
 
 #include "f32_kernels.h"
 
+#include "attn_common.h"
+
 namespace pkv {
 
 namespace {
@@ -271,21 +273,28 @@ __device__ __forceinline__ float col_sum(float v) {
 // the head, so that a lane's piece of a value row is C = D / 16 consecutive floats (one element
 // per load instead took 16 loads per tile and as long as the multiplications).  K and V of the
 // next tile are requested before the current one is used.
+//
+// S > 1, where all of them still have a CU of their own: S workgroups per tile of columns, each with its
+// C / S elements of every value row and all of the scores.  The two products, alike in size, are what
+// a workgroup spends its time on, so four take towards 5/8 of it, with the same bits and no parts to be
+// merged (us, 220 rows: 4 heads of 64, 1040 keys 19.4 -> 17.7, 4096 57.7 -> 50.8; 8 / 2 heads of 128,
+// where two share, 1040 keys 33.7 -> 26.5; 64 rows of them, four, 33.2 -> 24.1; 4 / 2 of 32 13.2 -> 12.0).
 constexpr int kColRow = 17;   // the merge reads down the columns: 16 would be 16 lanes to a bank
-template <int D, int NW>
+template <int D, int NW, int S>
 __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
     const int32_t* __restrict__ row_pos, float* __restrict__ out, float* __restrict__ lse_out,
     int m_all, int hq, int hkv, float scale, int chunk_len) {
-    constexpr int C = D / 16;
-    extern __shared__ __align__(16) float smem[];      // [NW][D][16] partial outputs, rows of 17
+    constexpr int C = D / 16, CS = C / S, DS = D / S;
+    extern __shared__ __align__(16) float smem[];      // [NW][DS][16] partial outputs, rows of 17
     __shared__ float s_m[NW][16], s_l[NW][16], s_f[NW][16], s_top[16];
     __shared__ int s_out[16];   // (row, head) of a column, -1: none
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int g4 = lane >> 4, l16 = lane & 15;
     const int g = blockIdx.y, group = hq / hkv;
-    const int tile = gridDim.x - 1 - blockIdx.x;       // rows in position order: heavy ones first
+    const int part = blockIdx.x % S;
+    const int tile = (gridDim.x - 1 - blockIdx.x) / S; // rows in position order: heavy ones first
     // rows and keys of chunk blockIdx.z start at row0 (one chunk: the keys are a cache of their own)
     const int row0 = (int)blockIdx.z * chunk_len;
     const int m = min(m_all, row0 + chunk_len);
@@ -301,12 +310,12 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     load_row<D>(q4, q + ((int64_t)(valid ? row : 0) * hq + head) * D, g4);
     const int64_t krow = (int64_t)hkv * D;
     const float* kb = kc + row0 * krow + (int64_t)g * D;
-    const float* vb = vc + row0 * krow + (int64_t)g * D + C * l16;
-    typedef float vrow_t __attribute__((ext_vector_type(C)));
-    f32x4 k4[C], kn[C], o_acc[C];
+    const float* vb = vc + row0 * krow + (int64_t)g * D + C * l16 + CS * part;
+    typedef float vrow_t __attribute__((ext_vector_type(CS)));
+    f32x4 k4[C], kn[C], o_acc[CS];
     vrow_t v4[4], vn[4];
 #pragma unroll
-    for (int c = 0; c < C; ++c) o_acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < CS; ++c) o_acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     float mx = -INFINITY, sum = 0.f;
     // keys beyond the tile's last visible one are never needed: re-read that one instead
     auto load_kv = [&](int t0) {
@@ -342,11 +351,11 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
         sum = sum * corr + ts;       // this lane group's keys only
         mx = mn;
 #pragma unroll
-        for (int c = 0; c < C; ++c) o_acc[c] *= corr;
+        for (int c = 0; c < CS; ++c) o_acc[c] *= corr;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int c = 0; c < C; ++c) o_acc[c] = mfma_f32(v4[j][c], s[j], o_acc[c]);
+            for (int c = 0; c < CS; ++c) o_acc[c] = mfma_f32(v4[j][c], s[j], o_acc[c]);
     }
     sum = col_sum(sum);
     if (g4 == 0) {
@@ -354,10 +363,10 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
         s_l[wave][l16] = sum;
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+    for (int c = 0; c < CS; ++c)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            smem[(wave * D + C * (4 * g4 + r) + c) * kColRow + l16] = o_acc[c][r];
+            smem[(wave * DS + CS * (4 * g4 + r) + c) * kColRow + l16] = o_acc[c][r];
     __syncthreads();
     if (tid < NW * 16) {        // the weight of every wave's part
         const int w = tid >> 4, cc = tid & 15;
@@ -372,17 +381,18 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int e0 = 0; e0 < D * 16; e0 += NW * 64) {
+    for (int e0 = 0; e0 < DS * 16; e0 += NW * 64) {
         const int e = e0 + tid;
-        if (D * 16 % (NW * 64) && e >= D * 16) break;   // head_dim 32 on 16 waves
-        const int cc = e / D, dd = e % D;
+        if (DS * 16 % (NW * 64) && e >= DS * 16) break;   // few elements on 16 waves
+        const int cc = e / DS, es = e % DS;
+        const int dd = es / CS * C + CS * part + es % CS;   // element of the head
         const int64_t oc = s_out[cc];
         if (oc < 0) continue;
         float acc = 0.f, l = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float f = s_f[w][cc];
-            acc += f * smem[(w * D + dd) * kColRow + cc];
+            acc += f * smem[(w * DS + es) * kColRow + cc];
             l += f * s_l[w][cc];
         }
         out[oc * D + dd] = acc / l;
@@ -545,20 +555,21 @@ __global__ __launch_bounds__(256) void score_sum_f32_kernel(
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-template <int D, int NW>
+template <int D, int NW, int S>
 pkv_status attn_f32_launch(dim3 grid, const float* q, const float* k, const float* v,
                            const int32_t* row_pos, float* out, float* lse, int64_t m, int hq,
                            int hkv, float scale, int chunk_len, hipStream_t st) {
-    constexpr size_t kBytes = (size_t)NW * D * kColRow * sizeof(float);
+    constexpr size_t kBytes = (size_t)NW * (D / S) * kColRow * sizeof(float);
+    grid.x *= S;
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, NW>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, NW, S>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)kBytes) != hipSuccess)
             return PKV_ERR_LAUNCH;
         configured.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((attn_f32_kernel<D, NW>), grid, dim3(NW * 64), kBytes, st, q, k, v, row_pos,
+    hipLaunchKernelGGL((attn_f32_kernel<D, NW, S>), grid, dim3(NW * 64), kBytes, st, q, k, v, row_pos,
                        out, lse, (int)m, hq, hkv, scale, chunk_len);
     return launch_status();
 }
@@ -622,11 +633,19 @@ pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float
     // as many waves as their registers allow: 16 up to head_dim 64, 8 with 128; four where that
     // is a tile or two of keys each (head_dim 128: a tile), so that fewer parts have to be merged
     const bool few = n_keys <= (cfg.head_dim == 128 ? 64 : 128);
-#define PKV_ATTN_F32(D, NW) \
-    attn_f32_launch<D, NW>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, (int)chunk_len, st)
-    if (cfg.head_dim == 32) return few ? PKV_ATTN_F32(32, 4) : PKV_ATTN_F32(32, 16);
-    if (cfg.head_dim == 64) return few ? PKV_ATTN_F32(64, 4) : PKV_ATTN_F32(64, 16);
-    return few ? PKV_ATTN_F32(128, 4) : PKV_ATTN_F32(128, 8);
+    // workgroups that share a tile of columns: as many as leave each a CU of its own (beyond, the scores
+    // made again would take the time that the shorter products save)
+    const int64_t tiles = (int64_t)grid.x * grid.y * grid.z, n_cu = attn_cu_count();
+    const int most = few ? 1 : 4 * tiles <= n_cu ? 4 : 2 * tiles <= n_cu ? 2 : 1;
+#define PKV_ATTN_F32(D, NW, S)                                                                   \
+    attn_f32_launch<D, NW, S>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, (int)chunk_len, st)
+#define PKV_ATTN_F32_SHARED(D, NW)                                                               \
+    (most == 4 && D > 32 ? PKV_ATTN_F32(D, NW, (D > 32 ? 4 : 2))                                 \
+                         : most > 1 ? PKV_ATTN_F32(D, NW, 2) : PKV_ATTN_F32(D, NW, 1))
+    if (cfg.head_dim == 32) return few ? PKV_ATTN_F32(32, 4, 1) : PKV_ATTN_F32_SHARED(32, 16);
+    if (cfg.head_dim == 64) return few ? PKV_ATTN_F32(64, 4, 1) : PKV_ATTN_F32_SHARED(64, 16);
+    return few ? PKV_ATTN_F32(128, 4, 1) : PKV_ATTN_F32_SHARED(128, 8);
+#undef PKV_ATTN_F32_SHARED
 #undef PKV_ATTN_F32
 }
 
