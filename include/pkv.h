@@ -306,7 +306,8 @@ pkv_status pkv_scatter_kv(const pkv_layer_cfg* cfg,
  * i < m, fp32 softmax and accumulation, one rounding to cfg->dtype.
  * row_pos[i] must lie in [0, n_keys); rows need not be sorted, but sorted
  * rows (the order step 3 returns) give balanced tiles.  lse_out, if not
- * NULL, receives the natural-log normaliser per (row, head).
+ * NULL, receives the natural-log normaliser per (row, head).  out may be q itself
+ * and overlaps no other operand.
  * softmax_scale == 0 means 1/sqrt(D).  m == 0 is a no-op.
  */
 pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg,
@@ -325,7 +326,8 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg,
  * chunk_len, the last one with what is left; row i attends the rows of its chunk up to
  * row_pos[i], which is counted from the chunk's first row: pkv_sparse_row_attn chunk by
  * chunk, in one launch where the chunks are short.  row_pos[i] must lie in [0, length of
- * the chunk).  Scratch: pkv_chunk_attn_workspace_bytes.  m == 0 is a no-op.
+ * the chunk).  out may be q itself and overlaps no other operand.  Scratch:
+ * pkv_chunk_attn_workspace_bytes.  m == 0 is a no-op.
  */
 pkv_status pkv_chunk_attn(const pkv_layer_cfg* cfg,
                           const void* q,          /* [m, Hq, D] */

@@ -634,9 +634,10 @@ pkv_status launch_attn_f32(const pkv_layer_cfg& cfg, const float* q, const float
     // is a tile or two of keys each (head_dim 128: a tile), so that fewer parts have to be merged
     const bool few = n_keys <= (cfg.head_dim == 128 ? 64 : 128);
     // workgroups that share a tile of columns: as many as leave each a CU of its own (beyond, the scores
-    // made again would take the time that the shorter products save)
+    // made again would take the time that the shorter products save).  One where the results replace
+    // q: the others would still read the rows that the first one has written.
     const int64_t tiles = (int64_t)grid.x * grid.y * grid.z, n_cu = attn_cu_count();
-    const int most = few ? 1 : 4 * tiles <= n_cu ? 4 : 2 * tiles <= n_cu ? 2 : 1;
+    const int most = few || out == q ? 1 : 4 * tiles <= n_cu ? 4 : 2 * tiles <= n_cu ? 2 : 1;
 #define PKV_ATTN_F32(D, NW, S)                                                                   \
     attn_f32_launch<D, NW, S>(grid, q, k, v, row_pos, out, lse, m, hq, hkv, scale, (int)chunk_len, st)
 #define PKV_ATTN_F32_SHARED(D, NW)                                                               \
