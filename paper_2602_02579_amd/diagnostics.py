@@ -50,7 +50,7 @@ def top_indices(score: torch.Tensor, k: int) -> torch.Tensor:
 
 # Chunks that pass through the layers together hold at most this many rows (one chunk may hold
 # more): the linear layers of 8192 rows fill the chip many times over and read the weights once
-# where 16 chunks of 512 read them 16 times; further rows only grow the buffers (0.7 GB at 4096 /
+# where 16 chunks of 512 read them 16 times; further rows only grow the buffers (0.6 GB at 4096 /
 # 14336 bf16).  16k tokens in chunks of 512 through two layers of 4096 / 14336, chunk by chunk ->
 # 2048 / 8192 / 16384 rows at once: 10.0 -> 6.8 / 5.8 / 5.8 ms; in chunks of 256 through four of
 # 1024 / 2048, where 64 chunks made 2000 small launches: 18.1 -> 2.5 / 1.5 / 1.3 ms.
@@ -65,7 +65,7 @@ class Diagnostics:
         self.cfg, self.inter, self.eps, self.device = cfg, int(inter), float(eps), device
         self.lc = layer_cfg(cfg)
         self.dt = self.lc.torch_dtype
-        self._prefill: Dict[Tuple[int, int], CarriedRows] = {}   # by rows and chunk length
+        self._prefill: Dict[int, CarriedRows] = {}   # by rows, rounded up: _prefill_rows
         self._stage1: Optional[CarriedRows] = None
 
     def _cache_pair(self, rows: int) -> Tuple[torch.Tensor, torch.Tensor]:
@@ -90,30 +90,55 @@ class Diagnostics:
         if tokens < 2:
             raise ValueError("a chunk needs at least two tokens")
 
+    # Buffers for t rows: kept by a power of two of rows, from 1024 on, so that whatever lengths an
+    # object is given it keeps less than twice the rows of the largest set (a set for each length
+    # would grow without end, and one set that grows would give memory back that work on another
+    # stream or a captured graph still uses).  A set is its rows of h, x, q, attn and g, and up to
+    # 67 MB of scratch for partial sums.  Every row is its own position; -rows turns keys back.
+    def _prefill_rows(self, t: int) -> CarriedRows:
+        rows = max(1024, 1 << (t - 1).bit_length())
+        cr = self._prefill.get(rows)
+        if cr is None:   # every row recomputed: all but one "selected" and one closing row
+            sub = self.cfg.with_(n_chunks=1, chunk_len=rows - 1, n_query=1)
+            cr = CarriedRows(sub, self.inter, self.eps, self.device, k=rows - 1)
+            cr.rows[:rows - 1] = torch.arange(rows - 1, dtype=torch.int32, device=self.device)
+            cr.neg_rows = -cr.rows
+            cr.in_chunks = {}   # chunk length -> positions inside chunks, and their negatives
+            cr.views = {}       # (t, chunk length) -> what a call takes of the buffers
+            self._prefill[rows] = cr
+        return cr
+
     # the same for chunks of chunk_len tokens, the last one with what is left, into given tensors:
     # every one of their T rows is written before anything reads it, and the inverse rotation runs
     # in place
     def _prefill_into(self, embed_rows: torch.Tensor, blocks: Sequence[Block],
                       k: List[torch.Tensor], v: List[torch.Tensor], chunk_len: int) -> None:
         t = embed_rows.shape[0]
-        cr = self._prefill.get((t, chunk_len))
-        if cr is None:   # every row recomputed: T - 1 "selected" rows and one closing row
-            sub = self.cfg.with_(n_chunks=1, chunk_len=t - 1, n_query=1)
-            cr = CarriedRows(sub, self.inter, self.eps, self.device, k=t - 1)
-            cr.rows[:t - 1] = torch.arange(t - 1, dtype=torch.int32, device=self.device)
-            cr.pos = cr.rows % chunk_len                            # inside the chunks
-            cr.neg_pos = -cr.pos
-            need = api.pkv_chunk_attn_workspace_bytes(self.lc, t, chunk_len)
-            if need > cr.ws.numel():
-                cr.ws = torch.empty(need, dtype=torch.uint8, device=self.device)
-            self._prefill[t, chunk_len] = cr
-        api.pkv_gather_rows(embed_rows.contiguous(), cr.rows, cr.h)
+        cr = self._prefill_rows(t)
+        if (t, chunk_len) not in cr.views:
+            if len(cr.views) == 64:   # views are cheap to make again
+                cr.views.clear()
+            pos, neg_pos = cr.rows, cr.neg_rows
+            if t > chunk_len:
+                if chunk_len not in cr.in_chunks:
+                    inside = cr.rows % chunk_len
+                    cr.in_chunks[chunk_len] = inside, -inside
+                pos, neg_pos = cr.in_chunks[chunk_len]
+            cr.views[t, chunk_len] = (
+                cr.h[:t], cr.rows[:t], pos[:t], neg_pos[:t],
+                api.pkv_chunk_attn_workspace_bytes(self.lc, t, chunk_len))
+        h, rows, pos, neg_pos, need = cr.views[t, chunk_len]
+        # the layers' scratch is largest with all rows of the set; the attention's depends on the
+        # chunks and may be more
+        ws = cr.ws if need <= cr.ws.numel() else torch.empty(need, dtype=torch.uint8,
+                                                             device=self.device)
+        api.pkv_gather_rows(embed_rows.contiguous(), rows, h)
         for li, b in enumerate(blocks):   # the last one stops at its cache rows
             L = {name: b[name] for name in BLOCK_WEIGHTS + VARIANT_WEIGHTS if name in b}
             L["k_cache"], L["v_cache"] = k[li], v[li]
-            cr._layer(L, cr.pos, t, score=None, caches_only=li == len(blocks) - 1,
-                      chunks=(cr.rows, chunk_len))
-        api.pkv_rope_restore_layers(self.lc, k, k, cr.neg_pos)   # inverse rotation
+            cr._layer(L, pos, t, score=None, caches_only=li == len(blocks) - 1,
+                      chunks=(rows, chunk_len), ws=ws)
+        api.pkv_rope_restore_layers(self.lc, k, k, neg_pos)   # inverse rotation
 
     def chunk_isolated_cache(self, embed: torch.Tensor, blocks: Sequence[Block],
                              chunk_len: int):
@@ -133,7 +158,7 @@ class Diagnostics:
         for a in range(0, end, group):   # straight into the group's rows of the whole
             b = min(a + group, end)
             self._prefill_into(embed[a:b], blocks, [x[a:b] for x in ks], [x[a:b] for x in vs],
-                               min(chunk_len, b - a))
+                               chunk_len)
         return [x[:end] for x in ks], [x[:end] for x in vs]
 
     def full_prefill_cache(self, embed: torch.Tensor, blocks: Sequence[Block]):

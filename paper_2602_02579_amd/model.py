@@ -98,7 +98,8 @@ class CarriedRows:
     # all of the caches, in chunks that attend within themselves, ``rows`` counting inside them
     def _layer(self, L: Dict[str, torch.Tensor], rows: torch.Tensor, cnt: int,
                score: Optional[bool], caches_only: bool = False,
-               scores_only: bool = False, chunks=None) -> None:
+               scores_only: bool = False, chunks=None,
+               ws: Optional[torch.Tensor] = None) -> None:
         # K and V go straight to their cache rows.  The score of Stage I reads only the context
         # rows of the key cache, which the query rows' own keys (stored behind the context) do
         # not touch.
@@ -106,7 +107,7 @@ class CarriedRows:
         api.pkv_layer_rows(
             self.lc, self.h, self.x, self.q, self.attn, self.g, cnt, L, VARIANT_WEIGHTS,
             L["k_cache"], L["v_cache"], rows, rows if chunks is None else chunks[0], self.eps,
-            self.ws, score=None if score is None else self.score,
+            self.ws if ws is None else ws, score=None if score is None else self.score,
             lse_ctx=self.lse_ctx if fused else None, n_ctx=self.n, accumulate=bool(score),
             chunk_len=0 if chunks is None else chunks[1],
             stop=api.LAYER_TO_CACHES if caches_only else
