@@ -501,8 +501,8 @@ size_t pkv_glue_workspace_bytes(int32_t dtype, int64_t m, int64_t k_in,
  * A model's layers are tens of small launches, and a caller in an interpreted language spends
  * more on marshalling each than the launch costs.  `call` is a HOST struct read during the
  * call.  The first call that fails ends it with its status; what was enqueued before stays.
- * In fp32 the normalisations are part of the launches that read them, where x is then not
- * written (their sums of squares in another order: a unit or two in the last place).
+ * In fp32 a launch may normalise short rows itself: that normalisation then does not write x,
+ * and sums the squares in another order than pkv_rmsnorm_rows (results to fp32 rounding).
  *   score == NULL:     no score.
  *   lse_ctx == NULL:   pkv_query_score over cache rows 0 .. n_ctx - 1, then the attention;
  *   otherwise:         pkv_sparse_row_attn_ctx_lse with it, then pkv_query_score_lse.

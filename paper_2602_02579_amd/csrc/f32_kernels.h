@@ -21,10 +21,12 @@ struct F32GemmParams {
     const int32_t* row_pos;    // [m]
     const int32_t* dst_row;    // [m] or null: rows of K and V
     const float* bias[3];      // or null
-    // projection and gated: gains [k] of an RMS norm of the rows of x before the product, or null
+    // gains [k] of an RMS norm of the rows of x before the product, where norm_f32_pays, or null
     const float* norm_w;
     float norm_eps;
 };
+// projection and gated: the rows normalised inside the launch cost less than by one of their own
+bool norm_f32_pays(int mode, const F32GemmParams& p);
 pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& tab,
                            hipStream_t st);
 // pointers of a linear layer allow 16-byte accesses (null counts as aligned), rows fit the grid

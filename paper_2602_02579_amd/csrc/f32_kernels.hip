@@ -67,8 +67,8 @@ template <int KS>
 constexpr int kTileRows = kTM / KS;
 
 // NORM: the rows are RMS-normalised on their way into LDS.  The workgroup first goes over its rows for
-// the sums of squares; in a decoder layer that costs less than a launch of its own for the rows
-// and their round trip (a model of three layers of 256 inputs at 700 tokens: 236 -> 215 us a pass).
+// the sums of squares; for short rows that costs less than a launch of its own for the rows and
+// their round trip (norm_f32_pays).
 template <int MODE, int KS, bool NORM>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, RopeTable tab) {
     constexpr int TM = kTileRows<KS>, kLoads = (TM + kTN) / 8;
@@ -581,25 +581,47 @@ bool f32_tiles_supported(const pkv_layer_cfg& cfg) {
            (cfg.head_dim == 32 || cfg.head_dim == 64 || cfg.head_dim == 128);
 }
 
+namespace {
+
+int gemm_f32_column_tiles(int mode, const F32GemmParams& p) {
+    return mode == kF32Rope ? p.tile_begin[3]
+                            : (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
+}
+// tiles of 16 rows that all run at once (four workgroups per CU)
+bool gemm_f32_low(int mode, const F32GemmParams& p) {
+    return ceil_div(p.m, kTileRows<4>) * gemm_f32_column_tiles(mode, p) <= 1024;
+}
+
+}  // namespace
+
+// Every tile of columns goes over the rows again for their sums of squares.  On tiles of 16 rows that is
+// two chains of k / 128 loads per thread, against 3 us for a launch of its own (normalisation and
+// products apart -> together, us, a projection of K and V / of Q, K and V in a layer call: 256
+// inputs, 209 rows 15.6 -> 13.1 / 18.7 -> 17.6, 768 inputs, 65 rows 15.5 -> 13.1 / 18.8 -> 17.2; 1024,
+// 25 rows 15.7 -> 13.2 / 20.1 -> 22.3; 2048, 13 rows 17.0 -> 19.1 / 23.4 -> 28.5).  Tiles of 64 rows make
+// eight such chains (256 inputs, 1261 rows 41 -> 45; 2048, 761 rows, K and V 54 -> 89).  The gated layer
+// has twice the weights to come behind the chain: whole layers of 256 inputs, 26 rows 27.6 -> 25.6, 145
+// rows 32.5 -> 31.5, of 384, 36 rows 34.3 -> 33.5, of 512 31 -> 32 at 2 rows and level at 3 to 51.
+bool norm_f32_pays(int mode, const F32GemmParams& p) {
+    return p.k <= (mode == kF32Rope ? 768 : 384) && gemm_f32_low(mode, p);
+}
+
 pkv_status launch_gemm_f32(int mode, const F32GemmParams& p, const RopeTable& tab, hipStream_t st) {
-    int n_ct;
-    if (mode == kF32Rope) n_ct = p.tile_begin[3];
-    else n_ct = (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
-    // tiles of 16 rows that all run at once (four workgroups per CU)
-    const bool low = ceil_div(p.m, kTileRows<4>) * n_ct <= 1024;
+    const bool low = gemm_f32_low(mode, p);
     const int64_t rows = ceil_div(p.m, low ? kTileRows<4> : kTM);
     if (rows > 65535) return PKV_ERR_SHAPE;
-    const dim3 grid((unsigned)n_ct, (unsigned)rows);
-#define PKV_GEMM_F32(MODE, NORM)                                                               \
-    {                                                                                          \
-        if (low) hipLaunchKernelGGL((gemm_f32_kernel<MODE, 4, NORM>), grid, dim3(256), 0, st, p, tab); \
-        else hipLaunchKernelGGL((gemm_f32_kernel<MODE, 1, NORM>), grid, dim3(256), 0, st, p, tab);     \
-    }
-    if (mode == kF32Rope && p.norm_w) PKV_GEMM_F32(kF32Rope, true)
-    else if (mode == kF32Rope) PKV_GEMM_F32(kF32Rope, false)
-    else if (mode == kF32Plain) PKV_GEMM_F32(kF32Plain, false)
-    else if (p.norm_w) PKV_GEMM_F32(kF32Gated, true)
-    else PKV_GEMM_F32(kF32Gated, false)
+    if (p.norm_w && (!low || mode == kF32Plain)) return PKV_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)gemm_f32_column_tiles(mode, p), (unsigned)rows);
+#define PKV_GEMM_F32(MODE, KS, NORM)                                                             \
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE, KS, NORM>), grid, dim3(256), 0, st, p, tab)
+    if (mode == kF32Rope && p.norm_w) PKV_GEMM_F32(kF32Rope, 4, true);
+    else if (mode == kF32Rope && low) PKV_GEMM_F32(kF32Rope, 4, false);
+    else if (mode == kF32Rope) PKV_GEMM_F32(kF32Rope, 1, false);
+    else if (mode == kF32Plain && low) PKV_GEMM_F32(kF32Plain, 4, false);
+    else if (mode == kF32Plain) PKV_GEMM_F32(kF32Plain, 1, false);
+    else if (p.norm_w) PKV_GEMM_F32(kF32Gated, 4, true);
+    else if (low) PKV_GEMM_F32(kF32Gated, 4, false);
+    else PKV_GEMM_F32(kF32Gated, 1, false);
 #undef PKV_GEMM_F32
     return launch_status();
 }

@@ -437,6 +437,7 @@ bool norm_proj_f32(const pkv_layer_cfg& cfg, const void* hidden, const void* nor
     fill_rope_table(&tab, cfg.head_dim, (double)cfg.rope_theta);
     F32GemmParams p = f32_proj_params(cfg, hidden, nullptr, row_pos, wq, wk, wv, ex, dst_row,
                                       q_out, k_out, v_out, m);
+    if (!norm_f32_pays(kF32Rope, p)) return false;
     p.norm_w = (const float*)norm_w;
     p.norm_eps = eps;
     *status = launch_gemm_f32(kF32Rope, p, tab, st);

@@ -325,18 +325,17 @@ pkv_status launch_linear_rows(int dtype, bool gated, const void* x, const void* 
 bool norm_swiglu_f32(const void* x, const void* norm_w, float eps, const void* w_gate,
                      const void* w_up, void* y, int64_t m, int64_t k_in, int64_t n_out,
                      hipStream_t st, pkv_status* status) {
-    // what the two calls refuse goes to them; few rows over many inputs have the wave per output,
-    // which is the faster one there by more than the launch that is saved
+    // what the two calls refuse goes to them
     if (m <= 0 || k_in <= 0 || n_out <= 0 || k_in % 8 || n_out % 8 || k_in > 16384 ||
         n_out > (1 << 30) || !(eps >= 0.f) || !std::isfinite(eps) || !x || !norm_w || !w_gate ||
-        !w_up || !y || !aligned16(norm_w) || !linear_f32_supported(x, w_gate, w_up, nullptr, y, m) ||
-        !(k_in <= 512 || linear_f32_pays(true, m, k_in, n_out)))
+        !w_up || !y || !aligned16(norm_w) || !linear_f32_supported(x, w_gate, w_up, nullptr, y, m))
         return false;
     F32GemmParams p = {};
     p.x = (const float*)x;
     p.w[0] = (const float*)w_gate; p.w[1] = (const float*)w_up;
     p.out[0] = (float*)y;
     p.m = (int)m; p.k = (int)k_in; p.n_out = (int)n_out;
+    if (!norm_f32_pays(kF32Gated, p)) return false;
     p.norm_w = (const float*)norm_w;
     p.norm_eps = eps;
     *status = launch_gemm_f32(kF32Gated, p, RopeTable{}, st);

@@ -1,6 +1,6 @@
 """A whole decoder layer in one call: what its host checks refuse, and (on the GPU) the same bits as
-the calls it stands for (fp32: the same values to rounding), in every form: with and without block variants, both ways of scoring,
-chunks, and the three places where it may stop."""
+the calls it stands for (fp32: the same values to rounding), in every form: with and without block
+variants, both ways of scoring, chunks, and the three places where it may stop."""
 
 import ctypes
 import os
@@ -115,11 +115,13 @@ def test_same_bits_as_the_calls(gpu_device, dtype, variant, form):
     for name in a:
         if dtype == "bf16":
             assert torch.equal(a[name], b[name]), name
-        elif name != "x":
-            # fp32: the normalisations' sums in another order and, in the gated layer of so few
-            # rows, another kernel's: a few units of 2^-24 of sums of at most 128 terms of order
-            # one, twice (x is then not written)
-            assert (a[name] - b[name]).abs().max() <= 2e-5 * max(1.0, b[name].abs().max()), name
+        elif name != "x":      # x is not written where a launch normalises the rows itself
+            # fp32, the normalisations' sums in another order and, in the gated layer of so few rows,
+            # another kernel's.  One stage: a sum of 64 products of rows that are off by the
+            # order of 64 squares, (64 + 32) units of 2^-24 at most; scores, attention and what
+            # follows have three more sums of at most 150 terms behind it.
+            tol = 96 * 2.0 ** -24 if name in ("q", "k", "v") else 2e-5
+            assert (a[name] - b[name]).abs().max() <= tol * max(1.0, b[name].abs().max()), name
 
 
 @pytest.mark.gpu
