@@ -321,6 +321,25 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg,
                                void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * Which kernel that call runs for m rows over n_keys keys: a pure host function of the sizes, with
+ * the scratch of pkv_workspace_bytes (and negative for sizes that the call refuses).  For
+ * programs that place their sizes, and for tests of the choice; every kernel gives the same
+ * results to rounding.
+ */
+typedef enum {
+    PKV_ATTN_GENERIC = 0,        /* a workgroup per (row, head) */
+    PKV_ATTN_F32 = 1,            /* fp32 matrix instructions, 16 columns (row, head) */
+    PKV_ATTN_TILES_64 = 2,       /* bf16, head_dim 64 */
+    PKV_ATTN_SHORT = 3,          /* bf16, head_dim 128 from here on: short caches */
+    PKV_ATTN_PAIRS = 4,          /* 128 columns, two groups of waves share the keys */
+    PKV_ATTN_ONE_JOB = 5,        /* 256 columns, one job per CU at most */
+    PKV_ATTN_QUEUE = 6,          /* 256 columns, a queue of jobs, tile by tile */
+    PKV_ATTN_QUEUE_BY_WEIGHT = 7 /* the same, the heaviest first */
+} pkv_attn_kernel;
+
+int32_t pkv_sparse_row_attn_kernel(const pkv_layer_cfg* cfg, int64_t n_keys, int64_t m);
+
+/*
  * Attention of rows inside their own chunks (paper: Sec. 2 - the method's input are chunks
  * prefilled one by one).  The m rows, and the m cache rows, are consecutive chunks of
  * chunk_len, the last one with what is left; row i attends the rows of its chunk up to

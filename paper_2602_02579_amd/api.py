@@ -24,7 +24,8 @@ __all__ = ["LayerCfg", "PkvError", "load_library", "library_path",
            "pkv_sparse_row_attn_ctx_lse_workspace_bytes",
            "pkv_topk_select", "pkv_gather_qkv_proj", "pkv_gather_qkv_proj_ex",
            "pkv_gather_qkv_proj_scatter", "pkv_scatter_kv",
-           "pkv_sparse_row_attn", "pkv_chunk_attn", "pkv_chunk_attn_workspace_bytes",
+           "pkv_sparse_row_attn", "pkv_sparse_row_attn_kernel", "pkv_chunk_attn",
+           "pkv_chunk_attn_workspace_bytes",
            "pkv_rmsnorm_rows", "pkv_gather_rows", "pkv_linear_rows", "pkv_swiglu_rows",
            "LayerCall", "pkv_layer_rows", "pkv_glue_workspace_bytes",
            "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
@@ -43,7 +44,7 @@ EXPORTED_SYMBOLS = [
     "pkv_glue_workspace_bytes", "pkv_query_score_lse", "pkv_sparse_row_attn_ctx_lse",
     "pkv_sparse_row_attn_ctx_lse_workspace_bytes", "pkv_chunk_attn",
     "pkv_chunk_attn_workspace_bytes", "pkv_layer_rows", "pkv_rope_restore_layers",
-    "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
+    "pkv_sparse_row_attn_kernel", "pkv_workspace_bytes", "pkv_status_string", "pkv_version",
 ]
 
 
@@ -162,6 +163,8 @@ def load_library() -> ctypes.CDLL:
                                    ctypes.c_size_t, vp]
     lib.pkv_rope_restore_layers.argtypes = [cfgp, vp, vp, ctypes.c_int32, i32p, i64, i64, vp]
     lib.pkv_layer_rows.argtypes = [cfgp, ctypes.POINTER(LayerCall), vp]
+    lib.pkv_sparse_row_attn_kernel.argtypes = [cfgp, i64, i64]
+    lib.pkv_sparse_row_attn_kernel.restype = ctypes.c_int32
     lib.pkv_chunk_attn_workspace_bytes.argtypes = [cfgp, i64, i64]
     lib.pkv_chunk_attn_workspace_bytes.restype = ctypes.c_size_t
     i32 = ctypes.c_int32
@@ -466,6 +469,15 @@ def pkv_sparse_row_attn(cfg: LayerCfg, q: torch.Tensor, k_cache: torch.Tensor,
         _ptr(v_cache, dt, "v_cache"), _ptr(row_pos, torch.int32, "row_pos"),
         _ptr(out, dt, "out"), _ptr(lse_out, torch.float32, "lse_out"), m, n_keys,
         float(softmax_scale), wp, wb, _stream()))
+
+
+(ATTN_GENERIC, ATTN_F32, ATTN_TILES_64, ATTN_SHORT, ATTN_PAIRS, ATTN_ONE_JOB, ATTN_QUEUE,
+ ATTN_QUEUE_BY_WEIGHT) = range(8)
+
+
+def pkv_sparse_row_attn_kernel(cfg: LayerCfg, n_keys: int, m: int) -> int:
+    """Which kernel ``pkv_sparse_row_attn`` runs for these sizes; negative where it refuses them."""
+    return int(load_library().pkv_sparse_row_attn_kernel(cfg._ref, int(n_keys), int(m)))
 
 
 def pkv_chunk_attn_workspace_bytes(cfg: LayerCfg, m: int, chunk_len: int) -> int:

@@ -56,6 +56,7 @@ bool attn_pair_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m);
 pkv_status launch_attn_pair(AttnParams p, hipStream_t st);
 // compute units of the current device (0: could not be asked)
 int attn_cu_count();
+constexpr int kPlanCus = 256;   // and those that the plans reckon with
 // Where the pipelined kernel can take the values from: 1 = from a V^T copy made by a pre-pass
 // (PKV_ATTN_VT=1 in the environment), 0 = from the cache as it is (PKV_ATTN_VT=0), -1 = either,
 // the caller chooses by size.  Read at every call; for comparisons and tests.

@@ -210,6 +210,15 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg, const void* q,
                                   ws, (hipStream_t)stream);
 }
 
+int32_t pkv_sparse_row_attn_kernel(const pkv_layer_cfg* cfg, int64_t n_keys, int64_t m) {
+    if (check_cfg(cfg) != PKV_OK || m <= 0 || m > kMaxTokens || n_keys <= 0 ||
+        n_keys > kMaxTokens || m * (int64_t)cfg->n_q_heads > INT32_MAX ||
+        (cfg->dtype == PKV_BF16 &&
+         (int64_t)cfg->head_dim * ((n_keys + 63) / 64 * 64) * 2 >= ((int64_t)1 << 32)))
+        return -1;
+    return sparse_row_attn_kernel(*cfg, n_keys, m);
+}
+
 pkv_status pkv_chunk_attn(const pkv_layer_cfg* cfg, const void* q, const void* k, const void* v,
                           const int32_t* row_pos, void* out, int64_t m, int64_t chunk_len,
                           float softmax_scale, void* ws, size_t ws_bytes, void* stream) {

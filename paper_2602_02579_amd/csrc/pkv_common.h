@@ -131,6 +131,9 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                                   float scale, void* ws, hipStream_t st,
                                   int64_t ctx_keys = 0, float* lse_ctx_out = nullptr);
 
+// what a call of these sizes runs
+pkv_attn_kernel sparse_row_attn_kernel(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m);
+
 size_t chunk_attn_ws_bytes(const pkv_layer_cfg& cfg, int64_t m, int64_t chunk_len);
 pkv_status launch_chunk_attn(const pkv_layer_cfg& cfg, const void* q, const void* k,
                              const void* v, const int32_t* row_pos, void* out, int64_t m,

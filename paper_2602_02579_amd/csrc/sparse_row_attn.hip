@@ -495,8 +495,6 @@ constexpr int kMaxCtxRanges = 32;   // ranges per tile when a boundary is forced
 bool attn_plan_splits_at(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int64_t ctx_keys,
                          int* n_splits, int* split_len);
 
-constexpr int kPlanCus = 256;       // CUs that the plans reckon with
-
 // Estimated time (us) of the pipelined launch when every row tile's keys are cut into `sp`
 // ranges, without the merge, for one layout of the row limits (the limits live on the device;
 // the host weighs two layouts): `spread` = rows in position order with limits evenly over the
@@ -648,10 +646,16 @@ bool attn_plan_splits_at(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, in
     return false;
 }
 
+// the CUs there are; without a device (its host side alone can be asked) those of the plans
+int attn_cus() {
+    const int n_cu = attn_cu_count();
+    return n_cu ? n_cu : kPlanCus;
+}
+
 // a launch whose jobs all run at once, one per CU, needs no work queue
 bool attn_one_job_per_cu(const pkv_layer_cfg& cfg, int64_t m, int n_splits) {
     const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
-    return ceil_div(m, bm) * cfg.n_kv_heads * n_splits <= attn_cu_count();
+    return ceil_div(m, bm) * cfg.n_kv_heads * n_splits <= attn_cus();
 }
 
 size_t attn_partial_bytes(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m,
@@ -712,7 +716,7 @@ bool sparse_row_attn_ctx_lse_supported(const pkv_layer_cfg& cfg, int64_t n_keys,
 // heads, 2500 at the end of 16.5k: 187 -> 197).
 bool attn_order_pays(const pkv_layer_cfg& cfg, int64_t m, int n_splits) {
     const int64_t per_head = ceil_div(m, 256 / (cfg.n_q_heads / cfg.n_kv_heads)) * n_splits;
-    const int64_t jobs = per_head * cfg.n_kv_heads, n_cu = attn_cu_count();
+    const int64_t jobs = per_head * cfg.n_kv_heads, n_cu = attn_cus();
     return n_splits > 1 && cfg.n_kv_heads % 8 == 0 && per_head <= kOrderJobs &&
            2 * jobs > 3 * n_cu && (n_splits > 2 || jobs > 2 * n_cu);
 }
@@ -745,6 +749,66 @@ pkv_status launch_attn_lse_partials(const pkv_layer_cfg& cfg, const void* q,
                                : launch_attn_mfma<64, false>(p, st);
 }
 
+namespace {
+
+// What a call runs, from its sizes alone
+struct AttnChoice {
+    pkv_attn_kernel kernel;
+    bool nat_v;                // values from the cache as it is, not from a V^T copy
+    int n_splits, split_len;   // ranges of the keys
+};
+
+AttnChoice attn_choose(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int64_t ctx_keys) {
+    const int d = cfg.head_dim;
+    AttnChoice c = {PKV_ATTN_GENERIC, false, 1, (int)pad64(n_keys)};
+    if (!mfma_attn_supported(cfg)) {
+        if (f32_tiles_supported(cfg) &&
+            ceil_div(m * (cfg.n_q_heads / cfg.n_kv_heads), 16) < (1 << 30) &&
+            cfg.n_kv_heads <= 65535)
+            c.kernel = PKV_ATTN_F32;
+        return c;
+    }
+    if (ctx_keys > 0) attn_plan_splits_at(cfg, n_keys, m, ctx_keys, &c.n_splits, &c.split_len);
+    else attn_plan_splits(cfg, n_keys, m, &c.n_splits, &c.split_len);
+    c.kernel = PKV_ATTN_TILES_64;
+    if (d != 128) return c;
+    // the work queue, which a launch with no more jobs than CUs does without
+    const bool queue = !attn_one_job_per_cu(cfg, m, c.n_splits);
+    c.kernel = queue ? PKV_ATTN_QUEUE : PKV_ATTN_ONE_JOB;
+    // The pipelined kernels can transpose the values on their way out of LDS instead of
+    // reading a V^T copy made here.  The loop then issues half as many bytes per LDS
+    // instruction and takes 2.0 % more time; the copy costs its bytes at ~5.5 TB/s plus a
+    // launch (with a work queue it also clears the counters, a launch that is needed
+    // anyway).  The copy is skipped when that is the cheaper side (measured, no copy ->
+    // copy: 3404 rows over 32k keys 801 -> 809 us, 6681 over 16k 745 -> 739, 6681 over
+    // 32k 1444 -> 1438, 13235 over 32k 2722 -> 2691, 26470 over 131k 21.5 -> 21.1 ms).
+    const int src = attn_dma128_v_source();
+    if (src <= 0 && ctx_keys <= 0 && attn_short_applies(cfg, n_keys, m, c.n_splits)) {
+        c.kernel = PKV_ATTN_SHORT;
+        c.nat_v = true;
+        return c;
+    }
+    if (src < 0) {
+        const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
+        const double copy_us = 3.0 + (double)pad64(n_keys) * cfg.n_kv_heads * d * 4.0 / 5.5e6;
+        const double main_us = 1.68 * (double)ceil_div(m, bm) * cfg.n_kv_heads *
+                               (double)(pad64(n_keys) / 64) * (m > 768 ? 0.5 : 1.0) / 256.0;
+        c.nat_v = copy_us - (queue ? 4.0 : 0.0) > 0.020 * main_us;
+    } else {
+        c.nat_v = src == 0;
+    }
+    if (!c.nat_v) return c;
+    if (ctx_keys <= 0 && attn_pair_applies(cfg, n_keys, m)) c.kernel = PKV_ATTN_PAIRS;
+    else if (queue && attn_order_pays(cfg, m, c.n_splits)) c.kernel = PKV_ATTN_QUEUE_BY_WEIGHT;
+    return c;
+}
+
+}  // namespace
+
+pkv_attn_kernel sparse_row_attn_kernel(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m) {
+    return attn_choose(cfg, n_keys, m, 0).kernel;
+}
+
 pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
                                   const void* k_cache, const void* v_cache,
                                   const int32_t* row_pos, void* out,
@@ -755,61 +819,26 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
     const int d = cfg.head_dim;
     if (lse_ctx_out && !sparse_row_attn_ctx_lse_supported(cfg, n_keys, m, ctx_keys))
         return PKV_ERR_UNSUPPORTED;
+    const AttnChoice choice = attn_choose(cfg, n_keys, m, lse_ctx_out ? ctx_keys : 0);
     if (mfma_attn_supported(cfg)) {
         const int n_pad = (int)pad64(n_keys);
         bf16_t* vt = (bf16_t*)ws;
-        int n_splits = 1, split_len = n_pad;
-        if (lse_ctx_out)
-            attn_plan_splits_at(cfg, n_keys, m, ctx_keys, &n_splits, &split_len);
-        else
-            attn_plan_splits(cfg, n_keys, m, &n_splits, &split_len);
-        // the work-queue counters, which a launch with no more jobs than CUs does without
-        int* queue = nullptr;
-        if (d == 128 && !attn_one_job_per_cu(cfg, m, n_splits))
-            queue = reinterpret_cast<int*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys));
-        // The pipelined kernels can transpose the values on their way out of LDS instead of
-        // reading a V^T copy made here.  The loop then issues half as many bytes per LDS
-        // instruction and takes 2.0 % more time; the copy costs its bytes at ~5.5 TB/s plus a
-        // launch (with a work queue it also clears the counters, a launch that is needed
-        // anyway).  The copy is skipped when that is the cheaper side (measured, no copy ->
-        // copy: 3404 rows over 32k keys 801 -> 809 us, 6681 over 16k 745 -> 739, 6681 over
-        // 32k 1444 -> 1438, 13235 over 32k 2722 -> 2691, 26470 over 131k 21.5 -> 21.1 ms).
-        bool nat_v = false, short_job = false;
-        if (d == 128) {
-            const int src = attn_dma128_v_source();
-            short_job = src <= 0 && !lse_ctx_out && attn_short_applies(cfg, n_keys, m, n_splits);
-            if (short_job) {
-                nat_v = true;
-            } else if (src < 0) {
-                const int bm = 256 / (cfg.n_q_heads / cfg.n_kv_heads);
-                const double copy_us = 3.0 + (double)n_pad * cfg.n_kv_heads * d * 4.0 / 5.5e6;
-                const double main_us = 1.68 * (double)ceil_div(m, bm) * cfg.n_kv_heads *
-                                       (double)(n_pad / 64) * (m > 768 ? 0.5 : 1.0) / 256.0;
-                nat_v = copy_us - (queue ? 4.0 : 0.0) > 0.020 * main_us;
-            } else {
-                nat_v = src == 0;
-            }
-        }
-        const bool pair_job = d == 128 && nat_v && !short_job && !lse_ctx_out &&
-                              attn_pair_applies(cfg, n_keys, m);
-        const bool ordered = nat_v && queue && !short_job && !pair_job &&
-                             attn_order_pays(cfg, m, n_splits);
-        if (nat_v) {
-            if (queue && !short_job && !pair_job && !ordered)
-                hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue,
-                                   cfg.n_kv_heads);
-        } else {
+        const bool by_weight = choice.kernel == PKV_ATTN_QUEUE_BY_WEIGHT;
+        int* const queue = by_weight || choice.kernel == PKV_ATTN_QUEUE
+            ? reinterpret_cast<int*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys)) : nullptr;
+        if (!choice.nat_v)
             hipLaunchKernelGGL(transpose_v_kernel,
                                dim3((unsigned)(n_pad / 64), (unsigned)(cfg.n_kv_heads * d / 64)),
                                dim3(256), 0, st, (const bf16_t*)v_cache, vt, (int)n_keys, n_pad,
                                cfg.n_kv_heads, d, queue, cfg.n_kv_heads);
-        }
+        else if (choice.kernel == PKV_ATTN_QUEUE)
+            hipLaunchKernelGGL(attn_clear_kernel, dim3(1), dim3(64), 0, st, queue, cfg.n_kv_heads);
         if (launch_status() != PKV_OK) return PKV_ERR_LAUNCH;
         AttnParams p = {};
         p.q = (const bf16_t*)q;
         p.k = (const bf16_t*)k_cache;
         p.vt = vt;
-        p.v = nat_v ? (const bf16_t*)v_cache : nullptr;
+        p.v = choice.nat_v ? (const bf16_t*)v_cache : nullptr;
         p.row_pos = row_pos;
         p.out = (bf16_t*)out;
         p.lse = lse_out;
@@ -827,28 +856,27 @@ pkv_status launch_sparse_row_attn(const pkv_layer_cfg& cfg, const void* q,
         p.scale = scale;
         p.scale_log2 = scale * 1.4426950408889634f;
         if (d != 128) return launch_attn_mfma<64, true>(p, st);
-        if (short_job) return launch_attn_short(p, st);
-        if (pair_job) return launch_attn_pair(p, st);
+        if (choice.kernel == PKV_ATTN_SHORT) return launch_attn_short(p, st);
+        if (choice.kernel == PKV_ATTN_PAIRS) return launch_attn_pair(p, st);
         p.queue = queue;
-        p.dma_splits = n_splits;
-        p.dma_split_len = split_len;
+        p.dma_splits = choice.n_splits;
+        p.dma_split_len = choice.split_len;
         p.lse_ctx = lse_ctx_out;
         p.ctx_keys = (int)ctx_keys;
-        if (ordered) {
+        if (by_weight) {
             int* const order = reinterpret_cast<int*>(vt);   // no V^T copy is made: its room is free
             hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(256), 0, st, p, queue, order);
             if (launch_status() != PKV_OK) return PKV_ERR_LAUNCH;
             p.order = order;
         }
-        if (n_splits > 1) {
+        if (choice.n_splits > 1) {
             p.part_o = reinterpret_cast<float*>((unsigned char*)ws + attn_vt_bytes(cfg, n_keys) +
                                                 attn_queue_bytes(cfg));
-            p.part_lse = p.part_o + (size_t)n_splits * m * cfg.n_q_heads * d;
+            p.part_lse = p.part_o + (size_t)choice.n_splits * m * cfg.n_q_heads * d;
         }
         return launch_attn_dma128(p, st);
     }
-    if (f32_tiles_supported(cfg) && ceil_div(m * (cfg.n_q_heads / cfg.n_kv_heads), 16) < (1 << 30) &&
-        cfg.n_kv_heads <= 65535)
+    if (choice.kernel == PKV_ATTN_F32)
         return launch_attn_f32(cfg, (const float*)q, (const float*)k_cache, (const float*)v_cache,
                                row_pos, (float*)out, lse_out, m, n_keys, scale, st);
     const int block = d <= 64 ? 64 : (d <= 128 ? 128 : 256);

@@ -1,5 +1,5 @@
-// Step 5, head_dim 128, bf16, for launches of about one to two and a half jobs of 128 columns per CU:
-// contexts of a few thousand keys and the rows selected from them.
+// Step 5, head_dim 128, bf16, for contexts of a few thousand keys and the rows selected from them: up to
+// two and a half jobs of 128 columns per CU, from a fifth of one on where the keys are few.
 // (Paper: Sec. 4.3 Stage II - complete recomputation, but only for the selected
 // tokens; Sec. 5.3 - this attention over the long cache dominates the cost.)
 //
@@ -430,18 +430,31 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pair_kernel(AttnParams p) {
 
 }  // namespace
 
-// Measured at 32 / 8 and 40 / 8 heads, 1k to 33k keys, 150 to 4500 rows, spread over the keys (ranges
-// and queue against this).  Fewer than one job per CU: the launch lasts as long as its longest job,
-// 0.6 us per 64 keys and 15 besides, so jobs have to be many or short (256 jobs over 4k keys 58 ->
-// 54 us, over 8k 93 -> 96).  More than two and a half: the wider tiles read the keys less often (3300
-// rows over 8k, 832 jobs: 205 -> 221).  Beyond 12k keys the two are level (1702 rows over 16.5k: 220
-// and 224; 2000 over 12k 218 -> 190).  Rows that all sit at the end of the cache gain more (1500 over
-// 8k 227 -> 188) but for counts just above a multiple of 256 jobs (1200 over 12k 238 -> 268).
+// Against ranges and queue at 400 sizes, heads 8 / 1 to 96 / 8, each with rows spread over the keys, as
+// a selection has them, and with all rows at the end of the cache (us, spread / end).
+// Up to one job per CU: the launch lasts as long as its longest job, 0.6 us per 64 keys and 15 besides,
+// so jobs have to be many or short: n_keys <= 20 jobs (32 / 8, 56 jobs over 1118 keys 24 -> 20 / 27 -> 21,
+// 192 over 3411 50 -> 44 / 57 -> 49; 256 over 8k 93 -> 96).
+// Up to two and a half: a CU's later, lighter jobs fill up what its first one leaves (280 jobs over 2.3k
+// 51 -> 36 / 51 -> 58, 448 over 4.8k 102 -> 80 / 120 -> 122, 600 over 10k 235 -> 216 / 400 -> 369); beyond, the
+// wider tiles read the keys less often (832 over 8k: 205 -> 221), and beyond 12k keys the two are
+// level (1702 rows over 16.5k: 220 and 224).  Rows at the end, all of one weight, lose where one more
+// job per CU is begun for a few of them, so the gain with spread rows has to be worth it.  It is not
+// - for a third job per CU where the wide tiles are one per CU (40 / 8, 520 over 4.8k 105 -> 100 /
+//   130 -> 172; 96 / 8, 536 over 10.7k 201 -> 199 / 336 -> 418),
+// - for groups that leave more than a twentieth of the 128 columns empty (96 / 8, 264 over 4k 57 -> 54 /
+//   75 -> 108, 400 over 1.1k 32 -> 32 / 34 -> 39),
+// - for large groups, whose jobs have few rows, over few keys (64 / 8, 480 over 1.1k 35 -> 37 / 35 -> 37).
 bool attn_pair_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m) {
     const int group = cfg.n_q_heads / cfg.n_kv_heads;
     if (group > kCols || n_keys > 12288) return false;
-    const int64_t jobs = ceil_div(m, kCols / group) * cfg.n_kv_heads;
-    return jobs <= 656 && (jobs > 256 || 20 * jobs >= n_keys);
+    const int rows = kCols / group;
+    const int64_t jobs = ceil_div(m, rows) * cfg.n_kv_heads;
+    if (jobs <= kPlanCus) return n_keys <= 20 * jobs;
+    const int64_t wide = ceil_div(m, 2 * kCols / group) * cfg.n_kv_heads;
+    return 2 * jobs <= 5 * kPlanCus && !(jobs > 2 * kPlanCus && wide <= kPlanCus) &&
+           20 * rows * group >= 19 * kCols &&
+           (group <= 5 || 2 * jobs <= 3 * kPlanCus || n_keys >= 1536);
 }
 
 pkv_status launch_attn_pair(AttnParams p, hipStream_t st) {

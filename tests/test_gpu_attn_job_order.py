@@ -5,6 +5,7 @@ tiles that the last row does not fill and caches that end inside a tile."""
 import numpy as np
 import pytest
 
+from paper_2602_02579_amd import api
 from tests.test_gpu_attn_short_ranges import check, planned_ranges
 from tests.test_gpu_kernels import lcfg, rnd
 
@@ -17,7 +18,9 @@ pytestmark = pytest.mark.gpu
     (640, 8001, 40, 8, 4),        # 250 of 256 columns; the cache ends in a tile of 64 keys
     (1030, 10001, 16, 16, 5)])    # heads of their own, 400 jobs
 def test_ranges_by_weight(gpu_device, m, n_keys, hq, hkv, ranges, order):
-    assert planned_ranges(lcfg("bf16", hq, hkv, 128), n_keys, m) == ranges
+    cfg = lcfg("bf16", hq, hkv, 128)
+    assert planned_ranges(cfg, n_keys, m) == ranges
+    assert api.pkv_sparse_row_attn_kernel(cfg, n_keys, m) == api.ATTN_QUEUE_BY_WEIGHT
     q, kc, vc = (rnd(s, shape, "bf16") for s, shape in
                  ((1, (m, hq, 128)), (2, (n_keys, hkv, 128)), (3, (n_keys, hkv, 128))))
     if order == "end":
