@@ -21,6 +21,7 @@ struct AttnParams {
     const int* order;        // [n_tiles * dma_splits] or null: a kv head's jobs, the heaviest first
     int* queue;              // [hkv] next unclaimed row tile per kv head, zero before the
                              // launch, or nullptr: one job per workgroup (pipelined kernel)
+    int dealt;               // workgroups whose first job goes by their number: all (the grid) or 0
     float* part_o;           // [dma_splits, m, hq, D] normalised partial outputs, and
     float* part_lse;         // [dma_splits, m, hq] their log-sum-exp (pipelined kernel with
                              // dma_splits > 1 only)
@@ -44,7 +45,7 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // merge of their key ranges (sparse_row_attn_dma.hip)
 pkv_status launch_attn_dma128(const AttnParams& p, hipStream_t st);
 pkv_status launch_attn_w8_main(const AttnParams& p, hipStream_t st);
-pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st);
+pkv_status launch_attn_w8n_main(AttnParams p, int n_cu, hipStream_t st);
 // sparse_row_attn_short.hip: up to 1024 keys, at most one job of 128 columns per CU; n_splits is
 // what the pipelined kernel would cut the keys into
 bool attn_short_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m, int n_splits);

@@ -122,24 +122,27 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
     const int g4 = lane >> 4;    // key octet of a 32-key sub-step this lane holds scores of
     const int l16 = lane & 15;   // its column in each of the wave's two 16-column blocks
 
-    // Work distribution: one workgroup per CU takes (kv head, row tile[, key range]) jobs,
-    // heaviest first (tiles from the last one on, or by p.order).  Its first one goes by its own number (256 workgroups at eight counters
-    // took 4 to 5 us to claim them: 1702 rows over 8k keys 132 -> 128 us); further ones it claims from one counter per kv head,
-    // preferring its home head (whose K/V its XCD's L2 holds) unless another head is kStealLag or
-    // more jobs behind.
+    // Work distribution: one workgroup per CU takes (kv head, row tile[, key range]) jobs, heaviest
+    // first (tiles from the last one on, or by p.order), claimed from one counter per kv head; it
+    // prefers its home head (whose K/V its XCD's L2 holds) unless another head is kStealLag or more
+    // jobs behind.  The first p.dealt jobs (one per workgroup, or none) go by the workgroup's number
+    // instead (deal_first_jobs).
     const int home = blockIdx.x % p.hkv;
     const int jobs_per_head = p.n_tiles * p.dma_splits;
-    // jobs of head h that went by number, and those claimed
+    // jobs of head h that went by number, and with those claimed (a division here, eight times a
+    // claim, took 1.4 us of every job)
+    const int dealt_each = p.dealt / p.hkv, dealt_rest = p.dealt % p.hkv;
+    auto dealt = [&](int h) { return dealt_each + (h < dealt_rest ? 1 : 0); };
     auto taken = [&](int h) {
-        return ((int)gridDim.x - h + p.hkv - 1) / p.hkv +
+        return dealt(h) +
                __hip_atomic_load(&p.queue[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-  for (bool first = true;; first = false) {
+  for (bool first = p.dealt > 0;; first = false) {
     if (tid == 0) {
-        // (the grid is no larger than the number of jobs, so there is one)
-        int job = first ? home * jobs_per_head + (int)(blockIdx.x / p.hkv) : -1;
+        // (the grid is no larger than the number of jobs, so there is a first one)
+        int head = home, j = first ? (int)(blockIdx.x / p.hkv) : jobs_per_head;
         // at most hkv failed claims: each one finds a head exhausted for good
-        for (int attempt = 0; attempt <= p.hkv && job < 0; ++attempt) {
+        for (int attempt = 0; attempt <= p.hkv && j >= jobs_per_head; ++attempt) {
             int best = home;
             int best_c = taken(home);
             if (best_c < jobs_per_head) best_c -= kStealLag;
@@ -153,11 +156,11 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
                 }
             }
             if (best_c >= jobs_per_head) break;   // nothing left anywhere
-            const int j = ((int)gridDim.x - best + p.hkv - 1) / p.hkv +
-                          atomicAdd(&p.queue[best], 1);
-            if (j < jobs_per_head) job = best * jobs_per_head + j;
+            head = best;
+            j = dealt(best) + atomicAdd(&p.queue[best], 1);
         }
-        if (p.order && job >= 0) job += p.order[job % jobs_per_head] - job % jobs_per_head;
+        int job = -1;
+        if (j < jobs_per_head) job = head * jobs_per_head + (p.order ? p.order[j] : j);
         s_job = job;
     }
     __syncthreads();
@@ -641,7 +644,20 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
 
 }  // namespace
 
-pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st) {
+// Whether a workgroup's first job goes by its number.  256 workgroups at the counters take 4 to 5 us to
+// claim theirs (claimed -> by number, us, spread rows: 128 / 8 heads, 559 rows over 1.2k keys 49 -> 44,
+// 32 / 32, 1141 over 13k in two ranges 184 -> 170, 28 / 4, 762 over 9.8k in four 84 -> 79).  Workgroups of
+// one number modulo eight share an XCD, and with kv heads that divide eight their first jobs lie 8 / hkv
+// apart: with two or four ranges some XCDs then begin with the fuller ranges only (8 / 2, 5614 over
+// 19.6k in two 231 -> 252, 16 / 2, 1459 over 17k in four 124 -> 131, 28 / 4, 1839 over 21k in two 259 ->
+// 273).  Fewer kv heads than XCDs and more than two jobs per CU: level or 2 % slower (28 / 4, 5096 over
+// 11.6k 366 -> 374).
+static bool deal_first_jobs(int hkv, int n_splits, int64_t jobs, int n_cu) {
+    if (hkv % 8 == 0) return true;
+    return jobs <= 2 * (int64_t)n_cu && !(hkv % 2 == 0 && (n_splits == 2 || n_splits == 4));
+}
+
+pkv_status launch_attn_w8n_main(AttnParams p, int n_cu, hipStream_t st) {
     static std::atomic<bool> configured{false};   // set twice at worst: the calls are idempotent
     if (!configured.load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_w8n_kernel<false>),
@@ -655,6 +671,8 @@ pkv_status launch_attn_w8n_main(const AttnParams& p, int n_cu, hipStream_t st) {
     }
     // one workgroup per CU (its LDS admits no second one), or per job if there are fewer
     const int64_t grid = std::min<int64_t>((int64_t)p.n_tiles * p.dma_splits * p.hkv, n_cu);
+    p.dealt = deal_first_jobs(p.hkv, p.dma_splits, (int64_t)p.n_tiles * p.dma_splits * p.hkv, n_cu)
+                  ? (int)grid : 0;
     if (p.v)   // the values as the cache holds them; p.vt is then not used
         hipLaunchKernelGGL(attn_w8n_kernel<true>, dim3((unsigned)grid), dim3(kThreads), kLdsBytes,
                            st, p);
