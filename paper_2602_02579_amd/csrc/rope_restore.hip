@@ -27,20 +27,25 @@ void fill_rope_table(RopeTable* t, int head_dim, double theta) {
 // and as long as their chain of loads, sines and stores.  Where even that leaves the chip idle the
 // heads of a token are dealt out too (blockIdx.z, heads_each of them): 512 tokens of 8 heads 4.7 ->
 // 3.8 us, 4001 5.9 -> 5.3; past one workgroup per CU the sines made again cost more than the shorter
-// chain gives (8192 tokens on 256, 512 and 1024 workgroups: 7.3, 7.5 and 7.8).  The launch itself
-// costs a single large cache 0.1 us more than one without layers (32768 tokens: 21.6 -> 21.7).
+// chain gives (8192 tokens on 256, 512 and 1024 workgroups: 7.3, 7.5 and 7.8).  Launches of a
+// single cache, and those that do not deal heads out, have neither in them: the pointers by the
+// layer's number and the heads between two variables cost 1 to 4 % (34.5k tokens of 8 heads 25.5 and
+// 25.1, 55k of 4 heads of 64 12.4 and 12.0).
+template <int L>
 struct RopeCaches {
-    const void* in[kRopeLayers];
-    void* out[kRopeLayers];
+    const void* in[L];
+    void* out[L];
 };
 
-template <typename T>
+template <typename T, int L, bool DEAL>
 __global__ __launch_bounds__(256) void rope_restore_kernel(
-    RopeCaches caches, const int32_t* __restrict__ pos, int64_t pos_base, int64_t n, int n_heads,
+    RopeCaches<L> caches, const int32_t* __restrict__ pos, int64_t pos_base, int64_t n, int n_heads,
     int heads_each, int head_dim, RopeTable tab) {
-    const T* const k_in = static_cast<const T*>(caches.in[blockIdx.y]);
-    T* const k_out = static_cast<T*>(caches.out[blockIdx.y]);
-    const int head0 = blockIdx.z * heads_each, head_end = min(n_heads, head0 + heads_each);
+    const int layer = L == 1 ? 0 : blockIdx.y;
+    const T* const k_in = static_cast<const T*>(caches.in[layer]);
+    T* const k_out = static_cast<T*>(caches.out[layer]);
+    const int head0 = DEAL ? blockIdx.z * heads_each : 0;
+    const int head_end = DEAL ? min(n_heads, head0 + heads_each) : n_heads;
     constexpr int V = Vec16<T>::N;
     typedef typename Vec16<T>::type vec_t;
     const int half = head_dim / 2;
@@ -100,6 +105,20 @@ __global__ __launch_bounds__(256) void rope_restore_kernel(
     }
 }
 
+template <typename T, int L, bool DEAL>
+static void rope_restore_launch(dim3 grid, const void* const* k_in, void* const* k_out,
+                                const int32_t* pos, int64_t pos_base, int64_t n,
+                                const pkv_layer_cfg& cfg, int heads_each, const RopeTable& tab,
+                                hipStream_t st) {
+    RopeCaches<L> caches = {};
+    for (unsigned l = 0; l < grid.y; ++l) {
+        caches.in[l] = k_in[l];
+        caches.out[l] = k_out[l];
+    }
+    hipLaunchKernelGGL((rope_restore_kernel<T, L, DEAL>), grid, dim3(256), 0, st, caches, pos, pos_base, n,
+                       cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
+}
+
 pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* const* k_in,
                                void* const* k_out, int n_layers, const int32_t* pos,
                                int64_t pos_base, int64_t n, hipStream_t st) {
@@ -117,20 +136,16 @@ pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* const* k_in
     const int64_t parts = std::min<int64_t>(
         cfg.n_kv_heads, std::max<int64_t>(1, kRopeFull / (grid * layers)));
     const int heads_each = (int)ceil_div(cfg.n_kv_heads, parts);
+    const bool bf16 = cfg.dtype == PKV_BF16, deal = heads_each < cfg.n_kv_heads;
     for (int l0 = 0; l0 < n_layers; l0 += kRopeLayers) {
-        RopeCaches caches = {};
         const int cnt = n_layers - l0 < kRopeLayers ? n_layers - l0 : kRopeLayers;
-        for (int l = 0; l < cnt; ++l) {
-            caches.in[l] = k_in[l0 + l];
-            caches.out[l] = k_out[l0 + l];
-        }
         const dim3 g((unsigned)grid, (unsigned)cnt, (unsigned)ceil_div(cfg.n_kv_heads, heads_each));
-        if (cfg.dtype == PKV_BF16)
-            hipLaunchKernelGGL(rope_restore_kernel<bf16_t>, g, dim3(block), 0, st, caches, pos,
-                               pos_base, n, cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
-        else
-            hipLaunchKernelGGL(rope_restore_kernel<float>, g, dim3(block), 0, st, caches, pos,
-                               pos_base, n, cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
+#define PKV_ROPE(T, L) (deal ? rope_restore_launch<T, L, true> : rope_restore_launch<T, L, false>)
+        auto* const launch = cnt == 1 ? (bf16 ? PKV_ROPE(bf16_t, 1) : PKV_ROPE(float, 1))
+                                      : (bf16 ? PKV_ROPE(bf16_t, kRopeLayers)
+                                              : PKV_ROPE(float, kRopeLayers));
+#undef PKV_ROPE
+        launch(g, k_in + l0, k_out + l0, pos, pos_base, n, cfg, heads_each, tab, st);
     }
     return launch_status();
 }
