@@ -29,6 +29,7 @@
 // is read from LDS six MFMAs before it, into a ring of eight registers quadruples.
 #include <atomic>
 
+#include "attn_tile.h"
 #include "score_common.h"
 
 namespace pkv {
@@ -42,19 +43,6 @@ constexpr int NS = 6;
 constexpr int kStage = kTile * D * 2;       // 16 KB
 constexpr int kLdsBytes = NS * kStage;
 
-__device__ __forceinline__ void dma16(const void* gbase, uint32_t voffset, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %2"
-        :
-        : "s"(lds_base), "v"(voffset), "s"(gbase)
-        : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

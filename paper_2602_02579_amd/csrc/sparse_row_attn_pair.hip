@@ -23,6 +23,7 @@
 #include <atomic>
 
 #include "attn_common.h"
+#include "attn_tile.h"
 
 namespace pkv {
 
@@ -38,32 +39,6 @@ constexpr int G = 2;                   // groups of four waves that share the ke
 constexpr int kThreads = G * 256;
 constexpr int kRing = 8 * kStage;      // a group's four stages of keys and four of values
 constexpr int kLdsBytes = G * kRing;
-
-// 16 bytes per lane from global memory straight into LDS: lane i of the wave
-// writes LDS bytes [lds_base + 16 i, +16); lds_base must be wave-uniform.
-__device__ __forceinline__ void dma16(const void* gbase, uint32_t voffset, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %2"
-        :
-        : "s"(lds_base), "v"(voffset), "s"(gbase)
-        : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// O^T accumulators pinned to their registers (never touched by the VALU inside the loop)
-__device__ __forceinline__ void mfma32_acc(bf16x8 a, bf16x8 b, f32x16& c) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-}
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char* ptr) {
-    const i16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) i16x4*)ptr);
-    return __builtin_bit_cast(bf16x4, v);
-}
 
 __global__ __launch_bounds__(kThreads, 2) void attn_pair_kernel(AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem_all[];

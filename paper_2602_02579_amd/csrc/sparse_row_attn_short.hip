@@ -21,6 +21,7 @@
 #include <atomic>
 
 #include "attn_common.h"
+#include "attn_tile.h"
 
 namespace pkv {
 
@@ -43,16 +44,6 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
         :
         : "s"(lds_base), "v"(gptr)
         : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char* ptr) {
-    const i16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) i16x4*)ptr);
-    return __builtin_bit_cast(bf16x4, v);
 }
 
 __global__ __launch_bounds__(kThreads) void attn_short_kernel(AttnParams p) {
