@@ -61,8 +61,8 @@ constexpr int kRow = kTK + 4;
 // contraction and meet in LDS - four times the workgroups, a quarter of the chain (linear layers,
 // 151 rows, 256 -> 512: 8.5 us with KS = 1, 4.4 with 4; 400 rows, 512 -> 1024: 14.8 and 14.1;
 // projection, 4 heads of 64, 256 inputs: 16 rows 6.4 and 4.4, 220 rows 6.7 and 5.3; 8 heads of 64,
-// 1024 inputs, 64 rows: 16.5 and 8.3; above 1024 tiles of 16 rows the higher tiles' better use of
-// the weights wins).
+// 1024 inputs, 64 rows: 16.5 and 8.3; with more tiles the higher ones' better use of the weights
+// wins, gemm_f32_low).
 template <int KS>
 constexpr int kTileRows = kTM / KS;
 
@@ -587,9 +587,16 @@ int gemm_f32_column_tiles(int mode, const F32GemmParams& p) {
     return mode == kF32Rope ? p.tile_begin[3]
                             : (int)ceil_div(p.n_out, mode == kF32Plain ? 32 : 16);
 }
-// tiles of 16 rows that all run at once (four workgroups per CU)
+// Tiles of 16 rows, where they all run at once (four workgroups per CU).  The projection, whose fp32
+// products are half as long as the linear layers' fp64 ones, takes a fourth one per CU only where its
+// tiles of 64 rows would be more than one per CU (64 rows -> 16, us: 1024 inputs, 768 tiles 16.8 -> 14.7,
+// 832 16.8 -> 18.0, 864 in place of 288 25.1 -> 18.1; 256 inputs, 768 6.9 -> 6.6, 864 7.0 -> 7.5; 4096,
+// 768 56.8 -> 46.8, 960 56.5 -> 59.0).
 bool gemm_f32_low(int mode, const F32GemmParams& p) {
-    return ceil_div(p.m, kTileRows<4>) * gemm_f32_column_tiles(mode, p) <= 1024;
+    const int64_t columns = gemm_f32_column_tiles(mode, p);
+    const int64_t tiles = ceil_div(p.m, kTileRows<4>) * columns;
+    return tiles <= 768 ||
+           (tiles <= 1024 && (mode != kF32Rope || ceil_div(p.m, kTM) * columns > 256));
 }
 
 }  // namespace

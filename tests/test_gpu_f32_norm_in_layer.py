@@ -58,7 +58,7 @@ def run(gpu_device, cfg, D, b, m, dst, stop):
 @pytest.mark.parametrize("m,hid,hq,hkv,d,inside", [
     (5, 8, 1, 1, 32, True), (33, 136, 4, 2, 64, True), (21, 264, 3, 3, 48, True),
     (672, 256, 4, 4, 64, True), (673, 256, 4, 4, 64, False),     # 42 and 43 x 24 tiles
-    (128, 640, 32, 16, 64, True), (129, 640, 32, 16, 64, False),  # 8 and 9 x 128
+    (96, 640, 32, 16, 64, True), (97, 640, 32, 16, 64, False),   # 6 and 7 x 128
     (37, 768, 2, 2, 32, True), (37, 776, 2, 2, 32, False), (1100, 136, 8, 4, 64, False)])
 @pytest.mark.parametrize("with_q", [True, False])
 def test_projection(gpu_device, m, hid, hq, hkv, d, inside, with_q):
@@ -66,9 +66,12 @@ def test_projection(gpu_device, m, hid, hq, hkv, d, inside, with_q):
     L, D, h, b = layer(gpu_device, m, hid, hq, hkv, d, 8, bias=hid == 136)
     order = np.random.default_rng(m).permutation(m).astype(np.int32)
     dst = torch.from_numpy(order).to(gpu_device)
-    # tiles are fewer without Q: the rows counts above are edges of the whole projection
-    fused = inside or (not with_q and hid <= 768 and
-                       -(-m // 16) * 2 * -(-hkv * d // 32) <= 1024)
+    # tiles are fewer without Q: the row counts above are edges of the whole projection
+    fused = inside
+    if not with_q:
+        columns = 2 * -(-hkv * d // 32)
+        low, high = -(-m // 16) * columns, -(-m // 64) * columns
+        fused = hid <= 768 and (low <= 768 or (low <= 1024 and high > 256))
     run(gpu_device, cfg, D, b, m, dst, api.LAYER_TO_SCORES if with_q else api.LAYER_TO_CACHES)
     x = MO.rmsnorm_rows(h, None, L["w_in"], EPS, "f64")
     pos = np.arange(m)
