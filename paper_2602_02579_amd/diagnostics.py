@@ -94,7 +94,7 @@ class Diagnostics:
     # object is given it keeps less than twice the rows of the largest set (a set for each length
     # would grow without end, and one set that grows would give memory back that work on another
     # stream or a captured graph still uses).  A set is its rows of h, x, q, attn and g, and up to
-    # 67 MB of scratch for partial sums.  Every row is its own position; -rows turns keys back.
+    # 67 MB of scratch for partial sums.  Row i is cache row i; -positions turn keys back.
     def _prefill_rows(self, t: int) -> CarriedRows:
         rows = max(1024, 1 << (t - 1).bit_length())
         cr = self._prefill.get(rows)
@@ -102,8 +102,7 @@ class Diagnostics:
             sub = self.cfg.with_(n_chunks=1, chunk_len=rows - 1, n_query=1)
             cr = CarriedRows(sub, self.inter, self.eps, self.device, k=rows - 1)
             cr.rows[:rows - 1] = torch.arange(rows - 1, dtype=torch.int32, device=self.device)
-            cr.neg_rows = -cr.rows
-            cr.in_chunks = {}   # chunk length -> positions inside chunks, and their negatives
+            cr.in_chunks = {}   # chunk length (0: one chunk) -> positions in it, and their negatives
             cr.views = {}       # (t, chunk length) -> what a call takes of the buffers
             self._prefill[rows] = cr
         return cr
@@ -118,12 +117,11 @@ class Diagnostics:
         if (t, chunk_len) not in cr.views:
             if len(cr.views) == 64:   # views are cheap to make again
                 cr.views.clear()
-            pos, neg_pos = cr.rows, cr.neg_rows
-            if t > chunk_len:
-                if chunk_len not in cr.in_chunks:
-                    inside = cr.rows % chunk_len
-                    cr.in_chunks[chunk_len] = inside, -inside
-                pos, neg_pos = cr.in_chunks[chunk_len]
+            length = chunk_len if t > chunk_len else 0
+            if length not in cr.in_chunks:
+                inside = cr.rows % length if length else cr.rows
+                cr.in_chunks[length] = inside, -inside
+            pos, neg_pos = cr.in_chunks[length]
             cr.views[t, chunk_len] = (
                 cr.h[:t], cr.rows[:t], pos[:t], neg_pos[:t],
                 api.pkv_chunk_attn_workspace_bytes(self.lc, t, chunk_len))
