@@ -50,12 +50,13 @@ __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<
 constexpr int kTM = 64, kTN = 32, kTK = 128;
 constexpr int kRow = kTK + 4;
 
-// Sums.  The projection sums in fp32, one product behind the other in each of its KS parts of the
-// contraction (3e-7 off the fp64 result at 256 inputs with one, 1.5e-7 with four).  The plain linear layers summed 64 interleaved parts and then these in a tree:
-// 0.6 to 1.2e-7 off the fp64 result (2-norm, 64 to 4096 inputs), where one chain is 0.9 to 8.4e-7
-// off.  So they sum in fp64 here (v_mfma_f64_16x16x4_f64, at half the rate; products of fp32 are
-// exact in it) and round once: 0.3e-7 at any length.  Its accumulator register r of lane group g is
-// row g + 4 r, not 4 g + r, so the weight rows go in permuted and the outputs come out alike.
+// Sums.  The projection sums in fp32, one product behind the other in each of its KS parts of
+// the contraction (3e-7 off the fp64 result at 256 inputs with one, 1.5e-7 with four).  The
+// plain linear layers summed 64 interleaved parts and then these in a tree: 0.6 to 1.2e-7 off
+// the fp64 result (2-norm, 64 to 4096 inputs), where one chain is 0.9 to 8.4e-7 off.  So they
+// sum in fp64 here (v_mfma_f64_16x16x4_f64, at half the rate; products of fp32 are exact in it)
+// and round once: 0.3e-7 at any length.  Its accumulator register r of lane group g is row g + 4
+// r, not 4 g + r, so the weight rows go in permuted and the outputs come out alike.
 //
 // KS = 4, where all tiles then run at once: a tile of 16 rows whose four waves share the
 // contraction and meet in LDS - four times the workgroups, a quarter of the chain (linear layers,

@@ -123,8 +123,9 @@ __global__ __launch_bounds__(256) void sparse_row_attn_generic(
 // blockIdx-encoded splits produces the per-column (max, sum) partials that
 // the query-score call needs for its normalisers.  For head_dim 128 the
 // attention proper runs in the kernels of sparse_row_attn_w8.hip (jobs up to
-// one per CU), sparse_row_attn_w8n.hip (more jobs), sparse_row_attn_pair.hip (a few
-// thousand keys) and sparse_row_attn_short.hip (short caches and few rows); this one serves head_dim 64 and the partials.
+// one per CU), sparse_row_attn_w8n.hip (more jobs), sparse_row_attn_pair.hip
+// (a few thousand keys) and sparse_row_attn_short.hip (short caches and few
+// rows); this one serves head_dim 64 and the partials.
 // ---------------------------------------------------------------------------
 
 template <int D>

@@ -405,21 +405,23 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pair_kernel(AttnParams p) {
 
 }  // namespace
 
-// Against ranges and queue at 400 sizes, heads 8 / 1 to 96 / 8, each with rows spread over the keys, as
-// a selection has them, and with all rows at the end of the cache (us, spread / end).
-// Up to one job per CU: the launch lasts as long as its longest job, 0.6 us per 64 keys and 15 besides,
-// so jobs have to be many or short: n_keys <= 20 jobs (32 / 8, 56 jobs over 1118 keys 24 -> 20 / 27 -> 21,
-// 192 over 3411 50 -> 44 / 57 -> 49; 256 over 8k 93 -> 96).
-// Up to two and a half: a CU's later, lighter jobs fill up what its first one leaves (280 jobs over 2.3k
-// 51 -> 36 / 51 -> 58, 448 over 4.8k 102 -> 80 / 120 -> 122, 600 over 10k 235 -> 216 / 400 -> 369); beyond, the
-// wider tiles read the keys less often (832 over 8k: 205 -> 221), and beyond 12k keys the two are
-// level (1702 rows over 16.5k: 220 and 224).  Rows at the end, all of one weight, lose where one more
-// job per CU is begun for a few of them, so the gain with spread rows has to be worth it.  It is not
-// - for a third job per CU where the wide tiles are one per CU (40 / 8, 520 over 4.8k 105 -> 100 /
-//   130 -> 172; 96 / 8, 536 over 10.7k 201 -> 199 / 336 -> 418),
-// - for groups that leave more than a twentieth of the 128 columns empty (96 / 8, 264 over 4k 57 -> 54 /
-//   75 -> 108, 400 over 1.1k 32 -> 32 / 34 -> 39),
-// - for large groups, whose jobs have few rows, over few keys (64 / 8, 480 over 1.1k 35 -> 37 / 35 -> 37).
+// Against ranges and queue at 400 sizes, heads 8 / 1 to 96 / 8, each with rows spread over the
+// keys, as a selection has them, and with all rows at the end of the cache (us, spread / end).
+// Up to one job per CU: the launch lasts as long as its longest job, 0.6 us per 64 keys and 15
+// besides, so jobs have to be many or short: n_keys <= 20 jobs (40 / 8, 56 jobs over 1118 keys
+// 24 -> 20 / 27 -> 21, 32 / 8, 192 over 3411 50 -> 44 / 57 -> 49; 256 over 8k 93 -> 96).
+// Up to two and a half: a CU's later, lighter jobs fill up what its first one leaves (40 / 8, 280
+// jobs over 2.3k 51 -> 36 / 51 -> 58, 32 / 8, 448 over 4.8k 102 -> 80 / 120 -> 122, 600 over 10k
+// 235 -> 216 / 400 -> 369); beyond, the wider tiles read the keys less often (832 over 8k: 205 -> 221), and
+// beyond 12k keys the two are level (1702 rows over 16.5k: 220 and 224).  Rows at the end, all
+// of one weight, lose where one more job per CU is begun for a few of them, so the gain with
+// spread rows has to be worth it.  It is not
+// - for a third job per CU where the wide tiles are one per CU (40 / 8, 520 over 4.8k 105 -> 100
+//   / 130 -> 172; 96 / 8, 536 over 10.7k 201 -> 199 / 336 -> 418),
+// - for groups that leave more than a twentieth of the 128 columns empty (96 / 8, 264 over 4k 57
+//   -> 54 / 75 -> 108, 400 over 1.1k 32 -> 32 / 34 -> 39),
+// - for large groups, whose jobs have few rows, over few keys (64 / 8, 480 over 1.1k 35 -> 37 /
+//   35 -> 37).
 bool attn_pair_applies(const pkv_layer_cfg& cfg, int64_t n_keys, int64_t m) {
     const int group = cfg.n_q_heads / cfg.n_kv_heads;
     if (group > kCols || n_keys > 12288) return false;

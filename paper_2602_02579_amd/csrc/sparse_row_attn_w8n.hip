@@ -619,14 +619,14 @@ __global__ __launch_bounds__(kThreads) void attn_w8n_kernel(AttnParams p) {
 
 }  // namespace
 
-// Whether a workgroup's first job goes by its number.  256 workgroups at the counters take 4 to 5 us to
-// claim theirs (claimed -> by number, us, spread rows: 128 / 8 heads, 559 rows over 1.2k keys 49 -> 44,
-// 32 / 32, 1141 over 13k in two ranges 184 -> 170, 28 / 4, 762 over 9.8k in four 84 -> 79).  Workgroups of
-// one number modulo eight share an XCD, and with kv heads that divide eight their first jobs lie 8 / hkv
-// apart: with two or four ranges some XCDs then begin with the fuller ranges only (8 / 2, 5614 over
-// 19.6k in two 231 -> 252, 16 / 2, 1459 over 17k in four 124 -> 131, 28 / 4, 1839 over 21k in two 259 ->
-// 273).  Fewer kv heads than XCDs and more than two jobs per CU: level or 2 % slower (28 / 4, 5096 over
-// 11.6k 366 -> 374).
+// Whether a workgroup's first job goes by its number.  256 workgroups at the counters take 4 to
+// 5 us to claim theirs (claimed -> by number, us, spread rows: 128 / 8 heads, 559 rows over 1.2k
+// keys 49 -> 44, 32 / 32, 1141 over 13k in two ranges 184 -> 170, 28 / 4, 762 over 9.8k in four
+// 84 -> 79).  Workgroups of one number modulo eight share an XCD, and with kv heads that divide
+// eight their first jobs lie 8 / hkv apart: with two or four ranges some XCDs then begin with
+// the fuller ranges only (8 / 2, 5614 over 19.6k in two 231 -> 252, 16 / 2, 1459 over 17k in
+// four 124 -> 131, 28 / 4, 1839 over 21k in two 259 -> 273).  Fewer kv heads than XCDs and more
+// than two jobs per CU: level or 2 % slower (28 / 4, 5096 over 11.6k 366 -> 374).
 static bool deal_first_jobs(int hkv, int n_splits, int64_t jobs, int n_cu) {
     if (hkv % 8 == 0) return true;
     return jobs <= 2 * (int64_t)n_cu && !(hkv % 2 == 0 && (n_splits == 2 || n_splits == 4));
