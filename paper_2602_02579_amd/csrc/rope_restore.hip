@@ -40,7 +40,7 @@ struct RopeCaches {
 template <typename T, int L, bool DEAL>
 __global__ __launch_bounds__(256) void rope_restore_kernel(
     RopeCaches<L> caches, const int32_t* __restrict__ pos, int64_t pos_base, int64_t n, int n_heads,
-    int heads_each, int head_dim, RopeTable tab) {
+    int head_dim, RopeTable tab, int heads_each) {
     const int layer = L == 1 ? 0 : blockIdx.y;
     const T* const k_in = static_cast<const T*>(caches.in[layer]);
     T* const k_out = static_cast<T*>(caches.out[layer]);
@@ -115,8 +115,8 @@ static void rope_restore_launch(dim3 grid, const void* const* k_in, void* const*
         caches.in[l] = k_in[l];
         caches.out[l] = k_out[l];
     }
-    hipLaunchKernelGGL((rope_restore_kernel<T, L, DEAL>), grid, dim3(256), 0, st, caches, pos, pos_base, n,
-                       cfg.n_kv_heads, heads_each, cfg.head_dim, tab);
+    hipLaunchKernelGGL((rope_restore_kernel<T, L, DEAL>), grid, dim3(256), 0, st, caches, pos,
+                       pos_base, n, cfg.n_kv_heads, cfg.head_dim, tab, heads_each);
 }
 
 pkv_status launch_rope_restore(const pkv_layer_cfg& cfg, const void* const* k_in,
