@@ -321,10 +321,10 @@ pkv_status pkv_sparse_row_attn(const pkv_layer_cfg* cfg,
                                void* ws, size_t ws_bytes, void* stream);
 
 /*
- * Which kernel that call runs for m rows over n_keys keys: a pure host function of the sizes, with
- * the scratch of pkv_workspace_bytes (and negative for sizes that the call refuses).  For
- * programs that place their sizes, and for tests of the choice; every kernel gives the same
- * results to rounding.
+ * Which kernel that call runs for m rows over n_keys keys: a pure host function of the sizes, of
+ * the compute units of the current device (256 where there is none) and of what the environment
+ * forces for comparisons; negative for sizes that the call refuses.  For programs that place
+ * their sizes, and for tests of the choice; every kernel gives the same results to rounding.
  */
 typedef enum {
     PKV_ATTN_GENERIC = 0,        /* a workgroup per (row, head) */
